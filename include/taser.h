@@ -98,6 +98,24 @@ int taser_tcsr_build(const int32_t* src, const int32_t* dst, const int64_t* ts,
                      const int32_t* eid, int64_t num_entries, int32_t num_nodes,
                      uint32_t flags, void* hip_stream, taser_tcsr** out);
 
+/* The same build in device memory of the caller's (for instance a framework's
+ * caching allocator: allocating and freeing gigabytes in the driver takes longer
+ * than sorting them). taser_tcsr_build_bytes says how many bytes a build with
+ * these sizes and flags needs (either out-pointer may be NULL): `storage` is what
+ * the graph lives in until taser_tcsr_free, `scratch` is free again when
+ * taser_tcsr_build_in returns. Both 256-byte aligned, contents arbitrary, on the
+ * current device, and not in use by work that `hip_stream` is not ordered after.
+ * taser_tcsr_free of such a graph waits for the whole device (as freeing device
+ * memory does) and leaves the storage to the caller. Errors: those of
+ * taser_tcsr_build, and TASER_E_RANGE if a block is too small, TASER_E_ARG if it
+ * is null or misaligned. */
+int taser_tcsr_build_bytes(int64_t num_entries, int32_t num_nodes, uint32_t flags,
+                           uint64_t* storage_bytes, uint64_t* scratch_bytes);
+int taser_tcsr_build_in(const int32_t* src, const int32_t* dst, const int64_t* ts,
+                        const int32_t* eid, int64_t num_entries, int32_t num_nodes,
+                        uint32_t flags, void* hip_stream, void* storage, uint64_t storage_bytes,
+                        void* scratch, uint64_t scratch_bytes, taser_tcsr** out);
+
 /* Size of a built graph (either out-pointer may be NULL). */
 int taser_tcsr_size(const taser_tcsr* g, int64_t* num_entries, int32_t* num_nodes);
 

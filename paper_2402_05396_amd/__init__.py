@@ -6,6 +6,7 @@ arguments: torch supplies device memory and the current stream, every step of
 the path runs in the library's HIP kernels. There is no fallback: if the
 library has not been built, or no GPU is present, calls raise.
 """
+import contextlib
 import ctypes
 import os
 
@@ -18,7 +19,7 @@ RECENT, UNIFORM, WEIGHTED, INVERSE_TIMESPAN = 0, 1, 2, 3
 INPUT_ON_DEVICE = 1
 MAX_K, MAX_M, MAX_HOPS = 64, 64, 3
 
-EXPORTS = ("taser_tcsr_build", "taser_tcsr_size", "taser_tcsr_view", "taser_tcsr_free", "taser_sample_temporal", "taser_sample_temporal_rows",
+EXPORTS = ("taser_tcsr_build", "taser_tcsr_build_bytes", "taser_tcsr_build_in", "taser_tcsr_size", "taser_tcsr_view", "taser_tcsr_free", "taser_sample_temporal", "taser_sample_temporal_rows",
            "taser_candidate_encodings", "taser_select_weighted", "taser_gather_features", "taser_cache_init", "taser_cache_lookup", "taser_cache_lookup_static", "taser_cache_prefetch", "taser_cache_gather", "taser_cache_tune", "taser_cache_count_accesses", "taser_cache_access_counts",
            "taser_cache_epoch_end", "taser_cache_residents",
            "taser_cache_free", "taser_selector_init", "taser_selector_draw", "taser_selector_update",
@@ -53,6 +54,8 @@ def lib():
         L = ctypes.CDLL(LIB_PATH)
         vp, i32, i64, u32, u64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint32, ctypes.c_uint64
         L.taser_tcsr_build.argtypes = [vp, vp, vp, vp, i64, i32, u32, vp, ctypes.POINTER(vp)]
+        L.taser_tcsr_build_bytes.argtypes = [i64, i32, u32, ctypes.POINTER(u64), ctypes.POINTER(u64)]
+        L.taser_tcsr_build_in.argtypes = [vp, vp, vp, vp, i64, i32, u32, vp, vp, u64, vp, u64, ctypes.POINTER(vp)]
         L.taser_tcsr_size.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i32)]
         L.taser_tcsr_view.argtypes = [vp, vp, vp, vp, vp, vp]
         L.taser_tcsr_free.argtypes = [vp]
@@ -117,15 +120,15 @@ def _want(t, dtype, name, cuda=True):
 
 
 class TCSR:
-    """Owner of a taser_tcsr handle."""
+    """Owner of a taser_tcsr handle and of the device memory it lives in."""
 
-    def __init__(self, handle, num_entries, num_nodes):
-        self.handle, self.num_entries, self.num_nodes = handle, num_entries, num_nodes
+    def __init__(self, handle, num_entries, num_nodes, storage=None):
+        self.handle, self.num_entries, self.num_nodes, self.storage = handle, num_entries, num_nodes, storage
 
     def free(self):
         if self.handle:
-            lib().taser_tcsr_free(self.handle)
-            self.handle = None
+            lib().taser_tcsr_free(self.handle)   # waits for the device: nothing reads the storage any more
+            self.handle = self.storage = None
 
     def __del__(self):
         try:
@@ -134,8 +137,17 @@ class TCSR:
             pass
 
 
-def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
-    """taser_tcsr_build. src/dst/eid int32, ts int64; all on the GPU or all on the host."""
+def tcsr_build_bytes(num_entries, num_nodes, on_device=True):
+    """taser_tcsr_build_bytes -> (storage bytes, scratch bytes)."""
+    storage, scratch = ctypes.c_uint64(), ctypes.c_uint64()
+    _check(lib().taser_tcsr_build_bytes(num_entries, num_nodes, INPUT_ON_DEVICE if on_device else 0, ctypes.byref(storage),
+                                        ctypes.byref(scratch)))
+    return storage.value, scratch.value
+
+
+def tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream=None):
+    """taser_tcsr_build_in: the graph lives in `storage` (kept alive by the returned object); `scratch` is free again on
+    return. Both: contiguous uint8 device tensors of at least tcsr_build_bytes() elements."""
     on_dev = src.is_cuda
     _want(src, torch.int32, "src", on_dev)
     _want(dst, torch.int32, "dst", on_dev)
@@ -145,10 +157,25 @@ def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
     n = src.numel()
     if dst.numel() != n or ts.numel() != n or (eid is not None and eid.numel() != n):
         raise ValueError("src, dst, ts, eid must have the same length")
+    _want(storage, torch.uint8, "storage")
+    _want(scratch, torch.uint8, "scratch")
     h = ctypes.c_void_p()
-    _check(lib().taser_tcsr_build(_ptr(src), _ptr(dst), _ptr(ts), _ptr(eid), n, num_nodes,
-                                  INPUT_ON_DEVICE if on_dev else 0, _stream(stream), ctypes.byref(h)))
-    return TCSR(h, n, num_nodes)
+    _check(lib().taser_tcsr_build_in(_ptr(src), _ptr(dst), _ptr(ts), _ptr(eid), n, num_nodes,
+                                     INPUT_ON_DEVICE if on_dev else 0, _stream(stream), _ptr(storage), storage.numel(),
+                                     _ptr(scratch), scratch.numel(), ctypes.byref(h)))
+    return TCSR(h, n, num_nodes, storage)
+
+
+def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
+    """taser_tcsr_build. src/dst/eid int32, ts int64; all on the GPU or all on the host. The device memory is torch's
+    (its caching allocator keeps freed blocks for the next call; the driver takes milliseconds per gigabyte)."""
+    sizes = tcsr_build_bytes(src.numel(), num_nodes, src.is_cuda)
+    try:
+        with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):   # blocks of that stream's pool
+            storage, scratch = (torch.empty(b, dtype=torch.uint8, device="cuda") for b in sizes)
+    except torch.OutOfMemoryError as e:
+        raise TaserError(-3, f"tcsr_build: {e}") from e
+    return tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream)
 
 
 def tcsr_size(g):

@@ -47,8 +47,9 @@ struct taser_tcsr {
     int32_t num_nodes;
     int64_t* indptr;   // device int64[num_nodes + 1]
     TaserRec* rec;     // device TaserRec[num_entries], T-CSR order
-    int64_t* time_index_storage;   // one device allocation behind time_index.level[*]
     TaserTimeIndex time_index;
+    void* owned_storage;           // the one device allocation behind all of the above, or null: the caller's memory
+    int device;                    // with the caller's memory: the device it is on
     int64_t* ts_only;              // device int64[num_entries] or null: the timestamps alone, made on first use by
                                    // the one finder that reads whole lists (inverse timespan)
 };

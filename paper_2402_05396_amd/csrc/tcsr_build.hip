@@ -2,114 +2,138 @@
 // node's outgoing entries contiguous and ordered by timestamp, ties by input
 // position. Built on the device by a stable least-significant-digit radix
 // sort over the composite key (node, ts):
-//   * digits of the timestamp first (only those bytes in which the timestamps
-//     actually differ, and none at all when the input is already time-sorted,
-//     which is how event streams arrive), then the digits of the node id;
-//   * one pass = per-block digit histogram -> exclusive scan over the
-//     (digit, block) counters -> stable scatter. Inside a block the stable rank
-//     of an item among equal digits comes from wave ballots (which lanes hold
-//     my digit, how many of them are below me) plus per-wave running counters
-//     in LDS, so no atomics decide an output position;
+//   * the key has only the bits that matter: those of the timestamp between the
+//     lowest and the highest bit in which the timestamps differ (none at all when
+//     the input is already time-sorted, which is how event streams arrive), then
+//     those of the node id. They are cut into equal digits of at most 9 bits, so a
+//     digit may hold the top of the one and the bottom of the other;
+//   * one pass = per-tile digit histogram -> per-digit scan over the tiles ->
+//     stable scatter. Inside a tile the stable rank of an item among equal digits
+//     comes from wave ballots (which lanes hold my digit, how many of them are
+//     below me) plus per-wave running counters in LDS, so no atomics decide an
+//     output position;
 //   * the 16-byte record {ts, nbr, eid} the sampler reads travels with the key,
-//     so the last pass leaves the final layout in place;
+//     so the last pass leaves the final layout in place. The first pass reads the
+//     caller's columns directly: nothing is packed beforehand;
 //   * indptr is read off the sorted node column (no atomics, no histogram).
+// All device memory is one storage block (what the graph keeps) and one scratch
+// block, either the caller's (taser_tcsr_build_in) or allocated here.
+#include <mutex>
 #include <new>
-#include <vector>
 
-#include "scan_kernels.h"
 #include "taser_internal.h"
 
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / kWave;
-constexpr int kItems = 16;                         // items per thread
-constexpr int kTile = kThreads * kItems;           // items per block
-constexpr int kBins = 256;                         // 8-bit digits
+constexpr int kMaxDigitBits = 9;
+constexpr int kBins = 1 << kMaxDigitBits;
+constexpr int kSortThreads = 512;                 // block of the sorting kernels: as many threads as digit values
+constexpr int kSortWaves = kSortThreads / kWave;
+static_assert(kSortThreads == kBins, "one digit per thread");
+constexpr int kSmallItems = 4, kLargeItems = 8;   // items per thread of a tile (see items_for)
 
+// Bits [s, s + bits) of the composite key, for s inside the timestamp's part (with from_ts) or above it.
 struct DigitSpec {
-    int from_ts;      // 1: digit of the (sign-biased) timestamp, 0: digit of the node id
-    int shift;
-    uint32_t mask;
+    int from_ts;           // the digit has timestamp bits
+    int ts_shift;          // where they start in the (sign-biased) timestamp
+    uint32_t ts_mask;      // and how many of them there are
+    int node_left;         // node bits above them: shift to the left (31: none fit)
+    int node_right;        // without timestamp bits: shift of the node id to the right
+    int bits;
 };
 
 __device__ __forceinline__ uint64_t biased(int64_t ts) { return (uint64_t)ts ^ 0x8000000000000000ull; }
 
-__device__ __forceinline__ uint32_t digit_at(const TaserRec* rec, const int32_t* key, int64_t i, DigitSpec d) {
-    if (d.from_ts) return (uint32_t)(biased(rec[i].ts) >> d.shift) & d.mask;
-    return ((uint32_t)key[i] >> d.shift) & d.mask;
+__device__ __forceinline__ uint32_t digit_of(const DigitSpec& d, int64_t ts, int32_t node) {
+    const uint32_t v = d.from_ts ? (((uint32_t)(biased(ts) >> d.ts_shift) & d.ts_mask) | ((uint32_t)node << d.node_left))
+                                 : (uint32_t)node >> d.node_right;
+    return v & ((1u << d.bits) - 1u);
 }
 
-// Item r of lane `lane` of wave `wave` inside a tile: rows of 64 consecutive
-// items per wave, so loads are coalesced and index order = (wave, row, lane).
-__device__ __forceinline__ int64_t item_index(int64_t tile0, int wave, int r, int lane) {
-    return tile0 + (int64_t)wave * (kWave * kItems) + r * kWave + lane;
+// Where a pass finds its items: the caller's columns (first pass) or the records and node keys of
+// the pass before.
+struct Items {
+    const TaserRec* rec;
+    const int32_t* key;    // node ids
+    const int32_t* dst;    // columns (rec == nullptr)
+    const int64_t* ts;
+    const int32_t* eid;    // may be null: the position
+};
+
+// Histogram of a tile in LDS: a digit's counter has kCopies copies, one per lane modulo kCopies, so
+// that equal digits of one wave instruction (popular nodes) meet at fewer addresses. Thread t clears
+// and adds up digit t's.
+constexpr uint32_t kCopies = 4;
+__device__ __forceinline__ void clear_digit(uint32_t* bins) {
+    for (uint32_t c = 0; c < kCopies; ++c) bins[threadIdx.x * kCopies + c] = 0;
+}
+__device__ __forceinline__ uint32_t count_of_digit(const uint32_t* bins) {
+    uint32_t sum = 0;
+    for (uint32_t c = 0; c < kCopies; ++c) sum += bins[threadIdx.x * kCopies + c];
+    return sum;
 }
 
-// Packs the input columns into the 16-byte records + node key the sort moves, and
-// inspects them on the way. Per block, partial[4 * block + ...]: [0] != 0: a node id
-// outside [0, num_nodes); [1] != 0: timestamps not non-decreasing in input order;
-// [2] / [3]: OR / AND of the biased timestamps (bytes in which they agree need no
-// sorting pass). fold_info_kernel combines the per-block words (atomics from every
-// block onto four shared words took longer than reading the input).
-// The block also counts its tile's node ids by their lowest digit, hist[bin * num_blocks +
-// tile] as radix_hist_kernel would: time-sorted input (the usual case) is sorted by the node
-// digits only, lowest first, and that pass then needs no histogram kernel of its own (the
-// counting hides behind this kernel's memory traffic).
-__global__ __launch_bounds__(kThreads) void pack_inspect_kernel(const int32_t* __restrict__ src,
-                                                                const int32_t* __restrict__ dst,
-                                                                const int64_t* __restrict__ ts,
-                                                                const int32_t* __restrict__ eid, int64_t n,
-                                                                int32_t num_nodes, TaserRec* __restrict__ rec,
-                                                                int32_t* __restrict__ key,
-                                                                unsigned long long* __restrict__ partial,
-                                                                uint32_t low_digit_mask, uint32_t* __restrict__ hist,
-                                                                uint32_t num_blocks) {
-    __shared__ uint32_t bins[kBins];
-    bins[threadIdx.x] = 0;
-    __syncthreads();
+// Inspects the input before the sort is planned: partial[4 * block + ...]: [0] != 0: a node id
+// outside [0, num_nodes); [1] != 0: timestamps not non-decreasing in input order; [2] / [3]: OR /
+// AND of the biased timestamps (bits in which they agree need no sorting). On the way it counts
+// every tile's node ids by their lowest digit, hist[tile * bins + bin] as radix_hist_kernel
+// would: time-sorted input is sorted by the node digits only, and its first pass then needs no
+// histogram kernel. It reads 12 of an entry's 20 bytes and writes nothing per entry: 0.18 ms for
+// 64 M entries (4.3 TB/s), where packing the columns into records here, and reading them back in
+// the first pass, took 0.50.
+constexpr unsigned kInspectBlocks = 1024;   // 4 per compute unit; the fold below is one block over their words
+template <int kItems>
+__global__ __launch_bounds__(kSortThreads) void inspect_kernel(const int32_t* __restrict__ src, const int64_t* __restrict__ ts,
+                                                           int64_t n, int32_t num_nodes,
+                                                           unsigned long long* __restrict__ partial, int low_bits,
+                                                           uint32_t* __restrict__ hist, uint32_t num_tiles) {
+    constexpr int kTile = kSortThreads * kItems;
+    __shared__ uint32_t bins[kBins * kCopies];
+    const uint32_t low_mask = (1u << low_bits) - 1u, copy = threadIdx.x % kCopies;
     unsigned long long any_or = 0, all_and = ~0ull;
     int bad = 0, unsorted = 0;
-    constexpr int kPer = 4;   // entries per thread and round: their loads are issued together
-    // a block packs one contiguous tile of kTile entries
-    const int64_t tile0 = (int64_t)blockIdx.x * kTile;
-    for (int round = 0; round < kItems / kPer; ++round) {
-        const int64_t i0 = tile0 + (int64_t)round * (kPer * kThreads) + threadIdx.x;
-        int32_t s[kPer], dn[kPer], e[kPer];
-        int64_t t[kPer], t_next[kPer];
+    for (uint32_t tile = blockIdx.x; tile < num_tiles; tile += gridDim.x) {
+        clear_digit(bins);
+        __syncthreads();
+        const int64_t tile0 = (int64_t)tile * kTile;
+        const bool whole = tile0 + kTile < n;   // uniform: every item of the tile has a successor
+        const uint32_t last = whole ? (uint32_t)kTile : (uint32_t)(n - 1 - tile0);   // place of the array's last item, if it is here
+        const int32_t* const tile_src = src + tile0;
+        const int64_t* const tile_ts = ts + tile0;
+        int32_t s[kItems];
+        int64_t t[kItems], t_end[kItems];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int64_t i = i0 + u * kThreads;
-            const int64_t at = i < n ? i : n - 1;            // clamped: every load stays in bounds
-            s[u] = src[at];
-            dn[u] = dst[at];
-            t[u] = ts[at];
-            t_next[u] = ts[at + 1 < n ? at + 1 : at];
-            e[u] = eid ? eid[at] : (int32_t)at;
+        for (int u = 0; u < kItems; ++u) {
+            uint32_t i = threadIdx.x + u * kSortThreads;
+            if (!whole && i > last) i = last;               // clamped: every load stays in bounds
+            s[u] = tile_src[i];
+            t[u] = tile_ts[i];
+            t_end[u] = 0;                                   // the item after the wave's last one; the others have it in a lane
+            if ((threadIdx.x & (kWave - 1)) == kWave - 1) t_end[u] = tile_ts[i < last ? i + 1 : i];
         }
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int64_t i = i0 + u * kThreads;
-            if (i >= n) continue;
-            bad |= (s[u] < 0 || s[u] >= num_nodes);
-            unsorted |= (t_next[u] < t[u]);
+        for (int u = 0; u < kItems; ++u) {
+            const uint32_t next_lo = __shfl_down((uint32_t)(uint64_t)t[u], 1, kWave), next_hi = __shfl_down((uint32_t)((uint64_t)t[u] >> 32), 1, kWave);
+            int64_t next = (int64_t)(((uint64_t)next_hi << 32) | next_lo);
+            if ((threadIdx.x & (kWave - 1)) == kWave - 1) next = t_end[u];
+            if (!whole && threadIdx.x + u * kSortThreads > last) continue;
+            bad |= (uint32_t)s[u] >= (uint32_t)num_nodes;   // negative ids included
+            unsorted |= (next < t[u]);
             any_or |= biased(t[u]);
             all_and &= biased(t[u]);
-            TaserRec r;
-            r.ts = t[u];
-            r.nbr = dn[u];
-            r.eid = e[u];
-            rec[i] = r;
-            key[i] = s[u];
-            atomicAdd(&bins[(uint32_t)s[u] & low_digit_mask], 1u);
+            atomicAdd(&bins[((uint32_t)s[u] & low_mask) * kCopies + copy], 1u);
         }
+        __syncthreads();
+        if (threadIdx.x <= low_mask) hist[((size_t)tile << low_bits) + threadIdx.x] = count_of_digit(bins);
+        // (each thread clears the counters it has just read)
     }
     for (int d = 1; d < kWave; d <<= 1) {
         any_or |= __shfl_xor(any_or, d, kWave);
         all_and &= __shfl_xor(all_and, d, kWave);
     }
-    __shared__ unsigned long long w_or[kWaves], w_and[kWaves];
-    __shared__ int w_bad[kWaves], w_unsorted[kWaves];
+    __shared__ unsigned long long w_or[kSortWaves], w_and[kSortWaves];
+    __shared__ int w_bad[kSortWaves], w_unsorted[kSortWaves];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const unsigned long long any_bad = __ballot(bad), any_unsorted = __ballot(unsorted);
     if (lane == 0) {
@@ -119,11 +143,10 @@ __global__ __launch_bounds__(kThreads) void pack_inspect_kernel(const int32_t* _
         w_unsorted[wave] = any_unsorted != 0;
     }
     __syncthreads();
-    if (hist) hist[(size_t)threadIdx.x * num_blocks + blockIdx.x] = bins[threadIdx.x];
     if (threadIdx.x == 0) {
         unsigned long long o = 0, a = ~0ull;
         int b = 0, u = 0;
-        for (int w = 0; w < kWaves; ++w) {
+        for (int w = 0; w < kSortWaves; ++w) {
             o |= w_or[w];
             a &= w_and[w];
             b |= w_bad[w];
@@ -136,28 +159,30 @@ __global__ __launch_bounds__(kThreads) void pack_inspect_kernel(const int32_t* _
     }
 }
 
-// info[4 * block + 0..3] = this block's share of the `blocks` per-block word groups of
-// pack_inspect_kernel combined (launched twice: many blocks, then one over their results).
-__global__ __launch_bounds__(kThreads) void fold_info_kernel(const unsigned long long* __restrict__ partial, uint32_t blocks,
+// One block: info[0..3] = the `blocks` per-block word groups of inspect_kernel combined.
+__global__ __launch_bounds__(kSortThreads) void fold_info_kernel(const unsigned long long* __restrict__ partial, uint32_t blocks,
                                                              unsigned long long* __restrict__ info) {
-    __shared__ unsigned long long part[4][kThreads];
+    __shared__ unsigned long long part[4][kSortWaves];
     unsigned long long v[4] = {0, 0, 0, ~0ull};
-    for (uint32_t b = blockIdx.x * kThreads + threadIdx.x; b < blocks; b += gridDim.x * kThreads) {
+    for (uint32_t b = threadIdx.x; b < blocks; b += kSortThreads) {
         v[0] |= partial[4 * (size_t)b + 0];
         v[1] |= partial[4 * (size_t)b + 1];
         v[2] |= partial[4 * (size_t)b + 2];
         v[3] &= partial[4 * (size_t)b + 3];
     }
-    for (int j = 0; j < 4; ++j) part[j][threadIdx.x] = v[j];
+    for (int d = 1; d < kWave; d <<= 1) {
+        for (int j = 0; j < 3; ++j) v[j] |= __shfl_xor(v[j], d, kWave);
+        v[3] &= __shfl_xor(v[3], d, kWave);
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0)
+        for (int j = 0; j < 4; ++j) part[j][threadIdx.x >> 6] = v[j];
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int t = 1; t < kThreads; ++t) {
-            v[0] |= part[0][t];
-            v[1] |= part[1][t];
-            v[2] |= part[2][t];
-            v[3] &= part[3][t];
+        for (int w = 1; w < kSortWaves; ++w) {
+            for (int j = 0; j < 3; ++j) v[j] |= part[j][w];
+            v[3] &= part[3][w];
         }
-        for (int j = 0; j < 4; ++j) info[4 * blockIdx.x + j] = v[j];
+        for (int j = 0; j < 4; ++j) info[j] = v[j];
     }
 }
 
@@ -167,163 +192,315 @@ __global__ __launch_bounds__(kThreads) void fold_info_kernel(const unsigned long
 // average for 256 digits) meet in its L2 and leave as whole lines. With tile = workgroup index
 // those pieces came from eight different L2s as partial lines (5.8 -> 3.6 ms for the 256-digit
 // pass over 382 M entries). The grid is rounded up to a multiple of kPartitions; tiles >=
-// num_blocks do not exist.
+// num_tiles do not exist.
 constexpr uint32_t kPartitions = 8;
-__device__ __forceinline__ uint32_t tile_of_block(uint32_t block, uint32_t num_blocks) {
-    const uint32_t per_part = (num_blocks + kPartitions - 1) / kPartitions;
+__device__ __forceinline__ uint32_t tile_of_block(uint32_t block, uint32_t num_tiles) {
+    const uint32_t per_part = (num_tiles + kPartitions - 1) / kPartitions;
     return (block % kPartitions) * per_part + block / kPartitions;
 }
-inline unsigned pass_grid(unsigned num_blocks) { return (num_blocks + kPartitions - 1) / kPartitions * kPartitions; }
+inline unsigned pass_grid(unsigned num_tiles) { return (num_tiles + kPartitions - 1) / kPartitions * kPartitions; }
 
-// hist[bin * num_blocks + tile] = items of the tile whose digit is bin.
-__global__ __launch_bounds__(kThreads) void radix_hist_kernel(const TaserRec* __restrict__ rec,
-                                                              const int32_t* __restrict__ key, int64_t n,
-                                                              DigitSpec d, uint32_t* __restrict__ hist,
-                                                              uint32_t num_blocks) {
-    __shared__ uint32_t bins[kBins];
+// hist[tile * bins + bin] = items of the tile whose digit is bin. (One row per tile: with one row
+// per digit value every counter went to a line of its own, and the kernel took 0.11 ms for 64 M
+// keys, with that and the copies of the counters 0.07.)
+template <int kItems>
+__global__ __launch_bounds__(kSortThreads) void radix_hist_kernel(const Items in, int64_t n, DigitSpec d,
+                                                              uint32_t* __restrict__ hist) {
+    constexpr int kTile = kSortThreads * kItems;
+    __shared__ uint32_t bins[kBins * kCopies];
     const uint32_t tile = blockIdx.x;   // (the partition-wise order of the scatter below does not pay here)
-    bins[threadIdx.x] = 0;
+    const uint32_t copy = threadIdx.x % kCopies;
+    clear_digit(bins);
     __syncthreads();
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int64_t tile0 = (int64_t)tile * kTile;
-    if (!d.from_ts && tile0 + kTile <= n) {
+    if (!d.from_ts && in.rec && tile0 + kTile <= n) {
         // a whole tile of node keys: which thread counts which item does not matter, so every thread
-        // takes four runs of four keys with 16-byte loads (tile0 is a multiple of the tile size and
-        // `key` the start of an allocation: aligned), all four loads in flight together
+        // takes runs of four keys with 16-byte loads (tile0 is a multiple of the tile size and the
+        // keys of a pass start an aligned part of the scratch block), all loads in flight together
         typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-        const i32x4* quads = reinterpret_cast<const i32x4*>(key + tile0);
+        const i32x4* quads = reinterpret_cast<const i32x4*>(in.key + tile0);
         i32x4 v[kItems / 4];
 #pragma unroll
-        for (int r = 0; r < kItems / 4; ++r) v[r] = quads[r * kThreads + threadIdx.x];
+        for (int r = 0; r < kItems / 4; ++r) v[r] = quads[r * kSortThreads + threadIdx.x];
 #pragma unroll
         for (int r = 0; r < kItems / 4; ++r) {
-            atomicAdd(&bins[((uint32_t)v[r].x >> d.shift) & d.mask], 1u);
-            atomicAdd(&bins[((uint32_t)v[r].y >> d.shift) & d.mask], 1u);
-            atomicAdd(&bins[((uint32_t)v[r].z >> d.shift) & d.mask], 1u);
-            atomicAdd(&bins[((uint32_t)v[r].w >> d.shift) & d.mask], 1u);
+            atomicAdd(&bins[digit_of(d, 0, v[r].x) * kCopies + copy], 1u);
+            atomicAdd(&bins[digit_of(d, 0, v[r].y) * kCopies + copy], 1u);
+            atomicAdd(&bins[digit_of(d, 0, v[r].z) * kCopies + copy], 1u);
+            atomicAdd(&bins[digit_of(d, 0, v[r].w) * kCopies + copy], 1u);
         }
     } else {
-#pragma unroll 4
-        for (int r = 0; r < kItems; ++r) {
-            const int64_t i = item_index(tile0, wave, r, lane);
-            if (i < n) atomicAdd(&bins[digit_at(rec, key, i, d)], 1u);
+        constexpr int kPer = 4;
+        for (int round = 0; round < kItems / kPer; ++round) {
+            const int64_t i0 = tile0 + (int64_t)round * (kPer * kSortThreads) + threadIdx.x;
+            int64_t t[kPer];
+            int32_t node[kPer];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int64_t i = i0 + u * kSortThreads;
+                const int64_t at = i < n ? i : n - 1;
+                t[u] = d.from_ts ? (in.rec ? in.rec[at].ts : in.ts[at]) : 0;
+                node[u] = in.key[at];
+            }
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (i0 + u * kSortThreads < n) atomicAdd(&bins[digit_of(d, t[u], node[u]) * kCopies + copy], 1u);
         }
     }
     __syncthreads();
-    hist[(size_t)threadIdx.x * num_blocks + tile] = bins[threadIdx.x];
+    if (threadIdx.x < (1u << d.bits)) hist[((size_t)tile << d.bits) + threadIdx.x] = count_of_digit(bins);
 }
 
-// Stable scatter of one tile. offs = the scanned histogram: offs[bin*num_blocks
-// + block] is where this block's first item with digit `bin` goes. The tile is
+// Per digit value: hist[...][bin] becomes its own exclusive scan over the tiles, and total[bin] the
+// digit's count (the scatter adds up the totals below its digits itself, which saves the two further
+// launches of a scan over the whole table). A block owns kScanCols digit values, that is a 32-byte
+// piece of every row; its 128 groups of lanes each take a run of consecutive tiles, sum it, and go
+// over it again with what came before. One launch, bound by the latency of its few loads: 6 us for
+// 656 rows of 512. From kChunkedTiles rows on there is too little of it in flight (15 600 rows of
+// 256: 0.11 ms) and two launches over chunks of rows do the same (0.014 ms).
+constexpr uint32_t kChunkedTiles = 2048;
+constexpr int kScanThreads = 1024, kScanCols = 8, kScanGroups = kScanThreads / kScanCols;
+__global__ __launch_bounds__(kScanThreads) void bin_scan_kernel(uint32_t* __restrict__ hist, uint32_t num_tiles, int bits,
+                                                                uint32_t* __restrict__ total) {
+    __shared__ uint32_t wave_total[kScanThreads / kWave][kScanCols];
+    constexpr int kAhead = 8;
+    const uint32_t col = threadIdx.x % kScanCols, group = threadIdx.x / kScanCols;
+    const uint32_t bin = blockIdx.x * kScanCols + col;
+    const bool live = bin < (1u << bits);
+    const uint32_t per_group = (num_tiles + kScanGroups - 1) / kScanGroups;
+    uint32_t r0 = group * per_group, r1 = r0 + per_group;
+    if (r1 > num_tiles) r1 = num_tiles;
+    if (!live || r0 > r1) r0 = r1;
+    uint32_t* const a = hist + bin;
+    uint32_t sum = 0;
+    for (uint32_t r = r0; r < r1; r += kAhead) {
+        uint32_t v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = r + u < r1 ? a[(size_t)(r + u) << bits] : 0u;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) sum += v[u];
+    }
+    // exclusive over the groups: a wave holds 64 / kScanCols of them, kScanCols lanes apart
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    uint32_t inc = sum;
+#pragma unroll
+    for (int d = kScanCols; d < kWave; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, kWave);
+        if (lane >= d) inc += y;
+    }
+    if (lane >= kWave - kScanCols) wave_total[wave][col] = inc;
+    __syncthreads();
+    uint32_t run = inc - sum, all = 0;
+#pragma unroll
+    for (int w = 0; w < kScanThreads / kWave; ++w) {
+        const uint32_t x = wave_total[w][col];
+        if (w < wave) run += x;
+        all += x;
+    }
+    if (live && group == 0) total[bin] = all;
+    for (uint32_t r = r0; r < r1; r += kAhead) {
+        uint32_t v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = r + u < r1 ? a[(size_t)(r + u) << bits] : 0u;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (r + u < r1) a[(size_t)(r + u) << bits] = run;
+            run += v[u];
+        }
+    }
+}
+
+// The same over chunks of rows: a block of the first kernel sums one chunk for 64 digit values (a row
+// piece of 256 bytes per wave instruction), a block of the second adds up the chunks before its own
+// and scans it. At most kMaxChunks chunks, so that adding up stays short.
+constexpr uint32_t kMaxChunks = 256;
+constexpr int kChunkWaves = kThreads / kWave;
+__global__ __launch_bounds__(kThreads) void chunk_sum_kernel(const uint32_t* __restrict__ hist, uint32_t num_tiles, int bits,
+                                                             uint32_t rows_per_chunk, uint32_t* __restrict__ chunk_sum) {
+    __shared__ uint32_t part[kChunkWaves][kWave];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const uint32_t bin = blockIdx.x * kWave + lane, bins = 1u << bits;
+    const uint32_t r0 = blockIdx.y * rows_per_chunk, r1 = r0 + rows_per_chunk < num_tiles ? r0 + rows_per_chunk : num_tiles;
+    uint32_t sum = 0;
+    if (bin < bins) {
+#pragma unroll 8
+        for (uint32_t r = r0 + wave; r < r1; r += kChunkWaves) sum += hist[((size_t)r << bits) + bin];
+    }
+    part[wave][lane] = sum;
+    __syncthreads();
+    if (wave == 0 && bin < bins) {
+        for (int w = 1; w < kChunkWaves; ++w) sum += part[w][lane];
+        chunk_sum[(size_t)blockIdx.y * bins + bin] = sum;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void chunk_scan_kernel(uint32_t* __restrict__ hist, uint32_t num_tiles, int bits,
+                                                              uint32_t rows_per_chunk, const uint32_t* __restrict__ chunk_sum,
+                                                              uint32_t* __restrict__ total) {
+    __shared__ uint32_t part[2][kChunkWaves][kWave];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const uint32_t bin = blockIdx.x * kWave + lane, bins = 1u << bits;
+    const bool live = bin < bins;
+    // the chunk's rows, a quarter per wave; the chunks before it, every fourth per wave
+    const uint32_t c0 = blockIdx.y * rows_per_chunk, c1 = c0 + rows_per_chunk < num_tiles ? c0 + rows_per_chunk : num_tiles;
+    const uint32_t per_wave = (rows_per_chunk + kChunkWaves - 1) / kChunkWaves;
+    uint32_t r0 = c0 + wave * per_wave, r1 = r0 + per_wave;
+    if (r0 > c1) r0 = c1;
+    if (r1 > c1) r1 = c1;
+    uint32_t before = 0, own = 0;
+    if (live) {
+#pragma unroll 8
+        for (uint32_t c = wave; c < blockIdx.y; c += kChunkWaves) before += chunk_sum[(size_t)c * bins + bin];
+#pragma unroll 8
+        for (uint32_t r = r0; r < r1; ++r) own += hist[((size_t)r << bits) + bin];
+    }
+    part[0][wave][lane] = before;
+    part[1][wave][lane] = own;
+    __syncthreads();
+    uint32_t run = 0;
+    for (uint32_t w = 0; w < (uint32_t)kChunkWaves; ++w) {
+        run += part[0][w][lane];
+        if (w < wave) run += part[1][w][lane];
+    }
+    if (!live) return;
+    constexpr uint32_t kAhead = 8;
+    for (uint32_t r = r0; r < r1; r += kAhead) {
+        uint32_t v[kAhead];
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) v[u] = r + u < r1 ? hist[((size_t)(r + u) << bits) + bin] : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < kAhead; ++u) {
+            if (r + u < r1) hist[((size_t)(r + u) << bits) + bin] = run;
+            run += v[u];
+        }
+    }
+    if (c1 == num_tiles && wave == kChunkWaves - 1) total[bin] = run;   // the last rows' running sum
+}
+
+// Exclusive prefix sum of one value per thread over the block of a sorting kernel. `wave_sum` is
+// written before and read after the one barrier inside.
+__device__ __forceinline__ uint32_t scan_digits(uint32_t own, uint32_t* wave_sum) {
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    uint32_t inc = own;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = __shfl_up(inc, d, kWave);
+        if (lane >= d) inc += y;
+    }
+    if (lane == kWave - 1) wave_sum[wave] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int w = 0; w < wave; ++w) before += wave_sum[w];
+    return before + inc - own;
+}
+
+// Stable scatter of one tile. offs / total = the scanned histogram: this tile's first item with
+// digit `bin` goes to (sum of total[] below bin) + offs[tile * bins + bin]. The tile is
 // first put in digit order in LDS (stable: rank among equal digits = ballots
 // inside a row of 64 + running per-wave counters + the waves before), then
 // written out in that order, so that consecutive lanes write consecutive
 // addresses of one digit's run instead of 64 scattered records. The ordered tile
-// passes through LDS in kParts slices (every item knows its place in the order;
-// a slice takes the items whose place falls into it): a whole tile of records
-// and keys, 80 KB, would leave room for one block per compute unit, a slice of
-// half a tile for three, which is what the registers allow.
+// passes through LDS in slices of at most kPart items (every item knows its place in
+// the order; a slice takes the items whose place falls into it): a whole tile of 4096
+// records and keys, 80 KB, would leave room for one block per compute unit, a slice of
+// half of it for two, which the registers allow (a third block, at 80 registers with spills: 0.62 and
+// 0.53 ms for the two passes over 64 M entries instead of 0.52 and 0.49). 20 bytes in and 20 out per
+// entry at 5 TB/s, the rate of a large copy.
 // `level1` (last pass only, else null): see the write-out.
-constexpr int kParts = 2;
-constexpr int kPart = kTile / kParts;
-__global__ __launch_bounds__(kThreads) void radix_scatter_kernel(
-    const TaserRec* __restrict__ rec_in, const int32_t* __restrict__ key_in, int64_t n, DigitSpec d,
-    const uint32_t* __restrict__ offs, uint32_t num_blocks, TaserRec* __restrict__ rec_out,
-    int32_t* __restrict__ key_out, int64_t* __restrict__ level1) {
-    __shared__ uint32_t wave_count[kWaves][kBins];   // items of each wave per digit, then exclusive over waves
-    __shared__ uint32_t block_base[kBins];           // global position of the block's first item of a digit
+constexpr int kMaxPart = 2048;
+template <bool kColumns, int kItems>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4))) void radix_scatter_kernel(
+    const Items in, int64_t n, DigitSpec d, const uint32_t* __restrict__ offs, const uint32_t* __restrict__ total,
+    uint32_t num_tiles, TaserRec* __restrict__ rec_out, int32_t* __restrict__ key_out, int64_t* __restrict__ level1) {
+    constexpr int kTile = kSortThreads * kItems;
+    constexpr int kPart = kTile < kMaxPart ? kTile : kMaxPart;
+    __shared__ uint16_t wave_count[kSortWaves][kBins];   // items of each wave per digit, then exclusive over waves
+    __shared__ uint32_t block_base[kBins];           // global position of the tile's first item of a digit
     __shared__ uint32_t local_base[kBins];           // position of that item inside the ordered tile
-    __shared__ uint32_t scan_tmp[kWaves];
+    __shared__ uint32_t scan_tmp[2][kSortWaves];
     __shared__ TaserRec tile_rec[kPart];
     __shared__ int32_t tile_key[kPart];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const uint32_t tile = tile_of_block(blockIdx.x, num_blocks);
-    if (tile >= num_blocks) return;
+    const uint32_t tile = tile_of_block(blockIdx.x, num_tiles);
+    if (tile >= num_tiles) return;
     const int64_t tile0 = (int64_t)tile * kTile;
-    for (int w = 0; w < kWaves; ++w) wave_count[w][threadIdx.x] = 0;
-    block_base[threadIdx.x] = offs[(size_t)threadIdx.x * num_blocks + tile];
-    __syncthreads();
+    const uint32_t count = n - tile0 < kTile ? (uint32_t)(n - tile0) : (uint32_t)kTile;   // items of this tile
+    const uint32_t mine = (uint32_t)wave * (kWave * kItems) + (uint32_t)lane;               // place of this lane's first item: rows
+                                                                                             // of 64 consecutive items per wave
 
-    uint32_t digit[kItems], rank[kItems];
     TaserRec item_rec[kItems];
     int32_t item_key[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const uint32_t i = mine + r * kWave;
+        if (i < count) {
+            item_key[r] = (in.key + tile0)[i];
+            if (kColumns) item_rec[r] = TaserRec{(in.ts + tile0)[i], (in.dst + tile0)[i], in.eid ? (in.eid + tile0)[i] : (int32_t)(tile0 + i)};
+            else item_rec[r] = (in.rec + tile0)[i];
+        }
+    }
+    const uint32_t own = threadIdx.x;   // the digit value this thread looks after
+    {
+        const bool live = own < (1u << d.bits);
+        const uint32_t all = live ? total[own] : 0u;
+        const uint32_t before = live ? offs[((size_t)tile << d.bits) + own] : 0u;
+        for (int w = 0; w < kSortWaves; ++w) wave_count[w][own] = 0;
+        block_base[own] = scan_digits(all, scan_tmp[0]) + before;   // (its barrier also covers the counters)
+    }
+
+    uint32_t rank[kItems];   // among the tile's items of its digit, the digit above bit 16 (one register for both)
     const uint64_t below = ((uint64_t)1 << lane) - 1;
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
-        const int64_t i = item_index(tile0, wave, r, lane);
-        const bool valid = i < n;
-        if (valid) {
-            item_rec[r] = rec_in[i];
-            item_key[r] = key_in[i];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-        const int64_t i = item_index(tile0, wave, r, lane);
-        const bool valid = i < n;
-        uint32_t dg = 0;
-        if (valid) dg = d.from_ts ? (uint32_t)(biased(item_rec[r].ts) >> d.shift) & d.mask : ((uint32_t)item_key[r] >> d.shift) & d.mask;
+        const bool valid = mine + r * kWave < count;
+        const uint32_t dg = valid ? digit_of(d, item_rec[r].ts, item_key[r]) : 0u;
         // lanes of this row that hold the same digit as me
         uint64_t same = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t has = __ballot(valid && ((dg >> b) & 1u));
-            same &= ((dg >> b) & 1u) ? has : ~has;
+        for (int b = 0; b < kMaxDigitBits; ++b) {
+            if (b < d.bits) {   // uniform
+                const uint64_t has = __ballot(valid && ((dg >> b) & 1u));
+                same &= ((dg >> b) & 1u) ? has : ~has;
+            }
         }
         const uint32_t before_me = (uint32_t)__popcll(same & below);
         uint32_t seen = 0;
         if (valid) seen = wave_count[wave][dg];            // equal for all lanes of a digit
-        if (valid && before_me == 0) wave_count[wave][dg] = seen + (uint32_t)__popcll(same);
-        digit[r] = dg;
-        rank[r] = seen + before_me;
+        if (valid && before_me == 0) wave_count[wave][dg] = (uint16_t)(seen + (uint32_t)__popcll(same));
+        rank[r] = (seen + before_me) | (dg << 16);
         __builtin_amdgcn_wave_barrier();   // keep the LDS counter update of row r ahead of row r+1's read
     }
     __syncthreads();
-    uint32_t mine_total = 0;
-    {   // per digit: exclusive prefix of the wave counts over the waves; thread b owns digit b
+    {   // per digit: exclusive prefix of the wave counts over the waves, then of the digit totals over the
+        // digits = where a digit's run starts in the tile
         uint32_t run = 0;
-        for (int w = 0; w < kWaves; ++w) {
-            const uint32_t c = wave_count[w][threadIdx.x];
-            wave_count[w][threadIdx.x] = run;
-            run += c;
+        for (int w = 0; w < kSortWaves; ++w) {
+            const uint32_t in_wave = wave_count[w][own];
+            wave_count[w][own] = (uint16_t)run;
+            run += in_wave;
         }
-        mine_total = run;
-    }
-    {   // exclusive prefix of the digit totals over the digits = where a digit's run starts in the tile
-        uint32_t inc = mine_total;
-        for (int dd = 1; dd < kWave; dd <<= 1) {
-            const uint32_t y = __shfl_up(inc, dd, kWave);
-            if (lane >= dd) inc += y;
-        }
-        if (lane == kWave - 1) scan_tmp[wave] = inc;
-        __syncthreads();
-        uint32_t before = 0;
-        for (int w = 0; w < wave; ++w) before += scan_tmp[w];
-        local_base[threadIdx.x] = before + inc - mine_total;
+        local_base[own] = scan_digits(run, scan_tmp[1]);
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kItems; ++r)   // rank becomes the item's place in the ordered tile
-        if (item_index(tile0, wave, r, lane) < n) rank[r] += local_base[digit[r]] + wave_count[wave][digit[r]];
-    const int64_t left = n - tile0;
-    const uint32_t count = left < kTile ? (uint32_t)left : (uint32_t)kTile;   // items of this tile
+        if (mine + r * kWave < count) rank[r] = (rank[r] & 0xffffu) + local_base[rank[r] >> 16] + wave_count[wave][rank[r] >> 16];
     for (uint32_t part0 = 0; part0 < count; part0 += kPart) {
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
             const uint32_t at = rank[r] - part0;   // wraps far beyond kPart for places before this slice
-            if (item_index(tile0, wave, r, lane) < n && at < (uint32_t)kPart) {
+            if (mine + r * kWave < count && at < (uint32_t)kPart) {
                 tile_rec[at] = item_rec[r];
                 tile_key[at] = item_key[r];
             }
         }
         __syncthreads();
-#pragma unroll 4
-        for (int r = 0; r < kItems / kParts; ++r) {
-            const uint32_t j = (uint32_t)r * kThreads + threadIdx.x;   // place inside the slice
+#pragma unroll 2
+        for (int r = 0; r < kPart / kSortThreads; ++r) {
+            const uint32_t j = (uint32_t)r * kSortThreads + threadIdx.x;   // place inside the slice
             if (part0 + j < count) {
                 const TaserRec rr = tile_rec[j];
                 const int32_t kk = tile_key[j];
-                const uint32_t dg = d.from_ts ? (uint32_t)(biased(rr.ts) >> d.shift) & d.mask : ((uint32_t)kk >> d.shift) & d.mask;
+                const uint32_t dg = digit_of(d, rr.ts, kk);
                 const uint32_t to = block_base[dg] + (part0 + j - local_base[dg]);
                 rec_out[to] = rr;
                 key_out[to] = kk;
@@ -371,188 +548,339 @@ __global__ __launch_bounds__(kThreads) void unpack_kernel(const TaserRec* __rest
     if (eid) eid[i] = r.eid;
 }
 
-// Device allocation released at scope exit unless taken over.
-struct DevBuf {
-    void* p = nullptr;
-    ~DevBuf() { if (p) (void)hipFree(p); }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1); }
-    template <typename T> T* as() const { return static_cast<T*>(p); }
-    template <typename T> T* release() { T* t = static_cast<T*>(p); p = nullptr; return t; }
-};
-
 inline unsigned blocks_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
-// Level 1 of the search index straight from the records, every further level from the one below.
-__global__ __launch_bounds__(kThreads) void time_index_first_kernel(const TaserRec* __restrict__ rec, int64_t n,
-                                                                    int64_t* __restrict__ out, int64_t len) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= len) return;
-    const int64_t last = 16 * (i + 1) - 1;
-    out[i] = rec[last < n ? last : n - 1].ts;
+// Levels 2 and up of the search index from level 1, which the last pass wrote: entry i of level l is
+// the level-1 entry of the last run of 16 records it covers. One launch for all of them.
+struct UpperLevels {
+    int64_t* out[kTimeIndexLevels - 1];    // level 2 first
+    int64_t end[kTimeIndexLevels - 1];     // running sum of their lengths
+};
+__global__ __launch_bounds__(kThreads) void time_index_upper_kernel(const int64_t* __restrict__ level1, int64_t len1,
+                                                                    UpperLevels up) {
+    const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    int64_t begin = 0;
+#pragma unroll
+    for (int l = 0; l < kTimeIndexLevels - 1; ++l) {
+        if (g >= begin && g < up.end[l]) {
+            const int64_t last = ((g - begin + 1) << (4 * (l + 1))) - 1;
+            up.out[l][g - begin] = level1[last < len1 ? last : len1 - 1];
+        }
+        begin = up.end[l];
+    }
 }
 
-__global__ __launch_bounds__(kThreads) void time_index_next_kernel(const int64_t* __restrict__ below, int64_t below_len,
-                                                                   int64_t* __restrict__ out, int64_t len) {
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= len) return;
-    const int64_t last = 16 * (i + 1) - 1;
-    out[i] = below[last < below_len ? last : below_len - 1];
+// ---- the two memory blocks of a build ----------------------------------------------
+// Items per thread of a tile: the large tile's longer runs per digit are what the scatter's writes
+// want, but with few entries its tiles do not fill 256 compute units and a pass takes the latency of
+// one tile. Whole builds, 2048- / 4096-item tiles, unsorted input: 20 k entries 112 / 120 us, 1.34 M
+// 160 / 163, 3 M 249 / 236, 12 M 717 / 677; sorted input 70 / 77, 91 / 97, 124 / 125, 319 / 316.
+constexpr int64_t kSmallEntries = (int64_t)1 << 21;
+inline int items_for(int64_t n) { return n <= kSmallEntries ? kSmallItems : kLargeItems; }
+
+struct Layout {
+    size_t indptr, rec, level[kTimeIndexLevels], storage;                                   // what the graph keeps
+    size_t src, dst, ts, eid, tmp_rec, key[2], hist, total, chunk_sum, partial, info, scratch;         // what the build needs
+    int64_t level_len[kTimeIndexLevels];
+    uint32_t tiles;
+};
+
+Layout layout_of(int64_t n, int32_t num_nodes, bool copy_input) {
+    Layout l = {};
+    size_t at = 0;
+    auto take = [&at](size_t bytes) {
+        const size_t here = at;
+        at += (bytes + 255) / 256 * 256;
+        return here;
+    };
+    l.indptr = take(((size_t)num_nodes + 1) * sizeof(int64_t));
+    l.rec = take((size_t)n * sizeof(TaserRec));
+    int64_t below = n;
+    for (int i = 0; i < kTimeIndexLevels; ++i) {
+        l.level_len[i] = below = (below + 15) / 16;
+        l.level[i] = take((size_t)below * sizeof(int64_t));
+    }
+    l.storage = at;
+    at = 0;
+    l.tiles = blocks_for(n, kSortThreads * items_for(n));
+    if (copy_input) {
+        l.src = take((size_t)n * sizeof(int32_t));
+        l.dst = take((size_t)n * sizeof(int32_t));
+        l.ts = take((size_t)n * sizeof(int64_t));
+        l.eid = take((size_t)n * sizeof(int32_t));
+    }
+    l.tmp_rec = take((size_t)n * sizeof(TaserRec));
+    l.key[0] = take((size_t)n * sizeof(int32_t));
+    l.key[1] = take((size_t)n * sizeof(int32_t));
+    l.hist = take((size_t)kBins * l.tiles * sizeof(uint32_t));
+    l.total = take(kBins * sizeof(uint32_t));
+    l.chunk_sum = take((size_t)kMaxChunks * kBins * sizeof(uint32_t));
+    l.partial = take((size_t)kInspectBlocks * 4 * sizeof(unsigned long long));
+    l.info = take(4 * sizeof(unsigned long long));
+    l.scratch = at;
+    return l;
 }
 
-}  // namespace
+int check_build_sizes(const char* what, int64_t num_entries, int32_t num_nodes, uint32_t flags) {
+    if (num_entries < 0 || num_entries >= 0x7fffffffLL) return taser_fail(TASER_E_RANGE, "%s: num_entries = %lld outside [0, 2^31 - 1)", what, (long long)num_entries);
+    if (num_nodes < 1 || num_nodes == 0x7fffffff) return taser_fail(TASER_E_RANGE, "%s: num_nodes = %d outside [1, 2^31 - 1)", what, num_nodes);
+    if (flags & ~(uint32_t)TASER_INPUT_ON_DEVICE) return taser_fail(TASER_E_ARG, "%s: unknown flags 0x%x", what, flags);
+    return TASER_OK;
+}
 
-
-extern "C" int taser_tcsr_build(const int32_t* src, const int32_t* dst, const int64_t* ts,
-                                const int32_t* eid, int64_t num_entries, int32_t num_nodes,
-                                uint32_t flags, void* hip_stream, taser_tcsr** out) {
-    if (!out) return taser_fail(TASER_E_ARG, "tcsr_build: null out");
-    *out = nullptr;
-    if (num_entries < 0 || num_entries >= 0x7fffffffLL) return taser_fail(TASER_E_RANGE, "tcsr_build: num_entries = %lld outside [0, 2^31 - 1)", (long long)num_entries);
-    if (num_nodes < 1 || num_nodes == 0x7fffffff) return taser_fail(TASER_E_RANGE, "tcsr_build: num_nodes = %d outside [1, 2^31 - 1)", num_nodes);
-    if (num_entries > 0 && (!src || !dst || !ts)) return taser_fail(TASER_E_ARG, "tcsr_build: null src/dst/ts");
-    if (flags & ~(uint32_t)TASER_INPUT_ON_DEVICE) return taser_fail(TASER_E_ARG, "tcsr_build: unknown flags 0x%x", flags);
-    taser_clear_stale_hip_error();
-    taser_resolve_device_constants();
-    hipStream_t stream = (hipStream_t)hip_stream;
-    const int64_t n = num_entries;
-
-    // ---- inputs in device memory
-    DevBuf in_src, in_dst, in_ts, in_eid;
-    if (!(flags & TASER_INPUT_ON_DEVICE) && n > 0) {
-        TASER_HIP_TRY(in_src.alloc(n * sizeof(int32_t)));
-        TASER_HIP_TRY(in_dst.alloc(n * sizeof(int32_t)));
-        TASER_HIP_TRY(in_ts.alloc(n * sizeof(int64_t)));
-        TASER_HIP_TRY(hipMemcpyAsync(in_src.p, src, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-        TASER_HIP_TRY(hipMemcpyAsync(in_dst.p, dst, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-        TASER_HIP_TRY(hipMemcpyAsync(in_ts.p, ts, n * sizeof(int64_t), hipMemcpyHostToDevice, stream));
-        src = in_src.as<int32_t>();
-        dst = in_dst.as<int32_t>();
-        ts = in_ts.as<int64_t>();
-        if (eid) {
-            TASER_HIP_TRY(in_eid.alloc(n * sizeof(int32_t)));
-            TASER_HIP_TRY(hipMemcpyAsync(in_eid.p, eid, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
-            eid = in_eid.as<int32_t>();
+template <int kItems>
+void launch_pass(const Layout& l, const Items& in, int64_t n, const DigitSpec& d, bool hist_known, uint32_t* hist, uint32_t* total, uint32_t* chunk_sum,
+                 TaserRec* rec_out, int32_t* key_out, int64_t* level1, hipStream_t stream) {
+    if (!hist_known) {
+        TaserProfileSpan span(stream, "tcsr_radix_hist");
+        hipLaunchKernelGGL((radix_hist_kernel<kItems>), dim3(l.tiles), dim3(kSortThreads), 0, stream, in, n, d, hist);
+    }
+    {
+        TaserProfileSpan span(stream, "tcsr_scan");
+        if (l.tiles >= kChunkedTiles) {
+            const uint32_t by_count = (l.tiles + kMaxChunks - 1) / kMaxChunks, rows = by_count > 64 ? by_count : 64;
+            const dim3 grid(((1u << d.bits) + kWave - 1) / kWave, (l.tiles + rows - 1) / rows);
+            hipLaunchKernelGGL(chunk_sum_kernel, grid, dim3(kThreads), 0, stream, hist, l.tiles, d.bits, rows, chunk_sum);
+            hipLaunchKernelGGL(chunk_scan_kernel, grid, dim3(kThreads), 0, stream, hist, l.tiles, d.bits, rows, chunk_sum, total);
+        } else {
+            hipLaunchKernelGGL(bin_scan_kernel, dim3(((1u << d.bits) + kScanCols - 1) / kScanCols), dim3(kScanThreads), 0, stream, hist,
+                               l.tiles, d.bits, total);
         }
     }
+    TaserProfileSpan span(stream, "tcsr_radix_scatter");
+    if (in.rec)
+        hipLaunchKernelGGL((radix_scatter_kernel<false, kItems>), dim3(pass_grid(l.tiles)), dim3(kSortThreads), 0, stream, in, n, d, hist,
+                           total, l.tiles, rec_out, key_out, level1);
+    else
+        hipLaunchKernelGGL((radix_scatter_kernel<true, kItems>), dim3(pass_grid(l.tiles)), dim3(kSortThreads), 0, stream, in, n, d, hist,
+                           total, l.tiles, rec_out, key_out, level1);
+}
 
-    // ---- pack into records, range check and sort plan in one pass over the input
-    DevBuf rec_a, key_a, rec_b, key_b, hist, partial, indptr;
-    TASER_HIP_TRY(rec_a.alloc(n * sizeof(TaserRec)));
-    TASER_HIP_TRY(key_a.alloc(n * sizeof(int32_t)));
-    unsigned long long info[4] = {0, 0, 0, ~0ull};
-    int node_bits = 0;
-    while (((int64_t)1 << node_bits) < (int64_t)num_nodes) ++node_bits;
-    const uint32_t num_blocks = blocks_for(n, kTile);
-    const int64_t hist_len = (int64_t)kBins * num_blocks;
-    const uint32_t low_digit_mask = (1u << (node_bits < 8 ? node_bits : 8)) - 1u;
-    if (n > 0) TASER_HIP_TRY(hist.alloc(hist_len * sizeof(uint32_t)));
+// Four words of page-locked host memory for one build's inspection result: the fold kernel writes
+// them there itself, so that planning the sort waits for a kernel and not for a copy behind it. 64
+// builds of the process can hold one at a time (a page that stays until it ends); a further one
+// reads its words back from the scratch block instead.
+struct PinnedInfo {
+    unsigned long long* words = nullptr;
+    PinnedInfo() {
+        std::lock_guard<std::mutex> lock(mutex());
+        State& s = state();
+        if (!s.page && !s.failed) {
+            void* p = nullptr;
+            if (hipHostMalloc(&p, 64 * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) s.page = static_cast<uint8_t*>(p);
+            else {
+                s.failed = true;
+                (void)hipGetLastError();
+            }
+        }
+        if (s.page && ~s.used) {
+            slot_ = __builtin_ctzll(~s.used);
+            s.used |= 1ull << slot_;
+            words = reinterpret_cast<unsigned long long*>(s.page + 64 * slot_);
+        }
+    }
+    ~PinnedInfo() {
+        if (!words) return;
+        std::lock_guard<std::mutex> lock(mutex());
+        state().used &= ~(1ull << slot_);
+    }
+    PinnedInfo(const PinnedInfo&) = delete;
+    PinnedInfo& operator=(const PinnedInfo&) = delete;
+
+private:
+    struct State {
+        uint8_t* page;
+        uint64_t used;
+        bool failed;
+    };
+    static State& state() { static State s = {nullptr, 0, false}; return s; }
+    static std::mutex& mutex() { static std::mutex m; return m; }
+    int slot_ = 0;
+};
+
+// The build itself, in `storage` and `scratch` (l.storage and l.scratch bytes of device memory, 256-byte
+// aligned). Synchronizes the stream before it returns TASER_OK.
+int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int64_t* ts, const int32_t* eid, int64_t n,
+             int32_t num_nodes, uint32_t flags, hipStream_t stream, uint8_t* storage, uint8_t* scratch, taser_tcsr** out) {
+    if (!(flags & TASER_INPUT_ON_DEVICE) && n > 0) {
+        TASER_HIP_TRY(hipMemcpyAsync(scratch + l.src, src, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+        TASER_HIP_TRY(hipMemcpyAsync(scratch + l.dst, dst, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+        TASER_HIP_TRY(hipMemcpyAsync(scratch + l.ts, ts, n * sizeof(int64_t), hipMemcpyHostToDevice, stream));
+        if (eid) TASER_HIP_TRY(hipMemcpyAsync(scratch + l.eid, eid, n * sizeof(int32_t), hipMemcpyHostToDevice, stream));
+        src = reinterpret_cast<const int32_t*>(scratch + l.src);
+        dst = reinterpret_cast<const int32_t*>(scratch + l.dst);
+        ts = reinterpret_cast<const int64_t*>(scratch + l.ts);
+        if (eid) eid = reinterpret_cast<const int32_t*>(scratch + l.eid);
+    }
+    const bool small = items_for(n) == kSmallItems;
+    int64_t* indptr = reinterpret_cast<int64_t*>(storage + l.indptr);
+    TaserRec* rec = reinterpret_cast<TaserRec*>(storage + l.rec);
+    int64_t* level1 = reinterpret_cast<int64_t*>(storage + l.level[0]);
+    uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
+    uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total);
+    uint32_t* chunk_sum = reinterpret_cast<uint32_t*>(scratch + l.chunk_sum);
+    const int32_t* sorted_key = src;
+
     if (n > 0) {
-        const unsigned grid = blocks_for(n, kTile);
-        constexpr unsigned kFoldBlocks = 128;
-        DevBuf d_partial, d_folded, d_info;
-        TASER_HIP_TRY(d_partial.alloc((size_t)grid * 4 * sizeof(unsigned long long)));
-        TASER_HIP_TRY(d_folded.alloc((size_t)kFoldBlocks * 4 * sizeof(unsigned long long)));
-        TASER_HIP_TRY(d_info.alloc(sizeof(info)));
+        // ---- what the input looks like
+        int node_bits = 0;
+        while (((int64_t)1 << node_bits) < (int64_t)num_nodes) ++node_bits;
+        // equal digits of at most kMaxDigitBits bits (one pass at least: it is what packs the records)
+        auto width_of = [](int bits) {
+            const int passes = (bits + kMaxDigitBits - 1) / kMaxDigitBits;
+            return passes > 0 ? (bits + passes - 1) / passes : 1;
+        };
+        unsigned long long info[4] = {0, 0, 0, ~0ull};
+        unsigned long long* partial = reinterpret_cast<unsigned long long*>(scratch + l.partial);
+        const PinnedInfo pinned;
+        unsigned long long* d_info = pinned.words ? pinned.words : reinterpret_cast<unsigned long long*>(scratch + l.info);
         {
-            TaserProfileSpan span(stream, "tcsr_pack_inspect");
-            hipLaunchKernelGGL(pack_inspect_kernel, dim3(grid), dim3(kThreads), 0, stream, src, dst, ts, eid, n, num_nodes,
-                               rec_a.as<TaserRec>(), key_a.as<int32_t>(), d_partial.as<unsigned long long>(), low_digit_mask,
-                               hist.as<uint32_t>(), num_blocks);
-            hipLaunchKernelGGL(fold_info_kernel, dim3(kFoldBlocks), dim3(kThreads), 0, stream,
-                               d_partial.as<unsigned long long>(), grid, d_folded.as<unsigned long long>());
-            hipLaunchKernelGGL(fold_info_kernel, dim3(1), dim3(kThreads), 0, stream, d_folded.as<unsigned long long>(),
-                               kFoldBlocks, d_info.as<unsigned long long>());
+            TaserProfileSpan span(stream, "tcsr_inspect");
+            const unsigned grid = l.tiles < kInspectBlocks ? l.tiles : kInspectBlocks;
+            if (small)
+                hipLaunchKernelGGL((inspect_kernel<kSmallItems>), dim3(grid), dim3(kSortThreads), 0, stream, src, ts, n, num_nodes, partial,
+                                   width_of(node_bits), hist, l.tiles);
+            else
+                hipLaunchKernelGGL((inspect_kernel<kLargeItems>), dim3(grid), dim3(kSortThreads), 0, stream, src, ts, n, num_nodes, partial,
+                                   width_of(node_bits), hist, l.tiles);
+            hipLaunchKernelGGL(fold_info_kernel, dim3(1), dim3(kSortThreads), 0, stream, partial, grid, d_info);
         }
         TASER_HIP_TRY(hipGetLastError());
-        TASER_HIP_TRY(hipMemcpyAsync(info, d_info.p, sizeof(info), hipMemcpyDeviceToHost, stream));
+        if (!pinned.words) TASER_HIP_TRY(hipMemcpyAsync(info, d_info, sizeof(info), hipMemcpyDeviceToHost, stream));
         TASER_HIP_TRY(hipStreamSynchronize(stream));
+        if (pinned.words)
+            for (int j = 0; j < 4; ++j) info[j] = __atomic_load_n(&pinned.words[j], __ATOMIC_RELAXED);
         if (info[0]) return taser_fail(TASER_E_RANGE, "tcsr_build: a src node id is outside [0, %d)", num_nodes);
-    }
-    std::vector<DigitSpec> passes;
-    if (info[1]) {
-        const unsigned long long differ = info[2] & ~info[3];
-        for (int b = 0; b < 8; ++b)
-            if ((differ >> (8 * b)) & 0xffull) passes.push_back(DigitSpec{1, 8 * b, 0xffu});
-    }
-    const bool first_hist_known = passes.empty();   // no timestamp passes: the first digit is the one pack_inspect_kernel counted
-    for (int shift = 0; shift < node_bits; shift += 8) {
-        const int width = node_bits - shift < 8 ? node_bits - shift : 8;
-        passes.push_back(DigitSpec{0, shift, (1u << width) - 1u});
-    }
-
-    // ---- search index over the sorted timestamps: storage (level 1 is written by the last sorting pass)
-    TaserTimeIndex index = {};
-    index.num_entries = n;
-    int64_t index_total = 0, level_at[kTimeIndexLevels];
-    for (int l = 0; l < kTimeIndexLevels; ++l) {
-        const int64_t below = l == 0 ? n : index.len[l - 1];
-        index.len[l] = (below + 15) / 16;
-        level_at[l] = index_total;
-        index_total += index.len[l];
-    }
-    DevBuf index_storage;
-    TASER_HIP_TRY(index_storage.alloc((size_t)(index_total > 0 ? index_total : 1) * sizeof(int64_t)));
-    for (int l = 0; l < kTimeIndexLevels; ++l) index.level[l] = index_storage.as<int64_t>() + level_at[l];
-    // ---- one stable pass per digit, ping-pong between two buffers
-    TASER_HIP_TRY(indptr.alloc(((size_t)num_nodes + 1) * sizeof(int64_t)));
-    const unsigned scan_blocks = taser_scan::num_partials(hist_len);
-    if (n > 0) {
-        if (!passes.empty()) {
-            TASER_HIP_TRY(rec_b.alloc(n * sizeof(TaserRec)));
-            TASER_HIP_TRY(key_b.alloc(n * sizeof(int32_t)));
-            TASER_HIP_TRY(partial.alloc((size_t)scan_blocks * sizeof(uint32_t)));
+        int ts_low = 0, ts_bits = 0;
+        if (info[1]) {
+            const unsigned long long differ = info[2] & ~info[3];   // not 0: the timestamps are not all equal
+            ts_low = __builtin_ctzll(differ);
+            ts_bits = 64 - __builtin_clzll(differ) - ts_low;
         }
-        for (size_t pass = 0; pass < passes.size(); ++pass) {
-            const DigitSpec& d = passes[pass];
-            if (pass > 0 || !first_hist_known) {
-                TaserProfileSpan span(stream, "tcsr_radix_hist");
-                hipLaunchKernelGGL(radix_hist_kernel, dim3(num_blocks), dim3(kThreads), 0, stream,
-                                   rec_a.as<TaserRec>(), key_a.as<int32_t>(), n, d, hist.as<uint32_t>(), num_blocks);
+
+        // ---- one stable pass per digit; the last one writes the graph's own records
+        const int key_bits = ts_bits + node_bits;
+        const int width = width_of(key_bits);
+        const int passes = key_bits > 0 ? (key_bits + width - 1) / width : 1;
+        TaserRec* tmp_rec = reinterpret_cast<TaserRec*>(scratch + l.tmp_rec);
+        Items in = {nullptr, src, dst, ts, eid};
+        for (int pass = 0; pass < passes; ++pass) {
+            const int s = pass * width;
+            DigitSpec d = {};
+            d.bits = key_bits - s < width ? key_bits - s : width;
+            if (d.bits < 1) d.bits = 1;               // a single node and sorted input: every digit is 0
+            if (s < ts_bits) {
+                const int have = ts_bits - s;         // timestamp bits from here on
+                d.from_ts = 1;
+                d.ts_shift = ts_low + s;
+                d.ts_mask = (1u << (have < d.bits ? have : d.bits)) - 1u;
+                d.node_left = have < 31 ? have : 31;
+            } else {
+                d.node_right = s - ts_bits;
             }
-            {
-                TaserProfileSpan span(stream, "tcsr_scan");
-                taser_scan::exclusive_scan_u32(hist.as<uint32_t>(), hist_len, partial.as<uint32_t>(), stream);
-            }
-            {
-                TaserProfileSpan span(stream, "tcsr_radix_scatter");
-                hipLaunchKernelGGL(radix_scatter_kernel, dim3(pass_grid(num_blocks)), dim3(kThreads), 0, stream,
-                                   rec_a.as<TaserRec>(), key_a.as<int32_t>(), n, d, hist.as<uint32_t>(), num_blocks,
-                                   rec_b.as<TaserRec>(), key_b.as<int32_t>(),
-                                   pass + 1 == passes.size() ? index_storage.as<int64_t>() + level_at[0] : nullptr);
-            }
-            void* t = rec_a.p; rec_a.p = rec_b.p; rec_b.p = t;
-            t = key_a.p; key_a.p = key_b.p; key_b.p = t;
+            const bool last = pass + 1 == passes;
+            TaserRec* rec_out = ((passes - 1 - pass) & 1) ? tmp_rec : rec;
+            int32_t* key_out = reinterpret_cast<int32_t*>(scratch + l.key[pass & 1]);
+            // without timestamp digits the first digit is the one that inspect_kernel counted
+            const bool hist_known = pass == 0 && ts_bits == 0;
+            if (small) launch_pass<kSmallItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
+            else launch_pass<kLargeItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
+            in = Items{rec_out, key_out, nullptr, nullptr, nullptr};
+            sorted_key = key_out;
         }
     }
     {
         TaserProfileSpan span(stream, "tcsr_indptr");
-        hipLaunchKernelGGL(indptr_kernel, dim3(blocks_for(n + 1, kThreads * 4)), dim3(kThreads), 0, stream,
-                           key_a.as<int32_t>(), n, num_nodes, indptr.as<int64_t>());
+        hipLaunchKernelGGL(indptr_kernel, dim3(blocks_for(n + 1, kThreads * 4)), dim3(kThreads), 0, stream, sorted_key, n, num_nodes, indptr);
+    }
+    TaserTimeIndex index = {};
+    index.num_entries = n;
+    for (int i = 0; i < kTimeIndexLevels; ++i) {
+        index.len[i] = l.level_len[i];
+        index.level[i] = reinterpret_cast<int64_t*>(storage + l.level[i]);
     }
     if (n > 0) {
         TaserProfileSpan span(stream, "tcsr_time_index");
-        if (passes.empty())   // nothing was sorted: level 1 from the records as they are
-            hipLaunchKernelGGL(time_index_first_kernel, dim3(blocks_for(index.len[0], kThreads)), dim3(kThreads), 0, stream,
-                               rec_a.as<TaserRec>(), n, index_storage.as<int64_t>() + level_at[0], index.len[0]);
-        for (int l = 1; l < kTimeIndexLevels; ++l)
-            hipLaunchKernelGGL(time_index_next_kernel, dim3(blocks_for(index.len[l], kThreads)), dim3(kThreads), 0, stream,
-                               index.level[l - 1], index.len[l - 1], index_storage.as<int64_t>() + level_at[l],
-                               index.len[l]);
+        UpperLevels up;
+        int64_t end = 0;
+        for (int i = 1; i < kTimeIndexLevels; ++i) {
+            up.out[i - 1] = reinterpret_cast<int64_t*>(storage + l.level[i]);
+            up.end[i - 1] = end += l.level_len[i];
+        }
+        hipLaunchKernelGGL(time_index_upper_kernel, dim3(blocks_for(end, kThreads)), dim3(kThreads), 0, stream, level1, l.level_len[0], up);
     }
     TASER_HIP_TRY(hipGetLastError());
     TASER_HIP_TRY(hipStreamSynchronize(stream));
 
     taser_tcsr* g = new (std::nothrow) taser_tcsr();
     if (!g) return taser_fail(TASER_E_OOM, "tcsr_build: host allocation failed");
+    *g = taser_tcsr{};
     g->num_entries = n;
     g->num_nodes = num_nodes;
-    g->indptr = indptr.release<int64_t>();
-    g->rec = rec_a.release<TaserRec>();
-    g->time_index_storage = index_storage.release<int64_t>();
+    g->indptr = indptr;
+    g->rec = rec;
     g->time_index = index;
-    g->ts_only = nullptr;
     *out = g;
     return TASER_OK;
+}
+
+}  // namespace
+
+extern "C" int taser_tcsr_build(const int32_t* src, const int32_t* dst, const int64_t* ts,
+                                const int32_t* eid, int64_t num_entries, int32_t num_nodes,
+                                uint32_t flags, void* hip_stream, taser_tcsr** out) {
+    if (!out) return taser_fail(TASER_E_ARG, "tcsr_build: null out");
+    *out = nullptr;
+    const int bad = check_build_sizes("tcsr_build", num_entries, num_nodes, flags);
+    if (bad != TASER_OK) return bad;
+    if (num_entries > 0 && (!src || !dst || !ts)) return taser_fail(TASER_E_ARG, "tcsr_build: null src/dst/ts");
+    taser_clear_stale_hip_error();
+    taser_resolve_device_constants();
+    const Layout l = layout_of(num_entries, num_nodes, !(flags & TASER_INPUT_ON_DEVICE));
+    void *storage = nullptr, *scratch = nullptr;
+    hipError_t e = hipMalloc(&storage, l.storage);
+    if (e == hipSuccess) e = hipMalloc(&scratch, l.scratch);
+    int rc = e == hipSuccess ? TASER_OK : taser_fail_hip(e, "tcsr_build: hipMalloc");
+    if (rc == TASER_OK)
+        rc = build_in(l, src, dst, ts, eid, num_entries, num_nodes, flags, (hipStream_t)hip_stream, static_cast<uint8_t*>(storage),
+                      static_cast<uint8_t*>(scratch), out);
+    (void)hipFree(scratch);
+    if (rc == TASER_OK) (*out)->owned_storage = storage;
+    else (void)hipFree(storage);
+    return rc;
+}
+
+extern "C" int taser_tcsr_build_bytes(int64_t num_entries, int32_t num_nodes, uint32_t flags, uint64_t* storage_bytes,
+                                      uint64_t* scratch_bytes) {
+    const int bad = check_build_sizes("tcsr_build_bytes", num_entries, num_nodes, flags);
+    if (bad != TASER_OK) return bad;
+    const Layout l = layout_of(num_entries, num_nodes, !(flags & TASER_INPUT_ON_DEVICE));
+    if (storage_bytes) *storage_bytes = l.storage;
+    if (scratch_bytes) *scratch_bytes = l.scratch;
+    return TASER_OK;
+}
+
+extern "C" int taser_tcsr_build_in(const int32_t* src, const int32_t* dst, const int64_t* ts,
+                                   const int32_t* eid, int64_t num_entries, int32_t num_nodes,
+                                   uint32_t flags, void* hip_stream, void* storage, uint64_t storage_bytes,
+                                   void* scratch, uint64_t scratch_bytes, taser_tcsr** out) {
+    if (!out) return taser_fail(TASER_E_ARG, "tcsr_build_in: null out");
+    *out = nullptr;
+    const int bad = check_build_sizes("tcsr_build_in", num_entries, num_nodes, flags);
+    if (bad != TASER_OK) return bad;
+    if (num_entries > 0 && (!src || !dst || !ts)) return taser_fail(TASER_E_ARG, "tcsr_build_in: null src/dst/ts");
+    const Layout l = layout_of(num_entries, num_nodes, !(flags & TASER_INPUT_ON_DEVICE));
+    if (!storage || !scratch) return taser_fail(TASER_E_ARG, "tcsr_build_in: null storage or scratch");
+    if (((uintptr_t)storage | (uintptr_t)scratch) & 255) return taser_fail(TASER_E_ARG, "tcsr_build_in: storage and scratch must be 256-byte aligned");
+    if (storage_bytes < l.storage || scratch_bytes < l.scratch)
+        return taser_fail(TASER_E_RANGE, "tcsr_build_in: %llu bytes of storage and %llu of scratch are needed", (unsigned long long)l.storage,
+                          (unsigned long long)l.scratch);
+    taser_clear_stale_hip_error();
+    taser_resolve_device_constants();
+    const int rc = build_in(l, src, dst, ts, eid, num_entries, num_nodes, flags, (hipStream_t)hip_stream, static_cast<uint8_t*>(storage),
+                            static_cast<uint8_t*>(scratch), out);
+    if (rc == TASER_OK && hipGetDevice(&(*out)->device) != hipSuccess) (*out)->device = -1;
+    return rc;
 }
 
 extern "C" int taser_tcsr_size(const taser_tcsr* g, int64_t* num_entries, int32_t* num_nodes) {
@@ -580,9 +908,17 @@ extern "C" int taser_tcsr_view(const taser_tcsr* g, int64_t* indptr, int32_t* nb
 
 extern "C" void taser_tcsr_free(taser_tcsr* g) {
     if (!g) return;
-    (void)hipFree(g->indptr);
-    (void)hipFree(g->rec);
-    (void)hipFree(g->time_index_storage);
+    if (g->owned_storage) {
+        (void)hipFree(g->owned_storage);
+    } else {
+        // the storage is the caller's and may go to other uses as soon as this returns: wait, as hipFree
+        // does, for whatever still reads it on any stream of the graph's device
+        int current = -1;
+        const bool other = g->device >= 0 && hipGetDevice(&current) == hipSuccess && current != g->device;
+        if (other) (void)hipSetDevice(g->device);
+        (void)hipDeviceSynchronize();
+        if (other) (void)hipSetDevice(current);
+    }
     (void)hipFree(g->ts_only);
     delete g;
 }

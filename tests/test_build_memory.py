@@ -1,0 +1,96 @@
+"""The T-CSR build at the edges of its tiles, digits and scans, and in memory of the caller's."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_05396_amd as T
+
+THREADS = min(16, oracle.max_threads())
+
+
+def _entries(n, nodes, ts_bits, shift, ordered, seed):
+    """`n` entries whose timestamps differ in `ts_bits` bits above bit `shift` (both ends of that range do differ)."""
+    rng = np.random.default_rng(seed)
+    src = (rng.zipf(1.3, n) % nodes).astype(np.int32)
+    ts = (rng.integers(0, 1 << ts_bits, n, dtype=np.int64) << shift) - (1 << 20)
+    if n > 1 and ts_bits:
+        ts[0], ts[-1] = -(1 << 20), (((1 << ts_bits) - 1) << shift) - (1 << 20)
+    if ordered:
+        ts.sort()
+    return src, rng.integers(0, nodes, n).astype(np.int32), ts, rng.permutation(n).astype(np.int32)
+
+
+def _check(g, ref):
+    for name, a, b in zip(("indptr", "nbr", "ts", "eid"), T.tcsr_view(g), ref):
+        assert np.array_equal(a.cpu().numpy(), b), name
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,nodes,ts_bits,shift,ordered", [
+    (1, 1, 0, 0, True), (5, 1, 0, 0, True), (3000, 1, 7, 3, False),          # no node digit at all
+    (2047, 600, 9, 0, False), (2048, 600, 10, 5, False), (2049, 513, 17, 40, False),   # small tiles; a digit of both parts
+    (5000, 512, 18, 0, False), (5000, 513, 62, 0, False), (100_001, 3, 1, 33, False),
+    (1 << 21, 1000, 12, 0, True), ((1 << 21) + 1, 1000, 12, 0, True), ((1 << 21) + 1, 1025, 13, 2, False),   # tile size changes
+    (8_388_607, 300, 20, 0, True), (8_388_609, 70_000, 3, 0, False),         # the two scans of the histogram
+])
+def test_build_matches_the_oracle(n, nodes, ts_bits, shift, ordered):
+    src, dst, ts, eid = _entries(n, nodes, ts_bits, shift, ordered, n + ts_bits)
+    g = T.tcsr_build(*(torch.from_numpy(x).cuda() for x in (src, dst, ts, eid)), nodes)
+    _check(g, oracle.tcsr_build(src, dst, ts, eid, nodes, THREADS))
+
+
+@pytest.mark.gpu
+def test_build_in_the_callers_memory():
+    src, dst, ts, eid = _entries(10_000, 77, 20, 0, False, 9)
+    ref = oracle.tcsr_build(src, dst, ts, eid, 77, THREADS)
+    host = [torch.from_numpy(x) for x in (src, dst, ts, eid)]
+    for on_device in (True, False):
+        args = [t.cuda() for t in host] if on_device else host
+        storage, scratch = (torch.full((b,), 0xA5, dtype=torch.uint8, device="cuda") for b in T.tcsr_build_bytes(10_000, 77, on_device))
+        g = T.tcsr_build_in(*args, 77, storage, scratch)
+        scratch.fill_(0x5A)                      # the graph does not need it any more
+        _check(g, ref)
+        g.free()
+        storage.fill_(0x5A)                      # nor, once freed, its storage
+        with pytest.raises(T.TaserError):
+            T.tcsr_build_in(*args, 77, storage, scratch[:-256].contiguous())
+        with pytest.raises(T.TaserError):
+            T.tcsr_build_in(*args, 77, torch.empty(storage.numel() + 8, dtype=torch.uint8, device="cuda")[8:], scratch)
+        g2 = T.tcsr_build_in(*args, 77, storage, scratch)   # the same blocks again
+        _check(g2, ref)
+
+
+@pytest.mark.gpu
+def test_plain_c_build_owns_its_memory():
+    src, dst, ts, eid = (torch.from_numpy(x).cuda() for x in _entries(5000, 40, 15, 0, False, 3))
+    h = ctypes.c_void_p()
+    torch.cuda.synchronize()
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert T.lib().taser_tcsr_build(p(src), p(dst), p(ts), p(eid), 5000, 40, T.INPUT_ON_DEVICE, None, ctypes.byref(h)) == 0
+    g = T.TCSR(h, 5000, 40)
+    torch.cuda.synchronize()
+    _check(g, oracle.tcsr_build(*(t.cpu().numpy() for t in (src, dst, ts, eid)), 40, THREADS))
+    g.free()
+
+
+def test_build_bytes_without_a_gpu():
+    storage, scratch = T.tcsr_build_bytes(1000, 10)
+    assert storage >= 1000 * 16 + 11 * 8 and scratch >= 1000 * 24
+    assert T.tcsr_build_bytes(1000, 10, False)[1] >= scratch + 1000 * 20
+    assert T.tcsr_build_bytes(0, 1)[0] >= 16
+    for n, nodes in ((-1, 3), (2 ** 31, 3), (4, 0)):
+        with pytest.raises(T.TaserError) as e:
+            T.tcsr_build_bytes(n, nodes)
+        assert e.value.code == -2
+    one, h = ctypes.c_void_p(256), ctypes.c_void_p()
+    build = T.lib().taser_tcsr_build_in
+    big = 1 << 40
+    assert build(one, one, one, None, 4, 3, 1, None, one, big, one, big, None) == -1
+    assert build(one, one, one, None, 4, 3, 1, None, None, big, one, big, ctypes.byref(h)) == -1
+    assert build(one, one, one, None, 4, 3, 1, None, ctypes.c_void_p(264), big, one, big, ctypes.byref(h)) == -1
+    assert build(one, one, one, None, 4, 3, 1, None, one, 8, one, big, ctypes.byref(h)) == -2
+    assert build(one, one, one, None, 4, 3, 1, None, one, big, one, 8, ctypes.byref(h)) == -2
+    assert build(None, one, one, None, 4, 3, 1, None, one, big, one, big, ctypes.byref(h)) == -1
