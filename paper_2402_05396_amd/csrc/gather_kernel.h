@@ -2,16 +2,17 @@
 //
 // The output is treated as one flat, dense stream, whatever the row length.
 // Two kernels:
-//   * gather_chunks_kernel (rows a multiple of 4 bytes, 16-byte aligned
-//     output): every thread produces 16 consecutive output bytes with one
-//     aligned 16-byte non-temporal store. The 16 bytes normally come from one
-//     source row and are read with a single 16-byte load that only needs 4-byte
-//     alignment; a thread whose bytes straddle a row end falls back to 4-byte
-//     loads. A wave instruction therefore moves 1 KiB, rows of any length
+//   * gather_chunks_kernel (16-byte aligned output; rows a multiple of 4 bytes,
+//     or of 2 bytes and at least 16 long): every thread produces 16 consecutive
+//     output bytes with one aligned 16-byte non-temporal store. The 16 bytes
+//     normally come from one source row and are read with a single 16-byte load
+//     that only needs the rows' alignment; a thread whose bytes straddle a row
+//     end falls back to 4-byte loads (2-byte rows: two 16-byte loads). A wave instruction therefore moves 1 KiB, rows of any length
 //     (372 B, 1652 B, ...) fill every lane, and the dense output is written in
 //     whole 128-byte lines.
-//   * gather_elems_kernel: the same flat scheme with one V-wide element (2, 4,
-//     8 or 16 bytes) per thread, for rows or bases that are only 2-byte aligned.
+//   * gather_elems_kernel: the same flat scheme with one V-wide element (2, 4
+//     or 8 bytes) per thread, for outputs that are not 16-byte aligned and for
+//     2-byte aligned rows shorter than 16 bytes.
 // Where a row comes from is a functor, so the kernels serve both a table in
 // device memory and the cache's choice of cache row / staged row / host row.
 #pragma once
@@ -25,21 +26,29 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 template <typename V> __device__ __forceinline__ V zero_of() { return V(0); }
-template <> __device__ __forceinline__ u32x4 zero_of<u32x4>() { return u32x4{0, 0, 0, 0}; }
 template <> __device__ __forceinline__ u32x2 zero_of<u32x2>() { return u32x2{0, 0}; }
 
 constexpr int kThreads = 256;
 constexpr int kUnroll = 4;
 constexpr int kTile = kThreads * kUnroll;   // elements (or 16-byte chunks) per block
 constexpr int kMaxTileRows = kTile * 4 + 2; // output rows a block of the chunk kernel can touch (rows of one dword)
+constexpr int kMaxTileLongRows = kTile + 2;  // and with rows of at least 16 bytes
 
-// 16 bytes that are only known to be 4-byte aligned.
+// 16 bytes that are only known to be 4-byte (2-byte) aligned.
 struct __attribute__((packed, aligned(4))) Chunk16 {
+    u32x4 v;
+};
+struct __attribute__((packed, aligned(2))) Chunk16By2 {
     u32x4 v;
 };
 
 typedef const __attribute__((address_space(1))) Chunk16* GlobalChunk16Ptr;
+typedef const __attribute__((address_space(1))) Chunk16By2* GlobalChunk16By2Ptr;
 typedef const __attribute__((address_space(1))) uint32_t* GlobalU32Ptr;
+
+template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) {
+    return ALIGN == 2 ? ((GlobalChunk16By2Ptr)at)->v : ((GlobalChunk16Ptr)at)->v;
+}
 
 // A Source says where output row i comes from, in two steps so that the kernel
 // can issue the (dependent) loads of several rows back to back:
@@ -47,29 +56,34 @@ typedef const __attribute__((address_space(1))) uint32_t* GlobalU32Ptr;
 //   address(key, i) first byte of the source row, or nullptr for a zero row.
 // row(i) is the two combined.
 
+// UNIT: the size that divides rows, pitches and source addresses, 4 or 2 bytes; offsets are counted
+// in it. With 2-byte units the rows are at least 16 bytes long. (One 16-byte load at any even address
+// costs what an aligned one does: 1.33 M rows of 826 bytes take 0.20 ms, where a load and a store per
+// 2 bytes took 0.71.)
 // USE_MAGIC: floor(e / d) = umulhi(e, magic) with magic = ceil(2^32 / d), exact
 // for e * d < 2^32 (the launcher checks that); otherwise a plain division.
-template <typename Source, bool USE_MAGIC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_chunks_kernel(Source source, uint32_t row_dwords, uint32_t magic,
-                                                                 int64_t total_dwords, int64_t last_row,
+template <typename Source, bool USE_MAGIC, int UNIT>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_chunks_kernel(Source source, uint32_t row_units, uint32_t magic,
+                                                                 int64_t total_units, int64_t last_row,
                                                                  const uint8_t* __restrict__ zeros,
-                                                                 uint32_t* __restrict__ out) {
-    const int64_t tile = (int64_t)blockIdx.x * (kTile * 4);   // first output dword of this block
+                                                                 uint8_t* __restrict__ out) {
+    constexpr uint32_t kPer = 16 / UNIT;                       // units of a chunk
+    const int64_t tile = (int64_t)blockIdx.x * (kTile * kPer);   // first output unit of this block
     int64_t row0;                                               // output row holding it
-    if (tile < ((int64_t)1 << 32)) row0 = (uint32_t)tile / row_dwords;
-    else row0 = tile / (int64_t)row_dwords;
-    const uint32_t col0 = (uint32_t)(tile - row0 * row_dwords);
+    if (tile < ((int64_t)1 << 32)) row0 = (uint32_t)tile / row_units;
+    else row0 = tile / (int64_t)row_units;
+    const uint32_t col0 = (uint32_t)(tile - row0 * row_units);
 
     // Pass 0: the tokens of every output row this tile touches, loaded once by consecutive
     // lanes into LDS. Without it each chunk's token is a wave-wide broadcast load at the head of
     // a chain of two dependent loads, and the kernel's speed follows the latency of the token
     // array (slower by a third when that array has dropped out of the memory-side cache).
-    __shared__ int32_t tile_key[kMaxTileRows];
+    __shared__ int32_t tile_key[UNIT == 4 ? kMaxTileRows : kMaxTileLongRows];
     {
-        int64_t tile_last = tile + kTile * 4 - 1;
-        if (tile_last >= total_dwords) tile_last = total_dwords - 1;
-        const uint32_t e_last = col0 + (uint32_t)(tile_last - tile);   // dword offset from the start of row0
-        const int rows_here = (int)(USE_MAGIC ? __umulhi(e_last, magic) : e_last / row_dwords) + 1;   // <= kMaxTileRows
+        int64_t tile_last = tile + kTile * kPer - 1;
+        if (tile_last >= total_units) tile_last = total_units - 1;
+        const uint32_t e_last = col0 + (uint32_t)(tile_last - tile);   // unit offset from the start of row0
+        const int rows_here = (int)(USE_MAGIC ? __umulhi(e_last, magic) : e_last / row_units) + 1;   // <= the array
         for (int r = threadIdx.x; r < rows_here; r += kThreads) tile_key[r] = source.key(row0 + r);
         __syncthreads();
     }
@@ -79,13 +93,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     bool whole[kUnroll], cross[kUnroll];   // inside one row / crossing a row end (neither: past the end)
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-        const uint32_t local = (threadIdx.x + u * kThreads) * 4u;
-        const uint32_t e = col0 + local;                        // dword offset from the start of row0
-        const uint32_t dr = USE_MAGIC ? __umulhi(e, magic) : e / row_dwords;
-        col[u] = e - dr * row_dwords;
+        const uint32_t local = (threadIdx.x + u * kThreads) * kPer;
+        const uint32_t e = col0 + local;                        // unit offset from the start of row0
+        const uint32_t dr = USE_MAGIC ? __umulhi(e, magic) : e / row_units;
+        col[u] = e - dr * row_units;
         row[u] = row0 + dr;
-        const bool live = tile + local < total_dwords;
-        whole[u] = live && col[u] + 4u <= row_dwords;
+        const bool live = tile + local < total_units;
+        whole[u] = live && col[u] + kPer <= row_units;
         cross[u] = live && !whole[u];
         if (row[u] > last_row) row[u] = last_row;               // keeps the token read below in bounds
     }
@@ -99,21 +113,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const uint8_t* base = source.address(key[u], row[u]);
-        const uint8_t* at = (whole[u] && base) ? base + (size_t)col[u] * 4u : zeros;
-        vals[u] = ((GlobalChunk16Ptr)at)->v;
+        const uint8_t* at = (whole[u] && base) ? base + (size_t)col[u] * UNIT : zeros;
+        vals[u] = load16<UNIT>(at);
     }
-    // Pass 3 (rare): chunks that cross one or more row ends, dword by dword.
+    // Pass 3 (rare): chunks that cross one or more row ends.
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         if (!cross[u]) continue;
-        const int64_t d = tile + (threadIdx.x + u * kThreads) * 4u;
+        const int64_t d = tile + (threadIdx.x + u * kThreads) * kPer;
+        if (UNIT == 2) {
+            // one row end (rows hold at least 16 bytes): the last 16 bytes of this row, the first 16 of
+            // the next one, and of those 32 the 16 that start where this row has `in_row` bytes left
+            const uint32_t in_row = (row_units - col[u]) * 2u;                    // 2 .. 14
+            const uint8_t* base = source.address(key[u], row[u]);
+            const uint8_t* next = row[u] < last_row ? source.address(tile_key[row[u] + 1 - row0], row[u] + 1) : nullptr;
+            const u32x4 t = load16<UNIT>(base ? base + (size_t)row_units * 2u - 16u : zeros);
+            const u32x4 h = load16<UNIT>(next ? next : zeros);
+            const uint32_t skip = 16u - in_row;                                   // bytes of t that belong to the chunk before
+            const bool by2 = skip & 8u, by1 = skip & 4u, half = skip & 2u;
+            const uint32_t y0 = by2 ? t.z : t.x, y1 = by2 ? t.w : t.y, y2 = by2 ? h.x : t.z, y3 = by2 ? h.y : t.w, y4 = by2 ? h.z : h.x,
+                           y5 = by2 ? h.w : h.y;
+            const uint32_t z0 = by1 ? y1 : y0, z1 = by1 ? y2 : y1, z2 = by1 ? y3 : y2, z3 = by1 ? y4 : y3, z4 = by1 ? y5 : y4;
+            vals[u] = u32x4{half ? __builtin_amdgcn_alignbyte(z1, z0, 2) : z0, half ? __builtin_amdgcn_alignbyte(z2, z1, 2) : z1,
+                            half ? __builtin_amdgcn_alignbyte(z3, z2, 2) : z2, half ? __builtin_amdgcn_alignbyte(z4, z3, 2) : z3};
+            continue;
+        }
         uint32_t c = col[u];
         int64_t r = row[u];
         uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            if (c >= row_dwords) { c = 0; ++r; }
-            if (d + i < total_dwords) {
+            if (c >= row_units) { c = 0; ++r; }
+            if (d + i < total_units) {
                 const uint8_t* base = source.address(tile_key[r - row0], r);
                 if (base) w[i] = ((GlobalU32Ptr)base)[c];
             }
@@ -123,14 +154,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-        const int64_t d = tile + (threadIdx.x + u * kThreads) * 4u;
-        if (d + 4 <= total_dwords) {
-            __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(out + d));
+        const int64_t d = tile + (threadIdx.x + u * kThreads) * kPer;
+        if (d + kPer <= total_units) {
+            __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(out + d * UNIT));
         } else {
             const uint32_t w[4] = {vals[u].x, vals[u].y, vals[u].z, vals[u].w};
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (d + i < total_dwords) out[d + i] = w[i];
+            for (int i = 0; i < (int)kPer; ++i) {
+                if (d + i >= total_units) continue;
+                if (UNIT == 4) reinterpret_cast<uint32_t*>(out)[d + i] = w[i];
+                else reinterpret_cast<uint16_t*>(out)[d + i] = (uint16_t)(w[i / 2] >> (16 * (i & 1)));
+            }
         }
     }
 }
@@ -314,6 +348,26 @@ inline void launch_elems(const Source& source, int32_t row_bytes, int64_t n, voi
                        row_elems, total, reinterpret_cast<V*>(out));
 }
 
+// Flat gather in 16-byte chunks of the output; UNIT (4 or 2) divides everything.
+template <int UNIT, typename Source>
+inline bool launch_chunks(const Source& source, int32_t row_bytes, int64_t n, void* out, const uint8_t* zeros, hipStream_t stream) {
+    const uint32_t row_units = (uint32_t)row_bytes / UNIT, tile_units = kTile * (16 / UNIT);
+    const int64_t total = n * (int64_t)row_units;
+    const int64_t blocks = (total + tile_units - 1) / tile_units;
+    if (blocks > 0x7fffffffLL) return false;
+    // the in-block offsets stay below row_units + tile_units: exact while that is < 2^32 / row_units
+    const bool small = (uint64_t)row_units * ((uint64_t)row_units + tile_units) < ((uint64_t)1 << 32);
+    if (small && row_units > 1) {
+        const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + row_units - 1) / row_units);
+        hipLaunchKernelGGL((gather_chunks_kernel<Source, true, UNIT>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, source,
+                           row_units, magic, total, n - 1, zeros, static_cast<uint8_t*>(out));
+    } else {
+        hipLaunchKernelGGL((gather_chunks_kernel<Source, false, UNIT>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, source,
+                           row_units, 0u, total, n - 1, zeros, static_cast<uint8_t*>(out));
+    }
+    return true;
+}
+
 // Device address of 16 zero bytes (defined once, in gather.hip); nullptr on failure.
 const uint8_t* zero_chunk();
 
@@ -326,28 +380,14 @@ inline bool launch(const Source& source, int src_align, int32_t row_bytes, int64
     const uint8_t* zeros = zero_chunk();
     if (!zeros) return false;
     const uint64_t out_bits = (uint64_t)(uintptr_t)out;
-    if (src_align >= 4 && (out_bits & 15) == 0) {
-        const uint32_t row_dwords = (uint32_t)row_bytes / 4u;
-        const int64_t total = n * (int64_t)row_dwords;
-        const int64_t blocks = (total + kTile * 4 - 1) / (kTile * 4);
-        if (blocks > 0x7fffffffLL) return false;
-        // the in-block offsets stay below row_dwords + 4 * kTile: exact while that is < 2^32 / row_dwords
-        const bool small = (uint64_t)row_dwords * ((uint64_t)row_dwords + 4u * kTile) < ((uint64_t)1 << 32);
-        if (small && row_dwords > 1) {
-            const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + row_dwords - 1) / row_dwords);
-            hipLaunchKernelGGL((gather_chunks_kernel<Source, true>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
-                               source, row_dwords, magic, total, n - 1, zeros, reinterpret_cast<uint32_t*>(out));
-        } else {
-            hipLaunchKernelGGL((gather_chunks_kernel<Source, false>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
-                               source, row_dwords, 0u, total, n - 1, zeros, reinterpret_cast<uint32_t*>(out));
-        }
-        return true;
-    }
+    // the chunk kernel wherever its 16-byte pieces apply: an aligned output, and rows that a piece
+    // crosses at most once unless its dword path can follow
+    if ((out_bits & 15) == 0 && (src_align >= 4 || row_bytes >= 16))
+        return src_align >= 4 ? launch_chunks<4>(source, row_bytes, n, out, zeros, stream) : launch_chunks<2>(source, row_bytes, n, out, zeros, stream);
     const int align = common_alignment((uint64_t)src_align | out_bits);
     const int64_t total = n * (int64_t)(row_bytes / align);
     if ((total + kTile - 1) / kTile > 0x7fffffffLL) return false;
     switch (align) {
-        case 16: launch_elems<u32x4>(source, row_bytes, n, out, stream); break;
         case 8: launch_elems<u32x2>(source, row_bytes, n, out, stream); break;
         case 4: launch_elems<uint32_t>(source, row_bytes, n, out, stream); break;
         default: launch_elems<uint16_t>(source, row_bytes, n, out, stream); break;
