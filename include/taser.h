@@ -300,7 +300,8 @@ int taser_gather_features(const void* table, int64_t rows, int32_t row_bytes,
  *                   memory directly.
  * This call synchronizes `hip_stream` before returning.
  *
- * taser_cache_lookup serves n rows into the dense `out` exactly like
+ * taser_cache_lookup serves n rows into the dense `out` (while missing rows are
+ * on the bus, what needs only resident rows is written) exactly like
  * taser_gather_features over the host table; which rows are resident never
  * changes the bytes served. hit_miss (device uint64[2], may be NULL) is
  * incremented by the number of requests with a resident id ([0]) and with a
@@ -352,7 +353,7 @@ int taser_cache_lookup_static(taser_cache* c, const int32_t* ids, int64_t n, voi
 
 /* Knobs for callers that run the halves of a lookup beside other kernels, and for measurements.
  *   stage_blocks  number of 256-thread blocks the host -> staging copy runs on
- *                 (default 64; 0 keeps the current value). The copy is bound by
+ *                 (default 32; 0 keeps the current value). The copy is bound by
  *                 the bus; fewer blocks copy somewhat slower but leave more of
  *                 the memory system's request slots to kernels running beside it.
  *   refresh_before_gather  non-zero: taser_cache_gather first re-writes its read

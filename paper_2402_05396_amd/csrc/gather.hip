@@ -7,11 +7,14 @@
 namespace {
 
 struct TableSource {
+    static constexpr int kAlign = 2;
     const uint8_t* table;
     int64_t pitch_bytes;
     const int32_t* ids;
     int64_t rows;
     __device__ __forceinline__ int32_t key(int64_t i) const { return ids[i]; }
+    __device__ __forceinline__ int32_t resolve(int32_t id) const { return id; }
+    __device__ __forceinline__ bool pending(int32_t) const { return false; }
     __device__ __forceinline__ const uint8_t* address(int32_t id, int64_t) const {
         const bool ok = id >= 0 && id < rows;
         const uint8_t* at = table + (int64_t)(ok ? id : 0) * pitch_bytes;   // computed either way: no branch

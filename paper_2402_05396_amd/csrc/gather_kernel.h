@@ -31,8 +31,8 @@ template <> __device__ __forceinline__ u32x2 zero_of<u32x2>() { return u32x2{0, 
 constexpr int kThreads = 256;
 constexpr int kUnroll = 4;
 constexpr int kTile = kThreads * kUnroll;   // elements (or 16-byte chunks) per block
-constexpr int kMaxTileRows = kTile * 4 + 2; // output rows a block of the chunk kernel can touch (rows of one dword)
-constexpr int kMaxTileLongRows = kTile + 2;  // and with rows of at least 16 bytes
+// Output rows a block of the chunk kernel can touch: rows of one dword, or with 2-byte units of at least 16 bytes.
+constexpr int tile_rows(int unit) { return unit == 4 ? kTile * 4 + 2 : kTile + 2; }
 
 // 16 bytes that are only known to be 4-byte (2-byte) aligned.
 struct __attribute__((packed, aligned(4))) Chunk16 {
@@ -54,7 +54,20 @@ template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) 
 // can issue the (dependent) loads of several rows back to back:
 //   key(i)          a 32-bit token read from memory (an id, a cache location);
 //   address(key, i) first byte of the source row, or nullptr for a zero row.
-// row(i) is the two combined.
+//
+// kAlign is what row size, pitch and addresses are known to share at least.
+//
+// A gather can run in two launches while some source rows are still on their way: PHASE 1 writes
+// what needs only rows that are there, PHASE 2, launched when all of them are, the rest; between them
+// every output byte is written (some dwords in both, with the same value). PHASE 0 is the whole
+// gather in one launch. For that a Source also has
+//   pending(key)    the row is on its way during PHASE 1;
+//   resolve(key)    the token for PHASES 0 and 2 (PHASE 1 takes it as it is read).
+
+template <int PHASE, typename Source> __device__ __forceinline__ int32_t source_token(const Source& source, int64_t i) {
+    const int32_t key = source.key(i);
+    return PHASE == 1 ? key : source.resolve(key);
+}
 
 // UNIT: the size that divides rows, pitches and source addresses, 4 or 2 bytes; offsets are counted
 // in it. With 2-byte units the rows are at least 16 bytes long. (One 16-byte load at any even address
@@ -62,13 +75,27 @@ template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) 
 // 2 bytes took 0.71.)
 // USE_MAGIC: floor(e / d) = umulhi(e, magic) with magic = ceil(2^32 / d), exact
 // for e * d < 2^32 (the launcher checks that); otherwise a plain division.
-template <typename Source, bool USE_MAGIC, int UNIT>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_chunks_kernel(Source source, uint32_t row_units, uint32_t magic,
-                                                                 int64_t total_units, int64_t last_row,
-                                                                 const uint8_t* __restrict__ zeros,
-                                                                 uint8_t* __restrict__ out) {
+// Beside: work for the first workgroups of the same launch (run() for `blocks` of them), or NothingBeside.
+// (The gather is the kernel's own body: as an inlined function of two kernels it came out with register copies
+// that waited for its loads, 0.180 instead of 0.178 ms for 1.32 M rows of 372 bytes.)
+constexpr int kBesideWords = 2048;   // words of LDS that run() gets
+struct NothingBeside {
+    static constexpr bool kAny = false;
+    static constexpr uint32_t blocks = 0;
+    static __device__ __forceinline__ void run(uint32_t, int32_t*) {}
+};
+template <typename Source, bool USE_MAGIC, int UNIT, int PHASE, typename Beside>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_chunks_kernel(
+    Source source, uint32_t row_units, uint32_t magic, int64_t total_units, int64_t last_row, const uint8_t* __restrict__ zeros,
+    uint8_t* __restrict__ out, const Beside beside) {
+    __shared__ int32_t tile_key[tile_rows(UNIT)];
+    if (Beside::kAny && blockIdx.x < beside.blocks) {
+        beside.run(blockIdx.x, tile_key);
+        return;
+    }
+    const uint32_t block = Beside::kAny ? blockIdx.x - beside.blocks : blockIdx.x;
     constexpr uint32_t kPer = 16 / UNIT;                       // units of a chunk
-    const int64_t tile = (int64_t)blockIdx.x * (kTile * kPer);   // first output unit of this block
+    const int64_t tile = (int64_t)block * (kTile * kPer);   // first output unit of this block
     int64_t row0;                                               // output row holding it
     if (tile < ((int64_t)1 << 32)) row0 = (uint32_t)tile / row_units;
     else row0 = tile / (int64_t)row_units;
@@ -78,13 +105,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     // lanes into LDS. Without it each chunk's token is a wave-wide broadcast load at the head of
     // a chain of two dependent loads, and the kernel's speed follows the latency of the token
     // array (slower by a third when that array has dropped out of the memory-side cache).
-    __shared__ int32_t tile_key[UNIT == 4 ? kMaxTileRows : kMaxTileLongRows];
     {
         int64_t tile_last = tile + kTile * kPer - 1;
         if (tile_last >= total_units) tile_last = total_units - 1;
         const uint32_t e_last = col0 + (uint32_t)(tile_last - tile);   // unit offset from the start of row0
         const int rows_here = (int)(USE_MAGIC ? __umulhi(e_last, magic) : e_last / row_units) + 1;   // <= the array
-        for (int r = threadIdx.x; r < rows_here; r += kThreads) tile_key[r] = source.key(row0 + r);
+        for (int r = threadIdx.x; r < rows_here; r += kThreads) tile_key[r] = source_token<PHASE>(source, row0 + r);
         __syncthreads();
     }
     // Pass 1 (ALU only): output row and column of each of this thread's chunks.
@@ -109,11 +135,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     int32_t key[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) key[u] = tile_key[row[u] - row0];
+    bool write[kUnroll];   // chunks that are this phase's (a chunk with a pending row's bytes is PHASE 2's)
     u32x4 vals[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-        const uint8_t* base = source.address(key[u], row[u]);
-        const uint8_t* at = (whole[u] && base) ? base + (size_t)col[u] * UNIT : zeros;
+        write[u] = PHASE == 0 || (PHASE == 2) == source.pending(key[u]);
+        const uint8_t* base = PHASE == 1 && !write[u] ? nullptr : source.address(key[u], row[u]);
+        const uint8_t* at = (whole[u] && write[u] && base) ? base + (size_t)col[u] * UNIT : zeros;
         vals[u] = load16<UNIT>(at);
     }
     // Pass 3 (rare): chunks that cross one or more row ends.
@@ -127,6 +155,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             const uint32_t in_row = (row_units - col[u]) * 2u;                    // 2 .. 14
             const uint8_t* base = source.address(key[u], row[u]);
             const uint8_t* next = row[u] < last_row ? source.address(tile_key[row[u] + 1 - row0], row[u] + 1) : nullptr;
+            static_assert(UNIT == 4 || PHASE == 0, "2-byte rows come from tables, which are all there");
             const u32x4 t = load16<UNIT>(base ? base + (size_t)row_units * 2u - 16u : zeros);
             const u32x4 h = load16<UNIT>(next ? next : zeros);
             const uint32_t skip = 16u - in_row;                                   // bytes of t that belong to the chunk before
@@ -141,20 +170,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         uint32_t c = col[u];
         int64_t r = row[u];
         uint32_t w[4] = {0u, 0u, 0u, 0u};
+        bool pending = false;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (c >= row_units) { c = 0; ++r; }
             if (d + i < total_units) {
-                const uint8_t* base = source.address(tile_key[r - row0], r);
-                if (base) w[i] = ((GlobalU32Ptr)base)[c];
+                const int32_t token = tile_key[r - row0];
+                if (PHASE != 0 && source.pending(token)) pending = true;
+                if (PHASE != 1 || !pending) {
+                    const uint8_t* base = source.address(token, r);
+                    if (base) w[i] = ((GlobalU32Ptr)base)[c];
+                }
             }
             ++c;
         }
+        if (PHASE != 0) write[u] = (PHASE == 2) == pending;
         vals[u] = u32x4{w[0], w[1], w[2], w[3]};
     }
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
         const int64_t d = tile + (threadIdx.x + u * kThreads) * kPer;
+        if (PHASE != 0 && !write[u]) continue;
         if (d + kPer <= total_units) {
             __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(out + d * UNIT));
         } else {
@@ -185,25 +221,47 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 // line that lie beyond the row's end belong to the next output row and are read there.
 // The assumption about where workgroups run only affects speed, never results.
 constexpr int kOwnerClasses = 8;
+// PHASE 2 usually has few rows (the cache's misses): one workgroup takes all of a super-tile's, so that there is
+// something for its lanes to do.
+constexpr int owner_classes(int phase) { return phase == 2 ? 1 : kOwnerClasses; }
 constexpr int kOwnedTileLines = 1536;     // 192 KiB of output per super-tile: about 1500 chunks per workgroup; smaller
                                           // tiles leave the workgroups' shares too uneven, larger ones cost LDS
+                                          // (PHASE 2 takes the same time from 768 to 3072)
 constexpr int kOwnedMinRowBytes = 512;
 constexpr int kOwnedMaxRowBytes = 16384;
 constexpr int kOwnedMaxRows = kOwnedTileLines * 128 / kOwnedMinRowBytes + 3;
 
-template <typename Source>
+// Geometry of such a launch, worked out by the host.
+struct OwnedLines {
+    uint32_t row_bytes, slots, slot_magic, step_rows, step_rest;   // slots: 16-byte chunks of the most lines a row can own
+    int64_t total_bytes, n_rows;
+};
+
+// In PHASE 1 only the lines of rows that are there are written, up to where a pending row begins. In
+// PHASE 2 a pending row's share is the whole range from its own first byte (inside a line of the row
+// before it) to the end of its last line.
+template <typename Source, int PHASE, typename Beside>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_owned_lines_kernel(
-    Source source, uint32_t row_bytes, uint32_t slots, uint32_t slot_magic, uint32_t step_rows, uint32_t step_rest,
-    int64_t total_bytes, int64_t n_rows, const uint8_t* __restrict__ zeros, uint8_t* __restrict__ out) {
+    Source source, const OwnedLines g, const uint8_t* __restrict__ zeros, uint8_t* __restrict__ out, const Beside beside) {
+    if (Beside::kAny && blockIdx.x < beside.blocks) {
+        __shared__ int32_t lds[Beside::kAny ? kBesideWords : 1];
+        beside.run(blockIdx.x, lds);
+        return;
+    }
+    const uint32_t block = Beside::kAny ? blockIdx.x - beside.blocks : blockIdx.x;
+    constexpr int kBias = PHASE == 2 ? 128 : 0;   // a PHASE 2 row's first line may begin before the row
     __shared__ int32_t tile_key[kOwnedMaxRows + 1];
     __shared__ const uint8_t* own_base[kOwnedMaxRows];   // source row, or `zeros` with the zero flag set
-    __shared__ const uint8_t* own_next[kOwnedMaxRows];   // source row of the next output row minus row_bytes (same flag rule)
-    __shared__ uint32_t own_meta[kOwnedMaxRows];          // first line in the tile + 256 | lines << 12 | bytes before the first line << 20
+    __shared__ const uint8_t* own_next[kOwnedMaxRows];   // source row of the next output row minus row_bytes (same flag rule); null: not to be written
+    __shared__ uint32_t own_meta[kOwnedMaxRows];          // first line in the tile + 256 | lines << 12 | (bytes before the first line + kBias) << 20
                                                           // | bit 30: this row is zeros | bit 31: the next row is zeros
     __shared__ uint32_t n_owned;
 
-    const uint32_t cls = blockIdx.x % kOwnerClasses;
-    const int64_t line0 = (int64_t)(blockIdx.x / kOwnerClasses) * kOwnedTileLines;
+    const uint32_t row_bytes = g.row_bytes, slots = g.slots;
+    const int64_t total_bytes = g.total_bytes, n_rows = g.n_rows;
+    constexpr uint32_t kClasses = owner_classes(PHASE);
+    const uint32_t cls = block % kClasses;
+    const int64_t line0 = (int64_t)(block / kClasses) * kOwnedTileLines;
     const int64_t total_lines = (total_bytes + 127) >> 7;
     const uint32_t lines_here = (uint32_t)(total_lines - line0 < kOwnedTileLines ? total_lines - line0 : kOwnedTileLines);
     const int64_t tile_byte0 = line0 * 128;
@@ -215,20 +273,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     const int rows_here = (int)(r_last - r0 + 1);                           // <= kOwnedMaxRows - 1
     const int keys_here = rows_here + (r_last + 1 < n_rows ? 1 : 0);        // + the row the last line may run into
     if (threadIdx.x == 0) n_owned = 0;
-    for (int i = threadIdx.x; i < keys_here; i += kThreads) tile_key[i] = source.key(r0 + i);
+    for (int i = threadIdx.x; i < keys_here; i += kThreads) tile_key[i] = source_token<PHASE>(source, r0 + i);
     __syncthreads();
     for (int i = threadIdx.x; i < rows_here; i += kThreads) {
         const int64_t r = r0 + i;
         const int32_t key = tile_key[i];
-        if (source.owner(key, r) != cls) continue;
+        if (PHASE != 0 && source.pending(key) != (PHASE == 2)) continue;
+        if (kClasses > 1 && source.owner(key, r) != cls) continue;
         const int64_t begin = r * row_bytes;
-        const int64_t first = (begin + 127) >> 7, next = (begin + row_bytes + 127) >> 7;   // lines whose first byte is in row r
+        // lines whose first byte is in row r, and in PHASE 2 the one that row r begins in
+        const int64_t first = (begin + (PHASE == 2 ? 0 : 127)) >> 7, next = (begin + row_bytes + 127) >> 7;
         const uint8_t* base = source.address(key, r);
-        const uint8_t* after = i + 1 < keys_here ? source.address(tile_key[i + 1], r + 1) : nullptr;
+        const bool later = PHASE == 1 && i + 1 < keys_here && source.pending(tile_key[i + 1]);   // the next row is PHASE 2's
+        const uint8_t* after = i + 1 < keys_here && !later ? source.address(tile_key[i + 1], r + 1) : nullptr;
         const uint32_t at = atomicAdd(&n_owned, 1u);
         own_base[at] = base ? base : zeros;
-        own_next[at] = after ? after - row_bytes : zeros;
-        own_meta[at] = (uint32_t)(first - line0 + 256) | ((uint32_t)(next - first) << 12) | ((uint32_t)(first * 128 - begin) << 20) |
+        own_next[at] = after ? after - row_bytes : (later ? nullptr : zeros);
+        own_meta[at] = (uint32_t)(first - line0 + 256) | ((uint32_t)(next - first) << 12) | ((uint32_t)(first * 128 - begin + kBias) << 20) |
                        (base ? 0u : 1u << 30) | (after ? 0u : 1u << 31);
     }
     __syncthreads();
@@ -238,28 +299,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         const uint8_t* from[kUnroll];
         uint32_t out_off[kUnroll], which[kUnroll], in_off[kUnroll];
         bool whole[kUnroll], cross[kUnroll];
+        // (in_off: bytes from the row's start; with PHASE 2 negative before it)
         // one division per thread: its further chunks lie kThreads = step_rows * slots + step_rest chunks on
         const uint32_t w0 = round + threadIdx.x;
-        uint32_t j = __umulhi(w0, slot_magic), within = w0 - j * slots;   // exact: w0 * slots < 2^32
+        uint32_t j = __umulhi(w0, g.slot_magic), within = w0 - j * slots;   // exact: w0 * slots < 2^32
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const bool live = round + threadIdx.x + u * kThreads < items;
             const uint32_t jj = live ? j : 0u;
             const uint32_t meta = own_meta[jj];
             const uint32_t line = (meta & 4095u) + (within >> 3) - 256u;          // relative to the tile; wraps if before it
-            const bool mine = live && (within >> 3) < ((meta >> 12) & 255u) && line < lines_here;
+            bool mine = live && (within >> 3) < ((meta >> 12) & 255u) && line < lines_here;
             out_off[u] = line * 128u + (within & 7u) * 16u;
-            uint32_t off = ((meta >> 20) & 255u) + within * 16u;                   // bytes from the row's start
-            const bool beyond = off >= row_bytes;                                  // the chunk lies in the next output row
+            const int32_t off = (int32_t)(((meta >> 20) & 255u) + within * 16u) - kBias;
+            const bool beyond = off >= (int32_t)row_bytes;                         // the chunk lies in the next output row
             const uint8_t* base = beyond ? own_next[jj] : own_base[jj];
             const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
-            whole[u] = mine && out_off[u] + 16u <= tile_limit && (beyond || off + 16u <= row_bytes);
+            if (PHASE == 1) mine = mine && base != nullptr;
+            if (PHASE == 2) mine = mine && off > -16;                              // wholly the row before's otherwise
+            whole[u] = mine && out_off[u] + 16u <= tile_limit && (beyond || off + 16 <= (int32_t)row_bytes) && (PHASE != 2 || off >= 0);
             cross[u] = mine && !whole[u] && out_off[u] < tile_limit;
             from[u] = (whole[u] && !zero) ? base + off : zeros;
-            in_off[u] = off;
+            in_off[u] = (uint32_t)off;
             which[u] = jj;
-            j += step_rows;
-            within += step_rest;
+            j += g.step_rows;
+            within += g.step_rest;
             if (within >= slots) {
                 within -= slots;
                 ++j;
@@ -271,31 +335,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             if (!cross[u]) continue;
-            // dword by dword: the rest of the row, then the start of the next one (or the output's ragged end)
+            // dword by dword: the rest of the row, then the start of the next one (or the output's ragged
+            // end); what another phase or the row before writes is left out
             const uint32_t meta = own_meta[which[u]];
             const uint8_t *a = own_base[which[u]], *b = own_next[which[u]];
             uint32_t wds[4] = {0u, 0u, 0u, 0u};
+            uint32_t* const to = reinterpret_cast<uint32_t*>(out + tile_byte0 + out_off[u]);
+            bool all = true;
+            bool ours[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const uint32_t off = in_off[u] + 4u * e;
-                if (out_off[u] + 4u * e >= tile_limit) continue;
-                const bool beyond = off >= row_bytes;
+                const int32_t off = (int32_t)in_off[u] + 4 * e;
+                const bool beyond = off >= (int32_t)row_bytes;
                 const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
-                if (!zero) wds[e] = *(GlobalU32Ptr)((beyond ? b : a) + off);
+                ours[e] = out_off[u] + 4u * e < tile_limit && (PHASE != 1 || !beyond || b) && (PHASE != 2 || off >= 0);
+                all = all && ours[e];
+                if (ours[e] && !zero) wds[e] = *(GlobalU32Ptr)((beyond ? b : a) + off);
             }
             vals[u] = u32x4{wds[0], wds[1], wds[2], wds[3]};
+            whole[u] = all;                  // stored below with the others
+            if (all) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (ours[e]) to[e] = wds[e];
         }
         uint8_t* tile_out = out + tile_byte0;
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            if (whole[u] || (cross[u] && out_off[u] + 16u <= tile_limit)) {
-                __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(tile_out + out_off[u]));
-            } else if (cross[u]) {
-                const uint32_t wds[4] = {vals[u].x, vals[u].y, vals[u].z, vals[u].w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (out_off[u] + 4u * e < tile_limit) reinterpret_cast<uint32_t*>(tile_out + out_off[u])[e] = wds[e];
-            }
+            if (whole[u]) __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(tile_out + out_off[u]));
         }
     }
 }
@@ -319,7 +386,7 @@ __global__ __launch_bounds__(kThreads) void gather_elems_kernel(Source source, u
         vals[u] = zero_of<V>();
         if (g < total_elems) {
             const int64_t row = row0 + dr;
-            const uint8_t* base = source.address(source.key(row), row);
+            const uint8_t* base = source.address(source_token<0>(source, row), row);
             if (base) vals[u] = reinterpret_cast<const V*>(base)[col];
         }
     }
@@ -349,21 +416,22 @@ inline void launch_elems(const Source& source, int32_t row_bytes, int64_t n, voi
 }
 
 // Flat gather in 16-byte chunks of the output; UNIT (4 or 2) divides everything.
-template <int UNIT, typename Source>
-inline bool launch_chunks(const Source& source, int32_t row_bytes, int64_t n, void* out, const uint8_t* zeros, hipStream_t stream) {
+template <int UNIT, int PHASE, typename Source, typename Beside = NothingBeside>
+inline bool launch_chunks(const Source& source, int32_t row_bytes, int64_t n, void* out, const uint8_t* zeros, hipStream_t stream,
+                          const Beside& beside = {}) {
     const uint32_t row_units = (uint32_t)row_bytes / UNIT, tile_units = kTile * (16 / UNIT);
     const int64_t total = n * (int64_t)row_units;
-    const int64_t blocks = (total + tile_units - 1) / tile_units;
+    const int64_t blocks = (total + tile_units - 1) / tile_units + beside.blocks;
     if (blocks > 0x7fffffffLL) return false;
     // the in-block offsets stay below row_units + tile_units: exact while that is < 2^32 / row_units
     const bool small = (uint64_t)row_units * ((uint64_t)row_units + tile_units) < ((uint64_t)1 << 32);
     if (small && row_units > 1) {
         const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + row_units - 1) / row_units);
-        hipLaunchKernelGGL((gather_chunks_kernel<Source, true, UNIT>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, source,
-                           row_units, magic, total, n - 1, zeros, static_cast<uint8_t*>(out));
+        hipLaunchKernelGGL((gather_chunks_kernel<Source, true, UNIT, PHASE, Beside>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
+                           source, row_units, magic, total, n - 1, zeros, static_cast<uint8_t*>(out), beside);
     } else {
-        hipLaunchKernelGGL((gather_chunks_kernel<Source, false, UNIT>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, source,
-                           row_units, 0u, total, n - 1, zeros, static_cast<uint8_t*>(out));
+        hipLaunchKernelGGL((gather_chunks_kernel<Source, false, UNIT, PHASE, Beside>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
+                           source, row_units, 0u, total, n - 1, zeros, static_cast<uint8_t*>(out), beside);
     }
     return true;
 }
@@ -382,38 +450,43 @@ inline bool launch(const Source& source, int src_align, int32_t row_bytes, int64
     const uint64_t out_bits = (uint64_t)(uintptr_t)out;
     // the chunk kernel wherever its 16-byte pieces apply: an aligned output, and rows that a piece
     // crosses at most once unless its dword path can follow
-    if ((out_bits & 15) == 0 && (src_align >= 4 || row_bytes >= 16))
-        return src_align >= 4 ? launch_chunks<4>(source, row_bytes, n, out, zeros, stream) : launch_chunks<2>(source, row_bytes, n, out, zeros, stream);
+    if ((out_bits & 15) == 0 && src_align >= 4) return launch_chunks<4, 0>(source, row_bytes, n, out, zeros, stream);
+    if constexpr (Source::kAlign < 4)
+        if ((out_bits & 15) == 0 && row_bytes >= 16) return launch_chunks<2, 0>(source, row_bytes, n, out, zeros, stream);
     const int align = common_alignment((uint64_t)src_align | out_bits);
     const int64_t total = n * (int64_t)(row_bytes / align);
     if ((total + kTile - 1) / kTile > 0x7fffffffLL) return false;
     switch (align) {
         case 8: launch_elems<u32x2>(source, row_bytes, n, out, stream); break;
         case 4: launch_elems<uint32_t>(source, row_bytes, n, out, stream); break;
-        default: launch_elems<uint16_t>(source, row_bytes, n, out, stream); break;
+        default:
+            if constexpr (Source::kAlign < 4) launch_elems<uint16_t>(source, row_bytes, n, out, stream);
+            break;
     }
     return true;
 }
 
-// The same for a Source that also has owner(key, i) (see gather_owned_lines_kernel), used when
-// the rows are long enough and the request count large enough for it to pay; otherwise, and for
-// an output that is not 16-byte aligned, this is launch().
-template <typename Source>
-inline bool launch_owned(const Source& source, int src_align, int32_t row_bytes, int64_t n, void* out, hipStream_t stream) {
-    const uint64_t out_bits = (uint64_t)(uintptr_t)out;
-    if (src_align < 4 || (out_bits & 15) || row_bytes < kOwnedMinRowBytes || row_bytes > kOwnedMaxRowBytes || n < 4096)
-        return launch(source, src_align, row_bytes, n, out, stream);
-    const uint8_t* zeros = zero_chunk();
-    if (!zeros) return false;
-    const int64_t total_bytes = n * (int64_t)row_bytes;
-    const uint32_t slots = (uint32_t)((row_bytes + 127) / 128) * 8u;       // chunks of the most lines a row can own
+// Whether the line-owner gather applies and pays: long enough rows, enough requests, an aligned output.
+inline bool owned_applies(int src_align, int32_t row_bytes, int64_t n, const void* out) {
+    return src_align >= 4 && ((uintptr_t)out & 15) == 0 && row_bytes >= kOwnedMinRowBytes && row_bytes <= kOwnedMaxRowBytes && n >= 4096;
+}
+
+template <int PHASE, typename Source, typename Beside = NothingBeside>
+inline bool launch_owned(const Source& source, int32_t row_bytes, int64_t n, void* out, const uint8_t* zeros, hipStream_t stream,
+                         const Beside& beside = {}) {
+    OwnedLines g = {};
+    g.row_bytes = (uint32_t)row_bytes;
+    g.total_bytes = n * (int64_t)row_bytes;
+    g.n_rows = n;
+    g.slots = (uint32_t)((row_bytes + 127) / 128 + (PHASE == 2 ? 1 : 0)) * 8u;
     // items of a workgroup stay far below 2^32 / slots: the multiply-high division is exact
-    const uint32_t slot_magic = (uint32_t)((((uint64_t)1 << 32) + slots - 1) / slots);
-    const int64_t tiles = ((total_bytes + 127) / 128 + kOwnedTileLines - 1) / kOwnedTileLines;
-    if (tiles * kOwnerClasses > 0x7fffffffLL) return false;
-    hipLaunchKernelGGL((gather_owned_lines_kernel<Source>), dim3((unsigned)(tiles * kOwnerClasses)), dim3(kThreads), 0, stream,
-                       source, (uint32_t)row_bytes, slots, slot_magic, (uint32_t)kThreads / slots, (uint32_t)kThreads % slots,
-                       total_bytes, n, zeros, static_cast<uint8_t*>(out));
+    g.slot_magic = (uint32_t)((((uint64_t)1 << 32) + g.slots - 1) / g.slots);
+    g.step_rows = (uint32_t)kThreads / g.slots;
+    g.step_rest = (uint32_t)kThreads % g.slots;
+    const int64_t blocks = ((g.total_bytes + 127) / 128 + kOwnedTileLines - 1) / kOwnedTileLines * owner_classes(PHASE) + beside.blocks;
+    if (blocks > 0x7fffffffLL) return false;
+    hipLaunchKernelGGL((gather_owned_lines_kernel<Source, PHASE, Beside>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, source, g,
+                       zeros, static_cast<uint8_t*>(out), beside);
     return true;
 }
 
