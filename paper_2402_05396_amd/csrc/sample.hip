@@ -434,193 +434,285 @@ __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
 }
 
 // ---- inverse-timespan finder -------------------------------------------------
-// Weight of an entry at time ts for a query at t > ts: max(1, floor(2^32 / (t - ts))).
-__device__ __forceinline__ uint64_t inverse_timespan_weight(int64_t t, int64_t ts) {
-    const uint64_t delta = (uint64_t)t - (uint64_t)ts;   // exact difference, >= 1
-    if (delta >> 32) return 1;                           // the quotient is 1 (delta = 2^32) or 0
-    const uint32_t d = (uint32_t)delta;
-    if (d >= 65536u) {
-        // quotient < 2^16: a single-precision reciprocal (relative error < 2^-21) lands within one of
-        // it; the exact remainder 2^32 - q d says which way to step
-        uint32_t q = (uint32_t)(4294967296.0f * __builtin_amdgcn_rcpf((float)d));
-        const int64_t rem = ((int64_t)1 << 32) - (int64_t)((uint64_t)q * d);
-        if (rem < 0) --q;
-        else if (rem >= (int64_t)d) ++q;
-        return q;
-    }
-    const uint32_t q = 0xFFFFFFFFu / d, r = 0xFFFFFFFFu - q * d;   // 2^32 = (2^32 - 1) + 1
-    return (uint64_t)q + (r == d - 1u ? 1u : 0u);
+// Weight of an entry at time ts for a query at t > ts: max(1, floor(2^32 / delta)), delta = t - ts.
+// Entries with delta >= 2^32 weigh 1 and are the first `ones` of a list; of the others the low words of
+// the timestamps say all: delta = (low word of t) - (low word of ts), in 32 bits.
+//
+// delta >= 65536, so the quotient is below 2^16. A single-precision reciprocal is off by less than
+// 2^-22 of the quotient (conversion, v_rcp_f32's one unit in the last place, the product); scaled down by
+// 2^-21 it gives the quotient or one less, and the exact remainder says which. NEAR: delta < 2^24, where
+// the product for the remainder is one full-rate 24-bit multiply and the quotient at least 256.
+template <bool NEAR> __device__ __forceinline__ uint32_t quotient_of_delta(uint32_t delta) {
+    const uint32_t q = (uint32_t)(4294967296.0f * (1.0f - 4.76837158203125e-7f) * __builtin_amdgcn_rcpf((float)delta));
+    const uint32_t rest = 0u - (NEAR ? __umul24(q, delta) : q * delta);   // 2^32 - q delta, below 2 delta; wraps only for delta > 2^31
+    const uint32_t w = q + (rest >= delta ? 1u : 0u);
+    return NEAR ? w : w > 1u ? w : 1u;                                    // (where the quotient is 1 in any case)
+}
+// Any delta >= 1.
+__device__ __forceinline__ uint64_t weight_of_delta(uint32_t delta) {
+    if (delta >= 65536u) return quotient_of_delta<false>(delta);
+    const uint32_t q = 0xFFFFFFFFu / delta, r = 0xFFFFFFFFu - q * delta;   // 2^32 = (2^32 - 1) + 1
+    return (uint64_t)q + (r == delta - 1u ? 1u : 0u);
 }
 
-constexpr int kTileRows = 8;                      // registers of tile sums per lane
-constexpr int kMaxTiles = kTileRows * kWave;      // tile sums per root
+constexpr int kTileRegs = 8;                      // registers of tile sums per lane
+constexpr int kMaxTiles = kTileRegs * kWave;      // tile sums per root
 constexpr int kListThreads = 256;                 // block of the finder that reads whole lists
+constexpr int kListWaves = kListThreads / kWave;
 
-// One block of four wavefronts per root: the weights 1/(t - ts) depend on the query,
-// so the whole valid list has to be read once per root (from a plain array of the
-// timestamps: half the bytes of the 16-byte records), and one wavefront walking a
-// long list alone waits out a memory round trip every few rows. The list is cut
-// into at most 512 tiles of whole 64-entry rows; in pass 1 the waves take the
-// tiles in turn and leave every tile's weight sum in LDS. The first wave then holds
-// the sums in registers (tile i in lane i % 64, register i / 64) and makes the k
-// draws: each walks the tile sums, re-reads only the tile it lands in, and takes the
-// picked weight out of the tile's sum, so a draw costs one tile, not the list.
-__global__ __launch_bounds__(kListThreads) void sample_hop_inverse_timespan_kernel(
-    const int64_t* __restrict__ indptr, const TaserRec* __restrict__ rec, const int64_t* __restrict__ ts_only,
-    const TaserTimeIndex index, const int32_t* __restrict__ roots,
-    const int64_t* __restrict__ times, int64_t num_roots, int32_t num_nodes, int k, uint32_t seed_lo, uint32_t seed_hi,
-    uint32_t hop, int32_t* __restrict__ o_nbr, int32_t* __restrict__ o_eid, int64_t* __restrict__ o_ts,
-    int32_t* __restrict__ o_count) {
-    __shared__ uint64_t tile_sum_shared[kMaxTiles];
-    __shared__ int64_t cnt_shared;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t q = blockIdx.x;   // the grid has exactly one block per root
+// What the whole block knows about its root.
+struct ListQuery {
+    uint32_t lo, cnt;            // its list begins at record lo; cnt valid entries
+    uint32_t ones;               // entries [0, ones) are 2^32 or more before the query
+    uint32_t t_low;              // low word of the query time
+    uint32_t rows_per_tile, tiles;
+    uint32_t near;               // every delta is below 2^24 (then ones == 0)
+};
 
-    int64_t lo = 0, hi = 0, t = 0;
-    const int32_t v = roots[q];
-    if (v >= 0 && v < num_nodes) {
-        t = times[q];
-        lo = indptr[v];
-        hi = indptr[v + 1];
-    }
-    if (wave == 0) {   // wave-uniform: the search's ballots stay inside the first wave
-        const int64_t c = group_cutoff<kWave>(rec, index, lo, hi, t, 0, lane);
-        if (lane == 0) cnt_shared = c;
-    }
-    __syncthreads();
-    const int64_t cnt = cnt_shared;
-    const int64_t out0 = q * k;
-    const TaserRec pad = {0, -1, -1};
-    if (cnt <= k) {   // everything, most recent first (block-uniform)
-        if (wave == 0) {
-            if (lane < k) store_slot(o_nbr, o_eid, o_ts, out0 + lane, lane < cnt ? rec[lo + cnt - 1 - lane] : pad);
-            if (lane == 0) o_count[q] = (int32_t)cnt;
-        }
-        return;
-    }
+// A query as the whole wave read it from LDS, in scalar registers.
+__device__ __forceinline__ ListQuery uniform(const ListQuery& v) {
+    auto get = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
+    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.rows_per_tile), get(v.tiles), get(v.near)};
+}
 
-    const int64_t rows = (cnt + kWave - 1) / kWave;                 // 64-entry rows of the valid list
-    // Rows per tile: every tile costs pass 1 a wave-wide reduction, every draw re-reads about half
-    // a tile with a wave-wide scan per row; the sum is smallest near sqrt(1.2 rows / k). The tiling
-    // never changes a result, only the cost. At most kMaxTiles tiles.
-    int64_t rows_per_tile = (int64_t)__builtin_sqrtf(1.2f * (float)rows / (float)k);
-    if (rows_per_tile < 1) rows_per_tile = 1;
-    if (rows_per_tile * kMaxTiles < rows) rows_per_tile = (rows + kMaxTiles - 1) / kMaxTiles;
-    const int tiles = (int)((rows + rows_per_tile - 1) / rows_per_tile);
-    const int tile_rows = (tiles + kWave - 1) / kWave;              // registers in use
+// delta of entry p (its low word loaded as `low`), 0xFFFFFFFF (weight 1) for the first `ones`.
+template <bool NEAR> __device__ __forceinline__ uint32_t delta_of(const ListQuery& q, uint32_t p, uint32_t low) {
+    return !NEAR && p < q.ones ? 0xFFFFFFFFu : q.t_low - low;
+}
 
-    // Pass 1: tile sums, the waves taking tiles in turn.
-    for (int tile = wave; tile < tiles; tile += kListThreads / kWave) {
-        const int64_t r0 = (int64_t)tile * rows_per_tile;
-        const int64_t r1 = r0 + rows_per_tile < rows ? r0 + rows_per_tile : rows;
-        uint64_t s = 0;
-        int64_t r = r0;
-        for (; r + 4 <= r1; r += 4) {   // four independent loads in flight
-            int64_t ts4[4];
+// Sum of the weights of one tile: rows [r0, r1) of 64 entries.
+template <bool NEAR>
+__device__ __forceinline__ uint64_t tile_weight(const ListQuery& q, const uint32_t* __restrict__ low, uint32_t r0, uint32_t r1, int lane) {
+    constexpr int kAhead = 4;    // rows whose loads are in flight together
+    uint32_t s = 0;              // quotients below 2^16; a tile has at most 2^16 rows
+    uint64_t s_big = 0;
+    bool big = false;
+    for (uint32_t r = r0; r < r1; r += kAhead) {
+        uint32_t v[kAhead];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t p = (r + i) * kWave + lane;
-                ts4[i] = ts_only[lo + (p < cnt ? p : cnt - 1)];
+        for (int i = 0; i < kAhead; ++i) {
+            const uint32_t p = (r + i) * kWave + lane;
+            v[i] = low[p < q.cnt ? p : q.cnt - 1u];
+        }
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const uint32_t p = (r + i) * kWave + lane;
+            const uint32_t delta = delta_of<NEAR>(q, p, v[i]);
+            const bool valid = p < q.cnt;
+            if (r + i >= r1) {                               // (uniform, like the next)
+            } else if (!__ballot(delta < 65536u)) {
+                const uint32_t w = quotient_of_delta<NEAR>(delta);
+                s += valid ? w : 0u;
+            } else {
+                big = true;
+                s_big += valid ? weight_of_delta(delta) : 0u;
             }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if ((r + i) * kWave + lane < cnt) s += inverse_timespan_weight(t, ts4[i]);
         }
-        for (; r < r1; ++r) {
-            const int64_t p = r * kWave + lane;
-            if (p < cnt) s += inverse_timespan_weight(t, ts_only[lo + p]);
-        }
-        s = wave_sum64(s);
-        if (lane == 0) tile_sum_shared[tile] = s;
     }
-    __syncthreads();
-    if (wave != 0) return;   // the draws are one wavefront's work
+    if (!big && r1 - r0 <= 1024u) return wave_sum32(s);      // below 2^32 over the wave (uniform)
+    return wave_sum64(s_big + s);
+}
 
-    uint64_t tile_sum[kTileRows];
+// Row r of the list, entries picked by the draws before number j left out (lane e of my_pick: draw e's
+// entry): finds the first entry whose running sum, `before` it included, exceeds x.
+// Returns its lane and its weight, or -1 and adds the row's sum to `before`.
+template <bool NEAR>
+__device__ __forceinline__ int pick_in_row(const ListQuery& q, uint32_t low, uint32_t r, uint64_t x, uint64_t& before, int j,
+                                           uint32_t my_pick, int lane, uint64_t& pick_w) {
+    const uint32_t p = r * kWave + lane;
+    const uint32_t delta = delta_of<NEAR>(q, p, low);
+    const bool small = !__ballot(delta < 65536u);            // uniform: weights below 2^16, sums below 2^22
+    bool valid = p < q.cnt;
+    for (uint64_t taken = __ballot(lane < j && my_pick / kWave == r); taken; taken &= taken - 1) {
+        const uint32_t gone = (uint32_t)__builtin_amdgcn_readlane((int)my_pick, __ffsll((long long)taken) - 1);
+        if (p == gone) valid = false;
+    }
+    const uint64_t rest = x - before;                        // x >= before
+    if (small) {
+        const uint32_t w = valid ? quotient_of_delta<NEAR>(delta) : 0u;
+        const uint32_t inc = wave_inclusive_scan32(w);
+        const uint64_t hit = __ballot((uint64_t)inc > rest);
+        if (hit) {
+            const int first = __ffsll((long long)hit) - 1;
+            pick_w = (uint32_t)__builtin_amdgcn_readlane((int)w, first);
+            return first;
+        }
+        before += (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+    } else {
+        const uint64_t w = valid ? weight_of_delta(delta) : 0u;
+        const uint64_t inc = wave_inclusive_scan64(w);
+        const uint64_t hit = __ballot(inc > rest);
+        if (hit) {
+            const int first = __ffsll((long long)hit) - 1;
+            pick_w = wave_get64(w, first);
+            return first;
+        }
+        before += wave_get64(inc, kWave - 1);
+    }
+    return -1;
+}
+
+// The k successive draws of one root, by one wavefront. The tile sums become one running sum over all
+// tiles, kept in registers (tile i in lane i % 64, register i / 64): a draw compares it with x, re-reads
+// only the tile it lands in, and the pick's weight leaves every running sum from its tile on, which is
+// what summing the remaining weights again would give. Lane j returns draw j's entry.
+template <bool NEAR>
+__device__ __forceinline__ uint32_t draw_entries(const ListQuery& q, const uint32_t* __restrict__ low, const uint64_t* tile_sum, int k,
+                                                 uint64_t u, int lane) {
+    const uint32_t rows = (q.cnt + kWave - 1) / kWave;
+    const int regs = (int)((q.tiles + kWave - 1) / kWave);   // registers in use
+    uint64_t run[kTileRegs];
     uint64_t total = 0;
 #pragma unroll
-    for (int i = 0; i < kTileRows; ++i) {
-        const int tile = i * kWave + lane;
-        tile_sum[i] = tile < tiles ? tile_sum_shared[tile] : 0;
-        total += tile_sum[i];
+    for (int i = 0; i < kTileRegs; ++i) {
+        run[i] = 0;
+        if (i < regs) {
+            const uint32_t tile = i * kWave + lane;
+            run[i] = total + wave_inclusive_scan64(tile < q.tiles ? tile_sum[tile] : 0);
+            total = wave_get64(run[i], kWave - 1);
+        }
     }
-    total = wave_sum64(total);
-
-    // k successive draws; lane j keeps the position picked by draw j.
-    uint64_t u = 0;
-    if (lane < k) u = draw64(seed_lo, seed_hi, hop, (uint64_t)q, (uint32_t)lane);
-    int64_t my_pick = 0;
+    uint32_t my_pick = 0;
     for (int j = 0; j < k; ++j) {
-        uint64_t x = __umul64hi(wave_get64(u, j), total);
-        // the tile whose running sum first exceeds x
+        const uint64_t x = __umul64hi(wave_get64(u, j), total);
+        // the tile whose running sum first exceeds x, and the sum before it
+        uint32_t tile = q.tiles - 1u;   // (always found while the sums are consistent, x < total; this keeps reads in bounds)
         uint64_t before = 0;
-        int tile = -1;
+        bool found = false;
 #pragma unroll
-        for (int i = 0; i < kTileRows; ++i) {
-            if (i < tile_rows && tile < 0) {
-                const uint64_t inc = wave_inclusive_scan64(tile_sum[i]);
-                const uint64_t hit = __ballot(before + inc > x);
+        for (int i = 0; i < kTileRegs; ++i) {
+            if (i < regs && !found) {
+                const uint64_t hit = __ballot(run[i] > x);
                 if (hit) {
                     const int first = __ffsll((long long)hit) - 1;
-                    x -= before + wave_get64(inc - tile_sum[i], first);
+                    if (first > 0) before = wave_get64(run[i], first - 1);
                     tile = i * kWave + first;
+                    found = true;
                 } else {
-                    before += wave_get64(inc, kWave - 1);
+                    before = wave_get64(run[i], kWave - 1);
                 }
             }
         }
-        if (tile < 0) tile = tiles - 1;   // cannot happen while the sums are consistent (x < total); keeps reads in bounds
-        // inside the tile, row by row; entries picked by earlier draws weigh nothing
-        const int64_t r0 = (int64_t)tile * rows_per_tile;
-        const int64_t r1 = r0 + rows_per_tile < rows ? r0 + rows_per_tile : rows;
-        before = 0;
-        int64_t pick = -1;
+        // inside the tile, row by row
+        const uint32_t r0 = tile * q.rows_per_tile, r1 = r0 + q.rows_per_tile < rows ? r0 + q.rows_per_tile : rows;
+        uint32_t pick = q.cnt - 1u;     // same remark
         uint64_t pick_w = 0;
-        for (int64_t r = r0; r < r1 && pick < 0; ++r) {
-            const int64_t p = r * kWave + lane;
-            uint64_t w = 0;
-            if (p < cnt) w = inverse_timespan_weight(t, ts_only[lo + p]);
-            for (int e = 0; e < j; ++e) {
-                const uint64_t taken = wave_get64((uint64_t)my_pick, e);
-                if ((uint64_t)p == taken) w = 0;
+        constexpr int kAhead = 2;
+        bool done = false;
+        for (uint32_t r = r0; r < r1 && !done; r += kAhead) {
+            uint32_t v[kAhead];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const uint32_t p = (r + i) * kWave + lane;
+                v[i] = low[p < q.cnt ? p : q.cnt - 1u];
             }
-            const uint64_t inc = wave_inclusive_scan64(w);
-            const uint64_t hit = __ballot(before + inc > x);
-            if (hit) {
-                const int first = __ffsll((long long)hit) - 1;
-                pick = r * kWave + first;
-                pick_w = wave_get64(w, first);
-            } else {
-                before += wave_get64(inc, kWave - 1);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                if (!done && r + i < r1) {
+                    const int at = pick_in_row<NEAR>(q, v[i], r + i, x, before, j, my_pick, lane, pick_w);
+                    if (at >= 0) {
+                        pick = (r + i) * kWave + at;
+                        done = true;
+                    }
+                }
             }
         }
-        if (pick < 0) pick = cnt - 1;     // same remark
         if (lane == j) my_pick = pick;
         total -= pick_w;
 #pragma unroll
-        for (int i = 0; i < kTileRows; ++i)
-            if (i == (tile >> 6) && lane == (tile & (kWave - 1))) tile_sum[i] -= pick_w;
+        for (int i = 0; i < kTileRegs; ++i)
+            if (i < regs && (uint32_t)(i * kWave + lane) >= tile) run[i] -= pick_w;
     }
-    if (lane < k) store_slot(o_nbr, o_eid, o_ts, out0 + lane, rec[lo + my_pick]);
-    if (lane == 0) o_count[q] = k;
+    return my_pick;
 }
 
-__global__ __launch_bounds__(kThreads) void timestamps_only_kernel(const TaserRec* __restrict__ rec, int64_t n,
-                                                                   int64_t* __restrict__ ts_only) {
+// The weights 1/(t - ts) depend on the query, so the whole valid list has to be looked at once per root
+// (from a plain array of the timestamps' low words: a quarter of the bytes of the 16-byte records). A
+// block of four wavefronts per root: the first finds the cutoff; all four sum the weights of the list's
+// tiles, at most 512 of whole 64-entry rows (one wavefront walking a long list alone would wait out a
+// memory round trip every few rows); the first makes the draws. Bound by vector instructions, about 15
+// per 64 weights and 100 per draw. Two hops of 10 from 4 000 roots (0.59 G weights): 1.04 ms with 64-bit
+// remainders and a scan of all tile sums per draw, 0.64 ms so. Two or four roots per block (fewer waves
+// idle while one draws) take 0.65 - 0.70 ms and leave the longest lists to fewer waves: one hop of 4 000
+// roots 0.115 ms with one root per block, 0.150 with two, 0.189 with four.
+__global__ __launch_bounds__(kListThreads) void sample_hop_inverse_timespan_kernel(
+    const int64_t* __restrict__ indptr, const TaserRec* __restrict__ rec, const uint32_t* __restrict__ ts_low,
+    const TaserTimeIndex index, const int32_t* __restrict__ roots,
+    const int64_t* __restrict__ times, int32_t num_nodes, int k, uint32_t seed_lo, uint32_t seed_hi,
+    uint32_t hop, int32_t* __restrict__ o_nbr, int32_t* __restrict__ o_eid, int64_t* __restrict__ o_ts,
+    int32_t* __restrict__ o_count) {
+    __shared__ uint64_t tile_sum[kMaxTiles];
+    __shared__ ListQuery query;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t root = blockIdx.x;   // the grid has exactly one block per root
+
+    if (wave == 0) {
+        int64_t lo = 0, hi = 0, t = 0;
+        const int32_t v = roots[root];
+        if (v >= 0 && v < num_nodes) {
+            t = times[root];
+            lo = indptr[v];
+            hi = indptr[v + 1];
+        }
+        const int64_t cnt = group_cutoff<kWave>(rec, index, lo, hi, t, 0, lane);
+        ListQuery q = {(uint32_t)lo, (uint32_t)cnt, 0u, (uint32_t)(uint64_t)t, 1u, 0u, 1u};
+        if (cnt <= k) {          // everything, most recent first
+            const TaserRec pad = {0, -1, -1};
+            if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, lane < cnt ? rec[lo + cnt - 1 - lane] : pad);
+            if (lane == 0) o_count[root] = (int32_t)cnt;
+        } else {
+            const uint64_t longest = (uint64_t)t - (uint64_t)rec[lo].ts;   // of all deltas
+            q.near = longest < (1u << 24);
+            // delta >= 2^32 is ts < t - (2^32 - 1); t is at least 2^32 above the smallest timestamp here
+            if (longest >> 32) q.ones = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - 0xFFFFFFFFll, 0, lane);
+            // Rows per tile: every tile costs the summing a wave-wide reduction, every draw re-reads about half
+            // a tile with a wave-wide scan per row; the sum is smallest near sqrt(rows / k). The tiling
+            // never changes a result, only the cost. At most kMaxTiles tiles.
+            const uint32_t rows = (q.cnt + kWave - 1) / kWave;
+            uint32_t per = (uint32_t)__builtin_sqrtf((float)rows / (float)k);
+            if (per < 1u) per = 1u;
+            if ((uint64_t)per * kMaxTiles < rows) per = (rows + kMaxTiles - 1) / kMaxTiles;
+            q.rows_per_tile = per;
+            q.tiles = (rows + per - 1) / per;
+        }
+        if (lane == 0) query = q;
+    }
+    __syncthreads();
+    const ListQuery q = uniform(query);
+    if (q.tiles == 0) return;         // served above
+    const uint32_t rows = (q.cnt + kWave - 1) / kWave;
+    const uint32_t* low = ts_low + q.lo;
+    for (uint32_t tile = wave; tile < q.tiles; tile += kListWaves) {
+        const uint32_t r0 = tile * q.rows_per_tile, r1 = r0 + q.rows_per_tile < rows ? r0 + q.rows_per_tile : rows;
+        const uint64_t s = q.near ? tile_weight<true>(q, low, r0, r1, lane) : tile_weight<false>(q, low, r0, r1, lane);
+        if (lane == 0) tile_sum[tile] = s;
+    }
+    __syncthreads();
+    if (wave != 0) return;            // the draws are one wavefront's work
+    uint64_t u = 0;
+    if (lane < k) u = draw64(seed_lo, seed_hi, hop, (uint64_t)root, (uint32_t)lane);
+    const uint32_t pick = q.near ? draw_entries<true>(q, low, tile_sum, k, u, lane) : draw_entries<false>(q, low, tile_sum, k, u, lane);
+    if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, rec[q.lo + pick]);
+    if (lane == 0) o_count[root] = k;
+}
+
+__global__ __launch_bounds__(kThreads) void timestamps_low_kernel(const TaserRec* __restrict__ rec, int64_t n,
+                                                                  uint32_t* __restrict__ ts_low) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i < n) ts_only[i] = rec[i].ts;
+    if (i < n) ts_low[i] = (uint32_t)(uint64_t)rec[i].ts;
 }
 
-// The plain timestamp array of a graph, made on the first call that needs it. The
+// The low words of a graph's timestamps, an array made on the first call that needs it. The
 // call that makes it waits for the fill, so later calls on any stream find it ready.
-std::mutex g_ts_only_mutex;
-int ensure_ts_only(const taser_tcsr* g_const, hipStream_t stream) {
+std::mutex g_ts_low_mutex;
+int ensure_ts_low(const taser_tcsr* g_const, hipStream_t stream) {
     taser_tcsr* g = const_cast<taser_tcsr*>(g_const);   // a cache inside the handle, not a change of the graph
-    std::lock_guard<std::mutex> lock(g_ts_only_mutex);
-    if (g->ts_only || g->num_entries == 0) return TASER_OK;
-    int64_t* p = nullptr;
-    TASER_HIP_TRY(hipMalloc((void**)&p, (size_t)g->num_entries * sizeof(int64_t)));
-    hipLaunchKernelGGL(timestamps_only_kernel, dim3((unsigned)((g->num_entries + kThreads - 1) / kThreads)), dim3(kThreads),
+    std::lock_guard<std::mutex> lock(g_ts_low_mutex);
+    if (g->ts_low || g->num_entries == 0) return TASER_OK;
+    uint32_t* p = nullptr;
+    TASER_HIP_TRY(hipMalloc((void**)&p, (size_t)g->num_entries * sizeof(uint32_t)));
+    hipLaunchKernelGGL(timestamps_low_kernel, dim3((unsigned)((g->num_entries + kThreads - 1) / kThreads)), dim3(kThreads),
                        0, stream, g->rec, g->num_entries, p);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -628,7 +720,7 @@ int ensure_ts_only(const taser_tcsr* g_const, hipStream_t stream) {
         (void)hipFree(p);
         return taser_fail_hip(e, "sample_temporal: building the timestamp array");
     }
-    g->ts_only = p;
+    g->ts_low = p;
     return TASER_OK;
 }
 
@@ -721,7 +813,7 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
                 const taser_hop_out* out, const RowRequest* want, hipStream_t stream) {
     taser_clear_stale_hip_error();
     if (policy == TASER_INVERSE_TIMESPAN) {
-        const int rc = ensure_ts_only(g, stream);
+        const int rc = ensure_ts_low(g, stream);
         if (rc != TASER_OK) return rc;
     }
     const int32_t* cur_roots = roots;
@@ -760,7 +852,7 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
                 TaserProfileSpan span(stream, "sample_hop_inverse_timespan");
                 const unsigned grid = (unsigned)n;   // one block per root (n < 2^31)
                 hipLaunchKernelGGL(sample_hop_inverse_timespan_kernel, dim3(grid), dim3(kListThreads), 0, stream, g->indptr, g->rec,
-                                   g->ts_only, g->time_index, cur_roots, cur_times, n, g->num_nodes, k, (uint32_t)seed, (uint32_t)(seed >> 32),
+                                   g->ts_low, g->time_index, cur_roots, cur_times, g->num_nodes, k, (uint32_t)seed, (uint32_t)(seed >> 32),
                                    (uint32_t)h, out[h].nbr, out[h].eid, out[h].ts, out[h].count);
                 break;
             }

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "taser_internal.h"
+
 namespace {
 
 // ---- Philox4x32-10 (Salmon et al., SC'11) --------------------------------
@@ -84,6 +86,23 @@ __device__ __forceinline__ uint64_t wave_get64(uint64_t v, int lane) {
 // Inclusive prefix sum over the whole wave, and the wave's total in every lane.
 __device__ __forceinline__ uint64_t wave_inclusive_scan64(uint64_t v) { return group_inclusive_scan64<64>(v, 0); }
 __device__ __forceinline__ uint64_t wave_sum64(uint64_t v) { return wave_get64(wave_inclusive_scan64(v), 63); }
+
+// The same for one 32-bit value per lane, whose sum over the wave stays below 2^32.
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ uint32_t dpp_take32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROW_MASK, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_scan32(uint32_t v) {
+    v += dpp_take32<0x111, 0xf>(v);
+    v += dpp_take32<0x112, 0xf>(v);
+    v += dpp_take32<0x114, 0xf>(v);
+    v += dpp_take32<0x118, 0xf>(v);
+    v += dpp_take32<0x142, 0xa>(v);
+    v += dpp_take32<0x143, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan32(v), kWave - 1);
+}
 
 // One of k successive weighted draws without replacement inside a group whose lane i
 // holds candidate i: `run` is the inclusive prefix sum of the weights still in play,

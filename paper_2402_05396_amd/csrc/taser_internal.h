@@ -50,8 +50,8 @@ struct taser_tcsr {
     TaserTimeIndex time_index;
     void* owned_storage;           // the one device allocation behind all of the above, or null: the caller's memory
     int device;                    // with the caller's memory: the device it is on
-    int64_t* ts_only;              // device int64[num_entries] or null: the timestamps alone, made on first use by
-                                   // the one finder that reads whole lists (inverse timespan)
+    uint32_t* ts_low;              // device uint32[num_entries] or null: the low words of the timestamps, made on first
+                                   // use by the one finder that reads whole lists (inverse timespan)
 };
 
 static constexpr int kWave = 64;

@@ -919,6 +919,6 @@ extern "C" void taser_tcsr_free(taser_tcsr* g) {
         (void)hipDeviceSynchronize();
         if (other) (void)hipSetDevice(current);
     }
-    (void)hipFree(g->ts_only);
+    (void)hipFree(g->ts_low);
     delete g;
 }
