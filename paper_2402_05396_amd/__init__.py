@@ -1,10 +1,13 @@
 """MI355X-native temporal neighbor finder + feature gather (TASER, arXiv 2402.05396).
 
-Thin ctypes binding over ``libtaser.so`` (C ABI declared in ``include/taser.h``).
+Thin binding over ``libtaser.so`` (C ABI declared in ``include/taser.h``).
 The functions here carry the same names as the C entry points and only marshal
 arguments: torch supplies device memory and the current stream, every step of
-the path runs in the library's HIP kernels. There is no fallback: if the
-library has not been built, or no GPU is present, calls raise.
+the path runs in the library's HIP kernels. The calls of a training loop are
+marshalled by ``_binding`` (C++) when their arguments are the plain ones; what it
+does not take (outputs of the caller's, other tensor types, errors in the
+arguments) goes through ctypes. There is no fallback: if the library has not
+been built, or no GPU is present, calls raise.
 """
 import contextlib
 import ctypes
@@ -93,6 +96,23 @@ def lib():
         L.taser_last_error.restype = ctypes.c_char_p
         _lib = L
     return _lib
+
+
+_native = None
+
+
+def _bind():
+    """The module `_binding`, given the addresses of the library's entry points."""
+    global _native
+    L = lib()
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise RuntimeError(f"{os.path.join(_HERE, '_binding.so')} is missing or does not load ({e}): build it with "
+                           "`python -m paper_2402_05396_amd.build` (there is no fallback path)") from e
+    _binding.bind(TaserError, {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS})
+    _native = _binding
+    return _binding
 
 
 def last_error():
@@ -236,6 +256,10 @@ def _hop_array(roots, times, n, k, edge_weight, out):
 def sample_temporal(g, roots, times, k, hops, policy, seed, m=0, edge_weight=None, out=None, stream=None):
     """taser_sample_temporal. Returns a list of `hops` dicts of device tensors
     nbr/eid/ts [R_h, k] and count [R_h] (allocated here unless `out` is given)."""
+    if out is None and g.handle:
+        r = (_native or _bind()).sample(g.handle.value, roots, times, k, hops, policy, seed, m, edge_weight, stream)
+        if r is not None:
+            return r
     n = roots.numel()
     if out is None:
         out = sample_outputs(n, k, hops, roots.device)
@@ -250,6 +274,10 @@ def sample_temporal_rows(g, roots, times, k, hops, policy, seed, table, m=0, edg
     """taser_sample_temporal_rows: sample_temporal plus, per hop, the rows of `table`
     (2-D device tensor with contiguous rows, as for gather_features) of the sampled edge
     ids. Returns (out, rows_out); rows_out[h] is [R_h * k, d] of the table's dtype."""
+    if out is None and rows_out is None and g.handle:
+        r = (_native or _bind()).sample(g.handle.value, roots, times, k, hops, policy, seed, m, edge_weight, stream, table, row_elems)
+        if r is not None:
+            return r
     if table.dim() != 2 or table.stride(1) != 1 or not table.is_cuda:
         raise TypeError("table: expected a 2-D device tensor with contiguous rows")
     n = roots.numel()
@@ -276,6 +304,9 @@ def sample_temporal_rows(g, roots, times, k, hops, policy, seed, table, m=0, edg
 def candidate_encodings(nbr, count, want_identity=True, stream=None):
     """taser_candidate_encodings. nbr int32[R, m], count int32[R] ->
     (freq int32[R, m], identity uint8[R, m, m] or None)."""
+    r = (_native or _bind()).encodings(nbr, count, want_identity, stream)
+    if r is not None:
+        return r
     _want(nbr, torch.int32, "nbr")
     _want(count, torch.int32, "count")
     if nbr.dim() != 2 or count.numel() != nbr.shape[0]:
@@ -292,6 +323,9 @@ def select_weighted(weight, count, k, seed, hop, candidates=None, stream=None):
     (sel int32[R, k], out_count int32[R], kept). With `candidates` (a dict of
     nbr/eid/ts [R, m] as sample_temporal returns) kept is a dict of nbr/eid/ts
     [R, k] and count, else None."""
+    r = (_native or _bind()).select(weight, count, k, seed, hop, candidates, stream)
+    if r is not None:
+        return r
     _want(weight, torch.int32, "weight (uint32 bits in an int32 tensor)")
     _want(count, torch.int32, "count")
     if weight.dim() != 2 or count.numel() != weight.shape[0]:
@@ -322,6 +356,9 @@ def select_weighted(weight, count, k, seed, hop, candidates=None, stream=None):
 def gather_features(table, ids, out=None, row_elems=None, stream=None):
     """taser_gather_features. table: 2-D device tensor whose rows are contiguous
     (row pitch = table.stride(0)); the first `row_elems` columns are gathered."""
+    r = (_native or _bind()).gather(table, ids, out, row_elems, stream)
+    if r is not None:
+        return r
     if table.dim() != 2 or table.stride(1) != 1 or not table.is_cuda:
         raise TypeError("table: expected a 2-D device tensor with contiguous rows")
     _want(ids, torch.int32, "ids")
@@ -374,6 +411,10 @@ def cache_init(host_table, capacity_rows, resident_ids=None, seed=0, staging_row
 
 def cache_lookup(c, ids, out=None, hit_miss=None, stream=None):
     """taser_cache_lookup. hit_miss: device int64[2] tensor that is incremented, or None."""
+    if c.handle:
+        r = (_native or _bind()).lookup(c.handle.value, c.host_table, c.row_elems, ids, out, hit_miss, stream)
+        if r is not None:
+            return r
     _want(ids, torch.int32, "ids")
     n = ids.numel()
     if out is None:
@@ -484,6 +525,10 @@ def selector_init(scores=None, n=None, initial_score=1, stream=None):
 
 def selector_draw(s, b, seed, iteration, out=None, stream=None):
     """taser_selector_draw -> device int32[b] edge indices."""
+    if s.handle:
+        r = (_native or _bind()).draw(s.handle.value, b, seed, iteration, out, stream)
+        if r is not None:
+            return r
     if out is None:
         out = torch.empty(b, dtype=torch.int32, device="cuda")
     else:
@@ -496,6 +541,8 @@ def selector_draw(s, b, seed, iteration, out=None, stream=None):
 
 def selector_update(s, batch, new_scores, stream=None):
     """taser_selector_update."""
+    if s.handle and (_native or _bind()).update(s.handle.value, batch, new_scores, stream):
+        return
     _want(batch, torch.int32, "batch")
     _want(new_scores, torch.int32, "new_scores (uint32 bits in an int32 tensor)")
     if batch.numel() != new_scores.numel():
@@ -505,6 +552,10 @@ def selector_update(s, batch, new_scores, stream=None):
 
 def selector_scores(s, want_total=True, stream=None):
     """taser_selector_scores -> (device int32[n] holding the uint32 scores, total or None)."""
+    if s.handle and not want_total:
+        r = (_native or _bind()).scores(s.handle.value, s.n, stream)
+        if r is not None:
+            return r, None
     out = torch.empty(s.n, dtype=torch.int32, device="cuda")
     total = ctypes.c_uint64()
     _check(lib().taser_selector_scores(s.handle, _ptr(out), ctypes.byref(total) if want_total else None,
