@@ -231,7 +231,7 @@ __device__ __forceinline__ void select_slots(
         // Candidate window: lane i of the group holds candidate i (the i-th most recent);
         // lane j notes which candidate draw j picked and fetches it from that lane at the end.
         TaserRec mine[R];
-        uint64_t w[R];
+        uint32_t w[R];
         int c[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -251,14 +251,9 @@ __device__ __forceinline__ void select_slots(
             int my_pick = (!draw && sub < c[r]) ? sub : -1;
             if (__ballot(draw)) {
                 uint64_t u = 0;
-                if (draw && sub < k) u = draw64(seed_lo, seed_hi, hop, (uint64_t)(q0 + r), (uint32_t)sub);
-                // running sums of the weights once; every draw then only takes its pick out of them
-                uint64_t run = group_inclusive_scan64<G>(w[r], sub);
-                uint64_t total = group_get64<G>(run, G - 1);
-                for (int j = 0; j < k; ++j) {
-                    const int pick = group_weighted_pick<G>(run, total, w[r], group_get64<G>(u, j), draw, group, sub);
-                    if (draw && sub == j) my_pick = pick;
-                }
+                if (draw && sub < k) u = draw64_wide(seed_lo, seed_hi, hop, (uint64_t)(q0 + r), (uint32_t)sub);
+                const int pick = group_weighted_picks<G>(w[r], u, k, draw, group, sub);
+                if (draw) my_pick = pick;
             }
             const int from = my_pick < 0 ? 0 : my_pick;   // the shuffles are executed by every lane
             const int32_t p_nbr = (int32_t)group_get<G>((uint32_t)mine[r].nbr, from);
@@ -366,12 +361,10 @@ __device__ __forceinline__ void copy_wave_rows(const RowCopy& rc, const int32_t*
     }
 }
 
-// G lanes per root: G >= k, and G >= m for the weighted policy. A group serves
-// kRootsPerGroup consecutive roots: their searches run side by side, their selections
-// stage by stage (measured: two roots per group pay for the most-recent finder on large
-// hops, 39 -> 32 us for 120 000 roots; the uniform and weighted finders, whose time is
-// mostly the arithmetic of their draws, gain nothing from them).
-// With ROWS (one root per group) a wavefront then also copies the table rows of the edges
+// G lanes per root: G >= k, and G >= m for the weighted policy. (Groups that serve two roots, their
+// searches side by side, gain nothing: the uniform and weighted finders' time is mostly the arithmetic
+// of their draws, and large hops of the most-recent finder have a kernel of their own below.)
+// With ROWS a wavefront then also copies the table rows of the edges
 // it sampled into the hop's dense row output: the finder is bound by instruction issue and
 // dependent reads, the copy by memory bandwidth, and in one kernel the wavefronts of a
 // compute unit that search overlap with those that copy.
@@ -691,7 +684,7 @@ __global__ __launch_bounds__(kListThreads) void sample_hop_inverse_timespan_kern
     __syncthreads();
     if (wave != 0) return;            // the draws are one wavefront's work
     uint64_t u = 0;
-    if (lane < k) u = draw64(seed_lo, seed_hi, hop, (uint64_t)root, (uint32_t)lane);
+    if (lane < k) u = draw64_wide(seed_lo, seed_hi, hop, (uint64_t)root, (uint32_t)lane);
     const uint32_t pick = q.near ? draw_entries<true>(q, low, tile_sum, k, u, lane) : draw_entries<false>(q, low, tile_sum, k, u, lane);
     if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, rec[q.lo + pick]);
     if (lane == 0) o_count[root] = k;
@@ -724,6 +717,108 @@ int ensure_ts_low(const taser_tcsr* g_const, hipStream_t stream) {
     return TASER_OK;
 }
 
+// ---- most-recent finder, large hops: four lanes per search ---------------------------
+// A 16-lane search spends its instructions on four roots per wave, and a hop of 10^5 roots puts 30 such
+// waves on every SIMD. Here a quad of lanes searches for one root, each lane comparing four neighboring
+// entries of a level (the same 128-byte line per level): 16 roots per wave for little more than the
+// instructions of four, and all waves resident at once. The slots are then handed out flat, k of them per
+// root whatever k is, so that all lanes load and store. What is left is the latency of one chain of reads.
+// k = 10, 4 M events, 16 lanes / 4 lanes per root: 6 000 roots 4.3 / 4.7 us, 12 000 4.5 / 4.8, 20 000 5.4 / 5.3,
+// 40 000 9.1 / 6.9, 120 000 18.8 / 13.7; k = 25: 6 000 4.7 / 5.8, 20 000 8.6 / 7.9, 120 000 32.1 / 23.1. The uniform
+// finder, searched the same way, gains nothing (60 000 roots 16.6 / 16.0 us, 6 000 roots 6.2 / 12.1): its draws
+// are then three rounds one after the other.
+constexpr int64_t kQuadMinRoots = 16384;
+constexpr int kQuadRoots = 16;          // roots per wave
+
+// 16 bytes of a time-index level, 8-byte aligned.
+struct __attribute__((packed, aligned(8))) TimePair {
+    int64_t a, b;
+};
+
+// As group_cutoff, for the root of this lane's quad. Entry e of level L lies wholly before position p
+// if e < p >> 4 L, so e is "before" if e < lo >> 4 L, or e < hi >> 4 L and its timestamp is below t. Reads
+// at most 15 entries behind a level's (or the record array's) last one: the build leaves room for them,
+// and what they hold does not matter (e >= hi >> 4 L).
+__device__ __forceinline__ uint32_t quad_cutoff(const TaserRec* __restrict__ rec, const TaserTimeIndex& index, uint32_t lo, uint32_t hi,
+                                                int64_t t, uint32_t sub) {
+    const uint32_t d = hi - lo;
+    const int bits = d ? 32 - __clz((int)d) : 0;
+    int top = bits ? (bits + 3) / 4 - 1 : 0;                            // see group_cutoff
+    if ((hi >> (4 * top)) - (lo >> (4 * top)) > 15u) ++top;
+    uint32_t at = 0;
+#pragma unroll
+    for (int L = kTimeIndexLevels; L >= 0; --L) {
+        if (!__ballot(L <= top)) continue;   // no list of this wave is at this level yet
+        if (L <= top) {
+            const uint32_t lo_l = lo >> (4 * L), hi_l = hi >> (4 * L);
+            const uint32_t first = L == top ? lo_l : at * 16u;
+            const uint32_t e = first + 4u * sub;
+            int64_t ts[4];
+            if (L > 0) {
+                const TimePair* p = reinterpret_cast<const TimePair*>(index.level[L > 0 ? L - 1 : 0] + e);
+                const TimePair x = p[0], y = p[1];
+                ts[0] = x.a; ts[1] = x.b; ts[2] = y.a; ts[3] = y.b;
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ts[i] = rec[e + i].ts;
+            }
+            uint32_t c = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c += (uint32_t)((e + i < hi_l && ts[i] < t) || e + i < lo_l);
+            c += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xB1, 0xf, 0xf, true);   // quad_perm [1, 0, 3, 2]
+            c += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0x4E, 0xf, 0xf, true);   // quad_perm [2, 3, 0, 1]
+            at = first + c;
+        }
+    }
+    return at - lo;
+}
+
+__global__ __launch_bounds__(kThreads) void sample_hop_recent_quads_kernel(
+    const int64_t* __restrict__ indptr, const TaserRec* __restrict__ rec, const TaserTimeIndex index,
+    const int32_t* __restrict__ roots, const int64_t* __restrict__ times, int64_t num_roots, int32_t num_nodes, int k, uint32_t magic_k,
+    int32_t* __restrict__ o_nbr, int32_t* __restrict__ o_eid, int64_t* __restrict__ o_ts, int32_t* __restrict__ o_count) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t q0 = ((int64_t)blockIdx.x * (kThreads / kWave) + wave) * kQuadRoots;   // first root of the wave
+    if (q0 >= num_roots) return;
+    const int here = num_roots - q0 < kQuadRoots ? (int)(num_roots - q0) : kQuadRoots;    // roots of the wave
+    const int quad = lane >> 2;
+    uint32_t lo = 0, hi = 0;
+    int64_t t = 0;
+    if (quad < here) {
+        const int32_t v = roots[q0 + quad];
+        if (v >= 0 && v < num_nodes) {   // anything else is a root without neighbors
+            t = times[q0 + quad];
+            lo = (uint32_t)indptr[v];
+            hi = (uint32_t)indptr[v + 1];
+        }
+    }
+    const uint32_t cnt = quad_cutoff(rec, index, lo, hi, t, (uint32_t)lane & 3u);
+    if ((lane & 3) == 0 && quad < here) o_count[q0 + quad] = (int32_t)(cnt < (uint32_t)k ? cnt : (uint32_t)k);
+    // slot s of the wave is slot s % k of root s / k
+    const TaserRec pad = {0, -1, -1};
+    constexpr int kAhead = 3;            // record loads of a lane in flight together
+    const uint32_t slots = (uint32_t)(here * k);
+    for (uint32_t s0 = 0; s0 < slots; s0 += kAhead * kWave) {
+        TaserRec got[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t s = s0 + u * kWave + lane;
+            uint32_t r = k == 1 ? s : __umulhi(s, magic_k);   // exact: s < 2^11, k <= 64
+            const uint32_t j = s - r * (uint32_t)k;
+            if (r > kQuadRoots - 1) r = kQuadRoots - 1;        // past the wave's slots
+            const uint32_t r_lo = __shfl(lo, (int)r * 4, kWave), r_cnt = __shfl(cnt, (int)r * 4, kWave);
+            got[u] = pad;
+            if (s < slots && j < r_cnt) got[u] = rec[r_lo + r_cnt - 1u - j];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const uint32_t s = s0 + u * kWave + lane;
+            if (s < slots) store_slot(o_nbr, o_eid, o_ts, q0 * k + s, got[u]);
+        }
+    }
+}
+
 template <int POLICY, int G, int kRootsPerGroup, bool ROWS>
 void launch_hop_gr(const taser_tcsr* g, const int32_t* roots, const int64_t* times, int64_t n, int k,
                    uint64_t seed, uint32_t hop, int m, const uint32_t* edge_weight, const taser_hop_out& o,
@@ -740,7 +835,6 @@ void launch_hop_g(const taser_tcsr* g, const int32_t* roots, const int64_t* time
                   uint64_t seed, uint32_t hop, int m, const uint32_t* edge_weight, const taser_hop_out& o,
                   const RowCopy* rows, hipStream_t stream) {
     if (rows) launch_hop_gr<POLICY, G, 1, true>(g, roots, times, n, k, seed, hop, m, edge_weight, o, *rows, stream);
-    else if (POLICY == TASER_RECENT && n >= 65536) launch_hop_gr<POLICY, G, 2, false>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
     else launch_hop_gr<POLICY, G, 1, false>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
 }
 
@@ -758,6 +852,14 @@ void launch_hop(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
                                             {"sample_rows_hop_recent", "sample_rows_hop_uniform", "sample_rows_hop_weighted"}};
     TaserProfileSpan span(stream, names[rows ? 1 : 0][POLICY]);
     const int lanes = group_lanes(POLICY, k, m);
+    if (POLICY == TASER_RECENT && !rows && n >= kQuadMinRoots) {
+        constexpr int roots_per_block = kThreads / kWave * kQuadRoots;
+        const unsigned grid = (unsigned)((n + roots_per_block - 1) / roots_per_block);
+        const uint32_t magic_k = k > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u;
+        hipLaunchKernelGGL(sample_hop_recent_quads_kernel, dim3(grid), dim3(kThreads), 0, stream, g->indptr, g->rec, g->time_index, roots,
+                           times, n, g->num_nodes, k, magic_k, o.nbr, o.eid, o.ts, o.count);
+        return;
+    }
     if (lanes == 16) launch_hop_g<POLICY, 16>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);
     else if (lanes == 32) launch_hop_g<POLICY, 32>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);
     else launch_hop_g<POLICY, 64>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);

@@ -35,6 +35,7 @@ struct __attribute__((aligned(16))) TaserRec {
 // the final, partial run). A search for a query time inside one node's list reads
 // one 128-byte line of 16 neighboring entries per level instead of 16 scattered
 // records; the upper levels are small enough to stay in L2.
+constexpr int kSearchSlack = 16;      // entries behind the end of each of these arrays that may be read (their values never matter)
 constexpr int kTimeIndexLevels = 7;   // 16^7 = 2^28: at the top a list of < 2^31 records spans < 16 entries
 struct TaserTimeIndex {
     const int64_t* level[kTimeIndexLevels];   // level[l - 1]: device int64[len[l - 1]]

@@ -594,11 +594,12 @@ Layout layout_of(int64_t n, int32_t num_nodes, bool copy_input) {
         return here;
     };
     l.indptr = take(((size_t)num_nodes + 1) * sizeof(int64_t));
-    l.rec = take((size_t)n * sizeof(TaserRec));
+    // kSearchSlack entries behind the records and behind every level: the search reads whole groups of 16
+    l.rec = take((size_t)(n + kSearchSlack) * sizeof(TaserRec));
     int64_t below = n;
     for (int i = 0; i < kTimeIndexLevels; ++i) {
         l.level_len[i] = below = (below + 15) / 16;
-        l.level[i] = take((size_t)below * sizeof(int64_t));
+        l.level[i] = take((size_t)(below + kSearchSlack) * sizeof(int64_t));
     }
     l.storage = at;
     at = 0;

@@ -9,10 +9,7 @@
 // weight per (root, candidate).
 //
 // Both kernels use a group of G = 16, 32 or 64 lanes per root (G >= m), one
-// lane per candidate, so a window never leaves registers: comparisons go
-// through lane shuffles, prefix sums through __shfl_up.
-#include <type_traits>
-
+// lane per candidate.
 #include "sampling_device.h"
 #include "taser_internal.h"
 
@@ -20,28 +17,33 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// floor(b / d) for small b: d = 1 is the identity, otherwise a multiply-high with
-// magic = ceil(2^32 / d), exact while b * d < 2^32 (here b < 2^13, d <= 2^12).
-__device__ __forceinline__ uint32_t small_div(uint32_t b, uint32_t d, uint32_t magic) {
-    return d == 1u ? b : __umulhi(b, magic);
+// Candidates [0, n) of a window, as bits of the mask's part that begins at candidate `from`.
+__device__ __forceinline__ uint32_t first_bits(int n, int from) {
+    const int k = n - from;
+    return k >= 32 ? ~0u : k <= 0 ? 0u : (1u << k) - 1u;
 }
 
-// freq + identity. Lane j of a group holds u_j and builds a bit mask over l of
-// the candidates equal to it; freq is the mask's population count. The m x m
-// identity bytes of the roots of one wavefront are contiguous in the output,
-// so the wave writes them as one flat range, four bytes per lane and store.
+// freq + identity. Lane j of a group holds u_j; the group's u are broadcast from LDS, four at a time, and
+// every lane shifts the outcomes of its comparisons into a bit mask over l of the candidates equal to it;
+// freq is the mask's population count. The m x m identity bytes are those masks, one bit per byte: the
+// masks of the block's roots go into LDS as one string of bits, and the block's range of the output is
+// written from it 16 bytes at a time (4 bits times 0x204081 are 4 bytes), whatever m and the alignment.
+// Bound by its output: 40 000 windows of 25 (33 MB in all) take 12 us; with one lane shuffle per comparison
+// and per output byte it was 24 us of vector and LDS instructions.
 template <int G>
 __global__ __launch_bounds__(kThreads) void candidate_encodings_kernel(
-    const int32_t* __restrict__ nbr, const int32_t* __restrict__ count, int64_t num_roots, int m, uint32_t magic_m,
-    uint32_t magic_mm, int32_t* __restrict__ freq, uint8_t* __restrict__ identity) {
-    constexpr int kGroups = kWave / G;
-    typedef typename std::conditional<(G > 32), uint64_t, uint32_t>::type Mask;   // one bit per candidate
-    const int lane = threadIdx.x & (kWave - 1);
-    const int group = lane / G, sub = lane % G;
-    const int64_t wave_root0 = ((int64_t)blockIdx.x * (kThreads / kWave) + (threadIdx.x >> 6)) * kGroups;
-    const int64_t q = wave_root0 + group;
+    const int32_t* __restrict__ nbr, const int32_t* __restrict__ count, int64_t num_roots, int m, int32_t* __restrict__ freq,
+    uint8_t* __restrict__ identity) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kRoots = kThreads / G;                // roots of a block
+    constexpr int kWords = kRoots * G * G / 32 + 1;     // bits of their identity matrices, and a word to read past the end
+    constexpr int kParts = G > 32 ? 2 : 1;              // 32-bit parts of a mask
+    __shared__ __align__(16) int32_t cand[kThreads];
+    __shared__ uint32_t bits[kWords];
+    const int group = threadIdx.x / G, sub = threadIdx.x % G;
+    const int64_t root0 = (int64_t)blockIdx.x * kRoots, q = root0 + group;
     const bool live = q < num_roots;
-
     int c = 0;
     if (live) {
         c = count[q];
@@ -50,57 +52,62 @@ __global__ __launch_bounds__(kThreads) void candidate_encodings_kernel(
     const bool mine_valid = sub < c;
     int32_t u = -1;
     if (mine_valid) u = nbr[q * m + sub];
+    cand[threadIdx.x] = u;
+    for (int i = threadIdx.x; i < kWords; i += kThreads) bits[i] = 0;
+    __syncthreads();
 
-    Mask same = 0;   // bit l: candidate l is valid and names the same node as mine
-    for (int l = 0; l < m; ++l) {
-        const int32_t other = (int32_t)group_get<G>((uint32_t)u, l);
-        if (mine_valid && l < c && other == u) same |= (Mask)1 << l;
+    uint32_t same[kParts];   // bit l: candidate l is valid and names the same node as mine
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) {
+        same[p] = 0;
+        const i32x4* from = reinterpret_cast<const i32x4*>(cand + group * G + 32 * p);
+#pragma unroll
+        for (int i = (G < 32 ? G : 32) / 4 - 1; i >= 0; --i) {
+            if (32 * p + 4 * i >= m) continue;          // uniform
+            const i32x4 v = from[i];
+            same[p] = 2u * same[p] + (uint32_t)(v.w == u);
+            same[p] = 2u * same[p] + (uint32_t)(v.z == u);
+            same[p] = 2u * same[p] + (uint32_t)(v.y == u);
+            same[p] = 2u * same[p] + (uint32_t)(v.x == u);
+        }
+        same[p] = mine_valid ? same[p] & first_bits(c, 32 * p) : 0u;
     }
-    if (live && sub < m) freq[q * m + sub] = (G > 32) ? __popcll((uint64_t)same) : __popc((uint32_t)same);
+    if (live && sub < m) {
+        int n = __popc(same[0]);
+        if (kParts == 2) n += __popc(same[kParts - 1]);
+        freq[q * m + sub] = n;
+    }
 
     if (identity == nullptr) return;   // uniform for the whole grid
-    // Flat byte range of this wave's roots: [base, end). Byte b of it belongs to root
-    // b / (m*m) of the wave, row (b % (m*m)) / m, column b % m.
-    const uint32_t mm = (uint32_t)(m * m);
-    int64_t roots_here = num_roots - wave_root0;
-    if (roots_here <= 0) return;       // uniform for the wave
-    if (roots_here > kGroups) roots_here = kGroups;
-    const uint64_t base = (uint64_t)(uintptr_t)identity + (uint64_t)wave_root0 * mm;   // address of the first byte
-    const uint32_t length = (uint32_t)roots_here * mm;
-    const uint32_t head = (uint32_t)(base & 3u);          // bytes between the aligned start and base
-    const uint64_t aligned = base - head;
-    const uint32_t chunks = (head + length + 3u) >> 2;
-    const uint32_t rounds = (chunks + kWave - 1) / kWave;   // the same for every lane: the shuffles below need them all
-    for (uint32_t it = 0; it < rounds; ++it) {
-        const uint32_t off = (it * kWave + (uint32_t)lane) * 4u;   // from `aligned`
-        uint32_t word = 0;
-        bool inside[4];
+    if (sub < m) {
+        const uint32_t at = (uint32_t)(group * m + sub) * (uint32_t)m;   // this row's place in the string of bits
+        const uint32_t shift = at & 31u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t o = off + (uint32_t)i;
-            inside[i] = o >= head && o < head + length;
-            const uint32_t b = inside[i] ? o - head : 0u;
-            const uint32_t r = small_div(b, mm, magic_mm), rem = b - r * mm;
-            const uint32_t row = small_div(rem, (uint32_t)m, magic_m), col = rem - row * (uint32_t)m;
-            // every lane takes part in the shuffle; its source is lane `row` of group r
-            const int src = (int)(r * G + row);
-            Mask mask;
-            if (G > 32) {
-                const uint32_t lo = (uint32_t)__shfl((int)(uint32_t)same, src, kWave);
-                const uint32_t hi = (uint32_t)__shfl((int)(uint32_t)((uint64_t)same >> 32), src, kWave);
-                mask = (Mask)(((uint64_t)hi << 32) | lo);
-            } else {
-                mask = (Mask)(uint32_t)__shfl((int)(uint32_t)same, src, kWave);
-            }
-            word |= (uint32_t)((mask >> col) & 1u) << (8 * i);
+        for (int p = 0; p < kParts; ++p) {
+            if (!same[p]) continue;
+            atomicOr(&bits[at / 32u + p], same[p] << shift);
+            if (shift) atomicOr(&bits[at / 32u + p + 1], same[p] >> (32u - shift));
         }
-        const uint64_t at = aligned + off;
-        if (inside[0] && inside[3]) {
-            *reinterpret_cast<uint32_t*>(at) = word;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (inside[i]) *reinterpret_cast<uint8_t*>(at + (uint32_t)i) = (uint8_t)(word >> (8 * i));
+    }
+    __syncthreads();
+    const int64_t roots_here = num_roots - root0 < kRoots ? num_roots - root0 : kRoots;
+    const uint32_t length = (uint32_t)roots_here * (uint32_t)(m * m);               // bytes of the block's range
+    const uint64_t base = (uint64_t)(uintptr_t)identity + (uint64_t)root0 * (uint64_t)(m * m);
+    const uint32_t head = (uint32_t)(base & 15u);                                   // bytes between the aligned start and base
+    uint8_t* const aligned = reinterpret_cast<uint8_t*>(base - head);
+    for (uint32_t off = threadIdx.x * 16u; off < head + length; off += kThreads * 16u) {
+        if (off >= head && off + 16u <= head + length) {
+            const uint32_t b = off - head;
+            const uint32_t x = __builtin_amdgcn_alignbit(bits[b / 32u + 1u], bits[b / 32u], b & 31u);
+            u32x4 v;
+            v.x = __umul24(x & 15u, 0x204081u) & 0x01010101u;
+            v.y = __umul24((x >> 4) & 15u, 0x204081u) & 0x01010101u;
+            v.z = __umul24((x >> 8) & 15u, 0x204081u) & 0x01010101u;
+            v.w = __umul24((x >> 12) & 15u, 0x204081u) & 0x01010101u;
+            *reinterpret_cast<u32x4*>(aligned + off) = v;
+        } else {   // the range's first or last bytes
+            for (uint32_t o = off; o < off + 16u; ++o)
+                if (o >= head && o < head + length) aligned[o] = (uint8_t)((bits[(o - head) / 32u] >> ((o - head) & 31u)) & 1u);
         }
     }
 }
@@ -108,7 +115,8 @@ __global__ __launch_bounds__(kThreads) void candidate_encodings_kernel(
 // n of m by per-slot weights: lane i of a group holds the weight of candidate i.
 // The running sums of the weights are taken once; each of the k rounds scales one
 // 64-bit draw to the remaining total, picks the first lane whose running sum exceeds
-// it and takes that lane's weight out of the sums after it. Lane j keeps round j's pick, so the outputs are written coalesced at the end.
+// it and takes that lane's weight out of the sums after it (group_weighted_picks). Lane j
+// keeps round j's pick, so the outputs are written coalesced at the end.
 template <int G>
 __global__ __launch_bounds__(kThreads) void select_weighted_kernel(
     const uint32_t* __restrict__ weight, const int32_t* __restrict__ count, int64_t num_roots, int m, int k,
@@ -126,20 +134,16 @@ __global__ __launch_bounds__(kThreads) void select_weighted_kernel(
         c = count[q];
         c = c < 0 ? 0 : (c > m ? m : c);
     }
-    uint64_t w = 0;
+    uint32_t w = 0;
     if (sub < c) w = weight[q * m + sub];
     const bool draw = c > k;
     const int filled = draw ? k : c;
     int32_t my_pick = (!draw && sub < c) ? sub : -1;   // slot `sub` of the output
     if (__ballot(draw)) {
         uint64_t u = 0;
-        if (draw && sub < k) u = draw64(seed_lo, seed_hi, hop, (uint64_t)q, (uint32_t)sub);
-        uint64_t run = group_inclusive_scan64<G>(w, sub);
-        uint64_t total = group_get64<G>(run, G - 1);
-        for (int j = 0; j < k; ++j) {
-            const int pick = group_weighted_pick<G>(run, total, w, group_get64<G>(u, j), draw, group, sub);   // -1 only if every remaining weight is 0
-            if (draw && sub == j) my_pick = pick;
-        }
+        if (draw && sub < k) u = draw64_wide(seed_lo, seed_hi, hop, (uint64_t)q, (uint32_t)sub);
+        const int pick = group_weighted_picks<G>(w, u, k, draw, group, sub);   // -1 only if every remaining weight is 0
+        if (draw) my_pick = pick;
     }
     if (live && sub < k) {
         const int64_t at = q * k + sub;
@@ -173,15 +177,12 @@ extern "C" int taser_candidate_encodings(const int32_t* nbr, const int32_t* coun
     taser_clear_stale_hip_error();
     hipStream_t stream = (hipStream_t)hip_stream;
     TaserProfileSpan span(stream, "candidate_encodings");
-    const uint32_t mm = (uint32_t)(m * m);
-    const uint32_t magic_m = m > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint32_t)m - 1) / (uint32_t)m) : 0u;
-    const uint32_t magic_mm = m > 1 ? (uint32_t)((((uint64_t)1 << 32) + mm - 1) / mm) : 0u;
     if (m <= 16)
-        hipLaunchKernelGGL((candidate_encodings_kernel<16>), dim3(grid_for<16>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, magic_m, magic_mm, freq, identity);
+        hipLaunchKernelGGL((candidate_encodings_kernel<16>), dim3(grid_for<16>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, freq, identity);
     else if (m <= 32)
-        hipLaunchKernelGGL((candidate_encodings_kernel<32>), dim3(grid_for<32>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, magic_m, magic_mm, freq, identity);
+        hipLaunchKernelGGL((candidate_encodings_kernel<32>), dim3(grid_for<32>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, freq, identity);
     else
-        hipLaunchKernelGGL((candidate_encodings_kernel<64>), dim3(grid_for<64>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, magic_m, magic_mm, freq, identity);
+        hipLaunchKernelGGL((candidate_encodings_kernel<64>), dim3(grid_for<64>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, freq, identity);
     TASER_HIP_TRY(hipGetLastError());
     return TASER_OK;
 }
