@@ -203,9 +203,8 @@ int taser_sample_temporal(const taser_tcsr* g, const int32_t* roots, const int64
  * 4, rows_out[h] 16-byte aligned and those bytes per wavefront a multiple of
  * 16. A hop for which any of it fails, every hop with longer rows (for which a
  * gather launch is the faster way) and every hop of TASER_INVERSE_TIMESPAN get
- * their rows from the gather kernel after the last hop, in one launch where the
- * hops' edge id arrays and row buffers follow one another in memory. The bytes
- * are the same either way.
+ * their rows from the gather kernel after the last hop, in one launch where all
+ * row buffers are 16-byte aligned. The bytes are the same either way.
  *   sampling arguments, `out`: as for taser_sample_temporal
  *   table, table_rows, row_bytes, pitch_bytes: as for taser_gather_features
  *   rows_out  host array of `hops` device pointers; rows_out[h] receives

@@ -22,6 +22,44 @@ struct TableSource {
     }
 };
 
+// Up to two gathers after the first: where their blocks begin, their ids and outputs.
+struct MoreParts {
+    static constexpr bool kMore = true;
+    struct Part {
+        uint32_t first_block;
+        const int32_t* ids;
+        int64_t total_units, last_row;
+        uint8_t* out;
+    } part[2];
+    __device__ __forceinline__ uint32_t enter(uint32_t block, TableSource& source, int64_t& total_units, int64_t& last_row,
+                                                    uint8_t* __restrict__& out) const {
+        const int p = block >= part[1].first_block ? 1 : block >= part[0].first_block ? 0 : -1;   // uniform
+        if (p < 0) return block;
+        source.ids = part[p].ids;
+        total_units = part[p].total_units;
+        last_row = part[p].last_row;
+        out = part[p].out;
+        return block - part[p].first_block;
+    }
+};
+
+template <int UNIT>
+bool launch_parts(const TableSource& source, int32_t row_bytes, const TaserGatherPart* parts, int n_parts, const uint8_t* zeros, hipStream_t stream) {
+    using namespace taser_gather;
+    int64_t blocks = chunk_blocks<UNIT>(row_bytes, parts[0].n);
+    const int64_t first = blocks;
+    MoreParts more;
+    for (int i = 0; i < 2; ++i) {
+        more.part[i] = MoreParts::Part{0xffffffffu, nullptr, 0, 0, nullptr};
+        if (i + 1 >= n_parts) continue;
+        const TaserGatherPart& p = parts[i + 1];
+        if (blocks > 0x7fffffffLL) return false;
+        more.part[i] = MoreParts::Part{(uint32_t)blocks, p.ids, p.n * (int64_t)(row_bytes / UNIT), p.n - 1, static_cast<uint8_t*>(p.out)};
+        blocks += chunk_blocks<UNIT>(row_bytes, p.n);
+    }
+    return launch_chunks<UNIT, 0>(source, row_bytes, parts[0].n, parts[0].out, zeros, stream, NothingBeside{}, more, blocks - first);
+}
+
 }  // namespace
 
 // 16 zero bytes in device memory. External linkage and "used": a device variable
@@ -54,6 +92,29 @@ int taser_launch_gather(const void* table, int64_t rows, int32_t row_bytes, int6
     if (!taser_gather::launch(source, align, row_bytes, n, out, stream))
         return taser_fail(TASER_E_RANGE, "gather: %lld rows of %d bytes exceed one launch", (long long)n, row_bytes);
     TASER_HIP_TRY(hipGetLastError());
+    return TASER_OK;
+}
+
+int taser_launch_gather_parts(const void* table, int64_t rows, int32_t row_bytes, int64_t pitch_bytes, const TaserGatherPart* parts,
+                              int n_parts, hipStream_t stream) {
+    const int align = taser_gather::common_alignment((uint64_t)row_bytes | (uint64_t)pitch_bytes | (uint64_t)(uintptr_t)table);
+    // one launch where every part's output suits the chunk kernel and all blocks fit
+    bool together = n_parts > 1 && n_parts <= 3 && (align >= 4 || row_bytes >= 16);
+    for (int i = 0; i < n_parts; ++i) together = together && parts[i].n > 0 && ((uintptr_t)parts[i].out & 15) == 0;
+    if (together) {
+        taser_clear_stale_hip_error();
+        const uint8_t* zeros = taser_gather::zero_chunk();
+        if (!zeros) return taser_fail(TASER_E_HIP, "gather: the zero constant is not available on this device");
+        const TableSource source{static_cast<const uint8_t*>(table), pitch_bytes, parts[0].ids, rows};
+        TaserProfileSpan span(stream, "gather_rows");
+        together = align >= 4 ? launch_parts<4>(source, row_bytes, parts, n_parts, zeros, stream)
+                              : launch_parts<2>(source, row_bytes, parts, n_parts, zeros, stream);
+        TASER_HIP_TRY(hipGetLastError());
+    }
+    for (int i = 0; i < n_parts && !together; ++i) {
+        const int rc = taser_launch_gather(table, rows, row_bytes, pitch_bytes, parts[i].ids, parts[i].n, parts[i].out, stream);
+        if (rc != TASER_OK) return rc;
+    }
     return TASER_OK;
 }
 

@@ -84,16 +84,22 @@ struct NothingBeside {
     static constexpr uint32_t blocks = 0;
     static __device__ __forceinline__ void run(uint32_t, int32_t*) {}
 };
-template <typename Source, bool USE_MAGIC, int UNIT, int PHASE, typename Beside>
+// Parts: further gathers from the same table in the same launch (a multi-hop call's hops each have ids and rows
+// of their own; a launch for the small first hop costs as much as its rows), or OnePart.
+struct OnePart {
+    static constexpr bool kMore = false;
+};
+template <typename Source, bool USE_MAGIC, int UNIT, int PHASE, typename Beside, typename Parts>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_chunks_kernel(
     Source source, uint32_t row_units, uint32_t magic, int64_t total_units, int64_t last_row, const uint8_t* __restrict__ zeros,
-    uint8_t* __restrict__ out, const Beside beside) {
+    uint8_t* __restrict__ out, const Beside beside, const Parts parts) {
     __shared__ int32_t tile_key[tile_rows(UNIT)];
     if (Beside::kAny && blockIdx.x < beside.blocks) {
         beside.run(blockIdx.x, tile_key);
         return;
     }
-    const uint32_t block = Beside::kAny ? blockIdx.x - beside.blocks : blockIdx.x;
+    uint32_t block = Beside::kAny ? blockIdx.x - beside.blocks : blockIdx.x;
+    if constexpr (Parts::kMore) block = parts.enter(block, source, total_units, last_row, out);
     constexpr uint32_t kPer = 16 / UNIT;                       // units of a chunk
     const int64_t tile = (int64_t)block * (kTile * kPer);   // first output unit of this block
     int64_t row0;                                               // output row holding it
@@ -416,22 +422,25 @@ inline void launch_elems(const Source& source, int32_t row_bytes, int64_t n, voi
 }
 
 // Flat gather in 16-byte chunks of the output; UNIT (4 or 2) divides everything.
-template <int UNIT, int PHASE, typename Source, typename Beside = NothingBeside>
+template <int UNIT> inline int64_t chunk_blocks(int32_t row_bytes, int64_t n) {
+    return (n * (int64_t)(row_bytes / UNIT) + kTile * (16 / UNIT) - 1) / (kTile * (16 / UNIT));
+}
+template <int UNIT, int PHASE, typename Source, typename Beside = NothingBeside, typename Parts = OnePart>
 inline bool launch_chunks(const Source& source, int32_t row_bytes, int64_t n, void* out, const uint8_t* zeros, hipStream_t stream,
-                          const Beside& beside = {}) {
+                          const Beside& beside = {}, const Parts& parts = {}, int64_t more_blocks = 0) {
     const uint32_t row_units = (uint32_t)row_bytes / UNIT, tile_units = kTile * (16 / UNIT);
     const int64_t total = n * (int64_t)row_units;
-    const int64_t blocks = (total + tile_units - 1) / tile_units + beside.blocks;
+    const int64_t blocks = chunk_blocks<UNIT>(row_bytes, n) + beside.blocks + more_blocks;
     if (blocks > 0x7fffffffLL) return false;
     // the in-block offsets stay below row_units + tile_units: exact while that is < 2^32 / row_units
     const bool small = (uint64_t)row_units * ((uint64_t)row_units + tile_units) < ((uint64_t)1 << 32);
     if (small && row_units > 1) {
         const uint32_t magic = (uint32_t)((((uint64_t)1 << 32) + row_units - 1) / row_units);
-        hipLaunchKernelGGL((gather_chunks_kernel<Source, true, UNIT, PHASE, Beside>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
-                           source, row_units, magic, total, n - 1, zeros, static_cast<uint8_t*>(out), beside);
+        hipLaunchKernelGGL((gather_chunks_kernel<Source, true, UNIT, PHASE, Beside, Parts>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
+                           source, row_units, magic, total, n - 1, zeros, static_cast<uint8_t*>(out), beside, parts);
     } else {
-        hipLaunchKernelGGL((gather_chunks_kernel<Source, false, UNIT, PHASE, Beside>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
-                           source, row_units, 0u, total, n - 1, zeros, static_cast<uint8_t*>(out), beside);
+        hipLaunchKernelGGL((gather_chunks_kernel<Source, false, UNIT, PHASE, Beside, Parts>), dim3((unsigned)blocks), dim3(kThreads), 0, stream,
+                           source, row_units, 0u, total, n - 1, zeros, static_cast<uint8_t*>(out), beside, parts);
     }
     return true;
 }

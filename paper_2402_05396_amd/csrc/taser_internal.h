@@ -62,6 +62,15 @@ static constexpr int kWave = 64;
 int taser_launch_gather(const void* table, int64_t rows, int32_t row_bytes, int64_t pitch_bytes,
                         const int32_t* ids, int64_t n, void* out, hipStream_t stream);
 
+// The same for several lists of ids and outputs (three at most go into one launch).
+struct TaserGatherPart {
+    const int32_t* ids;
+    int64_t n;
+    void* out;
+};
+int taser_launch_gather_parts(const void* table, int64_t rows, int32_t row_bytes, int64_t pitch_bytes, const TaserGatherPart* parts,
+                              int n_parts, hipStream_t stream);
+
 // Looks up, for the current device, the addresses of the library's device constants
 // (a symbol lookup the first time; nothing afterwards). Handle-making entry points call
 // it so that later gathers on the device only launch kernels.

@@ -73,3 +73,26 @@ def test_weights_on_both_sides_of_the_32_bit_draws(k, m, top):
     got = T.select_weighted(dev(w.view(np.int32)), dev(count), k, 3, 1)
     for a, b in zip(got[:2], want[:2]):
         assert np.array_equal(a.cpu().numpy(), b)
+
+
+@pytest.mark.parametrize("dtype,dim,pad,n,k", [(np.float32, 300, 0, 37, 5), (np.float16, 413, 0, 29, 6), (np.float16, 172, 20, 40, 4), (np.float32, 1030, 0, 1, 3)])
+def test_rows_of_three_hops_in_one_gather_launch(dtype, dim, pad, n, k):
+    """Rows too long for the hop kernels: one launch gathers all hops' rows where every buffer is 16-byte aligned, one per
+    hop where one is not; the hops' last blocks are partial."""
+    rng = np.random.default_rng(dim)
+    src, dst = rng.integers(0, 60, (2, 900)).astype(np.int32)
+    ts = np.sort(rng.integers(0, 700, 900)).astype(np.int64)
+    g, g_ref = both(src, dst, ts, 60)
+    full = rng.integers(-2 ** 15, 2 ** 15, (800, (dim + pad) * np.dtype(dtype).itemsize // 2)).astype(np.int16).view(dtype)   # ids from 800 on: zero rows
+    table, table_np = dev(full)[:, :dim], full[:, :dim]
+    roots, times = rng.integers(-1, 60, n).astype(np.int32), rng.integers(300, 701, n).astype(np.int64)
+    want = oracle.sample_temporal(g_ref, roots, times, k, 3, T.RECENT, 1, 0, None, THREADS)
+    out, rows = T.sample_temporal_rows(g, dev(roots), dev(times), k, 3, T.RECENT, 1, table)
+    odd = [torch.empty(w["eid"].size * dim + 8, dtype=table.dtype, device="cuda")[(2 if h == 1 else 0):][:w["eid"].size * dim].view(-1, dim)
+           for h, w in enumerate(want)]
+    _, rows2 = T.sample_temporal_rows(g, dev(roots), dev(times), k, 3, T.RECENT, 1, table, out=T.sample_outputs(n, k, 3, "cuda"), rows_out=odd)
+    for h in range(3):
+        assert np.array_equal(out[h]["eid"].cpu().numpy(), want[h]["eid"])
+        ids = want[h]["eid"].ravel()
+        bytes_ = oracle.gather(np.ascontiguousarray(table_np), np.where(ids >= 800, -1, ids)).tobytes()
+        assert rows[h].cpu().numpy().tobytes() == bytes_ and rows2[h].cpu().numpy().tobytes() == bytes_, h
