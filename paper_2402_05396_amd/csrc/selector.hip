@@ -7,8 +7,9 @@
 // linear in the number of training edges per iteration: the scores carry two
 // levels of partial sums (1024 scores per level-1 sum, 1024 level-1 sums per
 // level-2 sum) that an update adjusts by the difference it makes, and a draw
-// descends the three levels with one wavefront: at most 32 + 16 + 16 rows of
-// 64 values for 2^31 edges, 1 + 16 + 16 for a million.
+// descends the three levels with one wavefront: at most 32 rows of 64 values of
+// the top level for 2^31 edges, one for a million, then one group of 1024 values
+// of each lower level, read at once.
 #include <new>
 
 #include "sampling_device.h"
@@ -52,52 +53,80 @@ __device__ __forceinline__ int64_t wave_descend(const T* __restrict__ a, int64_t
     return end - 1;   // not reached while the guarantee holds
 }
 
-// The same for one group of up to 1024 values starting at a[begin]: lane l loads
-// values 16 l .. 16 l + 15 at once (all loads of the group in flight together),
-// one wave scan of the lane totals finds the lane, that lane walks its 16 values.
+// The same for one group of up to 1024 values starting at a[begin], all its loads in flight together. The
+// group is read in rows of 64 x 16 bytes, one piece per lane, so that a load covers whole lines (with 16
+// neighboring values per lane every load touched 64 lines; us a call, million edges:
+// 600 draws 6.0 -> 4.8, 2 000 7.7 -> 5.8, 6 000 15.6 -> 11.3). The scans of the rows do not depend on
+// one another; the row is found first, then the lane, then the value.
 template <typename T>
 __device__ __forceinline__ int64_t wave_descend_group(const T* __restrict__ a, int64_t begin, int64_t end, uint64_t& x,
                                                       int lane) {
-    constexpr int kPer = kFan / kWave;   // 16
-    T v[kPer];
-    const int64_t mine = begin + (int64_t)lane * kPer;
-    if (begin + kFan <= end) {   // a whole group (wave-uniform): 16-byte loads; the arrays come from hipMalloc and
-                                 // `mine` is a multiple of 16 values, so the address is 64-byte aligned
-        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-        constexpr int kVec = kPer * (int)sizeof(T) / 16;
-        u32x4 raw[kVec];
-        const u32x4* p = reinterpret_cast<const u32x4*>(a + mine);
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kVec = 16 / (int)sizeof(T);          // values per piece: 4 or 2
+    constexpr int kRows = kFan / (kWave * kVec);       // 4 or 8
+    T v[kRows][kVec];
+    const int64_t mine = begin + (int64_t)lane * kVec;
+    if (begin + kFan <= end) {   // a whole group (wave-uniform); `begin` is a multiple of 1024 values, so the address is aligned
+        u32x4 raw[kRows];
 #pragma unroll
-        for (int i = 0; i < kVec; ++i) raw[i] = p[i];
+        for (int r = 0; r < kRows; ++r) raw[r] = *reinterpret_cast<const u32x4*>(a + mine + r * kWave * kVec);
         __builtin_memcpy(v, raw, sizeof(v));
     } else {
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) v[i] = mine + i < end ? a[mine + i] : (T)0;
-    }
-    uint64_t own = 0;
+        for (int r = 0; r < kRows; ++r)
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) own += (uint64_t)v[i];
-    const uint64_t inc = wave_inclusive_scan64(own);
-    const uint64_t hit = __ballot(inc > x);
+            for (int i = 0; i < kVec; ++i) v[r][i] = mine + r * kWave * kVec + i < end ? a[mine + r * kWave * kVec + i] : (T)0;
+    }
+    uint64_t own[kRows], inc[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        own[r] = 0;
+#pragma unroll
+        for (int i = 0; i < kVec; ++i) own[r] += (uint64_t)v[r][i];
+        inc[r] = wave_inclusive_scan64(own[r]);
+    }
+    // the row where the running sum passes x; the last one while the guarantee does not hold
+    int row = kRows - 1;
+    uint64_t before = 0, rest = x;
+    T pick[kVec];
+    uint64_t pick_inc = inc[kRows - 1], pick_own = own[kRows - 1];
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) pick[i] = v[kRows - 1][i];
+    bool open = true;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const uint64_t total = wave_get64(inc[r], kWave - 1);
+        const bool here = open && (r == kRows - 1 || before + total > x);   // wave-uniform
+        if (here) {
+            row = r;
+            rest = x - before;
+            pick_inc = inc[r];
+            pick_own = own[r];
+#pragma unroll
+            for (int i = 0; i < kVec; ++i) pick[i] = v[r][i];
+            open = false;
+        }
+        before += total;
+    }
+    const uint64_t hit = __ballot(pick_inc > rest);
     const int first = hit ? __ffsll((long long)hit) - 1 : kWave - 1;   // hit is never 0 while the guarantee holds
-    uint64_t rest = x - wave_get64(inc - own, first);                  // what is left inside that lane
-    int found = kPer - 1;
-    uint64_t left = rest;
+    rest -= wave_get64(pick_inc - pick_own, first);                    // what is left inside that lane
+    int found = kVec - 1;
     bool done = false;
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
+    for (int i = 0; i < kVec; ++i) {
+        const uint64_t value = wave_get64((uint64_t)pick[i], first);
         if (!done) {
-            if ((uint64_t)v[i] > rest) {
+            if (value > rest) {
                 found = i;
-                left = rest;
                 done = true;
             } else {
-                rest -= (uint64_t)v[i];
+                rest -= value;
             }
         }
     }
-    x = wave_get64(left, first);
-    return begin + (int64_t)first * kPer + __shfl(found, first, kWave);
+    x = rest;
+    return begin + (int64_t)row * (kWave * kVec) + (int64_t)first * kVec + found;
 }
 
 // One block per partial sum: out[b] = sum of in[1024*b .. 1024*b+1023].
@@ -148,7 +177,26 @@ __global__ __launch_bounds__(kThreads) void batch_draw_kernel(const uint32_t* __
     if (lane == 0) out[j] = (int32_t)e;
 }
 
-// Update, step 1: for every named edge remember the latest batch position that names it.
+// Moves the partial sums by one edge's difference per lane (0: nothing), modulo 2^64. A whole wavefront calls it.
+__device__ __forceinline__ void move_sums(int32_t e, uint64_t diff, int lane, uint64_t* __restrict__ sum1, uint64_t* __restrict__ sum2) {
+    if (diff) atomicAdd((unsigned long long*)&sum1[e / kFan], (unsigned long long)diff);
+    // A million edges share one level-2 sum: thousands of atomics on one address would
+    // run one after the other. Lanes of a wavefront that change the same level-2 sum
+    // as its first changing lane add up first and issue a single atomic.
+    const uint64_t changing = __ballot(diff != 0);
+    if (changing == 0) return;   // wave-uniform
+    const int leader = __ffsll((long long)changing) - 1;
+    const int32_t top = diff ? e / (kFan * kFan) : -1;
+    const int32_t leader_top = __shfl(top, leader, kWave);
+    const uint64_t together = wave_sum64(top == leader_top ? diff : 0);
+    if (lane == leader) {
+        if (together) atomicAdd((unsigned long long*)&sum2[leader_top], (unsigned long long)together);
+    } else if (diff && top != leader_top) {
+        atomicAdd((unsigned long long*)&sum2[top], (unsigned long long)diff);
+    }
+}
+
+// Update of a large batch, step 1: for every named edge remember the latest batch position that names it.
 __global__ __launch_bounds__(kThreads) void claim_kernel(const int32_t* __restrict__ idx, int64_t b, int64_t n,
                                                          int32_t* __restrict__ owner) {
     const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -176,21 +224,48 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const int32_t* __restri
             diff = (uint64_t)now - (uint64_t)old;
         }
     }
-    if (diff) atomicAdd((unsigned long long*)&sum1[e / kFan], (unsigned long long)diff);
-    // A million edges share one level-2 sum: thousands of atomics on one address would
-    // run one after the other. Lanes of a wavefront that change the same level-2 sum
-    // as its first changing lane add up first and issue a single atomic.
-    const uint64_t changing = __ballot(diff != 0);
-    if (changing == 0) return;   // wave-uniform
-    const int leader = __ffsll((long long)changing) - 1;
-    const int32_t top = diff ? e / (kFan * kFan) : -1;
-    const int32_t leader_top = __shfl(top, leader, kWave);
-    const uint64_t together = wave_sum64(top == leader_top ? diff : 0);
-    if (lane == leader) {
-        if (together) atomicAdd((unsigned long long*)&sum2[leader_top], (unsigned long long)together);
-    } else if (diff && top != leader_top) {
-        atomicAdd((unsigned long long*)&sum2[top], (unsigned long long)diff);
+    move_sums(e, diff, lane, sum1, sum2);
+}
+
+// The whole update of a batch of at most 1 024 by one block: which position names an edge last is settled in
+// a hash table in LDS instead of the array of owners, so the chain of dependent reads is index -> score, in
+// one launch instead of two (us a call, million edges: 100 positions 3.4 -> 2.5, 600 4.3 -> 2.8, 1 024 4.4 -> 3.2).
+// With several positions per thread the random reads and adds of one compute unit outlast the second launch
+// (2 000 positions 4.4 -> 6.6).
+constexpr int kOneBlockThreads = 1024;
+
+__global__ __launch_bounds__(kOneBlockThreads) void update_one_block_kernel(const int32_t* __restrict__ idx, const uint32_t* __restrict__ value,
+                                                                            int32_t b, uint32_t slots, int64_t n, uint32_t* __restrict__ score,
+                                                                            uint64_t* __restrict__ sum1, uint64_t* __restrict__ sum2) {
+    __shared__ int32_t edge[2 * kOneBlockThreads];   // `slots` >= 2 b of them in use; -1: free
+    __shared__ int32_t last[2 * kOneBlockThreads];   // latest position that names it
+    const int32_t j = (int32_t)threadIdx.x;
+    for (uint32_t s = threadIdx.x; s < slots; s += kOneBlockThreads) {
+        edge[s] = -1;
+        last[s] = -1;
     }
+    int32_t e = j < b ? idx[j] : -1;
+    const uint32_t now = j < b ? value[j] : 0;
+    if (e >= n) e = -1;
+    const uint32_t old = e >= 0 ? score[e] : 0;   // every read lies before the barrier, every write after it
+    __syncthreads();
+    uint32_t slot = 0;
+    if (e >= 0) {
+        slot = ((uint32_t)e * 0x9E3779B1u) & (slots - 1);
+        for (;;) {   // at most half the slots are taken: ends at the edge or at a free one
+            const int32_t was = atomicCAS(&edge[slot], -1, e);
+            if (was == -1 || was == e) break;
+            slot = (slot + 1) & (slots - 1);
+        }
+        atomicMax(&last[slot], j);
+    }
+    __syncthreads();
+    uint64_t diff = 0;
+    if (e >= 0 && last[slot] == j) {
+        score[e] = now;
+        diff = (uint64_t)now - (uint64_t)old;
+    }
+    move_sums(e, diff, (int)(threadIdx.x & (kWave - 1)), sum1, sum2);
 }
 
 void free_all(taser_selector* s) {
@@ -268,10 +343,17 @@ extern "C" int taser_selector_update(taser_selector* s, const int32_t* batch, co
     taser_clear_stale_hip_error();
     hipStream_t stream = (hipStream_t)hip_stream;
     TaserProfileSpan span(stream, "selector_update");
-    const unsigned blocks = (unsigned)((b + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(claim_kernel, dim3(blocks), dim3(kThreads), 0, stream, batch, b, s->n, s->owner);
-    hipLaunchKernelGGL(apply_kernel, dim3(blocks), dim3(kThreads), 0, stream, batch, new_scores, b, s->n, s->score,
-                       s->sum1, s->sum2, s->owner);
+    if (b <= kOneBlockThreads) {
+        uint32_t slots = 2;
+        while (slots < 2 * (uint32_t)b) slots *= 2;
+        hipLaunchKernelGGL(update_one_block_kernel, dim3(1), dim3(kOneBlockThreads), 0, stream, batch, new_scores, (int32_t)b, slots, s->n, s->score,
+                           s->sum1, s->sum2);
+    } else {
+        const unsigned blocks = (unsigned)((b + kThreads - 1) / kThreads);
+        hipLaunchKernelGGL(claim_kernel, dim3(blocks), dim3(kThreads), 0, stream, batch, b, s->n, s->owner);
+        hipLaunchKernelGGL(apply_kernel, dim3(blocks), dim3(kThreads), 0, stream, batch, new_scores, b, s->n, s->score,
+                           s->sum1, s->sum2, s->owner);
+    }
     TASER_HIP_TRY(hipGetLastError());
     return TASER_OK;
 }
