@@ -431,10 +431,13 @@ __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
 // Entries with delta >= 2^32 weigh 1 and are the first `ones` of a list; of the others the low words of
 // the timestamps say all: delta = (low word of t) - (low word of ts), in 32 bits.
 //
-// delta >= 65536, so the quotient is below 2^16. A single-precision reciprocal is off by less than
-// 2^-22 of the quotient (conversion, v_rcp_f32's one unit in the last place, the product); scaled down by
-// 2^-21 it gives the quotient or one less, and the exact remainder says which. NEAR: delta < 2^24, where
-// the product for the remainder is one full-rate 24-bit multiply and the quotient at least 256.
+// delta > kLastLargeDelta, so the quotient is at most kSmallWeight. A single-precision reciprocal is off by
+// less than 2^-22 of the quotient (conversion, v_rcp_f32's one unit in the last place, the product); scaled
+// down by 2^-21 it gives the quotient or one less, and the exact remainder says which. NEAR: delta < 2^24,
+// where the product for the remainder is one full-rate 24-bit multiply and the quotient at least 256.
+constexpr uint32_t kLastLargeDelta = 65536;      // its quotient is 2^16 itself: with it a tile of ties would sum to 2^32
+constexpr uint32_t kSmallWeight = (uint32_t)(((uint64_t)1 << 32) / (kLastLargeDelta + 1));
+static_assert(kSmallWeight == 65535, "the quotient of every larger delta is below 2^16");
 template <bool NEAR> __device__ __forceinline__ uint32_t quotient_of_delta(uint32_t delta) {
     const uint32_t q = (uint32_t)(4294967296.0f * (1.0f - 4.76837158203125e-7f) * __builtin_amdgcn_rcpf((float)delta));
     const uint32_t rest = 0u - (NEAR ? __umul24(q, delta) : q * delta);   // 2^32 - q delta, below 2 delta; wraps only for delta > 2^31
@@ -443,7 +446,7 @@ template <bool NEAR> __device__ __forceinline__ uint32_t quotient_of_delta(uint3
 }
 // Any delta >= 1.
 __device__ __forceinline__ uint64_t weight_of_delta(uint32_t delta) {
-    if (delta >= 65536u) return quotient_of_delta<false>(delta);
+    if (delta > kLastLargeDelta) return quotient_of_delta<false>(delta);
     const uint32_t q = 0xFFFFFFFFu / delta, r = 0xFFFFFFFFu - q * delta;   // 2^32 = (2^32 - 1) + 1
     return (uint64_t)q + (r == delta - 1u ? 1u : 0u);
 }
@@ -452,6 +455,13 @@ constexpr int kTileRegs = 8;                      // registers of tile sums per 
 constexpr int kMaxTiles = kTileRegs * kWave;      // tile sums per root
 constexpr int kListThreads = 256;                 // block of the finder that reads whole lists
 constexpr int kListWaves = kListThreads / kWave;
+
+// Where weights of at most kSmallWeight may be summed in 32 bits: per lane over the rows of any tile (a list
+// has fewer than 2^31 entries), over a whole wave up to kWaveSumRows rows.
+constexpr uint64_t kMostTileRows = (((uint64_t)1 << 31) / kWave + kMaxTiles - 1) / kMaxTiles;
+constexpr uint32_t kWaveSumRows = 1024;
+static_assert(kMostTileRows * kSmallWeight < ((uint64_t)1 << 32), "a lane's sum");
+static_assert((uint64_t)kWaveSumRows * kWave * kSmallWeight < ((uint64_t)1 << 32), "a wave's sum");
 
 // What the whole block knows about its root.
 struct ListQuery {
@@ -477,7 +487,7 @@ template <bool NEAR> __device__ __forceinline__ uint32_t delta_of(const ListQuer
 template <bool NEAR>
 __device__ __forceinline__ uint64_t tile_weight(const ListQuery& q, const uint32_t* __restrict__ low, uint32_t r0, uint32_t r1, int lane) {
     constexpr int kAhead = 4;    // rows whose loads are in flight together
-    uint32_t s = 0;              // quotients below 2^16; a tile has at most 2^16 rows
+    uint32_t s = 0;              // weights of at most kSmallWeight
     uint64_t s_big = 0;
     bool big = false;
     for (uint32_t r = r0; r < r1; r += kAhead) {
@@ -493,7 +503,7 @@ __device__ __forceinline__ uint64_t tile_weight(const ListQuery& q, const uint32
             const uint32_t delta = delta_of<NEAR>(q, p, v[i]);
             const bool valid = p < q.cnt;
             if (r + i >= r1) {                               // (uniform, like the next)
-            } else if (!__ballot(delta < 65536u)) {
+            } else if (!__ballot(delta <= kLastLargeDelta)) {
                 const uint32_t w = quotient_of_delta<NEAR>(delta);
                 s += valid ? w : 0u;
             } else {
@@ -502,7 +512,7 @@ __device__ __forceinline__ uint64_t tile_weight(const ListQuery& q, const uint32
             }
         }
     }
-    if (!big && r1 - r0 <= 1024u) return wave_sum32(s);      // below 2^32 over the wave (uniform)
+    if (!big && r1 - r0 <= kWaveSumRows) return wave_sum32(s);   // (uniform)
     return wave_sum64(s_big + s);
 }
 
@@ -514,7 +524,7 @@ __device__ __forceinline__ int pick_in_row(const ListQuery& q, uint32_t low, uin
                                            uint32_t my_pick, int lane, uint64_t& pick_w) {
     const uint32_t p = r * kWave + lane;
     const uint32_t delta = delta_of<NEAR>(q, p, low);
-    const bool small = !__ballot(delta < 65536u);            // uniform: weights below 2^16, sums below 2^22
+    const bool small = !__ballot(delta <= kLastLargeDelta);  // uniform: a row's sum is below 2^22
     bool valid = p < q.cnt;
     for (uint64_t taken = __ballot(lane < j && my_pick / kWave == r); taken; taken &= taken - 1) {
         const uint32_t gone = (uint32_t)__builtin_amdgcn_readlane((int)my_pick, __ffsll((long long)taken) - 1);

@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2402_05396_amd as T
 
-
+THREADS = min(16, oracle.max_threads())
 
 
 @pytest.mark.gpu
@@ -35,8 +35,27 @@ def test_picks_equal_the_oracle(n, near, far):
             assert np.array_equal(got[f].cpu().numpy(), want[f]), (k, f)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("delta", [65_536, 65_537])
+def test_tiles_of_ties_at_the_largest_weights(delta):
+    """The shortest list whose tiles hold 1 024 rows of 64 entries, all of them one timestamp: a full tile weighs
+    65 536 * 65 536 = 2^32 where delta is 65 536, and 65 536 * 65 535 one later."""
+    n = 1023 * 512 * 64 + 1
+    ts = torch.zeros(n, dtype=torch.int64, device="cuda")
+    src = torch.zeros(n, dtype=torch.int32, device="cuda")
+    eid = torch.arange(n, dtype=torch.int32, device="cuda")
+    g = T.tcsr_build(src, eid, ts, eid, 1)
+    g_ref = oracle.tcsr_build(*(t.cpu().numpy() for t in (src, eid, ts, eid)), 1, THREADS)
+    roots, times = np.zeros(5, np.int32), np.full(5, delta, np.int64)
+    for k in (1, 10):
+        want = oracle.sample_temporal(g_ref, roots, times, k, 1, T.INVERSE_TIMESPAN, 3, threads=THREADS)[0]
+        got = T.sample_temporal(g, torch.from_numpy(roots).cuda(), torch.from_numpy(times).cuda(), k, 1, T.INVERSE_TIMESPAN, 3)[0]
+        for f in ("nbr", "eid", "ts", "count"):
+            assert np.array_equal(got[f].cpu().numpy(), want[f]), (k, f)
+
+
 def _quotient(delta, near):
-    """The device's arithmetic for delta >= 65536 in numpy: float32 products, the reciprocal off by up to one unit in the
+    """The device's arithmetic for delta > 65536 in numpy: float32 products, the reciprocal off by up to one unit in the
     last place either way, then the remainder's correction."""
     d = delta.astype(np.float32)
     r = np.float32(1) / d
