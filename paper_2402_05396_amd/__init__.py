@@ -124,6 +124,16 @@ def _check(rc):
         raise TaserError(rc, last_error())
 
 
+def _call(entry, *args):
+    """A C call that may allocate. The library's own buffers come from the driver, which has no use of the blocks that
+    torch keeps (after a large tcsr_build, its scratch): out of memory, the call is made again without those."""
+    rc = entry(*args)
+    if rc == -3:
+        torch.cuda.empty_cache()
+        rc = entry(*args)
+    _check(rc)
+
+
 def _stream(stream):
     s = torch.cuda.current_stream() if stream is None else stream
     return ctypes.c_void_p(s.cuda_stream)
@@ -187,8 +197,9 @@ def tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream=None):
 
 
 def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
-    """taser_tcsr_build. src/dst/eid int32, ts int64; all on the GPU or all on the host. The device memory is torch's
-    (its caching allocator keeps freed blocks for the next call; the driver takes milliseconds per gigabyte)."""
+    """taser_tcsr_build. src/dst/eid int32, ts int64; all on the GPU or all on the host. The device memory is torch's,
+    whose caching allocator keeps freed blocks for the next call (the driver takes milliseconds per gigabyte): the
+    scratch, 24 bytes per entry and more, stays reserved until torch.cuda.empty_cache()."""
     sizes = tcsr_build_bytes(src.numel(), num_nodes, src.is_cuda)
     try:
         with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):   # blocks of that stream's pool
@@ -264,8 +275,8 @@ def sample_temporal(g, roots, times, k, hops, policy, seed, m=0, edge_weight=Non
     if out is None:
         out = sample_outputs(n, k, hops, roots.device)
     arr = _hop_array(roots, times, n, k, edge_weight, out)
-    _check(lib().taser_sample_temporal(g.handle, _ptr(roots), _ptr(times), n, k, hops, policy, seed, m,
-                                       _ptr(edge_weight), arr, _stream(stream)))
+    _call(lib().taser_sample_temporal, g.handle, _ptr(roots), _ptr(times), n, k, hops, policy, seed, m,
+          _ptr(edge_weight), arr, _stream(stream))
     return out
 
 
@@ -295,9 +306,9 @@ def sample_temporal_rows(g, roots, times, k, hops, policy, seed, table, m=0, edg
         if t.dtype != table.dtype or not t.is_contiguous() or t.numel() < r * d:
             raise TypeError(f"rows_out[{h}]: expected a contiguous device tensor of the table's dtype with R_h*k*d elements")
         ptrs[h] = t.data_ptr()
-    _check(lib().taser_sample_temporal_rows(g.handle, _ptr(roots), _ptr(times), n, k, hops, policy, seed, m,
-                                            _ptr(edge_weight), _ptr(table), table.shape[0], d * es, table.stride(0) * es,
-                                            arr, ptrs, _stream(stream)))
+    _call(lib().taser_sample_temporal_rows, g.handle, _ptr(roots), _ptr(times), n, k, hops, policy, seed, m,
+          _ptr(edge_weight), _ptr(table), table.shape[0], d * es, table.stride(0) * es,
+          arr, ptrs, _stream(stream))
     return out, rows_out
 
 
@@ -403,9 +414,9 @@ def cache_init(host_table, capacity_rows, resident_ids=None, seed=0, staging_row
             raise ValueError("resident_ids must hold capacity_rows ids")
     es = host_table.element_size()
     h = ctypes.c_void_p()
-    _check(lib().taser_cache_init(_ptr(host_table), host_table.shape[0], host_table.shape[1] * es,
-                                  host_table.stride(0) * es, capacity_rows, _ptr(resident_ids), seed,
-                                  staging_rows, _stream(stream), ctypes.byref(h)))
+    _call(lib().taser_cache_init, _ptr(host_table), host_table.shape[0], host_table.shape[1] * es,
+          host_table.stride(0) * es, capacity_rows, _ptr(resident_ids), seed,
+          staging_rows, _stream(stream), ctypes.byref(h))
     return Cache(h, host_table, capacity_rows, host_table.shape[1])
 
 
@@ -423,7 +434,7 @@ def cache_lookup(c, ids, out=None, hit_miss=None, stream=None):
         raise TypeError("out: expected a contiguous device tensor of the table's dtype with n*d elements")
     if hit_miss is not None:
         _want(hit_miss, torch.int64, "hit_miss")
-    _check(lib().taser_cache_lookup(c.handle, _ptr(ids), n, _ptr(out), _ptr(hit_miss), _stream(stream)))
+    _call(lib().taser_cache_lookup, c.handle, _ptr(ids), n, _ptr(out), _ptr(hit_miss), _stream(stream))
     return out
 
 
@@ -444,7 +455,7 @@ def cache_prefetch(c, ids, hit_miss=None, stream=None):
     _want(ids, torch.int32, "ids")
     if hit_miss is not None:
         _want(hit_miss, torch.int64, "hit_miss")
-    _check(lib().taser_cache_prefetch(c.handle, _ptr(ids), ids.numel(), _ptr(hit_miss), _stream(stream)))
+    _call(lib().taser_cache_prefetch, c.handle, _ptr(ids), ids.numel(), _ptr(hit_miss), _stream(stream))
 
 
 def cache_gather(c, ids, out=None, stream=None):
@@ -467,7 +478,7 @@ def cache_tune(c, stage_blocks=0, refresh_before_gather=False, partitioned_gathe
 
 def cache_count_accesses(c, enable=True, stream=None):
     """taser_cache_count_accesses."""
-    _check(lib().taser_cache_count_accesses(c.handle, 1 if enable else 0, _stream(stream)))
+    _call(lib().taser_cache_count_accesses, c.handle, 1 if enable else 0, _stream(stream))
 
 
 def cache_access_counts(c, stream=None):
@@ -519,7 +530,7 @@ def selector_init(scores=None, n=None, initial_score=1, stream=None):
         _want(scores, torch.int32, "scores (uint32 bits in an int32 tensor)")
         n = scores.numel()
     h = ctypes.c_void_p()
-    _check(lib().taser_selector_init(_ptr(scores), n, initial_score, _stream(stream), ctypes.byref(h)))
+    _call(lib().taser_selector_init, _ptr(scores), n, initial_score, _stream(stream), ctypes.byref(h))
     return Selector(h, n)
 
 

@@ -3,8 +3,9 @@
 //
 // Every function here takes the arguments of the Python function of the same name, serves the plain case
 // (exact torch tensors of the expected types, ordinary integers) and returns None for anything else, which the
-// Python function then handles, or refuses, itself. Errors of the C library become TaserError. The library's
-// entry points come in as addresses (bind), so this file links against torch only.
+// Python function then handles, or refuses, itself; so also where the library's own allocations find no memory.
+// Errors of the C library become TaserError. The library's entry points come in as addresses (bind), so this file
+// links against torch only.
 //
 // One mini-batch of 1800 roots with edge rows: 24.6 us a call when marshalled in Python, 11.5 us so, of which the
 // two kernel launches take about 6; its kernels take 9.
@@ -165,6 +166,7 @@ PyObject* sample(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
         rc = api.sample_temporal(static_cast<taser_tcsr*>(handle), p_roots, p_times, n, (int32_t)k, (int32_t)hops, (int32_t)policy, seed,
                                  (int32_t)m, p_weight, out, stream);
     Py_END_ALLOW_THREADS
+    if (rc == TASER_E_OOM) return not_plain();
     if (rc != TASER_OK) return raise(rc);
     if (!table) return list.release();
     return PyTuple_Pack(2, list.p, rows.p);
@@ -293,6 +295,7 @@ PyObject* lookup(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
     rc = api.cache_lookup(static_cast<taser_cache*>(handle), static_cast<const int32_t*>(p_ids), n, p_out, static_cast<uint64_t*>(p_hit_miss),
                           stream);
     Py_END_ALLOW_THREADS
+    if (rc == TASER_E_OOM) return not_plain();
     if (rc != TASER_OK) return raise(rc);
     if (a[4] == Py_None) return THPVariable_Wrap(made);
     Py_INCREF(a[4]);
