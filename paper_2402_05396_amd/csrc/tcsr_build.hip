@@ -18,9 +18,9 @@
 //   * indptr is read off the sorted node column (no atomics, no histogram).
 // All device memory is one storage block (what the graph keeps) and one scratch
 // block, either the caller's (taser_tcsr_build_in) or allocated here.
-#include <mutex>
 #include <new>
 
+#include "pinned_info.h"
 #include "taser_internal.h"
 
 namespace {
@@ -657,48 +657,6 @@ void launch_pass(const Layout& l, const Items& in, int64_t n, const DigitSpec& d
                            total, l.tiles, rec_out, key_out, level1);
 }
 
-// Four words of page-locked host memory for one build's inspection result: the fold kernel writes
-// them there itself, so that planning the sort waits for a kernel and not for a copy behind it. 64
-// builds of the process can hold one at a time (a page that stays until it ends); a further one
-// reads its words back from the scratch block instead.
-struct PinnedInfo {
-    unsigned long long* words = nullptr;
-    PinnedInfo() {
-        std::lock_guard<std::mutex> lock(mutex());
-        State& s = state();
-        if (!s.page && !s.failed) {
-            void* p = nullptr;
-            if (hipHostMalloc(&p, 64 * 64, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) s.page = static_cast<uint8_t*>(p);
-            else {
-                s.failed = true;
-                (void)hipGetLastError();
-            }
-        }
-        if (s.page && ~s.used) {
-            slot_ = __builtin_ctzll(~s.used);
-            s.used |= 1ull << slot_;
-            words = reinterpret_cast<unsigned long long*>(s.page + 64 * slot_);
-        }
-    }
-    ~PinnedInfo() {
-        if (!words) return;
-        std::lock_guard<std::mutex> lock(mutex());
-        state().used &= ~(1ull << slot_);
-    }
-    PinnedInfo(const PinnedInfo&) = delete;
-    PinnedInfo& operator=(const PinnedInfo&) = delete;
-
-private:
-    struct State {
-        uint8_t* page;
-        uint64_t used;
-        bool failed;
-    };
-    static State& state() { static State s = {nullptr, 0, false}; return s; }
-    static std::mutex& mutex() { static std::mutex m; return m; }
-    int slot_ = 0;
-};
-
 // The build itself, in `storage` and `scratch` (l.storage and l.scratch bytes of device memory, 256-byte
 // aligned). Synchronizes the stream before it returns TASER_OK.
 int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int64_t* ts, const int32_t* eid, int64_t n,
@@ -733,8 +691,9 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         };
         unsigned long long info[4] = {0, 0, 0, ~0ull};
         unsigned long long* partial = reinterpret_cast<unsigned long long*>(scratch + l.partial);
-        const PinnedInfo pinned;
+        PinnedInfo pinned;
         unsigned long long* d_info = pinned.words ? pinned.words : reinterpret_cast<unsigned long long*>(scratch + l.info);
+        pinned.launched(stream);
         {
             TaserProfileSpan span(stream, "tcsr_inspect");
             const unsigned grid = l.tiles < kInspectBlocks ? l.tiles : kInspectBlocks;
@@ -749,6 +708,7 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         TASER_HIP_TRY(hipGetLastError());
         if (!pinned.words) TASER_HIP_TRY(hipMemcpyAsync(info, d_info, sizeof(info), hipMemcpyDeviceToHost, stream));
         TASER_HIP_TRY(hipStreamSynchronize(stream));
+        pinned.settled();
         if (pinned.words)
             for (int j = 0; j < 4; ++j) info[j] = __atomic_load_n(&pinned.words[j], __ATOMIC_RELAXED);
         if (info[0]) return taser_fail(TASER_E_RANGE, "tcsr_build: a src node id is outside [0, %d)", num_nodes);
@@ -880,7 +840,12 @@ extern "C" int taser_tcsr_build_in(const int32_t* src, const int32_t* dst, const
     taser_resolve_device_constants();
     const int rc = build_in(l, src, dst, ts, eid, num_entries, num_nodes, flags, (hipStream_t)hip_stream, static_cast<uint8_t*>(storage),
                             static_cast<uint8_t*>(scratch), out);
-    if (rc == TASER_OK && hipGetDevice(&(*out)->device) != hipSuccess) (*out)->device = -1;
+    if (rc != TASER_OK) {
+        (void)hipStreamSynchronize((hipStream_t)hip_stream);   // what was launched before the error still uses the caller's blocks
+        (void)hipGetLastError();
+    } else if (hipGetDevice(&(*out)->device) != hipSuccess) {
+        (*out)->device = -1;
+    }
     return rc;
 }
 
