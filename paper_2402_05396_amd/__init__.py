@@ -202,6 +202,8 @@ def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
     scratch, 24 bytes per entry and more, stays reserved until torch.cuda.empty_cache()."""
     sizes = tcsr_build_bytes(src.numel(), num_nodes, src.is_cuda)
     try:
+        if stream is not None and not isinstance(stream, torch.cuda.Stream):   # any object with a `cuda_stream` will do
+            stream = torch.cuda.ExternalStream(stream.cuda_stream)
         with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):   # blocks of that stream's pool
             storage, scratch = (torch.empty(b, dtype=torch.uint8, device="cuda") for b in sizes)
     except torch.OutOfMemoryError as e:

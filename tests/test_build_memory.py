@@ -1,5 +1,6 @@
 """The T-CSR build at the edges of its tiles, digits and scans, and in memory of the caller's."""
 import ctypes
+import types
 
 import numpy as np
 import pytest
@@ -61,6 +62,17 @@ def test_build_in_the_callers_memory():
             T.tcsr_build_in(*args, 77, torch.empty(storage.numel() + 8, dtype=torch.uint8, device="cuda")[8:], scratch)
         g2 = T.tcsr_build_in(*args, 77, storage, scratch)   # the same blocks again
         _check(g2, ref)
+
+
+@pytest.mark.gpu
+def test_build_on_any_object_with_a_cuda_stream():
+    src, dst, ts, eid = _entries(3000, 40, 15, 0, False, 4)
+    ref = oracle.tcsr_build(src, dst, ts, eid, 40, THREADS)
+    args = [torch.from_numpy(x).cuda() for x in (src, dst, ts, eid)]
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    for stream in (side, types.SimpleNamespace(cuda_stream=side.cuda_stream), types.SimpleNamespace(cuda_stream=0)):
+        _check(T.tcsr_build(*args, 40, stream=stream), ref)
 
 
 @pytest.mark.gpu
