@@ -175,9 +175,8 @@ def tcsr_build_bytes(num_entries, num_nodes, on_device=True):
     return storage.value, scratch.value
 
 
-def tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream=None):
-    """taser_tcsr_build_in: the graph lives in `storage` (kept alive by the returned object); `scratch` is free again on
-    return. Both: contiguous uint8 device tensors of at least tcsr_build_bytes() elements."""
+def _entries(src, dst, ts, eid):
+    """Checks a build's columns -> (number of entries, whether they are on the GPU)."""
     on_dev = src.is_cuda
     _want(src, torch.int32, "src", on_dev)
     _want(dst, torch.int32, "dst", on_dev)
@@ -187,6 +186,13 @@ def tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream=None):
     n = src.numel()
     if dst.numel() != n or ts.numel() != n or (eid is not None and eid.numel() != n):
         raise ValueError("src, dst, ts, eid must have the same length")
+    return n, on_dev
+
+
+def tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream=None):
+    """taser_tcsr_build_in: the graph lives in `storage` (kept alive by the returned object); `scratch` is free again on
+    return. Both: contiguous uint8 device tensors of at least tcsr_build_bytes() elements."""
+    n, on_dev = _entries(src, dst, ts, eid)
     _want(storage, torch.uint8, "storage")
     _want(scratch, torch.uint8, "scratch")
     h = ctypes.c_void_p()
@@ -200,7 +206,8 @@ def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
     """taser_tcsr_build. src/dst/eid int32, ts int64; all on the GPU or all on the host. The device memory is torch's,
     whose caching allocator keeps freed blocks for the next call (the driver takes milliseconds per gigabyte): the
     scratch, 24 bytes per entry and more, stays reserved until torch.cuda.empty_cache()."""
-    sizes = tcsr_build_bytes(src.numel(), num_nodes, src.is_cuda)
+    n, on_dev = _entries(src, dst, ts, eid)   # before any memory is taken for them
+    sizes = tcsr_build_bytes(n, num_nodes, on_dev)
     try:
         if stream is not None and not isinstance(stream, torch.cuda.Stream):   # any object with a `cuda_stream` will do
             stream = torch.cuda.ExternalStream(stream.cuda_stream)

@@ -106,3 +106,13 @@ def test_build_bytes_without_a_gpu():
     assert build(one, one, one, None, 4, 3, 1, None, one, 8, one, big, ctypes.byref(h)) == -2
     assert build(one, one, one, None, 4, 3, 1, None, one, big, one, 8, ctypes.byref(h)) == -2
     assert build(None, one, one, None, 4, 3, 1, None, one, big, one, big, ctypes.byref(h)) == -1
+
+
+def test_wrong_columns_are_refused_before_memory_is_taken():
+    """Without a GPU taking any would be another error."""
+    a, b = torch.zeros(4, dtype=torch.int32), torch.zeros(4, dtype=torch.int64)
+    for columns in ((b, a, b, None), (a, b, b, None), (a, a, a, None), (a, a, b, b), (a[::2], a[:2], b[:2], None)):
+        with pytest.raises(TypeError):
+            T.tcsr_build(*columns, 10)
+    with pytest.raises(ValueError):
+        T.tcsr_build(a, a[:3], b, None, 10)
