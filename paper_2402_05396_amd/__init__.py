@@ -6,12 +6,14 @@ arguments: torch supplies device memory and the current stream, every step of
 the path runs in the library's HIP kernels. The calls of a training loop are
 marshalled by ``_binding`` (C++) when their arguments are the plain ones; what it
 does not take (outputs of the caller's, other tensor types, errors in the
-arguments) goes through ctypes. There is no fallback: if the library has not
-been built, or no GPU is present, calls raise.
+arguments), and everything where it does not load, goes through ctypes to the
+same kernels. There is no fallback for those: if the library has not been built,
+or no GPU is present, calls raise.
 """
 import contextlib
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -102,17 +104,28 @@ _native = None
 
 
 def _bind():
-    """The module `_binding`, given the addresses of the library's entry points."""
+    """The module `_binding`, given the addresses of the library's entry points; where it does not load, what leaves every
+    call to the ctypes half."""
     global _native
+    from . import build
     L = lib()
     try:
+        if not build.binding_fits():
+            raise ImportError(f"it was not built for {build.binding_tag()}")
         from . import _binding
     except ImportError as e:
-        raise RuntimeError(f"{os.path.join(_HERE, '_binding.so')} is missing or does not load ({e}): build it with "
-                           "`python -m paper_2402_05396_amd.build` (there is no fallback path)") from e
+        warnings.warn(f"{build.BINDING} is missing or does not load ({e}): calls are marshalled through ctypes, which costs "
+                      "some 10 us each; build it with `python -m paper_2402_05396_amd.build`", RuntimeWarning, stacklevel=3)
+        _native = _TakesNothing()
+        return _native
     _binding.bind(TaserError, {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in EXPORTS})
     _native = _binding
     return _binding
+
+
+class _TakesNothing:
+    def __getattr__(self, name):
+        return lambda *args: None
 
 
 def last_error():

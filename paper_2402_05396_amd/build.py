@@ -3,6 +3,7 @@ binding) against torch with g++, in-tree."""
 import glob
 import os
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -21,11 +22,25 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def binding_tag():
+    """What a _binding.so has to be built for; it holds this text."""
+    import torch
+    return f"torch {torch.__version__}, Python {sys.version_info.major}.{sys.version_info.minor}"
+
+
+def binding_fits():
+    if not os.path.exists(BINDING):
+        return False
+    with open(BINDING, "rb") as f:
+        return f"built for {binding_tag()}.".encode() in f.read()
+
+
 def binding_command():
     from torch.utils import cpp_extension as torch_paths
     dirs = torch_paths.include_paths("cuda") + [sysconfig.get_paths()["include"]]
     libs = [p for p in torch_paths.library_paths("cuda") if os.path.isdir(p)]
     return (["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+             f'-DTASER_BINDING_TAG="{binding_tag()}"',
              "-I", os.path.join(ROOT, "include")] + [x for d in dirs for x in ("-isystem", d)] +
             ["-o", BINDING, os.path.join(CSRC, "binding.cpp")] + [x for d in libs for x in ("-L", d, "-Wl,-rpath," + d)] +
             ["-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"])
@@ -47,7 +62,7 @@ def build(verbose=False):
 
 
 def stale():
-    if not (os.path.exists(LIB) and os.path.exists(BINDING)):
+    if not (os.path.exists(LIB) and binding_fits()):
         return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(BINDING))
     deps = sources() + [p for e in ("*.h", "*.cpp") for p in glob.glob(os.path.join(CSRC, e))] + glob.glob(os.path.join(ROOT, "include", "*.h"))

@@ -391,7 +391,7 @@ PyObject* bind(PyObject*, PyObject* args) {
 PyMethodDef methods[] = {{"bind", bind, METH_VARARGS, nullptr}, FAST("sample", sample), FAST("gather", gather), FAST("encodings", encodings),
                          FAST("select", select), FAST("lookup", lookup), FAST("draw", draw), FAST("update", update), FAST("scores", scores),
                          {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", "Native half of the Python binding, built for " TASER_BINDING_TAG ".", -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 
