@@ -12,6 +12,7 @@
 // of each lower level, read at once.
 #include <new>
 
+#include "edge_hash.h"
 #include "sampling_device.h"
 #include "taser_internal.h"
 
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(kOneBlockThreads) void update_one_block_kernel(cons
     __syncthreads();
     uint32_t slot = 0;
     if (e >= 0) {
-        slot = ((uint32_t)e * 0x9E3779B1u) & (slots - 1);
+        slot = edge_hash((uint32_t)e) & (slots - 1);
         for (;;) {   // at most half the slots are taken: ends at the edge or at a free one
             const int32_t was = atomicCAS(&edge[slot], -1, e);
             if (was == -1 || was == e) break;
