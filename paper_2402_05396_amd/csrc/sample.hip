@@ -361,10 +361,12 @@ __device__ __forceinline__ void copy_wave_rows(const RowCopy& rc, const int32_t*
     }
 }
 
-// G lanes per root: G >= k, and G >= m for the weighted policy. (Groups that serve two roots, their
-// searches side by side, gain nothing: the uniform and weighted finders' time is mostly the arithmetic
-// of their draws, and large hops of the most-recent finder have a kernel of their own below.)
-// With ROWS a wavefront then also copies the table rows of the edges
+// G lanes per root: G >= k, and G >= m for the weighted policy. A group serves kRootsPerGroup
+// consecutive roots: their searches run side by side, their selections stage by stage. Two pay for
+// the most-recent finder on large hops that the kernel below does not take (lists of two entries, 32
+// slots, 160 000 roots: 26.2 us with one, 21.8 with two); the uniform and weighted finders, whose time
+// is mostly the arithmetic of their draws, gain nothing from them.
+// With ROWS (one root per group) a wavefront then also copies the table rows of the edges
 // it sampled into the hop's dense row output: the finder is bound by instruction issue and
 // dependent reads, the copy by memory bandwidth, and in one kernel the wavefronts of a
 // compute unit that search overlap with those that copy.
@@ -733,11 +735,29 @@ int ensure_ts_low(const taser_tcsr* g_const, hipStream_t stream) {
 // entries of a level (the same 128-byte line per level): 16 roots per wave for little more than the
 // instructions of four, and all waves resident at once. The slots are then handed out flat, k of them per
 // root whatever k is, so that all lanes load and store. What is left is the latency of one chain of reads.
-// k = 10, 4 M events, 16 lanes / 4 lanes per root: 6 000 roots 4.3 / 4.7 us, 12 000 4.5 / 4.8, 20 000 5.4 / 5.3,
-// 40 000 9.1 / 6.9, 120 000 18.8 / 13.7; k = 25: 6 000 4.7 / 5.8, 20 000 8.6 / 7.9, 120 000 32.1 / 23.1. The uniform
-// finder, searched the same way, gains nothing (60 000 roots 16.6 / 16.0 us, 6 000 roots 6.2 / 12.1): its draws
-// are then three rounds one after the other.
-constexpr int64_t kQuadMinRoots = 16384;
+// The uniform finder, searched the same way, gains nothing (60 000 roots 16.6 / 16.0 us, 6 000 roots 6.2 / 12.1): its
+// draws are then three rounds one after the other.
+//
+// Where it pays: the longer the lists, the longer the search that it makes cheaper; the more of its 16, 32 or 64 lanes
+// a root's slots fill in the other kernel, the less there is to gain. Time of this kernel over the other one's, k = 10,
+// 16, 25, 64, for graphs of 2, 100, 13 300 entries per node on average (the other one with two roots per group from
+// 65 536 roots on):
+//   16 384 roots:  1.15 1.22 1.21 1.28   1.10 1.16 1.12 1.10   1.06 1.10 1.03 1.00
+//   24 576 roots:  1.13 1.19 1.06 1.05   1.04 1.09 0.95 0.93   0.94 0.98 0.88 0.87
+//   32 768 roots:  1.08 1.21 0.97 0.94   1.00 1.06 0.91 0.90   0.89 1.00 0.79 0.86
+//   65 536 roots:  1.03 1.14 0.93 0.85   0.98 1.01 0.90 0.96   0.82 0.89 0.84 0.87
+//   640 000 roots: 1.13 1.23 0.82 0.75   0.97 1.08 0.96 0.83   0.89 0.95 0.86 0.85
+// (13 300 entries, k = 10: 120 000 roots 18.8 us by 16 lanes, 13.7 by 4.) Hence a line per group size and length of
+// list: the fewest roots, and how many eighths of its lanes a root's slots may fill (k = 4 takes 0.92 to 0.96 on the
+// shortest lists, k = 5 up to 1.03).
+inline bool quads_pay(int64_t entries, int64_t nodes, int64_t roots, int k, int lanes) {
+    struct Line { int roots, eighths; };
+    static constexpr Line lines[3][3] = {{{40960, 2}, {32768, 5}, {24576, 8}},    // 16 lanes: lists of less than 64, 256, more entries
+                                         {{32768, 7}, {24576, 8}, {20480, 8}},    // 32 lanes
+                                         {{32768, 8}, {24576, 8}, {16384, 8}}};   // 64 lanes
+    const Line line = lines[lanes / 32][entries >= 256 * nodes ? 2 : entries >= 64 * nodes ? 1 : 0];
+    return roots >= line.roots && 8 * k <= line.eighths * lanes;
+}
 constexpr int kQuadRoots = 16;          // roots per wave
 
 // 16 bytes of a time-index level, 8-byte aligned.
@@ -783,6 +803,7 @@ __device__ __forceinline__ uint32_t quad_cutoff(const TaserRec* __restrict__ rec
     return at - lo;
 }
 
+template <int kAhead>   // record loads of a lane in flight together
 __global__ __launch_bounds__(kThreads) void sample_hop_recent_quads_kernel(
     const int64_t* __restrict__ indptr, const TaserRec* __restrict__ rec, const TaserTimeIndex index,
     const int32_t* __restrict__ roots, const int64_t* __restrict__ times, int64_t num_roots, int32_t num_nodes, int k, uint32_t magic_k,
@@ -807,7 +828,6 @@ __global__ __launch_bounds__(kThreads) void sample_hop_recent_quads_kernel(
     if ((lane & 3) == 0 && quad < here) o_count[q0 + quad] = (int32_t)(cnt < (uint32_t)k ? cnt : (uint32_t)k);
     // slot s of the wave is slot s % k of root s / k
     const TaserRec pad = {0, -1, -1};
-    constexpr int kAhead = 3;            // record loads of a lane in flight together
     const uint32_t slots = (uint32_t)(here * k);
     for (uint32_t s0 = 0; s0 < slots; s0 += kAhead * kWave) {
         TaserRec got[kAhead];
@@ -845,6 +865,7 @@ void launch_hop_g(const taser_tcsr* g, const int32_t* roots, const int64_t* time
                   uint64_t seed, uint32_t hop, int m, const uint32_t* edge_weight, const taser_hop_out& o,
                   const RowCopy* rows, hipStream_t stream) {
     if (rows) launch_hop_gr<POLICY, G, 1, true>(g, roots, times, n, k, seed, hop, m, edge_weight, o, *rows, stream);
+    else if (POLICY == TASER_RECENT && n >= 65536) launch_hop_gr<POLICY, G, 2, false>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
     else launch_hop_gr<POLICY, G, 1, false>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
 }
 
@@ -862,11 +883,15 @@ void launch_hop(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
                                             {"sample_rows_hop_recent", "sample_rows_hop_uniform", "sample_rows_hop_weighted"}};
     TaserProfileSpan span(stream, names[rows ? 1 : 0][POLICY]);
     const int lanes = group_lanes(POLICY, k, m);
-    if (POLICY == TASER_RECENT && !rows && n >= kQuadMinRoots) {
+    if (POLICY == TASER_RECENT && !rows && quads_pay(g->num_entries, g->num_nodes, n, k, lanes)) {
         constexpr int roots_per_block = kThreads / kWave * kQuadRoots;
         const unsigned grid = (unsigned)((n + roots_per_block - 1) / roots_per_block);
         const uint32_t magic_k = k > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u;
-        hipLaunchKernelGGL(sample_hop_recent_quads_kernel, dim3(grid), dim3(kThreads), 0, stream, g->indptr, g->rec, g->time_index, roots,
+        // up to 12 slots per root all loads of a wave fit three rounds; where they don't, a second batch of loads waits
+        // for the stores of the first (16 slots, 24 576 roots: 5.71 us with batches of three, 5.56 with four; 64 slots,
+        // 16 384 roots: 10.6 with three, 10.2 with four, 9.8 with eight)
+        const auto kernel = k <= 12 ? sample_hop_recent_quads_kernel<3> : k <= 32 ? sample_hop_recent_quads_kernel<4> : sample_hop_recent_quads_kernel<8>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), 0, stream, g->indptr, g->rec, g->time_index, roots,
                            times, n, g->num_nodes, k, magic_k, o.nbr, o.eid, o.ts, o.count);
         return;
     }

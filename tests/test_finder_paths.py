@@ -30,7 +30,8 @@ def compare(g, g_ref, roots, times, k, hops, policy, m=0, weight=None):
 
 
 @pytest.mark.parametrize("entries", [0, 1, 15, 16, 17, 255, 256, 257, 4096, 65536, 70_001])
-@pytest.mark.parametrize("n,k", [(16_383, 10), (16_384, 1), (16_385, 3), (16_384 + 17, 10), (20_000, 25), (17_001, 64)])
+@pytest.mark.parametrize("n,k", [(16_383, 10), (16_384, 1), (16_385, 3), (16_384 + 17, 10), (20_000, 25), (17_001, 64),
+                                 (16_384, 33), (20_480, 32), (24_575, 10), (24_577, 13), (32_768 + 5, 10), (32_769, 28), (40_960 + 17, 1), (40_961, 4), (41_001, 25), (40_960 + 1, 50), (65_535, 16), (65_536, 31), (65_537, 16)])
 def test_recent_around_the_large_hop(entries, n, k):
     rng = np.random.default_rng(entries + n)
     nodes = 3 if entries < 5000 else 40
@@ -50,7 +51,8 @@ def test_recent_second_hop_is_the_large_one():
     src, dst = rng.integers(0, 500, (2, 40_000)).astype(np.int32)
     ts = np.sort(rng.integers(0, 9000, 40_000)).astype(np.int64)
     g, g_ref = both(src, dst, ts, 500)
-    compare(g, g_ref, rng.integers(0, 500, 1700).astype(np.int32), rng.integers(0, 9001, 1700).astype(np.int64), 10, 2, T.RECENT)
+    for n in (1700, 3300):
+        compare(g, g_ref, rng.integers(0, 500, n).astype(np.int32), rng.integers(0, 9001, n).astype(np.int64), 10, 2, T.RECENT)
 
 
 @pytest.mark.parametrize("k,m", [(1, 2), (5, 16), (10, 25), (31, 32), (10, 64), (63, 64)])
