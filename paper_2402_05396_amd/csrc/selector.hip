@@ -54,11 +54,42 @@ __device__ __forceinline__ int64_t wave_descend(const T* __restrict__ a, int64_t
     return end - 1;   // not reached while the guarantee holds
 }
 
+// Totals over the wave of R values per lane (rows of a group), 4 at a time: lanes exchange halves so that every
+// quarter of the wave ends up with one row's sums, 22 instructions for a row where a prefix sum takes 25. v[4 i]
+// then holds rows 4 i .. 4 i + 3, which total_of_row takes out.
+template <int R> __device__ __forceinline__ void fold_rows(uint64_t (&v)[R]) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    auto join = [](u32x2 lo, u32x2 hi) { return (((uint64_t)hi.x << 32) | lo.x) + (((uint64_t)hi.y << 32) | lo.y); };
+    auto halves = [&](uint64_t a, uint64_t b) {     // lower half of the wave: a's sums, upper half: b's
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)a, (uint32_t)b, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+        return join(u32x2{lo[0], lo[1]}, u32x2{hi[0], hi[1]});
+    };
+    auto quarters = [&](uint64_t a, uint64_t b) {   // of each half: a's sums, then b's
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)a, (uint32_t)b, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(a >> 32), (uint32_t)(b >> 32), false, false);
+        return join(u32x2{lo[0], lo[1]}, u32x2{hi[0], hi[1]});
+    };
+#pragma unroll
+    for (int i = 0; i < R; i += 4) {
+        uint64_t t = quarters(halves(v[i], v[i + 1]), halves(v[i + 2], v[i + 3]));
+        t += dpp_take64<0x128, 0xf>(t);             // rotations inside 16 lanes
+        t += dpp_take64<0x124, 0xf>(t);
+        t += dpp_take64<0x122, 0xf>(t);
+        t += dpp_take64<0x121, 0xf>(t);
+        v[i] = t;
+    }
+}
+template <int R> __device__ __forceinline__ uint64_t total_of_row(const uint64_t (&folded)[R], int r) {
+    return wave_get64(folded[r & ~3], (r & 1) * 32 + (r & 2) * 8);
+}
+
 // The same for one group of up to 1024 values starting at a[begin], all its loads in flight together. The
 // group is read in rows of 64 x 16 bytes, one piece per lane, so that a load covers whole lines (with 16
-// neighboring values per lane every load touched 64 lines; us a call, million edges:
-// 600 draws 6.0 -> 4.8, 2 000 7.7 -> 5.8, 6 000 15.6 -> 11.3). The scans of the rows do not depend on
-// one another; the row is found first, then the lane, then the value.
+// neighboring values per lane every load touched 64 lines). The row is found first, from the rows' totals, then
+// the lane by a prefix sum over that row alone, then the value. Draws from 1 M, 40 M, 500 M scores, us a launch with 16
+// neighboring values per lane / a prefix sum over every row / so: 600 draws 6.3 5.3 7.4 / 5.1 4.6 6.8 / 4.8 4.2 6.5,
+// 100 000 draws 193 119 175 / 136 130 200 / 88 83 141.
 template <typename T>
 __device__ __forceinline__ int64_t wave_descend_group(const T* __restrict__ a, int64_t begin, int64_t end, uint64_t& x,
                                                       int lane) {
@@ -78,37 +109,38 @@ __device__ __forceinline__ int64_t wave_descend_group(const T* __restrict__ a, i
 #pragma unroll
             for (int i = 0; i < kVec; ++i) v[r][i] = mine + r * kWave * kVec + i < end ? a[mine + r * kWave * kVec + i] : (T)0;
     }
-    uint64_t own[kRows], inc[kRows];
+    uint64_t own[kRows];
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
         own[r] = 0;
 #pragma unroll
         for (int i = 0; i < kVec; ++i) own[r] += (uint64_t)v[r][i];
-        inc[r] = wave_inclusive_scan64(own[r]);
     }
+    fold_rows(own);
     // the row where the running sum passes x; the last one while the guarantee does not hold
     int row = kRows - 1;
     uint64_t before = 0, rest = x;
     T pick[kVec];
-    uint64_t pick_inc = inc[kRows - 1], pick_own = own[kRows - 1];
 #pragma unroll
     for (int i = 0; i < kVec; ++i) pick[i] = v[kRows - 1][i];
     bool open = true;
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
-        const uint64_t total = wave_get64(inc[r], kWave - 1);
+        const uint64_t total = total_of_row(own, r);
         const bool here = open && (r == kRows - 1 || before + total > x);   // wave-uniform
         if (here) {
             row = r;
             rest = x - before;
-            pick_inc = inc[r];
-            pick_own = own[r];
 #pragma unroll
             for (int i = 0; i < kVec; ++i) pick[i] = v[r][i];
             open = false;
         }
         before += total;
     }
+    uint64_t pick_own = 0;
+#pragma unroll
+    for (int i = 0; i < kVec; ++i) pick_own += (uint64_t)pick[i];
+    const uint64_t pick_inc = wave_inclusive_scan64(pick_own);
     const uint64_t hit = __ballot(pick_inc > rest);
     const int first = hit ? __ffsll((long long)hit) - 1 : kWave - 1;   // hit is never 0 while the guarantee holds
     rest -= wave_get64(pick_inc - pick_own, first);                    // what is left inside that lane
