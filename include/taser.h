@@ -352,7 +352,8 @@ int taser_cache_lookup_static(taser_cache* c, const int32_t* ids, int64_t n, voi
 
 /* Knobs for callers that run the halves of a lookup beside other kernels, and for measurements.
  *   stage_blocks  number of 256-thread blocks the host -> staging copy runs on
- *                 (default 32; 0 keeps the current value). The copy is bound by
+ *                 (0 keeps the current value; by default 32, 64 below 256 MiB
+ *                 of output, 128 below 64 MiB). The copy is bound by
  *                 the bus; fewer blocks copy somewhat slower but leave more of
  *                 the memory system's request slots to kernels running beside it.
  *   refresh_before_gather  non-zero: taser_cache_gather first re-writes its read

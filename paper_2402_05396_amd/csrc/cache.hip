@@ -84,7 +84,7 @@ struct taser_cache {
     int64_t loc_capacity;
     const int32_t* prefetched_ids;   // what `loc` currently describes (set by taser_cache_prefetch)
     int64_t prefetched_n;
-    int stage_blocks;                // width of the host -> staging copy, in 256-thread blocks
+    int stage_blocks;                // width of the host -> staging copy, in 256-thread blocks (0: default_stage_blocks)
     bool refresh_before_gather;      // see rewrite_kernel
     int partitioned_gather;          // gather through gather_owned_lines_kernel where it applies (0 off, 1 on, 2: owners by position only, for measurements)
     std::vector<int32_t>* residents;   // host copy, slot order
@@ -263,12 +263,17 @@ __device__ __forceinline__ void count_block(const Service& v, int block, int32_t
 // claimed ones in LDS and copies their rows as one flat stream of 16-byte pieces,
 // two per lane in flight (a long row fills a wave; of 64-byte rows 32 are on
 // their way at once, where one row at a time left 60 of the 64 lanes idle).
-// More in flight makes a gather beside it slower than it makes the copy faster:
+// More in flight makes a long gather beside it slower than it makes the copy faster:
 // a lookup of 1.33 M rows of 1652 bytes takes 0.599 / 0.590 / 0.575 / 0.596 / 0.617 /
 // 0.725 ms with 16 / 24 / 32 / 40 / 48 / 64 blocks, rows of 744 bytes 0.315 / 0.309 /
-// 0.303 / 0.319 / 0.333 / 0.368; of 200 000 64-byte rows (30 000 misses) 0.192 /
-// 0.137 / 0.109 / 0.100 / 0.099 / 0.095.
-constexpr int kStageBlocks = 32;
+// 0.303 / 0.319 / 0.333 / 0.368. Where there is little to write meanwhile the copy should
+// just be fast, and few misses in a large table need waves that look for them. us with 32 /
+// 64 / 128 blocks: 110 000 rows of 1652 bytes, 4 % misses 80 / 83 / 92, 20 % 146 / 150 /
+// 143; 2.4 M rows of 64 bytes, 20 % 105 / 97 / 99; 20 000 rows of 1652 bytes, 50 % 104 / 98 /
+// 97; 30 000 rows of 64 bytes, 2 % 29 / 24 / 20; 1 000 rows of 1652 bytes, 80 % 31 / 28 / 27.
+inline int default_stage_blocks(int64_t out_bytes) {
+    return out_bytes >= (int64_t)1 << 28 ? 32 : out_bytes >= (int64_t)1 << 26 ? 64 : 128;
+}
 
 // `lds`: 2 * kWave words per wave
 __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, int32_t* __restrict__ lds) {
@@ -641,7 +646,7 @@ extern "C" int taser_cache_init(const void* host_table, int64_t rows, int32_t ro
     c->capacity = capacity_rows;
     c->host_rows = static_cast<const uint8_t*>(attr.devicePointer);
     c->dev_pitch = row_bytes;
-    c->stage_blocks = kStageBlocks;
+    c->stage_blocks = 0;
     c->refresh_before_gather = false;
     c->partitioned_gather = 1;
     c->residents = new (std::nothrow) std::vector<int32_t>();
@@ -741,7 +746,8 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     v.n = n;
     v.rows = c->rows;
     v.access_count = c->access_count;
-    v.stage_blocks = c->miss_size ? c->stage_blocks : hit_miss ? 1 : 0;
+    v.stage_blocks = hit_miss ? 1 : 0;
+    if (c->miss_size) v.stage_blocks = c->stage_blocks ? c->stage_blocks : default_stage_blocks(n * c->row_bytes);
     // fewer slots at a time where a small table would leave waves without any
     v.stage_span = kWave;
     while (v.stage_span > 8 && c->miss_size / v.stage_span < (uint32_t)v.stage_blocks * (kThreads / kWave)) v.stage_span /= 2;
