@@ -78,7 +78,7 @@ struct taser_cache {
     int64_t staging_rows;
     int32_t* miss_key;          // device [miss_size], all kEmpty between lookups
     int32_t* miss_row;          // device [miss_size]: staging row of a claimed slot (-1: the staging area was full)
-    uint32_t* stage_count;      // device [1]: staging rows handed out by the running call, 0 between calls
+    uint32_t* stage_count;      // device [2]: staging rows handed out by the running call; requests that missed (whole lookups)
     uint32_t miss_size;         // 0 or a power of two >= 2 * staging_rows
     int32_t* loc;               // device [loc_capacity], per-request outcome
     int64_t loc_capacity;
@@ -169,8 +169,8 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
 }
 
 // What a lookup does beside its gather, on blocks of their own in the launch after classify:
-// the first `stage_blocks` stage the missed rows (the very first adds up the hit/miss counts
-// before that), the next `count_blocks` count accesses. `blocks` in all, a multiple of the number
+// the first `stage_blocks` stage the missed rows, the next one adds up the hit/miss counts (if
+// tally_blocks), the next `count_blocks` count accesses. `blocks` in all, a multiple of the number
 // of L2 partitions, so that the gather's blocks behind them keep their places.
 struct Service {
     static constexpr bool kAny = true;
@@ -187,16 +187,17 @@ struct Service {
     uint32_t row_dwords;
     uint8_t* stage_rows;
     int32_t dev_pitch;
-    const uint32_t* block_tally;          // hit/miss counts of tally_blocks classify blocks, or hit_miss null
+    const uint32_t* block_tally;          // hit/miss counts of tally_blocks classify blocks (0: not wanted)
     int tally_blocks;
-    unsigned long long* hit_miss;
+    unsigned long long* hit_miss;         // the caller's counters, or null
+    uint32_t* missed;                     // the misses of this call alone, or null
     const int32_t* ids;                   // access counting
     int64_t n, rows;
     uint32_t* access_count;
     __device__ __forceinline__ void run(uint32_t block, int32_t* lds) const;
 };
 
-// One block: adds the per-block counts of the classify launch to the caller's two counters.
+// One block: adds up the per-block counts of the classify launch.
 __device__ __forceinline__ void tally_block(const Service& v) {
     __shared__ unsigned long long part[2][kThreads / kWave];
     unsigned long long h = 0, m = 0;
@@ -219,8 +220,9 @@ __device__ __forceinline__ void tally_block(const Service& v) {
             h += part[0][w];
             m += part[1][w];
         }
-        if (h) atomicAdd(&v.hit_miss[0], h);
-        if (m) atomicAdd(&v.hit_miss[1], m);
+        if (v.hit_miss && h) atomicAdd(&v.hit_miss[0], h);
+        if (v.hit_miss && m) atomicAdd(&v.hit_miss[1], m);
+        if (v.missed) *v.missed = m < 0xffffffffull ? (uint32_t)m : 0xffffffffu;
     }
 }
 
@@ -336,11 +338,12 @@ __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, in
 static_assert(taser_gather::kBesideWords >= 2 * kTallySlots && taser_gather::tile_rows(4) >= 2 * kTallySlots, "the LDS of run()");
 __device__ __forceinline__ void Service::run(uint32_t block, int32_t* lds) const {
     if ((int)block < stage_blocks) {
-        if (block == 0 && hit_miss) tally_block(*this);
         stage_block(*this, block, lds);
-    } else if ((int)block < stage_blocks + count_blocks) {
-        count_block(*this, (int)block - stage_blocks, lds);
+        return;
     }
+    int own = (int)block - stage_blocks;
+    if (tally_blocks && own-- == 0) tally_block(*this);
+    else if (own < count_blocks) count_block(*this, own, lds);
 }
 
 __global__ __launch_bounds__(kThreads) void service_kernel(const Service v) {
@@ -398,6 +401,8 @@ struct CacheSource {
     int owner_mode;   // 1: by source row; 2: by position only
     const int32_t* miss_row;
     __device__ __forceinline__ int32_t key(int64_t i) const { return loc[i]; }
+    const uint32_t* missed;   // requests that missed (whole lookups only)
+    __device__ __forceinline__ uint32_t late() const { return *missed; }
     // a missed row, on its way while the staging runs
     __device__ __forceinline__ bool pending(int32_t where) const { return where < kLocZero; }
     // from miss-table slot to staging row, once that is known
@@ -704,7 +709,7 @@ extern "C" int taser_cache_init(const void* host_table, int64_t rows, int32_t ro
         CACHE_TRY(hipMalloc((void**)&c->stage_rows, (size_t)staging_rows * c->dev_pitch));
         CACHE_TRY(hipMalloc((void**)&c->miss_key, (size_t)c->miss_size * sizeof(int32_t)));
         CACHE_TRY(hipMalloc((void**)&c->miss_row, (size_t)c->miss_size * sizeof(int32_t)));
-        CACHE_TRY(hipMalloc((void**)&c->stage_count, sizeof(uint32_t)));
+        CACHE_TRY(hipMalloc((void**)&c->stage_count, 2 * sizeof(uint32_t)));
         hipLaunchKernelGGL(fill_kernel, dim3((c->miss_size + kThreads - 1) / kThreads), dim3(kThreads), 0, stream,
                            c->miss_key, c->miss_size, kEmpty);
         hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(kThreads), 0, stream, reinterpret_cast<int32_t*>(c->stage_count), 1u, 0);
@@ -718,7 +723,8 @@ extern "C" int taser_cache_init(const void* host_table, int64_t rows, int32_t ro
 
 // Launches classify into `loc` (block counts into `tally`); *service = what the staging launch has to do.
 static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint64_t* hit_miss, hipStream_t stream,
-                             int32_t* loc, uint32_t* tally, Service* service) {
+                             int32_t* loc, uint32_t* tally, bool count_misses, Service* service) {
+    const bool counts = hit_miss || count_misses;
     int64_t blocks = (n + kThreads - 1) / kThreads;
     if (blocks > kClassifyBlocks) blocks = kClassifyBlocks;
     // miss_key is all-empty here: cache_init cleared it and every staging clears what it consumed
@@ -726,7 +732,7 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
         TaserProfileSpan span(stream, "cache_classify");
         hipLaunchKernelGGL(classify_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, ids, n, c->rows,
                            c->hash_key, c->hash_slot, c->hash_mask, c->miss_key, c->miss_size, loc,
-                           hit_miss ? tally : nullptr, c->stage_count);
+                           counts ? tally : nullptr, c->stage_count);
     }
     Service v = {};
     v.miss_key = c->miss_key;
@@ -740,13 +746,13 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     v.stage_rows = c->stage_rows;
     v.dev_pitch = c->dev_pitch;
     v.block_tally = tally;
-    v.tally_blocks = (int)blocks;
+    v.tally_blocks = counts ? (int)blocks : 0;
+    v.missed = count_misses ? c->stage_count + 1 : nullptr;
     v.hit_miss = reinterpret_cast<unsigned long long*>(hit_miss);
     v.ids = ids;
     v.n = n;
     v.rows = c->rows;
     v.access_count = c->access_count;
-    v.stage_blocks = hit_miss ? 1 : 0;
     if (c->miss_size) v.stage_blocks = c->stage_blocks ? c->stage_blocks : default_stage_blocks(n * c->row_bytes);
     // fewer slots at a time where a small table would leave waves without any
     v.stage_span = kWave;
@@ -755,12 +761,12 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
         const int64_t want = (n + 4 * kThreads - 1) / (4 * kThreads);
         v.count_blocks = (int)(want < kCountBlocks ? want : kCountBlocks);
     }
-    v.blocks = (uint32_t)((v.stage_blocks + v.count_blocks + taser_gather::kOwnerClasses - 1) / taser_gather::kOwnerClasses * taser_gather::kOwnerClasses);
+    v.blocks = (uint32_t)((v.stage_blocks + (counts ? 1 : 0) + v.count_blocks + taser_gather::kOwnerClasses - 1) / taser_gather::kOwnerClasses * taser_gather::kOwnerClasses);
     *service = v;
 }
 
 static CacheSource source_of(const taser_cache* c, const int32_t* ids, const int32_t* loc) {
-    return CacheSource{loc, ids, c->cache_rows, c->stage_rows, c->dev_pitch, c->host_rows, c->pitch_bytes, c->partitioned_gather, c->miss_row};
+    return CacheSource{loc, ids, c->cache_rows, c->stage_rows, c->dev_pitch, c->host_rows, c->pitch_bytes, c->partitioned_gather, c->miss_row, c->stage_count ? c->stage_count + 1 : nullptr};
 }
 
 static int source_alignment(const taser_cache* c) {
@@ -771,7 +777,7 @@ static int source_alignment(const taser_cache* c) {
 static int enqueue_prefetch(taser_cache* c, const int32_t* ids, int64_t n, uint64_t* hit_miss, hipStream_t stream,
                             int32_t* loc, uint32_t* tally) {
     Service v;
-    enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, &v);
+    enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, false, &v);
     if (v.blocks) {
         TaserProfileSpan span(stream, "cache_stage_misses");
         hipLaunchKernelGGL(service_kernel, dim3((unsigned)v.blocks), dim3(kThreads), 0, stream, v);
@@ -828,7 +834,7 @@ static int enqueue_lookup(taser_cache* c, const int32_t* ids, int64_t n, void* o
     const bool owned = c->partitioned_gather && tg::owned_applies(align, c->row_bytes, n, out);
     const CacheSource source = source_of(c, ids, loc);
     Service v;
-    enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, &v);
+    enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, true, &v);
     bool launched;
     {
         // the gather's blocks are behind the service blocks, so the staging starts first and its few blocks

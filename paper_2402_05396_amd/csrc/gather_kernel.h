@@ -62,7 +62,8 @@ template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) 
 // every output byte is written (some dwords in both, with the same value). PHASE 0 is the whole
 // gather in one launch. For that a Source also has
 //   pending(key)    the row is on its way during PHASE 1;
-//   resolve(key)    the token for PHASES 0 and 2 (PHASE 1 takes it as it is read).
+//   resolve(key)    the token for PHASES 0 and 2 (PHASE 1 takes it as it is read);
+//   late()          how many output rows PHASE 2 has to write (at most 2^32 - 1 of them counted).
 
 template <int PHASE, typename Source> __device__ __forceinline__ int32_t source_token(const Source& source, int64_t i) {
     const int32_t key = source.key(i);
@@ -99,6 +100,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         return;
     }
     uint32_t block = Beside::kAny ? blockIdx.x - beside.blocks : blockIdx.x;
+    if constexpr (PHASE == 2)
+        if (source.late() == 0) return;
     if constexpr (Parts::kMore) block = parts.enter(block, source, total_units, last_row, out);
     constexpr uint32_t kPer = 16 / UNIT;                       // units of a chunk
     const int64_t tile = (int64_t)block * (kTile * kPer);   // first output unit of this block
@@ -116,8 +119,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         if (tile_last >= total_units) tile_last = total_units - 1;
         const uint32_t e_last = col0 + (uint32_t)(tile_last - tile);   // unit offset from the start of row0
         const int rows_here = (int)(USE_MAGIC ? __umulhi(e_last, magic) : e_last / row_units) + 1;   // <= the array
-        for (int r = threadIdx.x; r < rows_here; r += kThreads) tile_key[r] = source_token<PHASE>(source, row0 + r);
-        __syncthreads();
+        bool late = false;
+        for (int r = threadIdx.x; r < rows_here; r += kThreads) {
+            const int32_t key = source_token<PHASE>(source, row0 + r);
+            tile_key[r] = key;
+            if (PHASE == 2) late |= source.pending(key);
+        }
+        if (PHASE != 2) __syncthreads();
+        else if (!__syncthreads_or(late)) return;               // nothing of this tile was on its way
     }
     // Pass 1 (ALU only): output row and column of each of this thread's chunks.
     uint32_t col[kUnroll];
@@ -227,9 +236,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 // line that lie beyond the row's end belong to the next output row and are read there.
 // The assumption about where workgroups run only affects speed, never results.
 constexpr int kOwnerClasses = 8;
-// PHASE 2 usually has few rows (the cache's misses): one workgroup takes all of a super-tile's, so that there is
-// something for its lanes to do.
-constexpr int owner_classes(int phase) { return phase == 2 ? 1 : kOwnerClasses; }
+// PHASE 2 can have few rows (the cache's misses) or most of the output; how many only the device knows, so the launch
+// decides at run time.
+//   * Few: one workgroup takes all of a super-tile's, so that there is something for its lanes to do. Below
+//     kOwnedLateBlocks units (as many as are resident twice over) all classes take part, since one each would leave
+//     compute units idle: 5 000 rows of 1652 bytes, 88 % late, 75 us with 43 workgroups, 60 with 344 (61 in PHASE 0
+//     after the staging).
+//   * From kWholeShare on: the whole output is written once more as in PHASE 0, every line once and by its class.
+//     1.33 M rows of 1652 bytes, lookups with all, 90, 80, 70 % of the rows late, requests without skew: 1.25, 1.12,
+//     1.00, 0.88 ms writing the late ones only, 1.05, 0.98, 0.92, 0.87 writing all (1.02, 0.95, 0.89, 0.84 in PHASE 0
+//     after the staging); with requests by a power law, rows read again and again by every partition anyhow, 1.31, 1.00
+//     (94 %), 0.88 (83 %), 0.77 (68 %) and 1.33, 1.06, 0.98, 0.95 (1.37, 1.05, 0.99, 0.94).
+constexpr uint32_t kOwnedLateBlocks = 4096;
+constexpr double kWholeShare = 0.78;
+constexpr int kLateUnits = 4;             // per workgroup; with one each, 90 000 empty ones cost a lookup without misses 11 us
 constexpr int kOwnedTileLines = 1536;     // 192 KiB of output per super-tile: about 1500 chunks per workgroup; smaller
                                           // tiles leave the workgroups' shares too uneven, larger ones cost LDS
                                           // (PHASE 2 takes the same time from 768 to 3072)
@@ -238,9 +258,14 @@ constexpr int kOwnedMaxRowBytes = 16384;
 constexpr int kOwnedMaxRows = kOwnedTileLines * 128 / kOwnedMinRowBytes + 3;
 
 // Geometry of such a launch, worked out by the host.
+struct ChunkGrid {   // slots: 16-byte chunks of the most lines a row can own; the rest for dividing by that
+    uint32_t slots, slot_magic, step_rows, step_rest;
+};
 struct OwnedLines {
-    uint32_t row_bytes, slots, slot_magic, step_rows, step_rest;   // slots: 16-byte chunks of the most lines a row can own
+    uint32_t row_bytes;
+    ChunkGrid chunks, late_chunks;   // PHASE 2 takes the second while it only writes the rows that were on their way
     int64_t total_bytes, n_rows;
+    uint32_t tiles, late_classes, whole_from;   // PHASE 2: super-tiles; classes; how many late rows make it write everything
 };
 
 // In PHASE 1 only the lines of rows that are there are written, up to where a pending row begins. In
@@ -255,121 +280,138 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         return;
     }
     const uint32_t block = Beside::kAny ? blockIdx.x - beside.blocks : blockIdx.x;
-    constexpr int kBias = PHASE == 2 ? 128 : 0;   // a PHASE 2 row's first line may begin before the row
     __shared__ int32_t tile_key[kOwnedMaxRows + 1];
     __shared__ const uint8_t* own_base[kOwnedMaxRows];   // source row, or `zeros` with the zero flag set
     __shared__ const uint8_t* own_next[kOwnedMaxRows];   // source row of the next output row minus row_bytes (same flag rule); null: not to be written
-    __shared__ uint32_t own_meta[kOwnedMaxRows];          // first line in the tile + 256 | lines << 12 | (bytes before the first line + kBias) << 20
+    __shared__ uint32_t own_meta[kOwnedMaxRows];          // first line in the tile + 256 | lines << 12 | (bytes before the first line + bias) << 20
                                                           // | bit 30: this row is zeros | bit 31: the next row is zeros
     __shared__ uint32_t n_owned;
 
-    const uint32_t row_bytes = g.row_bytes, slots = g.slots;
+    const uint32_t row_bytes = g.row_bytes;
     const int64_t total_bytes = g.total_bytes, n_rows = g.n_rows;
-    constexpr uint32_t kClasses = owner_classes(PHASE);
-    const uint32_t cls = block % kClasses;
-    const int64_t line0 = (int64_t)(block / kClasses) * kOwnedTileLines;
-    const int64_t total_lines = (total_bytes + 127) >> 7;
-    const uint32_t lines_here = (uint32_t)(total_lines - line0 < kOwnedTileLines ? total_lines - line0 : kOwnedTileLines);
-    const int64_t tile_byte0 = line0 * 128;
-    const uint32_t tile_limit = (uint32_t)(total_bytes - tile_byte0 < (int64_t)kOwnedTileLines * 128 ? total_bytes - tile_byte0
-                                                                                                  : (int64_t)kOwnedTileLines * 128);
-    const int64_t r0 = tile_byte0 / row_bytes;                              // row holding the tile's first byte
-    int64_t r_last = (tile_byte0 + (int64_t)lines_here * 128 - 1) / row_bytes;   // row holding its last byte
-    if (r_last > n_rows - 1) r_last = n_rows - 1;
-    const int rows_here = (int)(r_last - r0 + 1);                           // <= kOwnedMaxRows - 1
-    const int keys_here = rows_here + (r_last + 1 < n_rows ? 1 : 0);        // + the row the last line may run into
-    if (threadIdx.x == 0) n_owned = 0;
-    for (int i = threadIdx.x; i < keys_here; i += kThreads) tile_key[i] = source_token<PHASE>(source, r0 + i);
-    __syncthreads();
-    for (int i = threadIdx.x; i < rows_here; i += kThreads) {
-        const int64_t r = r0 + i;
-        const int32_t key = tile_key[i];
-        if (PHASE != 0 && source.pending(key) != (PHASE == 2)) continue;
-        if (kClasses > 1 && source.owner(key, r) != cls) continue;
-        const int64_t begin = r * row_bytes;
-        // lines whose first byte is in row r, and in PHASE 2 the one that row r begins in
-        const int64_t first = (begin + (PHASE == 2 ? 0 : 127)) >> 7, next = (begin + row_bytes + 127) >> 7;
-        const uint8_t* base = source.address(key, r);
-        const bool later = PHASE == 1 && i + 1 < keys_here && source.pending(tile_key[i + 1]);   // the next row is PHASE 2's
-        const uint8_t* after = i + 1 < keys_here && !later ? source.address(tile_key[i + 1], r + 1) : nullptr;
-        const uint32_t at = atomicAdd(&n_owned, 1u);
-        own_base[at] = base ? base : zeros;
-        own_next[at] = after ? after - row_bytes : (later ? nullptr : zeros);
-        own_meta[at] = (uint32_t)(first - line0 + 256) | ((uint32_t)(next - first) << 12) | ((uint32_t)(first * 128 - begin + kBias) << 20) |
-                       (base ? 0u : 1u << 30) | (after ? 0u : 1u << 31);
+    // a unit of work is a super-tile's rows of one class (or all); outside PHASE 2 a workgroup has exactly one
+    uint32_t classes = kOwnerClasses, units = 0;
+    bool only_late = false;   // write the rows that were on their way in PHASE 1, not the others
+    if constexpr (PHASE == 2) {
+        const uint32_t late = source.late();
+        if (late == 0) return;
+        only_late = late < g.whole_from;
+        if (only_late) classes = g.late_classes;
+        units = classes * g.tiles;
+        if (block >= units) return;
     }
-    __syncthreads();
+    const ChunkGrid chunks = only_late ? g.late_chunks : g.chunks;
+    const uint32_t slots = chunks.slots;
+    const int32_t bias = only_late ? 128 : 0;   // the first line of a row may then begin before the row
+    for (uint32_t unit = block;;) {
+        const uint32_t cls = unit % classes;
+        const int64_t line0 = (int64_t)(unit / classes) * kOwnedTileLines;
+        const int64_t total_lines = (total_bytes + 127) >> 7;
+        const uint32_t lines_here = (uint32_t)(total_lines - line0 < kOwnedTileLines ? total_lines - line0 : kOwnedTileLines);
+        const int64_t tile_byte0 = line0 * 128;
+        const uint32_t tile_limit = (uint32_t)(total_bytes - tile_byte0 < (int64_t)kOwnedTileLines * 128 ? total_bytes - tile_byte0
+                                                                                                      : (int64_t)kOwnedTileLines * 128);
+        const int64_t r0 = tile_byte0 / row_bytes;                              // row holding the tile's first byte
+        int64_t r_last = (tile_byte0 + (int64_t)lines_here * 128 - 1) / row_bytes;   // row holding its last byte
+        if (r_last > n_rows - 1) r_last = n_rows - 1;
+        const int rows_here = (int)(r_last - r0 + 1);                           // <= kOwnedMaxRows - 1
+        const int keys_here = rows_here + (r_last + 1 < n_rows ? 1 : 0);        // + the row the last line may run into
+        if (threadIdx.x == 0) n_owned = 0;
+        for (int i = threadIdx.x; i < keys_here; i += kThreads) tile_key[i] = source_token<PHASE>(source, r0 + i);
+        __syncthreads();
+        for (int i = threadIdx.x; i < rows_here; i += kThreads) {
+            const int64_t r = r0 + i;
+            const int32_t key = tile_key[i];
+            if (PHASE == 1 && source.pending(key)) continue;
+            if (only_late && !source.pending(key)) continue;
+            if ((PHASE != 2 || classes > 1) && source.owner(key, r) != cls) continue;
+            const int64_t begin = r * row_bytes;
+            // lines whose first byte is in row r, and for late rows the one that row r begins in
+            const int64_t first = (begin + (only_late ? 0 : 127)) >> 7, next = (begin + row_bytes + 127) >> 7;
+            const uint8_t* base = source.address(key, r);
+            const bool later = PHASE == 1 && i + 1 < keys_here && source.pending(tile_key[i + 1]);   // the next row is PHASE 2's
+            const uint8_t* after = i + 1 < keys_here && !later ? source.address(tile_key[i + 1], r + 1) : nullptr;
+            const uint32_t at = atomicAdd(&n_owned, 1u);
+            own_base[at] = base ? base : zeros;
+            own_next[at] = after ? after - row_bytes : (later ? nullptr : zeros);
+            own_meta[at] = (uint32_t)(first - line0 + 256) | ((uint32_t)(next - first) << 12) | ((uint32_t)(first * 128 - begin + bias) << 20) |
+                           (base ? 0u : 1u << 30) | (after ? 0u : 1u << 31);
+        }
+        __syncthreads();
 
-    const uint32_t items = n_owned * slots;          // `slots` 16-byte chunks per owned row, some of them beyond its lines
-    for (uint32_t round = 0; round < items; round += kTile) {
-        const uint8_t* from[kUnroll];
-        uint32_t out_off[kUnroll], which[kUnroll], in_off[kUnroll];
-        bool whole[kUnroll], cross[kUnroll];
-        // (in_off: bytes from the row's start; with PHASE 2 negative before it)
-        // one division per thread: its further chunks lie kThreads = step_rows * slots + step_rest chunks on
-        const uint32_t w0 = round + threadIdx.x;
-        uint32_t j = __umulhi(w0, g.slot_magic), within = w0 - j * slots;   // exact: w0 * slots < 2^32
+        const uint32_t items = n_owned * slots;          // `slots` 16-byte chunks per owned row, some of them beyond its lines
+        for (uint32_t round = 0; round < items; round += kTile) {
+            const uint8_t* from[kUnroll];
+            uint32_t out_off[kUnroll], which[kUnroll], in_off[kUnroll];
+            bool whole[kUnroll], cross[kUnroll];
+            // (in_off: bytes from the row's start; with PHASE 2 negative before it)
+            // one division per thread: its further chunks lie kThreads = step_rows * slots + step_rest chunks on
+            const uint32_t w0 = round + threadIdx.x;
+            uint32_t j = __umulhi(w0, chunks.slot_magic), within = w0 - j * slots;   // exact: w0 * slots < 2^32
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const bool live = round + threadIdx.x + u * kThreads < items;
-            const uint32_t jj = live ? j : 0u;
-            const uint32_t meta = own_meta[jj];
-            const uint32_t line = (meta & 4095u) + (within >> 3) - 256u;          // relative to the tile; wraps if before it
-            bool mine = live && (within >> 3) < ((meta >> 12) & 255u) && line < lines_here;
-            out_off[u] = line * 128u + (within & 7u) * 16u;
-            const int32_t off = (int32_t)(((meta >> 20) & 255u) + within * 16u) - kBias;
-            const bool beyond = off >= (int32_t)row_bytes;                         // the chunk lies in the next output row
-            const uint8_t* base = beyond ? own_next[jj] : own_base[jj];
-            const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
-            if (PHASE == 1) mine = mine && base != nullptr;
-            if (PHASE == 2) mine = mine && off > -16;                              // wholly the row before's otherwise
-            whole[u] = mine && out_off[u] + 16u <= tile_limit && (beyond || off + 16 <= (int32_t)row_bytes) && (PHASE != 2 || off >= 0);
-            cross[u] = mine && !whole[u] && out_off[u] < tile_limit;
-            from[u] = (whole[u] && !zero) ? base + off : zeros;
-            in_off[u] = (uint32_t)off;
-            which[u] = jj;
-            j += g.step_rows;
-            within += g.step_rest;
-            if (within >= slots) {
-                within -= slots;
-                ++j;
-            }
-        }
-        u32x4 vals[kUnroll];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) vals[u] = ((GlobalChunk16Ptr)from[u])->v;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            if (!cross[u]) continue;
-            // dword by dword: the rest of the row, then the start of the next one (or the output's ragged
-            // end); what another phase or the row before writes is left out
-            const uint32_t meta = own_meta[which[u]];
-            const uint8_t *a = own_base[which[u]], *b = own_next[which[u]];
-            uint32_t wds[4] = {0u, 0u, 0u, 0u};
-            uint32_t* const to = reinterpret_cast<uint32_t*>(out + tile_byte0 + out_off[u]);
-            bool all = true;
-            bool ours[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int32_t off = (int32_t)in_off[u] + 4 * e;
-                const bool beyond = off >= (int32_t)row_bytes;
+            for (int u = 0; u < kUnroll; ++u) {
+                const bool live = round + threadIdx.x + u * kThreads < items;
+                const uint32_t jj = live ? j : 0u;
+                const uint32_t meta = own_meta[jj];
+                const uint32_t line = (meta & 4095u) + (within >> 3) - 256u;          // relative to the tile; wraps if before it
+                bool mine = live && (within >> 3) < ((meta >> 12) & 255u) && line < lines_here;
+                out_off[u] = line * 128u + (within & 7u) * 16u;
+                const int32_t off = (int32_t)(((meta >> 20) & 255u) + within * 16u) - bias;
+                const bool beyond = off >= (int32_t)row_bytes;                         // the chunk lies in the next output row
+                const uint8_t* base = beyond ? own_next[jj] : own_base[jj];
                 const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
-                ours[e] = out_off[u] + 4u * e < tile_limit && (PHASE != 1 || !beyond || b) && (PHASE != 2 || off >= 0);
-                all = all && ours[e];
-                if (ours[e] && !zero) wds[e] = *(GlobalU32Ptr)((beyond ? b : a) + off);
+                if (PHASE == 1) mine = mine && base != nullptr;
+                if (PHASE == 2) mine = mine && off > -16;                              // wholly the row before's otherwise
+                whole[u] = mine && out_off[u] + 16u <= tile_limit && (beyond || off + 16 <= (int32_t)row_bytes) && (PHASE != 2 || off >= 0);
+                cross[u] = mine && !whole[u] && out_off[u] < tile_limit;
+                from[u] = (whole[u] && !zero) ? base + off : zeros;
+                in_off[u] = (uint32_t)off;
+                which[u] = jj;
+                j += chunks.step_rows;
+                within += chunks.step_rest;
+                if (within >= slots) {
+                    within -= slots;
+                    ++j;
+                }
             }
-            vals[u] = u32x4{wds[0], wds[1], wds[2], wds[3]};
-            whole[u] = all;                  // stored below with the others
-            if (all) continue;
+            u32x4 vals[kUnroll];
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (ours[e]) to[e] = wds[e];
-        }
-        uint8_t* tile_out = out + tile_byte0;
+            for (int u = 0; u < kUnroll; ++u) vals[u] = ((GlobalChunk16Ptr)from[u])->v;
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            if (whole[u]) __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(tile_out + out_off[u]));
+            for (int u = 0; u < kUnroll; ++u) {
+                if (!cross[u]) continue;
+                // dword by dword: the rest of the row, then the start of the next one (or the output's ragged
+                // end); what another phase or the row before writes is left out
+                const uint32_t meta = own_meta[which[u]];
+                const uint8_t *a = own_base[which[u]], *b = own_next[which[u]];
+                uint32_t wds[4] = {0u, 0u, 0u, 0u};
+                uint32_t* const to = reinterpret_cast<uint32_t*>(out + tile_byte0 + out_off[u]);
+                bool all = true;
+                bool ours[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int32_t off = (int32_t)in_off[u] + 4 * e;
+                    const bool beyond = off >= (int32_t)row_bytes;
+                    const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
+                    ours[e] = out_off[u] + 4u * e < tile_limit && (PHASE != 1 || !beyond || b) && (PHASE != 2 || off >= 0);
+                    all = all && ours[e];
+                    if (ours[e] && !zero) wds[e] = *(GlobalU32Ptr)((beyond ? b : a) + off);
+                }
+                vals[u] = u32x4{wds[0], wds[1], wds[2], wds[3]};
+                whole[u] = all;                  // stored below with the others
+                if (all) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (ours[e]) to[e] = wds[e];
+            }
+            uint8_t* tile_out = out + tile_byte0;
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                if (whole[u]) __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(tile_out + out_off[u]));
+            }
         }
+        if (PHASE != 2 || (unit += gridDim.x) >= units) return;
+        __syncthreads();   // the lists are made again
     }
 }
 
@@ -480,6 +522,16 @@ inline bool owned_applies(int src_align, int32_t row_bytes, int64_t n, const voi
     return src_align >= 4 && ((uintptr_t)out & 15) == 0 && row_bytes >= kOwnedMinRowBytes && row_bytes <= kOwnedMaxRowBytes && n >= 4096;
 }
 
+inline ChunkGrid chunk_grid(uint32_t lines) {
+    ChunkGrid g;
+    g.slots = lines * 8u;
+    // items of a workgroup stay far below 2^32 / slots: the multiply-high division is exact
+    g.slot_magic = (uint32_t)((((uint64_t)1 << 32) + g.slots - 1) / g.slots);
+    g.step_rows = (uint32_t)kThreads / g.slots;
+    g.step_rest = (uint32_t)kThreads % g.slots;
+    return g;
+}
+
 template <int PHASE, typename Source, typename Beside = NothingBeside>
 inline bool launch_owned(const Source& source, int32_t row_bytes, int64_t n, void* out, const uint8_t* zeros, hipStream_t stream,
                          const Beside& beside = {}) {
@@ -487,12 +539,23 @@ inline bool launch_owned(const Source& source, int32_t row_bytes, int64_t n, voi
     g.row_bytes = (uint32_t)row_bytes;
     g.total_bytes = n * (int64_t)row_bytes;
     g.n_rows = n;
-    g.slots = (uint32_t)((row_bytes + 127) / 128 + (PHASE == 2 ? 1 : 0)) * 8u;
-    // items of a workgroup stay far below 2^32 / slots: the multiply-high division is exact
-    g.slot_magic = (uint32_t)((((uint64_t)1 << 32) + g.slots - 1) / g.slots);
-    g.step_rows = (uint32_t)kThreads / g.slots;
-    g.step_rest = (uint32_t)kThreads % g.slots;
-    const int64_t blocks = ((g.total_bytes + 127) / 128 + kOwnedTileLines - 1) / kOwnedTileLines * owner_classes(PHASE) + beside.blocks;
+    const uint32_t lines = (uint32_t)(row_bytes + 127) / 128;
+    g.chunks = chunk_grid(lines);
+    const int64_t tiles = ((g.total_bytes + 127) / 128 + kOwnedTileLines - 1) / kOwnedTileLines;
+    int64_t blocks = tiles * kOwnerClasses;
+    if (blocks > 0x7fffffffLL) return false;
+    if (PHASE == 2) {
+        g.late_chunks = chunk_grid(lines + 1);
+        g.tiles = (uint32_t)tiles;
+        g.late_classes = blocks <= kOwnedLateBlocks ? kOwnerClasses : 1;
+        const int64_t whole_from = (int64_t)((double)n * kWholeShare);
+        g.whole_from = whole_from < 0xffffffffLL ? (uint32_t)whole_from : 0xffffffffu;
+        // several units to a workgroup of a large launch, since few rows leave most of it without any; a multiple of the
+        // classes, so that the units of class c are done by workgroups whose number is c modulo the classes
+        if (blocks > kOwnedLateBlocks) blocks = blocks / kLateUnits > kOwnedLateBlocks ? blocks / kLateUnits : kOwnedLateBlocks;
+        blocks = (blocks + kOwnerClasses - 1) / kOwnerClasses * kOwnerClasses;
+    }
+    blocks += beside.blocks;
     if (blocks > 0x7fffffffLL) return false;
     hipLaunchKernelGGL((gather_owned_lines_kernel<Source, PHASE, Beside>), dim3((unsigned)blocks), dim3(kThreads), 0, stream, source, g,
                        zeros, static_cast<uint8_t*>(out), beside);

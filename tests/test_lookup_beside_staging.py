@@ -66,6 +66,29 @@ def test_lookup_equals_the_oracle(dim, n, kind):
         T.cache_free(c)
 
 
+@pytest.mark.parametrize("dim,n", [(128, 4097), (413, 5001), (413, 70_003), (155, 330_001), (16, 9001)])
+@pytest.mark.parametrize("resident", [0, 150, 900, 1990, 2000])
+def test_lookup_whatever_the_share_of_misses(dim, n, resident):
+    """From none to all of the requests missing, which decides how the second launch writes them: small launches, and
+    ones whose workgroups take several units."""
+    rng = np.random.default_rng(dim + n + resident)
+    rows = 2000
+    host = torch.from_numpy(rng.standard_normal((rows, dim)).astype(np.float32)).pin_memory()
+    ids = torch.from_numpy(rng.integers(0, rows, n).astype(np.int32)).cuda()
+    ids[5::97], ids[7::89] = -1, rows
+    table = torch.cat([host.cuda(), torch.zeros((1, dim), device="cuda")])
+    want = table[torch.where((ids >= 0) & (ids < rows), ids.long(), torch.full_like(ids, rows).long())]
+    residents = torch.from_numpy(rng.permutation(rows)[:resident].astype(np.int32))
+    for staging in (2000, 300):
+        c = T.cache_init(host, resident, residents, staging_rows=staging)
+        for mode in (1, 0, 2):
+            T.cache_tune(c, partitioned_gather=mode)
+            buf = torch.full((n * dim + 40,), 7.0, device="cuda")
+            out = T.cache_lookup(c, ids, out=buf[:n * dim].view(n, dim))
+            assert torch.equal(out, want) and bool((buf[n * dim:] == 7.0).all()), (staging, mode)
+        T.cache_free(c)
+
+
 def test_lookup_replays_from_a_hip_graph_with_other_requests():
     rng = np.random.default_rng(3)
     rows, dim, n = 3000, 160, 6000
