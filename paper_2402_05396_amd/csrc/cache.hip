@@ -105,6 +105,27 @@ __global__ __launch_bounds__(kThreads) void fill_kernel(int32_t* a, uint32_t n, 
     if (i < n) a[i] = v;
 }
 
+// Claims the slot at `at` of the miss table for `id`; returns what was there before (kEmpty: now claimed). Called by the
+// active lanes of a wave together; `lanes` is the wave's own scratch. When a launch begins, every wave sees the slot of
+// a popular missing row empty, and swaps on one address run one after the other: of the lanes that name the same row
+// only one swaps, the others take its result. (The lanes meet in scratch at the slot's low bits; one that meets
+// a lane of another row swaps for itself.) 200 000 requests of which a quarter name one missing row: 180 us with a swap per
+// lane, 42 so; 1.33 M requests by a power law, no row resident: 355 and 176.
+__device__ __forceinline__ int32_t claim(int32_t* at, int32_t id, uint32_t slot, uint32_t* lanes) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    lanes[slot & (kWave - 1)] = lane;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS operations complete in order
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t first = lanes[slot & (kWave - 1)];         // an active lane: this one, or another that wrote later
+    const bool follow = __shfl(id, (int)first, kWave) == id && first != lane;
+    int32_t key = kEmpty;
+    if (!follow) key = atomicCAS(at, kEmpty, id);
+    const int32_t of_first = __shfl(key, (int)first, kWave);
+    __builtin_amdgcn_wave_barrier();                          // the scratch is written again by the next call
+    return follow ? of_first : key;
+}
+
 // Grid-stride over the requests; hit/miss counts are summed per block and left in
 // block_tally for the next launch (even one atomic pair per block on the caller's two
 // counters, thousands on one address, took longer than the classification itself).
@@ -113,6 +134,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
     const int32_t* __restrict__ hash_slot, uint32_t hash_mask, int32_t* miss_key, uint32_t miss_size,
     int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count) {
     __shared__ uint32_t block_hits[kThreads / kWave], block_misses[kThreads / kWave];
+    __shared__ uint32_t claim_lane[kThreads / kWave][kWave];
     if (stage_count && blockIdx.x == 0 && threadIdx.x == 0) *stage_count = 0;   // for the staging that follows
     uint32_t hits = 0, misses = 0;
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
@@ -137,7 +159,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
                     uint32_t s = hash_id(id, miss_size - 1);
                     for (int probe = 0; probe < kMaxMissProbes; ++probe) {
                         int32_t key = miss_key[s];
-                        if (key == kEmpty) key = atomicCAS(&miss_key[s], kEmpty, id);
+                        if (key == kEmpty) key = claim(&miss_key[s], id, s, claim_lane[threadIdx.x >> 6]);
                         if (key == kEmpty || key == id) { where = loc_of_stage(s); break; }
                         s = (s + 1) & (miss_size - 1);
                     }
