@@ -267,9 +267,10 @@ int taser_select_weighted(const uint32_t* weight, const int32_t* count, int64_t 
  *   row_bytes    > 0, even; pitch_bytes >= row_bytes, even
  *   ids          int32[n], device; an id >= rows is served like a negative one
  *   out          device, n * row_bytes bytes, must not overlap the table
- * Into a 16-byte aligned `out`, rows of at least 16 bytes (any multiple of 4
- * bytes if size, pitch and table are) move in 16-byte pieces whatever their
- * alignment; otherwise in pieces of the common alignment.
+ * Into a 16-byte aligned `out`, rows whose size, pitch and table are multiples
+ * of 4 bytes move in 16-byte pieces, and so do rows that are only 2-byte aligned
+ * where there are enough bytes for it to pay; otherwise rows move in pieces of
+ * the common alignment.
  * ------------------------------------------------------------------------- */
 int taser_gather_features(const void* table, int64_t rows, int32_t row_bytes,
                           int64_t pitch_bytes, const int32_t* ids, int64_t n, void* out,

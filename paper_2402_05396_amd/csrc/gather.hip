@@ -12,6 +12,7 @@ struct TableSource {
     int64_t pitch_bytes;
     const int32_t* ids;
     int64_t rows;
+    int64_t table_bytes() const { return rows * pitch_bytes; }
     __device__ __forceinline__ int32_t key(int64_t i) const { return ids[i]; }
     __device__ __forceinline__ int32_t resolve(int32_t id) const { return id; }
     __device__ __forceinline__ bool pending(int32_t) const { return false; }
@@ -99,7 +100,9 @@ int taser_launch_gather_parts(const void* table, int64_t rows, int32_t row_bytes
                               int n_parts, hipStream_t stream) {
     const int align = taser_gather::common_alignment((uint64_t)row_bytes | (uint64_t)pitch_bytes | (uint64_t)(uintptr_t)table);
     // one launch where every part's output suits the chunk kernel and all blocks fit
-    bool together = n_parts > 1 && n_parts <= 3 && (align >= 4 || row_bytes >= 16);
+    int64_t n = 0;
+    for (int i = 0; i < n_parts; ++i) n += parts[i].n;
+    bool together = n_parts > 1 && n_parts <= 3 && (align >= 4 || taser_gather::two_byte_chunks_pay(row_bytes, n * row_bytes, rows * pitch_bytes));
     for (int i = 0; i < n_parts; ++i) together = together && parts[i].n > 0 && ((uintptr_t)parts[i].out & 15) == 0;
     if (together) {
         taser_clear_stale_hip_error();

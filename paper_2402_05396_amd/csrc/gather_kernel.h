@@ -12,7 +12,7 @@
 //     whole 128-byte lines.
 //   * gather_elems_kernel: the same flat scheme with one V-wide element (2, 4
 //     or 8 bytes) per thread, for outputs that are not 16-byte aligned and for
-//     2-byte aligned rows shorter than 16 bytes.
+//     2-byte aligned rows where that is faster (see two_byte_chunks_pay).
 // Where a row comes from is a functor, so the kernels serve both a table in
 // device memory and the cache's choice of cache row / staged row / host row.
 #pragma once
@@ -490,6 +490,18 @@ inline bool launch_chunks(const Source& source, int32_t row_bytes, int64_t n, vo
 // Device address of 16 zero bytes (defined once, in gather.hip); nullptr on failure.
 const uint8_t* zero_chunk();
 
+// Rows that are only 2-byte aligned: whether the chunk kernel is faster than an element of 2 bytes per thread. Its blocks
+// write 16 KiB where the other's write 2, so small outputs leave compute units idle; in short rows most pieces cross a
+// row end, which costs two loads from rows that are far apart. Time over the other kernel's, table of 20 000 / 1 M rows:
+// 66-byte rows 1.27 / 1.24 at 1 MiB of output, 0.97 / 0.97 at 4, 0.75 / 0.74 at 16; 2050-byte rows 1.17 / 1.18, 0.89 /
+// 0.89, 0.51 / 0.49; 34-byte rows 1.03 / 0.84 at 7 MB, 0.94 / 1.34 at 34, 0.62 / 1.35 at 136 (the second from 3 M rows, out
+// of cache); 48-byte rows, which no piece crosses, 0.98 / 0.99, 0.79 / 0.77, 0.55 / 0.71.
+inline bool two_byte_chunks_pay(int32_t row_bytes, int64_t out_bytes, int64_t table_bytes) {
+    if (row_bytes >= 32 && row_bytes % 16 == 0) return out_bytes >= (int64_t)1 << 20;
+    if (row_bytes >= 56) return out_bytes >= (int64_t)1 << 22;
+    return row_bytes >= 16 && out_bytes >= (int64_t)1 << 25 && table_bytes <= (int64_t)1 << 22;   // a table that one L2 holds
+}
+
 // `src_align`: power of two dividing the row size, every source pitch and every
 // source base address. Returns false if the launch would need more blocks than
 // a grid dimension holds.
@@ -499,11 +511,12 @@ inline bool launch(const Source& source, int src_align, int32_t row_bytes, int64
     const uint8_t* zeros = zero_chunk();
     if (!zeros) return false;
     const uint64_t out_bits = (uint64_t)(uintptr_t)out;
-    // the chunk kernel wherever its 16-byte pieces apply: an aligned output, and rows that a piece
-    // crosses at most once unless its dword path can follow
+    // the chunk kernel wherever its 16-byte pieces apply (an aligned output, and rows that a piece crosses at most once
+    // unless its dword path can follow) and pay
     if ((out_bits & 15) == 0 && src_align >= 4) return launch_chunks<4, 0>(source, row_bytes, n, out, zeros, stream);
     if constexpr (Source::kAlign < 4)
-        if ((out_bits & 15) == 0 && row_bytes >= 16) return launch_chunks<2, 0>(source, row_bytes, n, out, zeros, stream);
+        if ((out_bits & 15) == 0 && two_byte_chunks_pay(row_bytes, n * row_bytes, source.table_bytes()))
+            return launch_chunks<2, 0>(source, row_bytes, n, out, zeros, stream);
     const int align = common_alignment((uint64_t)src_align | out_bits);
     const int64_t total = n * (int64_t)(row_bytes / align);
     if ((total + kTile - 1) / kTile > 0x7fffffffLL) return false;
