@@ -488,6 +488,7 @@ template <bool NEAR> __device__ __forceinline__ uint32_t delta_of(const ListQuer
 // Sum of the weights of one tile: rows [r0, r1) of 64 entries.
 template <bool NEAR>
 __device__ __forceinline__ uint64_t tile_weight(const ListQuery& q, const uint32_t* __restrict__ low, uint32_t r0, uint32_t r1, int lane) {
+    if (!NEAR && r1 * kWave <= q.ones) return (uint64_t)(r1 - r0) * kWave;   // (uniform) every entry weighs 1
     constexpr int kAhead = 4;    // rows whose loads are in flight together
     uint32_t s = 0;              // weights of at most kSmallWeight
     uint64_t s_big = 0;
