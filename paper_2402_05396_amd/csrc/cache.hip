@@ -86,6 +86,7 @@ struct taser_cache {
     int64_t prefetched_n;
     int stage_blocks;                // width of the host -> staging copy, in 256-thread blocks (0: default_stage_blocks)
     bool refresh_before_gather;      // see rewrite_kernel
+    bool popular_residents;          // at least half of the resident rows were among the most requested of the last counted epoch
     int partitioned_gather;          // gather through gather_owned_lines_kernel where it applies (0 off, 1 on, 2: owners by position only, for measurements)
     std::vector<int32_t>* residents;   // host copy, slot order
     int32_t* resident_dev;             // device copy of the same
@@ -110,7 +111,9 @@ __global__ __launch_bounds__(kThreads) void fill_kernel(int32_t* a, uint32_t n, 
 // a popular missing row empty, and swaps on one address run one after the other: of the lanes that name the same row
 // only one swaps, the others take its result. (The lanes meet in scratch at the slot's low bits; one that meets
 // a lane of another row swaps for itself.) 200 000 requests of which a quarter name one missing row: 180 us with a swap per
-// lane, 42 so; 1.33 M requests by a power law, no row resident: 355 and 176.
+// lane, 42 so; 1.33 M requests by a power law, no row resident: 355 and 176. Where the missing rows are the less
+// popular ones few lanes of a wave meet, and the detour costs more than it saves: 324 000 requests of 1 430 rows, the
+// 429 most requested resident, 25 and 31. So it is taken until an epoch's end has found the residents by their counts.
 __device__ __forceinline__ int32_t claim(int32_t* at, int32_t id, uint32_t slot, uint32_t* lanes) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     lanes[slot & (kWave - 1)] = lane;
@@ -132,7 +135,7 @@ __device__ __forceinline__ int32_t claim(int32_t* at, int32_t id, uint32_t slot,
 __global__ __launch_bounds__(kThreads) void classify_kernel(
     const int32_t* __restrict__ ids, int64_t n, int64_t rows, const int32_t* __restrict__ hash_key,
     const int32_t* __restrict__ hash_slot, uint32_t hash_mask, int32_t* miss_key, uint32_t miss_size,
-    int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count) {
+    int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count, const bool share_claims) {
     __shared__ uint32_t block_hits[kThreads / kWave], block_misses[kThreads / kWave];
     __shared__ uint32_t claim_lane[kThreads / kWave][kWave];
     if (stage_count && blockIdx.x == 0 && threadIdx.x == 0) *stage_count = 0;   // for the staging that follows
@@ -159,7 +162,8 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
                     uint32_t s = hash_id(id, miss_size - 1);
                     for (int probe = 0; probe < kMaxMissProbes; ++probe) {
                         int32_t key = miss_key[s];
-                        if (key == kEmpty) key = claim(&miss_key[s], id, s, claim_lane[threadIdx.x >> 6]);
+                        if (key == kEmpty)
+                            key = share_claims ? claim(&miss_key[s], id, s, claim_lane[threadIdx.x >> 6]) : atomicCAS(&miss_key[s], kEmpty, id);
                         if (key == kEmpty || key == id) { where = loc_of_stage(s); break; }
                         s = (s + 1) & (miss_size - 1);
                     }
@@ -754,7 +758,7 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
         TaserProfileSpan span(stream, "cache_classify");
         hipLaunchKernelGGL(classify_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, ids, n, c->rows,
                            c->hash_key, c->hash_slot, c->hash_mask, c->miss_key, c->miss_size, loc,
-                           counts ? tally : nullptr, c->stage_count);
+                           counts ? tally : nullptr, c->stage_count, !c->popular_residents);
     }
     Service v = {};
     v.miss_key = c->miss_key;
@@ -1050,6 +1054,7 @@ extern "C" int taser_cache_epoch_end(taser_cache* c, int64_t min_overlap, int64_
             c->prefetched_n = 0;
         }
     }
+    c->popular_residents = replace || 2 * both >= k;
     // which of the (new) residents were hot this epoch, then the counters start again
     hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(kThreads), 0, stream, reinterpret_cast<int32_t*>(c->epoch_overlap), 4u, 0);
     hipLaunchKernelGGL(sum_counts_kernel, dim3(row_blocks < 256 ? row_blocks : 256), dim3(kThreads), 0, stream, c->access_count,
