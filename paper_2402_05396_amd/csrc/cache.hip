@@ -78,7 +78,7 @@ struct taser_cache {
     int64_t staging_rows;
     int32_t* miss_key;          // device [miss_size], all kEmpty between lookups
     int32_t* miss_row;          // device [miss_size]: staging row of a claimed slot (-1: the staging area was full)
-    uint32_t* stage_count;      // device [2]: staging rows handed out by the running call; requests that missed (whole lookups)
+    uint32_t* stage_count;      // device [3]: staging rows handed out by the running call; Service::missed
     uint32_t miss_size;         // 0 or a power of two >= 2 * staging_rows
     int32_t* loc;               // device [loc_capacity], per-request outcome
     int64_t loc_capacity;
@@ -216,7 +216,8 @@ struct Service {
     const uint32_t* block_tally;          // hit/miss counts of tally_blocks classify blocks (0: not wanted)
     int tally_blocks;
     unsigned long long* hit_miss;         // the caller's counters, or null
-    uint32_t* missed;                     // the misses of this call alone, or null
+    uint32_t* missed;                     // [2]: the misses of this call alone, whether one row has many of them; or null
+    const int32_t* loc;                   // the call's locations, with `missed`
     const int32_t* ids;                   // access counting
     int64_t n, rows;
     uint32_t* access_count;
@@ -224,7 +225,33 @@ struct Service {
 };
 
 // One block: adds up the per-block counts of the classify launch.
-__device__ __forceinline__ void tally_block(const Service& v) {
+// With `missed`, also whether one missing row is asked for often, from a sample of the requests: then the
+// second launch does not tie rows to partitions (see CacheSource::late_skewed).
+constexpr int kSample = 2048, kSampleSlots = 1024;
+__device__ __forceinline__ void tally_block(const Service& v, int32_t* __restrict__ lds) {
+    if (v.missed) {
+        __shared__ uint32_t most[kThreads / kWave];
+        uint32_t* const seen = reinterpret_cast<uint32_t*>(lds);
+        for (int s = threadIdx.x; s < kSampleSlots; s += kThreads) seen[s] = 0;
+        __syncthreads();
+        for (int s = threadIdx.x; s < kSample; s += kThreads) {
+            const int32_t where = v.loc[(uint64_t)s * (uint64_t)v.n / kSample];
+            if (where < kLocZero && where != kLocHost) atomicAdd(&seen[(uint32_t)(-2 - where) % kSampleSlots], 1u);
+        }
+        __syncthreads();
+        uint32_t m = 0;
+        for (int s = threadIdx.x; s < kSampleSlots; s += kThreads) m = m > seen[s] ? m : seen[s];
+        for (int d = kWave / 2; d > 0; d >>= 1) {
+            const uint32_t other = __shfl_down(m, d, kWave);
+            m = m > other ? m : other;
+        }
+        if ((threadIdx.x & (kWave - 1)) == 0) most[threadIdx.x >> 6] = m;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < kThreads / kWave; ++w) m = m > most[w] ? m : most[w];
+            v.missed[1] = m >= kSample / 64;
+        }
+    }
     __shared__ unsigned long long part[2][kThreads / kWave];
     unsigned long long h = 0, m = 0;
     for (int b = threadIdx.x; b < v.tally_blocks; b += kThreads) {
@@ -248,7 +275,7 @@ __device__ __forceinline__ void tally_block(const Service& v) {
         }
         if (v.hit_miss && h) atomicAdd(&v.hit_miss[0], h);
         if (v.hit_miss && m) atomicAdd(&v.hit_miss[1], m);
-        if (v.missed) *v.missed = m < 0xffffffffull ? (uint32_t)m : 0xffffffffu;
+        if (v.missed) v.missed[0] = m < 0xffffffffull ? (uint32_t)m : 0xffffffffu;
     }
 }
 
@@ -361,14 +388,14 @@ __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, in
     }
 }
 
-static_assert(taser_gather::kBesideWords >= 2 * kTallySlots && taser_gather::tile_rows(4) >= 2 * kTallySlots, "the LDS of run()");
+static_assert(taser_gather::kBesideWords >= kSampleSlots && taser_gather::kBesideWords >= 2 * kTallySlots && taser_gather::tile_rows(4) >= 2 * kTallySlots, "the LDS of run()");
 __device__ __forceinline__ void Service::run(uint32_t block, int32_t* lds) const {
     if ((int)block < stage_blocks) {
         stage_block(*this, block, lds);
         return;
     }
     int own = (int)block - stage_blocks;
-    if (tally_blocks && own-- == 0) tally_block(*this);
+    if (tally_blocks && own-- == 0) tally_block(*this, lds);
     else if (own < count_blocks) count_block(*this, own, lds);
 }
 
@@ -427,8 +454,9 @@ struct CacheSource {
     int owner_mode;   // 1: by source row; 2: by position only
     const int32_t* miss_row;
     __device__ __forceinline__ int32_t key(int64_t i) const { return loc[i]; }
-    const uint32_t* missed;   // requests that missed (whole lookups only)
-    __device__ __forceinline__ uint32_t late() const { return *missed; }
+    const uint32_t* missed;   // [2]: requests that missed, whether one row has many of them (whole lookups only)
+    __device__ __forceinline__ uint32_t late() const { return missed[0]; }
+    __device__ __forceinline__ bool late_skewed() const { return missed[1] != 0; }
     // a missed row, on its way while the staging runs
     __device__ __forceinline__ bool pending(int32_t where) const { return where < kLocZero; }
     // from miss-table slot to staging row, once that is known
@@ -735,7 +763,7 @@ extern "C" int taser_cache_init(const void* host_table, int64_t rows, int32_t ro
         CACHE_TRY(hipMalloc((void**)&c->stage_rows, (size_t)staging_rows * c->dev_pitch));
         CACHE_TRY(hipMalloc((void**)&c->miss_key, (size_t)c->miss_size * sizeof(int32_t)));
         CACHE_TRY(hipMalloc((void**)&c->miss_row, (size_t)c->miss_size * sizeof(int32_t)));
-        CACHE_TRY(hipMalloc((void**)&c->stage_count, 2 * sizeof(uint32_t)));
+        CACHE_TRY(hipMalloc((void**)&c->stage_count, 3 * sizeof(uint32_t)));
         hipLaunchKernelGGL(fill_kernel, dim3((c->miss_size + kThreads - 1) / kThreads), dim3(kThreads), 0, stream,
                            c->miss_key, c->miss_size, kEmpty);
         hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(kThreads), 0, stream, reinterpret_cast<int32_t*>(c->stage_count), 1u, 0);
@@ -774,6 +802,7 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     v.block_tally = tally;
     v.tally_blocks = counts ? (int)blocks : 0;
     v.missed = count_misses ? c->stage_count + 1 : nullptr;
+    v.loc = loc;
     v.hit_miss = reinterpret_cast<unsigned long long*>(hit_miss);
     v.ids = ids;
     v.n = n;

@@ -63,7 +63,8 @@ template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) 
 // gather in one launch. For that a Source also has
 //   pending(key)    the row is on its way during PHASE 1;
 //   resolve(key)    the token for PHASES 0 and 2 (PHASE 1 takes it as it is read);
-//   late()          how many output rows PHASE 2 has to write (at most 2^32 - 1 of them counted).
+//   late()          how many output rows PHASE 2 has to write (at most 2^32 - 1 of them counted);
+//   late_skewed()   many of them are copies of the same source row.
 
 template <int PHASE, typename Source> __device__ __forceinline__ int32_t source_token(const Source& source, int64_t i) {
     const int32_t key = source.key(i);
@@ -245,8 +246,8 @@ constexpr int kOwnerClasses = 8;
 //   * From kWholeShare on: the whole output is written once more as in PHASE 0, every line once and by its class.
 //     1.33 M rows of 1652 bytes, lookups with all, 90, 80, 70 % of the rows late, requests without skew: 1.25, 1.12,
 //     1.00, 0.88 ms writing the late ones only, 1.05, 0.98, 0.92, 0.87 writing all (1.02, 0.95, 0.89, 0.84 in PHASE 0
-//     after the staging); with requests by a power law, rows read again and again by every partition anyhow, 1.31, 1.00
-//     (94 %), 0.88 (83 %), 0.77 (68 %) and 1.33, 1.06, 0.98, 0.95 (1.37, 1.05, 0.99, 0.94).
+//     after the staging). Not where a popular row is late: its class has more to do than the others, and every partition
+//     has it in its L2 anyhow (power-law requests, 83 % late: 0.88 ms the late ones only, 0.98 all).
 constexpr uint32_t kOwnedLateBlocks = 4096;
 constexpr double kWholeShare = 0.78;
 constexpr int kLateUnits = 4;             // per workgroup; with one each, 90 000 empty ones cost a lookup without misses 11 us
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
     if constexpr (PHASE == 2) {
         const uint32_t late = source.late();
         if (late == 0) return;
-        only_late = late < g.whole_from;
+        only_late = late < g.whole_from || source.late_skewed();
         if (only_late) classes = g.late_classes;
         units = classes * g.tiles;
         if (block >= units) return;
