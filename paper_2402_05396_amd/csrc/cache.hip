@@ -217,7 +217,7 @@ struct Service {
     int tally_blocks;
     unsigned long long* hit_miss;         // the caller's counters, or null
     uint32_t* missed;                     // [2]: the misses of this call alone, whether one row has many of them; or null
-    const int32_t* loc;                   // the call's locations, with `missed`
+    const int32_t* loc;                   // the call's locations where missed[1] is wanted, else null
     const int32_t* ids;                   // access counting
     int64_t n, rows;
     uint32_t* access_count;
@@ -225,11 +225,11 @@ struct Service {
 };
 
 // One block: adds up the per-block counts of the classify launch.
-// With `missed`, also whether one missing row is asked for often, from a sample of the requests: then the
-// second launch does not tie rows to partitions (see CacheSource::late_skewed).
+// With `loc`, also whether one missing row is asked for often, from a sample of the requests: then the second
+// launch does not tie rows to partitions (see CacheSource::late_skewed).
 constexpr int kSample = 2048, kSampleSlots = 1024;
 __device__ __forceinline__ void tally_block(const Service& v, int32_t* __restrict__ lds) {
-    if (v.missed) {
+    if (v.loc) {
         __shared__ uint32_t most[kThreads / kWave];
         uint32_t* const seen = reinterpret_cast<uint32_t*>(lds);
         for (int s = threadIdx.x; s < kSampleSlots; s += kThreads) seen[s] = 0;
@@ -802,7 +802,6 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     v.block_tally = tally;
     v.tally_blocks = counts ? (int)blocks : 0;
     v.missed = count_misses ? c->stage_count + 1 : nullptr;
-    v.loc = loc;
     v.hit_miss = reinterpret_cast<unsigned long long*>(hit_miss);
     v.ids = ids;
     v.n = n;
@@ -890,6 +889,7 @@ static int enqueue_lookup(taser_cache* c, const int32_t* ids, int64_t n, void* o
     const CacheSource source = source_of(c, ids, loc);
     Service v;
     enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, true, &v);
+    if (owned) v.loc = loc;
     bool launched;
     {
         // the gather's blocks are behind the service blocks, so the staging starts first and its few blocks
