@@ -103,7 +103,7 @@ int taser_tcsr_build(const int32_t* src, const int32_t* dst, const int64_t* ts,
  * than sorting them). taser_tcsr_build_bytes says how many bytes a build with
  * these sizes and flags needs (either out-pointer may be NULL): `storage` is what
  * the graph lives in until taser_tcsr_free, `scratch` is free again when
- * taser_tcsr_build_in returns. Both 256-byte aligned, contents arbitrary, on the
+ * taser_tcsr_build_in returns (both are if it returns an error). Both 256-byte aligned, contents arbitrary, on the
  * current device, and not in use by work that `hip_stream` is not ordered after.
  * taser_tcsr_free of such a graph waits for the whole device (as freeing device
  * memory does) and leaves the storage to the caller. Errors: those of

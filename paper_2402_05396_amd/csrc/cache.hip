@@ -21,7 +21,8 @@
 //      They wait for the bus; the others meanwhile write all output that needs
 //      only resident (or zero) rows;
 //   3. the rest of the output: rows that were staged, or straight from host memory
-//      for requests that found the miss table or the staging area full.
+//      for requests that found the miss table or the staging area full (or, where
+//      most requests missed, the whole output: see PHASE 2 in gather_kernel.h).
 // taser_cache_prefetch is 1 and the staging blocks of 2 alone, taser_cache_gather
 // the whole output in one launch; a caller that has other work for the time of the
 // staging takes those.

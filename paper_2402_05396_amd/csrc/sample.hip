@@ -19,6 +19,8 @@
 //     pure function of the inputs, independent of scheduling;
 //   * weighted selection keeps the candidate window in registers (one lane per
 //     candidate) and uses integer prefix sums across the group's lanes;
+//   * large hops of the most-recent finder search with four lanes per root and
+//     hand out the slots of a wave's 16 roots flat (see quads_pay);
 //   * the inverse-timespan finder, whose weights depend on the query time, reads
 //     the whole valid list with a block per root (see its kernel).
 #include <mutex>
