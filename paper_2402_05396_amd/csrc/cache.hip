@@ -114,7 +114,9 @@ __global__ __launch_bounds__(kThreads) void fill_kernel(int32_t* a, uint32_t n, 
 // a lane of another row swaps for itself.) 200 000 requests of which a quarter name one missing row: 180 us with a swap per
 // lane, 42 so; 1.33 M requests by a power law, no row resident: 355 and 176. Where the missing rows are the less
 // popular ones few lanes of a wave meet, and the detour costs more than it saves: 324 000 requests of 1 430 rows, the
-// 429 most requested resident, 25 and 31. So it is taken until an epoch's end has found the residents by their counts.
+// 429 most requested resident, 25 and 31. So it is taken until an epoch's end has found the residents by their counts,
+// and where at most three quarters of the rows are resident (else few can be missing: 600 000 requests, nine tenths of
+// the rows resident, a whole lookup 145 and 160).
 __device__ __forceinline__ int32_t claim(int32_t* at, int32_t id, uint32_t slot, uint32_t* lanes) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     lanes[slot & (kWave - 1)] = lane;
@@ -787,7 +789,8 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
         TaserProfileSpan span(stream, "cache_classify");
         hipLaunchKernelGGL(classify_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, ids, n, c->rows,
                            c->hash_key, c->hash_slot, c->hash_mask, c->miss_key, c->miss_size, loc,
-                           counts ? tally : nullptr, c->stage_count, !c->popular_residents);
+                           counts ? tally : nullptr, c->stage_count,
+                           !c->popular_residents && 4 * c->capacity <= 3 * c->rows);
     }
     Service v = {};
     v.miss_key = c->miss_key;
