@@ -208,6 +208,10 @@ def tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream=None):
     n, on_dev = _entries(src, dst, ts, eid)
     _want(storage, torch.uint8, "storage")
     _want(scratch, torch.uint8, "scratch")
+    return _build_in(src, dst, ts, eid, n, on_dev, num_nodes, storage, scratch, stream)
+
+
+def _build_in(src, dst, ts, eid, n, on_dev, num_nodes, storage, scratch, stream):
     h = ctypes.c_void_p()
     _check(lib().taser_tcsr_build_in(_ptr(src), _ptr(dst), _ptr(ts), _ptr(eid), n, num_nodes,
                                      INPUT_ON_DEVICE if on_dev else 0, _stream(stream), _ptr(storage), storage.numel(),
@@ -228,7 +232,7 @@ def tcsr_build(src, dst, ts, eid, num_nodes, stream=None):
             storage, scratch = (torch.empty(b, dtype=torch.uint8, device="cuda") for b in sizes)
     except torch.OutOfMemoryError as e:
         raise TaserError(-3, f"tcsr_build: {e}") from e
-    return tcsr_build_in(src, dst, ts, eid, num_nodes, storage, scratch, stream)
+    return _build_in(src, dst, ts, eid, n, on_dev, num_nodes, storage, scratch, stream)
 
 
 def tcsr_size(g):
