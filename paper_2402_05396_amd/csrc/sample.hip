@@ -21,8 +21,8 @@
 //     candidate) and uses integer prefix sums across the group's lanes;
 //   * large hops of the most-recent finder search with four lanes per root and
 //     hand out the slots of a wave's 16 roots flat (see quads_pay);
-//   * the inverse-timespan finder, whose weights depend on the query time, reads
-//     the whole valid list with a block per root (see its kernel).
+//   * the inverse-timespan finder, whose weights depend on the query time, sums
+//     the whole valid list, by entries or by weights (see its kernel).
 #include <mutex>
 
 #include "gather_kernel.h"
@@ -438,48 +438,65 @@ __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
 // delta > kLastLargeDelta, so the quotient is at most kSmallWeight. A single-precision reciprocal is off by
 // less than 2^-22 of the quotient (conversion, v_rcp_f32's one unit in the last place, the product); scaled
 // down by 2^-21 it gives the quotient or one less, and the exact remainder says which. NEAR: delta < 2^24,
-// where the product for the remainder is one full-rate 24-bit multiply and the quotient at least 256.
+// where the quotient is at least 256 and one full-rate 24-bit multiply-add does for the remainder.
 constexpr uint32_t kLastLargeDelta = 65536;      // its quotient is 2^16 itself: with it a tile of ties would sum to 2^32
 constexpr uint32_t kSmallWeight = (uint32_t)(((uint64_t)1 << 32) / (kLastLargeDelta + 1));
 static_assert(kSmallWeight == 65535, "the quotient of every larger delta is below 2^16");
 template <bool NEAR> __device__ __forceinline__ uint32_t quotient_of_delta(uint32_t delta) {
     const uint32_t q = (uint32_t)(4294967296.0f * (1.0f - 4.76837158203125e-7f) * __builtin_amdgcn_rcpf((float)delta));
-    const uint32_t rest = 0u - (NEAR ? __umul24(q, delta) : q * delta);   // 2^32 - q delta, below 2 delta; wraps only for delta > 2^31
+    if (NEAR) return q + ((int32_t)(__umul24(q, delta) + delta) <= 0 ? 1u : 0u);   // (q + 1) delta is at most 2^32 (it is within delta of it)
+    const uint32_t rest = 0u - q * delta;                                 // 2^32 - q delta, below 2 delta; wraps only for delta > 2^31
     const uint32_t w = q + (rest >= delta ? 1u : 0u);
-    return NEAR ? w : w > 1u ? w : 1u;                                    // (where the quotient is 1 in any case)
+    return w > 1u ? w : 1u;                                               // (where the quotient is 1 in any case)
 }
-// Any delta >= 1.
+// Any delta >= 1; the quotient has up to 33 bits. The first estimate is at most 2^-20 of it too small (or one,
+// where that is less), so that the remainder is below 2^13 + 2 delta; the remainder's own quotient, found the same
+// way, is exact or one too small.
 __device__ __forceinline__ uint64_t weight_of_delta(uint32_t delta) {
-    if (delta > kLastLargeDelta) return quotient_of_delta<false>(delta);
-    const uint32_t q = 0xFFFFFFFFu / delta, r = 0xFFFFFFFFu - q * delta;   // 2^32 = (2^32 - 1) + 1
-    return (uint64_t)q + (r == delta - 1u ? 1u : 0u);
+    const float r = (1.0f - 4.76837158203125e-7f) * __builtin_amdgcn_rcpf((float)delta);
+    const uint32_t q = (uint32_t)(4294967296.0f * r);
+    const uint32_t rest = 0u - q * delta;                 // 2^32 - q delta; wraps only for delta > 2^31 (q == 0)
+    const uint32_t more = (uint32_t)((float)rest * r), left = rest - more * delta;
+    const uint64_t w = (uint64_t)q + (more + (left >= delta ? 1u : 0u));
+    return w > 1u ? w : 1u;
 }
 
-constexpr int kTileRegs = 8;                      // registers of tile sums per lane
-constexpr int kMaxTiles = kTileRegs * kWave;      // tile sums per root
+constexpr int kMaxTiles = 4 * kWave;              // tile sums per root
+constexpr int kSamples = 512;                     // of a far part, per root
 constexpr int kListThreads = 256;                 // block of the finder that reads whole lists
 constexpr int kListWaves = kListThreads / kWave;
 
-// Where weights of at most kSmallWeight may be summed in 32 bits: per lane over the rows of any tile (a list
-// has fewer than 2^31 entries), over a whole wave up to kWaveSumRows rows.
-constexpr uint64_t kMostTileRows = (((uint64_t)1 << 31) / kWave + kMaxTiles - 1) / kMaxTiles;
-constexpr uint32_t kWaveSumRows = 1024;
-static_assert(kMostTileRows * kSmallWeight < ((uint64_t)1 << 32), "a lane's sum");
-static_assert((uint64_t)kWaveSumRows * kWave * kSmallWeight < ((uint64_t)1 << 32), "a wave's sum");
+constexpr int kMostNearTiles = kMaxTiles / 2, kMostFarTiles = kMaxTiles - kMostNearTiles;
 
-// What the whole block knows about its root.
+// What is known about a root. Its valid entries are cut into a far part, [0, first), whose weights are below
+// w_end, and a near part, [first, cnt). The far part is described by its weights: the entries of weight w are
+// one run of the list, found by a search, so that a lane's work is a weight and not an entry. The near part is
+// read entry by entry, in rows of 64.
 struct ListQuery {
     uint32_t lo, cnt;            // its list begins at record lo; cnt valid entries
     uint32_t ones;               // entries [0, ones) are 2^32 or more before the query
     uint32_t t_low;              // low word of the query time
-    uint32_t rows_per_tile, tiles;
-    uint32_t near;               // every delta is below 2^24 (then ones == 0)
+    uint32_t first;              // first entry of the near part
+    uint32_t tile_shift;         // near part: log2 of the rows of a tile
+    uint32_t stride;             // far part: entries between two samples
+    uint32_t alone;              // one wavefront's work
+    uint32_t w_first, w_end;     // far part: weight of the list's first entry, and the first weight of the near part
+    uint32_t batches;            // batches of kBatch weights per far tile
+    uint32_t far_tiles, tiles;   // far tiles come first
+    uint32_t k;                  // the call's
+    uint32_t near;               // every delta of the near part is below 2^24 (then none of it is among the `ones`)
 };
+struct __attribute__((packed, aligned(4))) Low4 {
+    uint32_t w[4];
+};
+constexpr uint32_t kBatch = kWave - 1;   // weights of a far batch: the last lane only says where the last run ends
 
 // A query as the whole wave read it from LDS, in scalar registers.
 __device__ __forceinline__ ListQuery uniform(const ListQuery& v) {
     auto get = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
-    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.rows_per_tile), get(v.tiles), get(v.near)};
+    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.first), get(v.tile_shift), get(v.stride), get(v.alone),
+                     get(v.w_first), get(v.w_end),
+                     get(v.batches), get(v.far_tiles), get(v.tiles), get(v.k), get(v.near)};
 }
 
 // delta of entry p (its low word loaded as `low`), 0xFFFFFFFF (weight 1) for the first `ones`.
@@ -487,57 +504,142 @@ template <bool NEAR> __device__ __forceinline__ uint32_t delta_of(const ListQuer
     return !NEAR && p < q.ones ? 0xFFFFFFFFu : q.t_low - low;
 }
 
-// Sum of the weights of one tile: rows [r0, r1) of 64 entries.
-template <bool NEAR>
-__device__ __forceinline__ uint64_t tile_weight(const ListQuery& q, const uint32_t* __restrict__ low, uint32_t r0, uint32_t r1, int lane) {
-    if (!NEAR && r1 * kWave <= q.ones) return (uint64_t)(r1 - r0) * kWave;   // (uniform) every entry weighs 1
-    constexpr int kAhead = 4;    // rows whose loads are in flight together
-    uint32_t s = 0;              // weights of at most kSmallWeight
-    uint64_t s_big = 0;
-    bool big = false;
-    for (uint32_t r = r0; r < r1; r += kAhead) {
-        uint32_t v[kAhead];
-#pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-            const uint32_t p = (r + i) * kWave + lane;
-            v[i] = low[p < q.cnt ? p : q.cnt - 1u];
-        }
-#pragma unroll
-        for (int i = 0; i < kAhead; ++i) {
-            const uint32_t p = (r + i) * kWave + lane;
-            const uint32_t delta = delta_of<NEAR>(q, p, v[i]);
-            const bool valid = p < q.cnt;
-            if (r + i >= r1) {                               // (uniform, like the next)
-            } else if (!__ballot(delta <= kLastLargeDelta)) {
-                const uint32_t w = quotient_of_delta<NEAR>(delta);
-                s += valid ? w : 0u;
-            } else {
-                big = true;
-                s_big += valid ? weight_of_delta(delta) : 0u;
-            }
-        }
-    }
-    if (!big && r1 - r0 <= kWaveSumRows) return wave_sum32(s);   // (uniform)
-    return wave_sum64(s_big + s);
+// What a wave wrote to LDS for itself alone can be read by its other lanes: its LDS operations complete in order.
+__device__ __forceinline__ void own_lds_ready() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Row r of the list, entries picked by the draws before number j left out (lane e of my_pick: draw e's
+// The sums over the wave of eight 32-bit values per lane, value l % 8 in lane l: three exchanges in which a lane
+// keeps half of its values and adds the other lane's half of the same ones, then the eighths of the wave.
+__device__ __forceinline__ uint32_t wave_sums_of_8(const uint32_t (&a)[8], int lane) {
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    uint32_t b[4], c[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        b[i] = (b0 ? a[2 * i + 1] : a[2 * i]) +
+               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b0 ? a[2 * i] : a[2 * i + 1]), 0xB1, 0xf, 0xf, true);   // quad_perm [1, 0, 3, 2]
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        c[i] = (b1 ? b[2 * i + 1] : b[2 * i]) +
+               (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(b1 ? b[2 * i] : b[2 * i + 1]), 0x4E, 0xf, 0xf, true);   // quad_perm [2, 3, 0, 1]
+    const int give = (int)(b2 ? c[0] : c[1]);
+    int got = __builtin_amdgcn_update_dpp(0, give, 0x104, 0xf, 0x5, false);   // row_shl:4 into the banks below,
+    got = __builtin_amdgcn_update_dpp(got, give, 0x114, 0xf, 0xA, false);     // row_shr:4 into those above
+    uint32_t d = (b2 ? c[1] : c[0]) + (uint32_t)got;
+    d += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)d, 0x128, 0xf, 0xf, true);   // row_ror:8
+    d += __shfl_xor(d, 16, kWave);
+    d += __shfl_xor(d, 32, kWave);
+    return d;
+}
+// The same, added up over every 2^shift (at most 8) neighboring values: correct in lanes whose low `shift` bits are 0.
+__device__ __forceinline__ uint64_t tile_sums_of_8(const uint32_t (&a)[8], uint32_t shift, int lane) {
+    uint64_t s = wave_sums_of_8(a, lane);
+    for (uint32_t i = 0; i < shift; ++i) s += __shfl_xor(s, 1 << i, kWave);
+    return s;
+}
+
+// A row whose deltas are this large has a sum below 2^32.
+constexpr uint32_t kRowSumDelta = 128;
+static_assert((((uint64_t)1 << 32) / kRowSumDelta) * kWave < ((uint64_t)1 << 32), "a row's sum");
+
+// Sums of the near part's tiles, by units of kGroup rows (or of one tile, where that is more): units
+// first, first + step, ... The rows of a group are loaded together.
+constexpr uint32_t kGroup = 8;
+template <bool NEAR>
+__device__ __forceinline__ void sum_near_tiles(const ListQuery& q, const uint32_t* __restrict__ low, uint32_t first, uint32_t step,
+                                               uint64_t* tile_sum, int lane) {
+    const uint32_t rows = (q.cnt - q.first + kWave - 1) / kWave, per = 1u << q.tile_shift;
+    const uint32_t unit = per < kGroup ? kGroup : per;
+    for (uint32_t u0 = first * unit; u0 < rows; u0 += step * unit) {
+        uint64_t sum = 0;        // of a tile of more than a group
+        const uint32_t u1 = u0 + unit < rows ? u0 + unit : rows;
+        for (uint32_t r = u0; r < u1; r += kGroup) {
+            const uint32_t p0 = q.first + r * kWave;
+            uint32_t v[kGroup];
+            const bool whole = p0 + kGroup * kWave <= q.cnt;
+            if (whole) {
+                const uint32_t* at = low + p0 + (uint32_t)lane;
+#pragma unroll
+                for (uint32_t i = 0; i < kGroup; ++i) v[i] = at[i * kWave];
+            } else {
+#pragma unroll
+                for (uint32_t i = 0; i < kGroup; ++i) {
+                    const uint32_t p = p0 + i * kWave + (uint32_t)lane;
+                    v[i] = r + i < u1 ? low[p < q.cnt ? p : q.cnt - 1u] : 0u;   // (uniform) a row that there is
+                }
+            }
+            // (uniform) the last deltas are the smallest; half rows and rows with sums beyond 32 bits take the last path
+            const uint32_t least = delta_of<NEAR>(q, p0 + (kGroup - 1) * kWave + (uint32_t)lane, v[kGroup - 1]);
+            bool split = false;
+            uint32_t high[kGroup];       // of a weight, above its low 16 bits
+            if (whole && !__ballot(least <= kLastLargeDelta)) {
+#pragma unroll
+                for (uint32_t i = 0; i < kGroup; ++i) v[i] = quotient_of_delta<NEAR>(delta_of<NEAR>(q, p0 + i * kWave + (uint32_t)lane, v[i]));
+            } else if (whole && !__ballot(least < kRowSumDelta)) {
+#pragma unroll
+                for (uint32_t i = 0; i < kGroup; ++i) v[i] = (uint32_t)weight_of_delta(delta_of<NEAR>(q, p0 + i * kWave + (uint32_t)lane, v[i]));
+            } else {
+#pragma unroll
+                for (uint32_t i = 0; i < kGroup; ++i) {
+                    uint32_t w_low = 0, w_high = 0;
+                    if (r + i < u1) {    // uniform, like the next
+                        const uint32_t p = p0 + i * kWave + (uint32_t)lane, delta = delta_of<NEAR>(q, p, v[i]);
+                        const bool valid = p < q.cnt;
+                        if (__ballot(valid && delta <= kLastLargeDelta)) {
+                            split = true;
+                            const uint64_t w = weight_of_delta(delta);
+                            w_low = valid ? (uint32_t)w & 0xffffu : 0u;
+                            w_high = valid ? (uint32_t)(w >> 16) : 0u;
+                        } else {
+                            const uint32_t w = quotient_of_delta<NEAR>(delta);
+                            w_low = valid ? w : 0u;
+                        }
+                    }
+                    v[i] = w_low;
+                    high[i] = w_high;
+                }
+            }
+            if (per <= kGroup) {         // whole tiles: rows' sums in the lanes, then the tiles'
+                uint64_t s = tile_sums_of_8(v, q.tile_shift, lane);
+                if (split) s += tile_sums_of_8(high, q.tile_shift, lane) << 16;
+                if ((uint32_t)lane < u1 - r && (uint32_t)lane < kGroup && ((uint32_t)lane & (per - 1u)) == 0)
+                    tile_sum[q.far_tiles + ((r + (uint32_t)lane) >> q.tile_shift)] = s;
+            } else {
+                uint64_t s = 0;          // eight weights below 2^26 each: 64 lanes of them do not fit 32 bits
+                uint32_t lane_sum = 0;
+#pragma unroll
+                for (uint32_t i = 0; i < kGroup; ++i) lane_sum += v[i];
+                s = (uint64_t)wave_sum32(lane_sum & 0xffffu) + ((uint64_t)wave_sum32(lane_sum >> 16) << 16);
+                if (split) {
+                    uint32_t h = 0;      // 8 x 2^17 per lane
+#pragma unroll
+                    for (uint32_t i = 0; i < kGroup; ++i) h += high[i];
+                    s += (uint64_t)wave_sum32(h) << 16;
+                }
+                sum += s;
+            }
+        }
+        if (per > kGroup && lane == 0) tile_sum[q.far_tiles + (u0 >> q.tile_shift)] = sum;
+    }
+}
+
+// Row r of the near part, entries picked by the draws before number j left out (lane e of my_pick: draw e's
 // entry): finds the first entry whose running sum, `before` it included, exceeds x.
 // Returns its lane and its weight, or -1 and adds the row's sum to `before`.
-template <bool NEAR>
 __device__ __forceinline__ int pick_in_row(const ListQuery& q, uint32_t low, uint32_t r, uint64_t x, uint64_t& before, int j,
                                            uint32_t my_pick, int lane, uint64_t& pick_w) {
-    const uint32_t p = r * kWave + lane;
-    const uint32_t delta = delta_of<NEAR>(q, p, low);
-    const bool small = !__ballot(delta <= kLastLargeDelta);  // uniform: a row's sum is below 2^22
+    const uint32_t p0 = q.first + r * kWave, p = p0 + lane;
+    const uint32_t delta = delta_of<false>(q, p, low);
     bool valid = p < q.cnt;
-    for (uint64_t taken = __ballot(lane < j && my_pick / kWave == r); taken; taken &= taken - 1) {
+    for (uint64_t taken = __ballot(lane < j && my_pick - p0 < (uint32_t)kWave); taken; taken &= taken - 1) {
         const uint32_t gone = (uint32_t)__builtin_amdgcn_readlane((int)my_pick, __ffsll((long long)taken) - 1);
         if (p == gone) valid = false;
     }
     const uint64_t rest = x - before;                        // x >= before
-    if (small) {
-        const uint32_t w = valid ? quotient_of_delta<NEAR>(delta) : 0u;
+    if (!__ballot(delta < kRowSumDelta)) {                   // (uniform)
+        const uint32_t w = valid ? (uint32_t)weight_of_delta(delta) : 0u;
         const uint32_t inc = wave_inclusive_scan32(w);
         const uint64_t hit = __ballot((uint64_t)inc > rest);
         if (hit) {
@@ -560,102 +662,269 @@ __device__ __forceinline__ int pick_in_row(const ListQuery& q, uint32_t low, uin
     return -1;
 }
 
-// The k successive draws of one root, by one wavefront. The tile sums become one running sum over all
-// tiles, kept in registers (tile i in lane i % 64, register i / 64): a draw compares it with x, re-reads
-// only the tile it lands in, and the pick's weight leaves every running sum from its tile on, which is
-// what summing the remaining weights again would give. Lane j returns draw j's entry.
-template <bool NEAR>
-__device__ __forceinline__ uint32_t draw_entries(const ListQuery& q, const uint32_t* __restrict__ low, const uint64_t* tile_sum, int k,
-                                                 uint64_t u, int lane) {
-    const uint32_t rows = (q.cnt + kWave - 1) / kWave;
-    const int regs = (int)((q.tiles + kWave - 1) / kWave);   // registers in use
-    uint64_t run[kTileRegs];
-    uint64_t total = 0;
+// Far part: where the entries of weight w and more begin, that is how many entries have a delta above
+// floor(2^32 / w). w_first is the weight of entry 0. The samples (the deltas of every stride-th entry, in LDS) say between
+// which two, the list itself the rest: three probes a step, sixteen neighbors in the last. Probes behind the far
+// part read an entry of the near part or the list's last one, which is not above unless the whole list is.
+__device__ __forceinline__ uint32_t run_begin(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t w) {
+    const uint32_t most = (uint32_t)weight_of_delta(w < 2u ? 2u : w < kLastLargeDelta ? w : kLastLargeDelta);   // floor(2^32 / w)
+    uint32_t at = 0;
 #pragma unroll
-    for (int i = 0; i < kTileRegs; ++i) {
-        run[i] = 0;
-        if (i < regs) {
-            const uint32_t tile = i * kWave + lane;
-            run[i] = total + wave_inclusive_scan64(tile < q.tiles ? tile_sum[tile] : 0);
-            total = wave_get64(run[i], kWave - 1);
+    for (uint32_t half = kSamples / 2; half > 0; half /= 2)
+        if (sample[at + half - 1u] > most) at += half;
+    at = q.ones + at * q.stride;             // one sample is left out: the last one stands for the end of the far part
+    for (uint32_t len = q.stride; len > 16u;) {
+        const uint32_t part = (len + 3u) / 4u;
+        uint32_t v[3];
+#pragma unroll
+        for (uint32_t i = 0; i < 3; ++i) {
+            const uint32_t p = at + (i + 1u) * part - 1u;
+            v[i] = low[p < q.cnt ? p : q.cnt - 1u];
         }
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 3; ++i) c += q.t_low - v[i] > most ? 1u : 0u;
+        at += c * part;
+        len = part;
+    }
+    if (at > q.cnt - 16u) at = q.cnt - 16u;  // (a list with a far part has kFarEntries entries and more)
+    const Low4* p = reinterpret_cast<const Low4*>(low + at);
+    Low4 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = p[i];
+    uint32_t d[16];                          // the neighbors, halved in registers
+#pragma unroll
+    for (int i = 0; i < 16; ++i) d[i] = v[i / 4].w[i % 4];
+    uint32_t c = 0;
+#pragma unroll
+    for (int half = 8; half > 0; half /= 2) {
+        const uint32_t upper = q.t_low - d[half - 1] > most ? 0xFFFFFFFFu : 0u;   // a mask, or the selects become searches for an index
+        c += upper & (uint32_t)half;
+#pragma unroll
+        for (int i = 0; i < half; ++i) d[i] = (upper & d[half + i]) | (~upper & d[i]);
+    }
+    at += c + (q.t_low - d[0] > most ? 1u : 0u);
+    return w <= q.w_first ? 0u : w >= q.w_end || at > q.first ? q.first : at;
+}
+
+// The runs of one batch of a far tile: lane l < kBatch has the entries [begin, end) of weight w.
+struct Runs {
+    uint32_t w, begin, end;
+};
+__device__ __forceinline__ Runs far_runs(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t batch, int lane) {
+    Runs r;
+    r.w = q.w_first + batch * kBatch + (uint32_t)lane;
+    r.begin = run_begin(q, low, sample, r.w);
+    r.end = __shfl_down(r.begin, 1, kWave);
+    if (lane == kWave - 1) r.end = r.begin;
+    return r;
+}
+
+__device__ __forceinline__ uint64_t far_tile_weight(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t tile, int lane) {
+    uint64_t s = 0;
+    #pragma unroll 1
+    for (uint32_t b = tile * q.batches; b < (tile + 1u) * q.batches; ++b) {
+        const Runs r = far_runs(q, low, sample, b, lane);
+        s += (uint64_t)(r.end - r.begin) * r.w;
+    }
+    return wave_sum64(s);
+}
+
+// As pick_in_row, for a whole far tile: returns the entry.
+__device__ __forceinline__ uint32_t pick_in_far_tile(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t tile,
+                                                     uint64_t x, uint64_t before, int j, uint32_t my_pick, int lane, uint64_t& pick_w) {
+    #pragma unroll 1
+    for (uint32_t b = tile * q.batches; b < (tile + 1u) * q.batches; ++b) {
+        const Runs r = far_runs(q, low, sample, b, lane);
+        uint32_t left = r.end - r.begin;
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)r.begin, 0), b1 = (uint32_t)__builtin_amdgcn_readlane((int)r.begin, kWave - 1);
+        for (uint64_t taken = __ballot(lane < j && my_pick >= b0 && my_pick < b1); taken; taken &= taken - 1) {
+            const uint32_t gone = (uint32_t)__builtin_amdgcn_readlane((int)my_pick, __ffsll((long long)taken) - 1);
+            if (gone >= r.begin && gone < r.end) --left;
+        }
+        const uint64_t inc = wave_inclusive_scan64((uint64_t)left * r.w);
+        const uint64_t hit = __ballot(inc > x - before);
+        if (hit) {
+            const int at = __ffsll((long long)hit) - 1;
+            const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)r.w, at);
+            const uint32_t begin = (uint32_t)__builtin_amdgcn_readlane((int)r.begin, at);
+            const uint64_t rest = x - before - (at ? wave_get64(inc, at - 1) : 0);
+            const uint32_t nth = (rest >> 32) ? (uint32_t)(rest / w) : (uint32_t)rest / w;   // of the run's entries that are left
+            uint32_t pick = begin + nth;
+            for (;;) {   // ends: pick only grows, and is at most begin + nth + j
+                const uint32_t skipped = (uint32_t)__popcll(__ballot(lane < j && my_pick >= begin && my_pick <= pick));
+                if (begin + nth + skipped == pick) break;
+                pick = begin + nth + skipped;
+            }
+            pick_w = w;
+            return pick;
+        }
+        before += wave_get64(inc, kWave - 1);
+    }
+    return q.cnt - 1u;   // (never while the sums are consistent)
+}
+
+// The k successive draws of one root, by one wavefront. The tile sums become running sums within groups of
+// 64 tiles (in LDS, where the sums were) and over the groups (group g's in lane g): a draw compares x with
+// both, re-reads only the tile it lands in, and the pick's weight leaves every running sum from its tile on,
+// which is what summing the remaining weights again would give. Lane j returns draw j's entry.
+__device__ __forceinline__ uint32_t draw_entries(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint64_t* tile_sum,
+                                                 uint64_t u, int lane) {
+    const uint32_t rows = (q.cnt - q.first + kWave - 1) / kWave;
+    const int groups = (int)((q.tiles + kWave - 1) / kWave);
+    uint64_t group_run = 0, total = 0;
+#pragma unroll 1
+    for (int g = 0; g < groups; ++g) {
+        const uint32_t tile = (uint32_t)(g * kWave + lane);
+        const uint64_t inc = wave_inclusive_scan64(tile < q.tiles ? tile_sum[tile] : 0);
+        tile_sum[tile] = inc;               // (kMaxTiles is a multiple of kWave)
+        total += wave_get64(inc, kWave - 1);
+        if (lane >= g) group_run = total;   // lane g: the sum of the groups up to g; beyond the last one: all
     }
     uint32_t my_pick = 0;
-    for (int j = 0; j < k; ++j) {
+#pragma unroll 1
+    for (int j = 0; j < (int)q.k; ++j) {
         const uint64_t x = __umul64hi(wave_get64(u, j), total);
-        // the tile whose running sum first exceeds x, and the sum before it
-        uint32_t tile = q.tiles - 1u;   // (always found while the sums are consistent, x < total; this keeps reads in bounds)
-        uint64_t before = 0;
-        bool found = false;
-#pragma unroll
-        for (int i = 0; i < kTileRegs; ++i) {
-            if (i < regs && !found) {
-                const uint64_t hit = __ballot(run[i] > x);
-                if (hit) {
-                    const int first = __ffsll((long long)hit) - 1;
-                    if (first > 0) before = wave_get64(run[i], first - 1);
-                    tile = i * kWave + first;
-                    found = true;
-                } else {
-                    before = wave_get64(run[i], kWave - 1);
-                }
-            }
-        }
-        // inside the tile, row by row
-        const uint32_t r0 = tile * q.rows_per_tile, r1 = r0 + q.rows_per_tile < rows ? r0 + q.rows_per_tile : rows;
+        // the tile whose running sum first exceeds x, and the sum before it. There always is one while the sums
+        // are consistent (x < total); the last lane or tile otherwise, which keeps the reads in bounds.
+        const uint64_t in_group = __ballot(group_run > x);
+        int g = in_group ? __ffsll((long long)in_group) - 1 : groups - 1;
+        if (g > groups - 1) g = groups - 1;
+        uint64_t before = g > 0 ? wave_get64(group_run, g - 1) : 0;
+        own_lds_ready();
+        uint64_t run = tile_sum[g * kWave + lane];
+        const uint64_t in_tile = __ballot(run > x - before);
+        const int t = in_tile ? __ffsll((long long)in_tile) - 1 : kWave - 1;
+        if (t > 0) before += wave_get64(run, t - 1);
+        uint32_t tile = (uint32_t)(g * kWave + t);
+        if (tile > q.tiles - 1u) tile = q.tiles - 1u;
         uint32_t pick = q.cnt - 1u;     // same remark
         uint64_t pick_w = 0;
-        constexpr int kAhead = 2;
-        bool done = false;
-        for (uint32_t r = r0; r < r1 && !done; r += kAhead) {
-            uint32_t v[kAhead];
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i) {
-                const uint32_t p = (r + i) * kWave + lane;
-                v[i] = low[p < q.cnt ? p : q.cnt - 1u];
-            }
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i) {
-                if (!done && r + i < r1) {
-                    const int at = pick_in_row<NEAR>(q, v[i], r + i, x, before, j, my_pick, lane, pick_w);
-                    if (at >= 0) {
-                        pick = (r + i) * kWave + at;
-                        done = true;
-                    }
+        if (tile < q.far_tiles) {
+            pick = pick_in_far_tile(q, low, sample, tile, x, before, j, my_pick, lane, pick_w);
+        } else {   // inside the tile, row by row
+            const uint32_t r0 = (tile - q.far_tiles) << q.tile_shift, end = r0 + (1u << q.tile_shift), r1 = end < rows ? end : rows;
+            for (uint32_t r = r0; r < r1; ++r) {
+                const uint32_t p = q.first + r * kWave + (uint32_t)lane;
+                const int at = pick_in_row(q, low[p < q.cnt ? p : q.cnt - 1u], r, x, before, j, my_pick, lane, pick_w);
+                if (at >= 0) {
+                    pick = q.first + r * kWave + (uint32_t)at;
+                    break;
                 }
             }
         }
         if (lane == j) my_pick = pick;
         total -= pick_w;
-#pragma unroll
-        for (int i = 0; i < kTileRegs; ++i)
-            if (i < regs && (uint32_t)(i * kWave + lane) >= tile) run[i] -= pick_w;
+        if (lane >= g) group_run -= pick_w;
+        if (lane >= t) tile_sum[g * kWave + lane] = run - pick_w;
     }
     return my_pick;
 }
 
-// The weights 1/(t - ts) depend on the query, so the whole valid list has to be looked at once per root
-// (from a plain array of the timestamps' low words: a quarter of the bytes of the 16-byte records). A
-// block of four wavefronts per root: the first finds the cutoff; all four sum the weights of the list's
-// tiles, at most 512 of whole 64-entry rows (one wavefront walking a long list alone would wait out a
-// memory round trip every few rows); the first makes the draws. Bound by vector instructions, about 15
-// per 64 weights and 100 per draw. Two hops of 10 from 4 000 roots (0.59 G weights): 1.04 ms with 64-bit
-// remainders and a scan of all tile sums per draw, 0.64 ms so. Two or four roots per block (fewer waves
-// idle while one draws) take 0.65 - 0.70 ms and leave the longest lists to fewer waves: one hop of 4 000
-// roots 0.115 ms with one root per block, 0.150 with two, 0.189 with four.
-__global__ __launch_bounds__(kListThreads) void sample_hop_inverse_timespan_kernel(
+// Sums of a wave's share of the tiles.
+__device__ __forceinline__ void sum_tiles(const ListQuery& q, const uint32_t* __restrict__ ts_low, const uint32_t* sample, uint32_t first,
+                                          uint32_t step, uint64_t* tile_sum, int lane) {
+    const uint32_t* low = ts_low + q.lo;
+    for (uint32_t tile = first; tile < q.far_tiles; tile += step) {
+        const uint64_t s = far_tile_weight(q, low, sample, tile, lane);
+        if (lane == 0) tile_sum[tile] = s;
+    }
+    if (q.near) sum_near_tiles<true>(q, low, first, step, tile_sum, lane);
+    else sum_near_tiles<false>(q, low, first, step, tile_sum, lane);
+}
+
+// Entries per weight from which a list is described by its weights: a batch of 63 weights costs about 180 vector
+// instructions, a row of 64 entries 16 (8, 12, 16 entries: 248, 245, 247 us for 40 000 roots over lists of 13 000
+// entries), and the shortest list that is looked at for it.
+constexpr float kRunEntries = 12.0f;
+constexpr uint32_t kFarEntries = 512;
+constexpr uint32_t kWaveRows = 48, kFewRows = 8;   // a list of no more rows is one wavefront's work, in a block of its own and else
+
+// Roots per block of kListWaves wavefronts. With as many roots as wavefronts none of these is idle while lists are
+// short or while draws are made, with one the longest lists are spread widest. Lists of 4, 20, 141, 300 and 2 000
+// entries on average, one / two / four roots per block, us:
+//   4 000 roots:  20.9 19.1 18.8   28.3 25.9 26.6   34.6 29.6 29.3   53.3 56.6 69.5   74.1 74.1 86.9
+//   8 000 roots:  32.2 28.4 25.5   44.6 37.5 32.9   58.4 43.5 42.0   88.0 71.1 78.7    112  100  107
+//   16 000 roots: 52.0 43.6 37.6   76.1 58.9 50.1    107 76.0 64.4    142  112  105    195  152  159
+// (600 and 2 000 roots: one per block, or the same.)
+int list_roots_per_block(int64_t entries, int64_t nodes, int64_t roots) {
+    if (entries < 256 * nodes) return roots < 4000 ? 1 : 4;
+    return roots < 6000 ? 1 : roots < 12000 ? 2 : 4;
+}
+
+// How a list of cnt > k valid entries is cut up. By one wavefront.
+__device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec, const TaserTimeIndex& index, int64_t lo, int64_t hi,
+                                               int64_t t, uint32_t cnt, int k, uint32_t alone_rows, int lane) {
+    ListQuery q = {};
+    q.lo = (uint32_t)lo;
+    q.cnt = cnt;
+    q.t_low = (uint32_t)(uint64_t)t;
+    q.k = (uint32_t)k;
+    q.batches = 1u;
+    uint64_t longest = (uint64_t)t - (uint64_t)rec[lo].ts;   // of all deltas
+    // delta >= 2^32 is ts < t - (2^32 - 1); t is at least 2^32 above the smallest timestamp here
+    if (longest >> 32) q.ones = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - 0xFFFFFFFFll, 0, lane);
+    if (cnt - q.ones >= kFarEntries && longest > kLastLargeDelta) {
+        const float every = (float)longest / (float)cnt;       // time between two entries
+        float from = __builtin_sqrtf(kRunEntries * 4294967296.0f * every);   // around it a weight has kRunEntries entries
+        if (from < (float)(kLastLargeDelta + 1u)) from = (float)(kLastLargeDelta + 1u);
+        const uint32_t w_first = longest >> 32 ? 1u : quotient_of_delta<false>((uint32_t)longest);
+        uint32_t w_end = (uint32_t)(4294967296.0f / from);
+        if (w_end > kSmallWeight) w_end = kSmallWeight;
+        const float far = (float)cnt * (1.0f - from / (float)longest);   // entries, were they spread evenly
+        if (w_end > w_first && far > kRunEntries * (float)(w_end - w_first) + 1024.0f) {
+            // weights below w_end are deltas above floor(2^32 / w_end), which is less than `longest`
+            const uint32_t first = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - (int64_t)weight_of_delta(w_end), 0, lane);
+            if (first / (uint32_t)kRunEntries > w_end - w_first) {
+                q.first = first;
+                q.w_first = w_first;
+                q.w_end = w_end;
+                const uint32_t batches = (w_end - w_first + kBatch - 1) / kBatch;
+                q.batches = (batches + kMostFarTiles - 1) / kMostFarTiles;
+                q.far_tiles = (batches + q.batches - 1) / q.batches;
+                q.stride = (first - q.ones + kSamples - 1) / kSamples;
+                longest = first < cnt ? (uint64_t)t - (uint64_t)rec[lo + first].ts : 1;
+            }
+        }
+    }
+    q.near = longest < (1u << 24);
+    // Rows per tile: every tile costs the summing a wave-wide reduction, every draw re-reads about half
+    // a tile with a wave-wide scan per row; the sum is smallest near sqrt(rows / k). The tiling
+    // never changes a result, only the cost.
+    const uint32_t rows = (cnt - q.first + kWave - 1) / kWave;
+    uint32_t per = (uint32_t)__builtin_sqrtf((float)rows / (float)k);
+    q.tile_shift = per > 1u ? 31u - (uint32_t)__clz((int)per) : 0u;
+    while (((uint64_t)kMostNearTiles << q.tile_shift) < rows) ++q.tile_shift;
+    per = 1u << q.tile_shift;
+    q.alone = rows + 4u * q.far_tiles * q.batches <= alone_rows;
+    q.tiles = q.far_tiles + (rows + per - 1) / per;
+    return q;
+}
+
+// The weights 1/(t - ts) depend on the query, so the whole valid list counts for every root. What an entry adds to
+// the sums is a whole number that changes slowly far from the query: entries between floor(2^32 / (w + 1)) and
+// floor(2^32 / w) before it all weigh w. Where a weight has kRunEntries entries and more, the list is summed by
+// weights (the far part: a search per weight), elsewhere by entries (from a plain array of the timestamps' low words, a
+// quarter of the bytes of the records). A block of four wavefronts: each finds the cutoff of a root and cuts up its
+// list; all of them sum the long lists' tiles; then each wavefront sums its own list if it is short, and makes its
+// root's draws. Bound by vector instructions (82 % of the issue slots): 16 per 64 entries, 180 per 63 weights, about 90 per
+// draw. Two hops of 10 from 4 000 roots (0.4 G weights, 0.23 G of them in far parts): 0.62 ms when every entry was weighed
+// and one root had a block, 0.32 so. Eight wavefronts per SIMD take 96 scalar registers, which is what the attribute asks
+// for (0.36 ms with seven).
+__global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8))) void sample_hop_inverse_timespan_kernel(
     const int64_t* __restrict__ indptr, const TaserRec* __restrict__ rec, const uint32_t* __restrict__ ts_low,
     const TaserTimeIndex index, const int32_t* __restrict__ roots,
-    const int64_t* __restrict__ times, int32_t num_nodes, int k, uint32_t seed_lo, uint32_t seed_hi,
+    const int64_t* __restrict__ times, int64_t num_roots, int per_block, int32_t num_nodes, int k, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t hop, int32_t* __restrict__ o_nbr, int32_t* __restrict__ o_eid, int64_t* __restrict__ o_ts,
     int32_t* __restrict__ o_count) {
-    __shared__ uint64_t tile_sum[kMaxTiles];
-    __shared__ ListQuery query;
+    __shared__ uint64_t tile_sum[kListWaves][kMaxTiles];
+    __shared__ uint32_t sample[kListWaves][kSamples];
+    __shared__ ListQuery query[kListWaves];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t root = blockIdx.x;   // the grid has exactly one block per root
-
-    if (wave == 0) {
+    const int64_t root = (int64_t)blockIdx.x * per_block + wave;
+    if (lane == 0) query[wave].tiles = 0;      // nothing (more) to do for this wave's root
+    if (wave < per_block && root < num_roots) {
         int64_t lo = 0, hi = 0, t = 0;
         const int32_t v = roots[root];
         if (v >= 0 && v < num_nodes) {
@@ -663,44 +932,43 @@ __global__ __launch_bounds__(kListThreads) void sample_hop_inverse_timespan_kern
             lo = indptr[v];
             hi = indptr[v + 1];
         }
-        const int64_t cnt = group_cutoff<kWave>(rec, index, lo, hi, t, 0, lane);
-        ListQuery q = {(uint32_t)lo, (uint32_t)cnt, 0u, (uint32_t)(uint64_t)t, 1u, 0u, 1u};
+        const int cnt = __builtin_amdgcn_readfirstlane((int)group_cutoff<kWave>(rec, index, lo, hi, t, 0, lane));   // below 2^31
         if (cnt <= k) {          // everything, most recent first
             const TaserRec pad = {0, -1, -1};
             if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, lane < cnt ? rec[lo + cnt - 1 - lane] : pad);
-            if (lane == 0) o_count[root] = (int32_t)cnt;
+            if (lane == 0) o_count[root] = cnt;
         } else {
-            const uint64_t longest = (uint64_t)t - (uint64_t)rec[lo].ts;   // of all deltas
-            q.near = longest < (1u << 24);
-            // delta >= 2^32 is ts < t - (2^32 - 1); t is at least 2^32 above the smallest timestamp here
-            if (longest >> 32) q.ones = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - 0xFFFFFFFFll, 0, lane);
-            // Rows per tile: every tile costs the summing a wave-wide reduction, every draw re-reads about half
-            // a tile with a wave-wide scan per row; the sum is smallest near sqrt(rows / k). The tiling
-            // never changes a result, only the cost. At most kMaxTiles tiles.
-            const uint32_t rows = (q.cnt + kWave - 1) / kWave;
-            uint32_t per = (uint32_t)__builtin_sqrtf((float)rows / (float)k);
-            if (per < 1u) per = 1u;
-            if ((uint64_t)per * kMaxTiles < rows) per = (rows + kMaxTiles - 1) / kMaxTiles;
-            q.rows_per_tile = per;
-            q.tiles = (rows + per - 1) / per;
+            const ListQuery q = uniform(plan_list(rec, index, lo, hi, t, (uint32_t)cnt, k, per_block == 1 ? kFewRows : kWaveRows, lane));
+            if (lane == 0) query[wave] = q;
+            if (q.far_tiles) {
+                uint32_t s[kSamples / kWave];
+#pragma unroll
+                for (uint32_t i = 0; i < kSamples / kWave; ++i) {
+                    const uint64_t p = (uint64_t)(i * kWave + (uint32_t)lane + 1u) * q.stride - 1u + q.ones;
+                    s[i] = ts_low[q.lo + (p < q.first ? (uint32_t)p : q.first - 1u)];
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < kSamples / kWave; ++i) sample[wave][i * kWave + (uint32_t)lane] = q.t_low - s[i];
+            }
         }
-        if (lane == 0) query = q;
+    }
+    // the long lists by all waves, then every wave its own
+    __syncthreads();
+#pragma unroll 1
+    for (int w = 0; w < per_block; ++w) {
+        const ListQuery q = uniform(query[w]);
+        if (q.tiles > 0 && !q.alone) sum_tiles(q, ts_low, sample[w], (uint32_t)wave, kListWaves, tile_sum[w], lane);
     }
     __syncthreads();
-    const ListQuery q = uniform(query);
-    if (q.tiles == 0) return;         // served above
-    const uint32_t rows = (q.cnt + kWave - 1) / kWave;
-    const uint32_t* low = ts_low + q.lo;
-    for (uint32_t tile = wave; tile < q.tiles; tile += kListWaves) {
-        const uint32_t r0 = tile * q.rows_per_tile, r1 = r0 + q.rows_per_tile < rows ? r0 + q.rows_per_tile : rows;
-        const uint64_t s = q.near ? tile_weight<true>(q, low, r0, r1, lane) : tile_weight<false>(q, low, r0, r1, lane);
-        if (lane == 0) tile_sum[tile] = s;
+    const ListQuery q = uniform(query[wave]);
+    if (q.tiles == 0) return;
+    if (q.alone) {
+        sum_tiles(q, ts_low, sample[wave], 0, 1, tile_sum[wave], lane);
+        own_lds_ready();
     }
-    __syncthreads();
-    if (wave != 0) return;            // the draws are one wavefront's work
     uint64_t u = 0;
     if (lane < k) u = draw64_wide(seed_lo, seed_hi, hop, (uint64_t)root, (uint32_t)lane);
-    const uint32_t pick = q.near ? draw_entries<true>(q, low, tile_sum, k, u, lane) : draw_entries<false>(q, low, tile_sum, k, u, lane);
+    const uint32_t pick = draw_entries(q, ts_low + q.lo, sample[wave], tile_sum[wave], u, lane);
     if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, rec[q.lo + pick]);
     if (lane == 0) o_count[root] = k;
 }
@@ -986,10 +1254,11 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
             case TASER_UNIFORM: launch_hop<TASER_UNIFORM>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, stream); break;
             case TASER_INVERSE_TIMESPAN: {
                 TaserProfileSpan span(stream, "sample_hop_inverse_timespan");
-                const unsigned grid = (unsigned)n;   // one block per root (n < 2^31)
+                const int per_block = list_roots_per_block(g->num_entries, g->num_nodes, n);
+                const unsigned grid = (unsigned)((n + per_block - 1) / per_block);   // n < 2^31
                 hipLaunchKernelGGL(sample_hop_inverse_timespan_kernel, dim3(grid), dim3(kListThreads), 0, stream, g->indptr, g->rec,
-                                   g->ts_low, g->time_index, cur_roots, cur_times, g->num_nodes, k, (uint32_t)seed, (uint32_t)(seed >> 32),
-                                   (uint32_t)h, out[h].nbr, out[h].eid, out[h].ts, out[h].count);
+                                   g->ts_low, g->time_index, cur_roots, cur_times, n, per_block, g->num_nodes, k, (uint32_t)seed,
+                                   (uint32_t)(seed >> 32), (uint32_t)h, out[h].nbr, out[h].eid, out[h].ts, out[h].count);
                 break;
             }
             default: launch_hop<TASER_WEIGHTED>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, stream); break;

@@ -1,0 +1,82 @@
+"""The inverse-timespan finder where it sums a list by weights instead of by entries (the far part of long lists), and
+with one, two and four roots per block."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_05396_amd as T
+
+THREADS = os.cpu_count() or 4
+NOW = 1 << 45
+
+
+def _deltas(shape, n, rng):
+    if shape == "even":                    # many entries per weight from a third of the span on
+        return rng.integers(1, 20_000_000, n)
+    if shape == "log":                     # as many entries per factor of time: few far ones, many near
+        return np.exp(rng.uniform(0, np.log(5e8), n)).astype(np.int64) + 1
+    if shape == "old burst":               # one weight holds nearly all, the near part is one row
+        return np.concatenate([rng.integers(900_000_000, 900_050_000, n - 5), rng.integers(1, 100, 5)])
+    if shape == "all far":                 # every entry among the far ones, or all but a few
+        return rng.integers(1 << 30, 1 << 31, n)
+    if shape == "beyond 2^32":             # weight 1 from entry 0 on, the low words wrap inside the far part
+        return rng.integers(1 << 20, 1 << 34, n)
+    if shape == "dense":                   # 40 000 weights: several batches per far tile, ties everywhere
+        return rng.integers(1, 400_000, n)
+    return np.repeat(rng.integers(1, 30_000_000, n // 16 + 1), 16)[:n]   # "ties": runs of one timestamp across samples
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,n", [("even", 511), ("even", 513), ("even", 5000), ("even", 8209), ("even", 300_000), ("log", 40_000),
+                                     ("old burst", 600), ("old burst", 70_001), ("all far", 3000), ("all far", 100_000), ("beyond 2^32", 2000),
+                                     ("beyond 2^32", 150_000), ("dense", 3_000_000), ("ties", 513), ("ties", 100_000)])
+def test_far_parts_match_the_oracle(shape, n):
+    rng = np.random.default_rng(n)
+    ts = np.sort(NOW - _deltas(shape, n, rng)).astype(np.int64)
+    src, dst, eid = np.zeros(n, np.int32), rng.integers(0, 9, n).astype(np.int32), np.arange(n, dtype=np.int32)
+    g = T.tcsr_build(*(torch.from_numpy(x).cuda() for x in (src, dst, ts, eid)), 9)
+    g_ref = oracle.tcsr_build(src, dst, ts, eid, 9, THREADS)
+    times = np.concatenate([[NOW, NOW + 1, NOW + 70_000, ts[-1], ts[n // 2], ts[n // 2] + 1], NOW + rng.integers(-1000, 1000, 4)]).astype(np.int64)
+    roots = np.zeros(times.shape[0], np.int32)
+    for k in (1, 10, 64) if n < 1_000_000 else (10,):
+        want = oracle.sample_temporal(g_ref, roots, times, k, 1, T.INVERSE_TIMESPAN, 5, threads=THREADS)[0]
+        got = T.sample_temporal(g, torch.from_numpy(roots).cuda(), torch.from_numpy(times).cuda(), k, 1, T.INVERSE_TIMESPAN, 5)[0]
+        for f in ("nbr", "eid", "ts", "count"):
+            assert np.array_equal(got[f].cpu().numpy(), want[f]), (k, f)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("roots,entries", [(3999, 20_000), (4001, 20_000), (4003, 60_000), (5999, 60_000), (6001, 60_000), (12_001, 60_000)])
+def test_roots_per_block(roots, entries):
+    """100 nodes: on both sides of 256 entries per node, with numbers of roots that leave a block's last places empty."""
+    rng = np.random.default_rng(roots)
+    nodes = 100
+    src = (np.minimum(rng.zipf(1.4, entries), nodes) - 1).astype(np.int32)
+    ts = np.sort(rng.integers(0, 50_000_000, entries)).astype(np.int64)
+    dst, eid = rng.integers(0, nodes, entries).astype(np.int32), np.arange(entries, dtype=np.int32)
+    g = T.tcsr_build(*(torch.from_numpy(x).cuda() for x in (src, dst, ts, eid)), nodes)
+    g_ref = oracle.tcsr_build(src, dst, ts, eid, nodes, THREADS)
+    q, t = rng.integers(-1, nodes, roots).astype(np.int32), rng.integers(0, 50_000_100, roots).astype(np.int64)
+    want = oracle.sample_temporal(g_ref, q, t, 4, 1, T.INVERSE_TIMESPAN, 11, threads=THREADS)[0]
+    got = T.sample_temporal(g, torch.from_numpy(q).cuda(), torch.from_numpy(t).cuda(), 4, 1, T.INVERSE_TIMESPAN, 11)[0]
+    for f in ("nbr", "eid", "ts", "count"):
+        assert np.array_equal(got[f].cpu().numpy(), want[f]), f
+
+
+def test_the_weight_of_every_delta_is_exact_whatever_the_reciprocals_last_bit():
+    rng = np.random.default_rng(2)
+    w = np.arange(1, 70_000, dtype=np.int64)
+    d = np.concatenate([np.arange(1, 1 << 20), 2 ** 32 // w, 2 ** 32 // w + 1, rng.integers(1 << 20, 1 << 32, 500_000), 2 ** 32 - np.arange(1, 999)])
+    d = d[(d >= 1) & (d < 1 << 32)].astype(np.uint64)
+    f, m = np.float32, np.uint64(0xffffffff)
+    for off in (None, f(np.inf), f(-np.inf)):
+        rcp = f(1) / d.astype(f)
+        r = f(1 - 2.0 ** -21) * (rcp if off is None else np.nextafter(rcp, off))
+        q = (f(4294967296.0) * r).astype(np.uint64)
+        rest = (np.uint64(0) - q * d) & m
+        more = (rest.astype(f) * r).astype(np.uint64)
+        left = (rest - more * d) & m
+        assert np.array_equal(np.maximum(q + more + (left >= d), 1), np.uint64(1 << 32) // d)
