@@ -15,7 +15,9 @@
 //   * the 16-byte record {ts, nbr, eid} the sampler reads travels with the key,
 //     so the last pass leaves the final layout in place. The first pass reads the
 //     caller's columns directly: nothing is packed beforehand;
-//   * indptr is read off the sorted node column (no atomics, no histogram).
+//   * indptr is read off the sorted node column (no atomics, no histogram);
+//   * time-sorted input with node ids of two digits, the usual case, has two passes of its own that move fewer bytes
+//     (node_scatter_kernel), and its indptr comes from the scanned histogram.
 // All device memory is one storage block (what the graph keeps) and one scratch
 // block, either the caller's (taser_tcsr_build_in) or allocated here.
 #include <new>
@@ -65,12 +67,12 @@ struct Items {
 // that equal digits of one wave instruction (popular nodes) meet at fewer addresses. Thread t clears
 // and adds up digit t's.
 constexpr uint32_t kCopies = 4;
-__device__ __forceinline__ void clear_digit(uint32_t* bins) {
-    for (uint32_t c = 0; c < kCopies; ++c) bins[threadIdx.x * kCopies + c] = 0;
+template <uint32_t kOf = kCopies> __device__ __forceinline__ void clear_digit(uint32_t* bins) {
+    for (uint32_t c = 0; c < kOf; ++c) bins[threadIdx.x * kOf + c] = 0;
 }
-__device__ __forceinline__ uint32_t count_of_digit(const uint32_t* bins) {
+template <uint32_t kOf = kCopies> __device__ __forceinline__ uint32_t count_of_digit(const uint32_t* bins) {
     uint32_t sum = 0;
-    for (uint32_t c = 0; c < kCopies; ++c) sum += bins[threadIdx.x * kCopies + c];
+    for (uint32_t c = 0; c < kOf; ++c) sum += bins[threadIdx.x * kOf + c];
     return sum;
 }
 
@@ -79,10 +81,16 @@ __device__ __forceinline__ uint32_t count_of_digit(const uint32_t* bins) {
 // AND of the biased timestamps (bits in which they agree need no sorting). On the way it counts
 // every tile's node ids by their lowest digit, hist[tile * bins + bin] as radix_hist_kernel
 // would: time-sorted input is sorted by the node digits only, and its first pass then needs no
-// histogram kernel. It reads 12 of an entry's 20 bytes and writes nothing per entry: 0.18 ms for
-// 64 M entries (4.3 TB/s), where packing the columns into records here, and reading them back in
-// the first pass, took 0.50.
+// histogram kernel. It reads 12 of an entry's 20 bytes and writes nothing per entry: 0.17 ms for
+// 64 M entries (4.5 TB/s, with 4- and 8-byte loads 0.177 ms), where packing the columns into records here, and
+// reading them back in the first pass, took 0.50.
 constexpr unsigned kInspectBlocks = 1024;   // 4 per compute unit; the fold below is one block over their words
+struct __attribute__((packed, aligned(4))) FourNodes {
+    int32_t v[4];
+};
+struct __attribute__((packed, aligned(8))) TwoTimes {
+    int64_t a, b;
+};
 template <int kItems>
 __global__ __launch_bounds__(kSortThreads) void inspect_kernel(const int32_t* __restrict__ src, const int64_t* __restrict__ ts,
                                                            int64_t n, int32_t num_nodes,
@@ -101,28 +109,44 @@ __global__ __launch_bounds__(kSortThreads) void inspect_kernel(const int32_t* __
         const uint32_t last = whole ? (uint32_t)kTile : (uint32_t)(n - 1 - tile0);   // place of the array's last item, if it is here
         const int32_t* const tile_src = src + tile0;
         const int64_t* const tile_ts = ts + tile0;
-        int32_t s[kItems];
-        int64_t t[kItems], t_end[kItems];
+        if (whole) {   // a thread takes runs of four entries, in wide loads (the columns are aligned to their elements only)
+            FourNodes s[kItems / 4];
+            TwoTimes t[kItems / 4][2];
+            int64_t t_end[kItems / 4];                          // the entry after the wave's last run; the others have it in a lane
 #pragma unroll
-        for (int u = 0; u < kItems; ++u) {
-            uint32_t i = threadIdx.x + u * kSortThreads;
-            if (!whole && i > last) i = last;               // clamped: every load stays in bounds
-            s[u] = tile_src[i];
-            t[u] = tile_ts[i];
-            t_end[u] = 0;                                   // the item after the wave's last one; the others have it in a lane
-            if ((threadIdx.x & (kWave - 1)) == kWave - 1) t_end[u] = tile_ts[i < last ? i + 1 : i];
-        }
+            for (int u = 0; u < kItems / 4; ++u) {
+                const uint32_t i = (threadIdx.x + u * kSortThreads) * 4u;
+                s[u] = *reinterpret_cast<const FourNodes*>(tile_src + i);
+                t[u][0] = *reinterpret_cast<const TwoTimes*>(tile_ts + i);
+                t[u][1] = *reinterpret_cast<const TwoTimes*>(tile_ts + i + 2);
+                t_end[u] = 0;
+                if ((threadIdx.x & (kWave - 1)) == kWave - 1) t_end[u] = tile_ts[i + 4];
+            }
 #pragma unroll
-        for (int u = 0; u < kItems; ++u) {
-            const uint32_t next_lo = __shfl_down((uint32_t)(uint64_t)t[u], 1, kWave), next_hi = __shfl_down((uint32_t)((uint64_t)t[u] >> 32), 1, kWave);
-            int64_t next = (int64_t)(((uint64_t)next_hi << 32) | next_lo);
-            if ((threadIdx.x & (kWave - 1)) == kWave - 1) next = t_end[u];
-            if (!whole && threadIdx.x + u * kSortThreads > last) continue;
-            bad |= (uint32_t)s[u] >= (uint32_t)num_nodes;   // negative ids included
-            unsorted |= (next < t[u]);
-            any_or |= biased(t[u]);
-            all_and &= biased(t[u]);
-            atomicAdd(&bins[((uint32_t)s[u] & low_mask) * kCopies + copy], 1u);
+            for (int u = 0; u < kItems / 4; ++u) {
+                const int64_t x[4] = {t[u][0].a, t[u][0].b, t[u][1].a, t[u][1].b};
+                const uint32_t next_lo = __shfl_down((uint32_t)(uint64_t)x[0], 1, kWave), next_hi = __shfl_down((uint32_t)((uint64_t)x[0] >> 32), 1, kWave);
+                int64_t next = (int64_t)(((uint64_t)next_hi << 32) | next_lo);
+                if ((threadIdx.x & (kWave - 1)) == kWave - 1) next = t_end[u];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    bad |= (uint32_t)s[u].v[j] >= (uint32_t)num_nodes;   // negative ids included
+                    unsorted |= (j < 3 ? x[j + 1] : next) < x[j];
+                    any_or |= biased(x[j]);
+                    all_and &= biased(x[j]);
+                    atomicAdd(&bins[((uint32_t)s[u].v[j] & low_mask) * kCopies + copy], 1u);
+                }
+            }
+        } else {
+            for (uint32_t i = threadIdx.x; i <= last; i += kSortThreads) {
+                const int32_t node = tile_src[i];
+                const int64_t x = tile_ts[i];
+                bad |= (uint32_t)node >= (uint32_t)num_nodes;
+                unsorted |= tile_ts[i < last ? i + 1 : i] < x;
+                any_or |= biased(x);
+                all_and &= biased(x);
+                atomicAdd(&bins[((uint32_t)node & low_mask) * kCopies + copy], 1u);
+            }
         }
         __syncthreads();
         if (threadIdx.x <= low_mask) hist[((size_t)tile << low_bits) + threadIdx.x] = count_of_digit(bins);
@@ -159,9 +183,10 @@ __global__ __launch_bounds__(kSortThreads) void inspect_kernel(const int32_t* __
     }
 }
 
-// One block: info[0..3] = the `blocks` per-block word groups of inspect_kernel combined.
+// One block: info[0..3] = the `blocks` per-block word groups of inspect_kernel combined; where the input is in time
+// order info[2] and info[3] are the first and the last timestamp instead.
 __global__ __launch_bounds__(kSortThreads) void fold_info_kernel(const unsigned long long* __restrict__ partial, uint32_t blocks,
-                                                             unsigned long long* __restrict__ info) {
+                                                             const int64_t* __restrict__ ts, int64_t n, unsigned long long* __restrict__ info) {
     __shared__ unsigned long long part[4][kSortWaves];
     unsigned long long v[4] = {0, 0, 0, ~0ull};
     for (uint32_t b = threadIdx.x; b < blocks; b += kSortThreads) {
@@ -181,6 +206,10 @@ __global__ __launch_bounds__(kSortThreads) void fold_info_kernel(const unsigned 
         for (int w = 1; w < kSortWaves; ++w) {
             for (int j = 0; j < 3; ++j) v[j] |= part[j][w];
             v[3] &= part[3][w];
+        }
+        if (!v[1]) {
+            v[2] = (unsigned long long)ts[0];
+            v[3] = (unsigned long long)ts[n - 1];
         }
         for (int j = 0; j < 4; ++j) info[j] = v[j];
     }
@@ -393,6 +422,50 @@ __device__ __forceinline__ uint32_t scan_digits(uint32_t own, uint32_t* wave_sum
     return before + inc - own;
 }
 
+// Stable rank of a lane's item among its wave's items with the same digit, in the rows of 64 so far: `seen` of the
+// rows before plus the lanes below it in this one. counts: the wave's, one per digit.
+__device__ __forceinline__ uint32_t rank_in_wave(uint32_t dg, bool valid, int bits, uint16_t* counts) {
+    // lanes of this row that hold the same digit as me: per bit a ballot, and of the lanes left those that agree
+    const uint64_t all = __ballot(valid);
+    uint32_t same_lo = (uint32_t)all, same_hi = (uint32_t)(all >> 32);
+#pragma unroll
+    for (int b = 0; b < kMaxDigitBits; ++b) {
+        if (b < bits) {   // uniform
+            const uint32_t mine = (uint32_t)((int32_t)(dg << (31 - b)) >> 31);   // my bit, everywhere
+            const uint64_t has = __ballot(mine != 0);
+            same_lo &= ~((uint32_t)has ^ mine);
+            same_hi &= ~((uint32_t)(has >> 32) ^ mine);
+        }
+    }
+    const uint32_t before_me = __builtin_amdgcn_mbcnt_hi(same_hi, __builtin_amdgcn_mbcnt_lo(same_lo, 0u));
+    uint32_t seen = 0;
+    if (valid) seen = counts[dg];            // equal for all lanes of a digit
+    if (valid && before_me == 0) counts[dg] = (uint16_t)(seen + (uint32_t)(__popc(same_lo) + __popc(same_hi)));
+    __builtin_amdgcn_wave_barrier();         // keep the LDS counter update of this row ahead of the next row's read
+    return seen + before_me;
+}
+
+// The ranks of a tile's items are known, wave_count says how many of every digit each wave has. Thread t, for digit t:
+// wave_count[w] becomes the place in the ordered tile of wave w's first item of it, `base` (global position of the
+// tile's first item of the digit) what has to be added to a place of the digit.
+__device__ __forceinline__ void places_of_digit(uint16_t (*wave_count)[kBins], uint32_t* base, uint32_t* scan_tmp) {
+    const uint32_t own = threadIdx.x;
+    uint32_t in_wave[kSortWaves], all = 0;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+        in_wave[w] = wave_count[w][own];
+        all += in_wave[w];
+    }
+    const uint32_t start = scan_digits(all, scan_tmp);
+    base[own] -= start;
+    uint32_t run = start;
+#pragma unroll
+    for (int w = 0; w < kSortWaves; ++w) {
+        wave_count[w][own] = (uint16_t)run;
+        run += in_wave[w];
+    }
+}
+
 // Stable scatter of one tile. offs / total = the scanned histogram: this tile's first item with
 // digit `bin` goes to (sum of total[] below bin) + offs[tile * bins + bin]. The tile is
 // first put in digit order in LDS (stable: rank among equal digits = ballots
@@ -413,9 +486,8 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
     uint32_t num_tiles, TaserRec* __restrict__ rec_out, int32_t* __restrict__ key_out, int64_t* __restrict__ level1) {
     constexpr int kTile = kSortThreads * kItems;
     constexpr int kPart = kTile < kMaxPart ? kTile : kMaxPart;
-    __shared__ uint16_t wave_count[kSortWaves][kBins];   // items of each wave per digit, then exclusive over waves
-    __shared__ uint32_t block_base[kBins];           // global position of the tile's first item of a digit
-    __shared__ uint32_t local_base[kBins];           // position of that item inside the ordered tile
+    __shared__ uint16_t wave_count[kSortWaves][kBins];   // items of each wave per digit, then the place of its first one
+    __shared__ uint32_t block_base[kBins];           // what makes a place of a digit a global position
     __shared__ uint32_t scan_tmp[2][kSortWaves];
     __shared__ TaserRec tile_rec[kPart];
     __shared__ int32_t tile_key[kPart];
@@ -448,42 +520,18 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
     }
 
     uint32_t rank[kItems];   // among the tile's items of its digit, the digit above bit 16 (one register for both)
-    const uint64_t below = ((uint64_t)1 << lane) - 1;
 #pragma unroll
     for (int r = 0; r < kItems; ++r) {
         const bool valid = mine + r * kWave < count;
         const uint32_t dg = valid ? digit_of(d, item_rec[r].ts, item_key[r]) : 0u;
-        // lanes of this row that hold the same digit as me
-        uint64_t same = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < kMaxDigitBits; ++b) {
-            if (b < d.bits) {   // uniform
-                const uint64_t has = __ballot(valid && ((dg >> b) & 1u));
-                same &= ((dg >> b) & 1u) ? has : ~has;
-            }
-        }
-        const uint32_t before_me = (uint32_t)__popcll(same & below);
-        uint32_t seen = 0;
-        if (valid) seen = wave_count[wave][dg];            // equal for all lanes of a digit
-        if (valid && before_me == 0) wave_count[wave][dg] = (uint16_t)(seen + (uint32_t)__popcll(same));
-        rank[r] = (seen + before_me) | (dg << 16);
-        __builtin_amdgcn_wave_barrier();   // keep the LDS counter update of row r ahead of row r+1's read
+        rank[r] = rank_in_wave(dg, valid, d.bits, wave_count[wave]) | (dg << 16);
     }
     __syncthreads();
-    {   // per digit: exclusive prefix of the wave counts over the waves, then of the digit totals over the
-        // digits = where a digit's run starts in the tile
-        uint32_t run = 0;
-        for (int w = 0; w < kSortWaves; ++w) {
-            const uint32_t in_wave = wave_count[w][own];
-            wave_count[w][own] = (uint16_t)run;
-            run += in_wave;
-        }
-        local_base[own] = scan_digits(run, scan_tmp[1]);
-    }
+    places_of_digit(wave_count, block_base, scan_tmp[1]);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kItems; ++r)   // rank becomes the item's place in the ordered tile
-        if (mine + r * kWave < count) rank[r] = (rank[r] & 0xffffu) + local_base[rank[r] >> 16] + wave_count[wave][rank[r] >> 16];
+        if (mine + r * kWave < count) rank[r] = (rank[r] & 0xffffu) + wave_count[wave][rank[r] >> 16];
     for (uint32_t part0 = 0; part0 < count; part0 += kPart) {
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
@@ -501,7 +549,7 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
                 const TaserRec rr = tile_rec[j];
                 const int32_t kk = tile_key[j];
                 const uint32_t dg = digit_of(d, rr.ts, kk);
-                const uint32_t to = block_base[dg] + (part0 + j - local_base[dg]);
+                const uint32_t to = block_base[dg] + (part0 + j);
                 rec_out[to] = rr;
                 key_out[to] = kk;
                 // the last pass knows the final positions: it also leaves level 1 of the search index
@@ -535,6 +583,169 @@ __global__ __launch_bounds__(kThreads) void indptr_kernel(const int32_t* __restr
         if (p0 + j > n) break;
         for (int32_t v = k[j] + 1; v <= k[1 + j]; ++v) indptr[v] = p0 + j;
     }
+}
+
+// ---- time-sorted input, two node digits ------------------------------------------------------
+// How event streams arrive, with node ids of 10 to 18 bits. The entries only go by their node: by its low digit first
+// (an exact histogram of it came with the inspection), then by the rest. Between the two passes an entry is 12 bytes
+// (the timestamp as a 32-bit distance from the first one, where the whole range allows it) and the rest of its
+// node id in 2: 20 bytes in, 14 out, 2 for the second histogram, 14 in and 16 out, where the passes below move 20 at
+// every step and another 4 twice for the sorted node column. The lists' starts come from the scanned second histogram
+// instead of that column. 64 M entries, 17 000 nodes, against the passes below: first pass 508 -> 450 us, second histogram
+// 68 -> 39, second pass 487 -> 384, starts 61 -> 8.
+struct NarrowRec {
+    uint32_t ts;
+    int32_t nbr, eid;
+};
+
+// kFirst: from the caller's columns to narrow records by the low `bits` bits of the node id; else from those to the
+// graph's records by the other bits. Otherwise as radix_scatter_kernel. Bound by the memory (34 and 30 bytes per entry at
+// 4.8 and 5.0 TB/s; a large copy moves 5.2), as long as three blocks fit a compute unit: with the 84 registers that the
+// compiler takes by itself there are two, and the passes took 551 and 494 us. The low digit is the shorter one where the
+// node id has an odd number of bits: the first pass, whose runs of a digit are short in any input, gains what the second
+// loses (6, 7, 8 of 15 bits: 852, 842, 852 us for both).
+template <bool kFirst, int kItems>
+__global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(6))) void node_scatter_kernel(
+    const Items in, const NarrowRec* __restrict__ narrow_in, const uint16_t* __restrict__ rest_in, int64_t ts_first, int64_t n, int bits,
+    const uint32_t* __restrict__ offs, const uint32_t* __restrict__ total, uint32_t num_tiles, NarrowRec* __restrict__ narrow_out,
+    uint16_t* __restrict__ rest_out, TaserRec* __restrict__ rec_out, int64_t* __restrict__ level1) {
+    constexpr int kTile = kSortThreads * kItems;
+    constexpr int kPart = 1024;
+    __shared__ uint16_t wave_count[kSortWaves][kBins];   // as in radix_scatter_kernel
+    __shared__ uint32_t block_base[kBins];
+    __shared__ uint32_t scan_tmp[2][kSortWaves];
+    __shared__ NarrowRec tile_rec[kPart];
+    __shared__ uint32_t tile_key[kPart];                 // the digit, and above bit 9 the rest of the node id
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const uint32_t tile = tile_of_block(blockIdx.x, num_tiles);
+    if (tile >= num_tiles) return;
+    const int64_t tile0 = (int64_t)tile * kTile;
+    const uint32_t count = n - tile0 < kTile ? (uint32_t)(n - tile0) : (uint32_t)kTile;
+    const uint32_t mine = (uint32_t)wave * (kWave * kItems) + (uint32_t)lane;
+
+    uint32_t item_ts[kItems], key[kItems];
+    int32_t item_nbr[kItems], item_eid[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const uint32_t i = mine + r * kWave;
+        if (i < count) {
+            if (kFirst) {
+                const uint32_t node = (uint32_t)(in.key + tile0)[i];
+                key[r] = (node & ((1u << bits) - 1u)) | (node >> bits << kMaxDigitBits);
+                item_ts[r] = (uint32_t)((uint64_t)(in.ts + tile0)[i] - (uint64_t)ts_first);
+                item_nbr[r] = (in.dst + tile0)[i];
+                item_eid[r] = in.eid ? (in.eid + tile0)[i] : (int32_t)(tile0 + i);
+            } else {
+                key[r] = (rest_in + tile0)[i];
+                const NarrowRec* from = narrow_in + tile0 + i;
+                item_ts[r] = from->ts;
+                item_nbr[r] = from->nbr;
+                item_eid[r] = from->eid;
+            }
+        }
+    }
+    const uint32_t own = threadIdx.x;   // the digit value this thread looks after
+    {
+        const bool live = own < (1u << bits);
+        const uint32_t all = live ? total[own] : 0u;
+        const uint32_t before = live ? offs[((size_t)tile << bits) + own] : 0u;
+        for (int w = 0; w < kSortWaves; ++w) wave_count[w][own] = 0;
+        block_base[own] = scan_digits(all, scan_tmp[0]) + before;   // (its barrier also covers the counters)
+    }
+    uint32_t place[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const bool valid = mine + r * kWave < count;
+        place[r] = rank_in_wave(valid ? key[r] & (kBins - 1u) : 0u, valid, bits, wave_count[wave]);
+    }
+    __syncthreads();
+    places_of_digit(wave_count, block_base, scan_tmp[1]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kItems; ++r)
+        if (mine + r * kWave < count) place[r] += wave_count[wave][key[r] & (kBins - 1u)];
+    for (uint32_t part0 = 0; part0 < count; part0 += kPart) {
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            const uint32_t at = place[r] - part0;
+            if (mine + r * kWave < count && at < (uint32_t)kPart) {
+                tile_rec[at] = NarrowRec{item_ts[r], item_nbr[r], item_eid[r]};
+                tile_key[at] = key[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll 2
+        for (int r = 0; r < kPart / kSortThreads; ++r) {
+            const uint32_t j = (uint32_t)r * kSortThreads + threadIdx.x;
+            if (part0 + j < count) {
+                const NarrowRec x = tile_rec[j];
+                const uint32_t k = tile_key[j], dg = k & (kBins - 1u);
+                const uint32_t to = block_base[dg] + (part0 + j);
+                if (kFirst) {
+                    narrow_out[to] = x;
+                    rest_out[to] = (uint16_t)(k >> kMaxDigitBits);
+                } else {
+                    const int64_t ts = (int64_t)((uint64_t)ts_first + x.ts);
+                    rec_out[to] = TaserRec{ts, x.nbr, x.eid};
+                    if ((to & 15u) == 15u || (int64_t)to == n - 1) level1[to >> 4] = ts;
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// hist[tile * bins + bin] of the second digit, from its column. The entries of a tile share their low digit, and often a popular
+// node has most of them: bound by LDS atomics on few addresses, hence eight copies of every counter (64 M entries: 4, 8, 16
+// copies 49, 39, 50 us).
+constexpr uint32_t kRestCopies = 8;
+template <int kItems>
+__global__ __launch_bounds__(kSortThreads) void rest_hist_kernel(const uint16_t* __restrict__ rest, int64_t n, int bits,
+                                                             uint32_t* __restrict__ hist) {
+    constexpr int kTile = kSortThreads * kItems;
+    __shared__ uint32_t bins[kBins * kRestCopies];
+    const uint32_t copy = threadIdx.x % kRestCopies;
+    clear_digit<kRestCopies>(bins);
+    __syncthreads();
+    const int64_t tile0 = (int64_t)blockIdx.x * kTile;
+    if (tile0 + kTile <= n) {   // every thread takes kItems neighbors (the column starts an aligned part of the scratch block)
+        typedef uint16_t Some __attribute__((ext_vector_type(kItems)));
+        const Some v = reinterpret_cast<const Some*>(rest + tile0)[threadIdx.x];
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) atomicAdd(&bins[v[r] * kRestCopies + copy], 1u);
+    } else {
+        for (int64_t i = tile0 + threadIdx.x; i < n; i += kSortThreads) atomicAdd(&bins[rest[i] * kRestCopies + copy], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < (1u << bits)) hist[((size_t)blockIdx.x << bits) + threadIdx.x] = count_of_digit<kRestCopies>(bins);
+}
+
+// Where every list starts. Block b: the nodes whose low digit is b; thread t: the one of them whose rest is t.
+// Before it lie the items with a smaller rest and, of those with its rest, the ones that the first pass left before the
+// first item of low digit b: the tiles before that item's (the scanned histogram) and a part of its own tile.
+template <int kItems>
+__global__ __launch_bounds__(kSortThreads) void list_starts_kernel(const uint32_t* __restrict__ low_total, const uint16_t* __restrict__ rest,
+                                                               int64_t n, int low_bits, int rest_bits, const uint32_t* __restrict__ offs,
+                                                               const uint32_t* __restrict__ total, uint32_t num_tiles, int32_t num_nodes,
+                                                               int64_t* __restrict__ indptr) {
+    constexpr uint32_t kTile = kSortThreads * kItems;
+    __shared__ uint32_t bins[kBins * kCopies];
+    __shared__ uint32_t scan_tmp[2][kSortWaves];
+    __shared__ uint32_t low_start;
+    const uint32_t own = threadIdx.x, low = blockIdx.x, copy = threadIdx.x % kCopies;
+    clear_digit(bins);
+    const uint32_t low_before = scan_digits(own < (1u << low_bits) ? low_total[own] : 0u, scan_tmp[0]);
+    if (own == low) low_start = low_before;
+    __syncthreads();
+    const uint32_t tile = low_start / kTile, part = low_start % kTile;
+    for (uint32_t i = own; i < part; i += kSortThreads) atomicAdd(&bins[rest[(size_t)tile * kTile + i] * kCopies + copy], 1u);
+    const bool live = own < (1u << rest_bits);
+    const uint32_t all = live ? total[own] : 0u;
+    const uint32_t tiles_before = !live ? 0u : tile < num_tiles ? offs[((size_t)tile << rest_bits) + own] : all;
+    const uint32_t smaller = scan_digits(all, scan_tmp[1]);   // (its barrier also covers the counting)
+    const uint32_t node = (own << low_bits) | low;
+    if (live && node < (uint32_t)num_nodes) indptr[node] = (int64_t)smaller + tiles_before + count_of_digit(bins);
+    if (low == 0 && own == 0) indptr[num_nodes] = n;
 }
 
 __global__ __launch_bounds__(kThreads) void unpack_kernel(const TaserRec* __restrict__ rec, int64_t n,
@@ -580,7 +791,7 @@ inline int items_for(int64_t n) { return n <= kSmallEntries ? kSmallItems : kLar
 
 struct Layout {
     size_t indptr, rec, level[kTimeIndexLevels], storage;                                   // what the graph keeps
-    size_t src, dst, ts, eid, tmp_rec, key[2], hist, total, chunk_sum, partial, info, scratch;         // what the build needs
+    size_t src, dst, ts, eid, tmp_rec, key[2], hist, total[2], chunk_sum, partial, info, scratch;         // what the build needs
     int64_t level_len[kTimeIndexLevels];
     uint32_t tiles;
 };
@@ -614,7 +825,7 @@ Layout layout_of(int64_t n, int32_t num_nodes, bool copy_input) {
     l.key[0] = take((size_t)n * sizeof(int32_t));
     l.key[1] = take((size_t)n * sizeof(int32_t));
     l.hist = take((size_t)kBins * l.tiles * sizeof(uint32_t));
-    l.total = take(kBins * sizeof(uint32_t));
+    for (int i = 0; i < 2; ++i) l.total[i] = take(kBins * sizeof(uint32_t));
     l.chunk_sum = take((size_t)kMaxChunks * kBins * sizeof(uint32_t));
     l.partial = take((size_t)kInspectBlocks * 4 * sizeof(unsigned long long));
     l.info = take(4 * sizeof(unsigned long long));
@@ -629,6 +840,51 @@ int check_build_sizes(const char* what, int64_t num_entries, int32_t num_nodes, 
     return TASER_OK;
 }
 
+// hist becomes its exclusive scan per digit over the tiles, total the digits' counts.
+void launch_scan(const Layout& l, int bits, uint32_t* hist, uint32_t* total, uint32_t* chunk_sum, hipStream_t stream) {
+    TaserProfileSpan span(stream, "tcsr_scan");
+    if (l.tiles >= kChunkedTiles) {
+        const uint32_t by_count = (l.tiles + kMaxChunks - 1) / kMaxChunks, rows = by_count > 64 ? by_count : 64;
+        const dim3 grid(((1u << bits) + kWave - 1) / kWave, (l.tiles + rows - 1) / rows);
+        hipLaunchKernelGGL(chunk_sum_kernel, grid, dim3(kThreads), 0, stream, hist, l.tiles, bits, rows, chunk_sum);
+        hipLaunchKernelGGL(chunk_scan_kernel, grid, dim3(kThreads), 0, stream, hist, l.tiles, bits, rows, chunk_sum, total);
+    } else {
+        hipLaunchKernelGGL(bin_scan_kernel, dim3(((1u << bits) + kScanCols - 1) / kScanCols), dim3(kScanThreads), 0, stream, hist,
+                           l.tiles, bits, total);
+    }
+}
+
+// Time-sorted input whose node digit of `low_bits` bits is counted in hist and whose others are `rest_bits`: both passes
+// and indptr.
+template <int kItems>
+void launch_sorted(const Layout& l, const Items& in, int64_t ts_first, int64_t n, int32_t num_nodes, int low_bits, int rest_bits, uint8_t* scratch,
+                   TaserRec* rec, int64_t* level1, int64_t* indptr, hipStream_t stream) {
+    uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
+    uint32_t* total[2] = {reinterpret_cast<uint32_t*>(scratch + l.total[0]), reinterpret_cast<uint32_t*>(scratch + l.total[1])};
+    uint32_t* chunk_sum = reinterpret_cast<uint32_t*>(scratch + l.chunk_sum);
+    NarrowRec* narrow = reinterpret_cast<NarrowRec*>(scratch + l.tmp_rec);   // 12 of its 16 bytes per entry
+    uint16_t* rest = reinterpret_cast<uint16_t*>(scratch + l.key[0]);
+    launch_scan(l, low_bits, hist, total[0], chunk_sum, stream);
+    {
+        TaserProfileSpan span(stream, "tcsr_radix_scatter");
+        hipLaunchKernelGGL((node_scatter_kernel<true, kItems>), dim3(pass_grid(l.tiles)), dim3(kSortThreads), 0, stream, in, nullptr, nullptr, ts_first, n,
+                           low_bits, hist, total[0], l.tiles, narrow, rest, nullptr, nullptr);
+    }
+    {
+        TaserProfileSpan span(stream, "tcsr_radix_hist");
+        hipLaunchKernelGGL((rest_hist_kernel<kItems>), dim3(l.tiles), dim3(kSortThreads), 0, stream, rest, n, rest_bits, hist);
+    }
+    launch_scan(l, rest_bits, hist, total[1], chunk_sum, stream);
+    {
+        TaserProfileSpan span(stream, "tcsr_radix_scatter");
+        hipLaunchKernelGGL((node_scatter_kernel<false, kItems>), dim3(pass_grid(l.tiles)), dim3(kSortThreads), 0, stream, in, narrow, rest, ts_first, n,
+                           rest_bits, hist, total[1], l.tiles, nullptr, nullptr, rec, level1);
+    }
+    TaserProfileSpan span(stream, "tcsr_indptr");
+    hipLaunchKernelGGL((list_starts_kernel<kItems>), dim3(1u << low_bits), dim3(kSortThreads), 0, stream, total[0], rest, n, low_bits, rest_bits,
+                       hist, total[1], l.tiles, num_nodes, indptr);
+}
+
 template <int kItems>
 void launch_pass(const Layout& l, const Items& in, int64_t n, const DigitSpec& d, bool hist_known, uint32_t* hist, uint32_t* total, uint32_t* chunk_sum,
                  TaserRec* rec_out, int32_t* key_out, int64_t* level1, hipStream_t stream) {
@@ -636,18 +892,7 @@ void launch_pass(const Layout& l, const Items& in, int64_t n, const DigitSpec& d
         TaserProfileSpan span(stream, "tcsr_radix_hist");
         hipLaunchKernelGGL((radix_hist_kernel<kItems>), dim3(l.tiles), dim3(kSortThreads), 0, stream, in, n, d, hist);
     }
-    {
-        TaserProfileSpan span(stream, "tcsr_scan");
-        if (l.tiles >= kChunkedTiles) {
-            const uint32_t by_count = (l.tiles + kMaxChunks - 1) / kMaxChunks, rows = by_count > 64 ? by_count : 64;
-            const dim3 grid(((1u << d.bits) + kWave - 1) / kWave, (l.tiles + rows - 1) / rows);
-            hipLaunchKernelGGL(chunk_sum_kernel, grid, dim3(kThreads), 0, stream, hist, l.tiles, d.bits, rows, chunk_sum);
-            hipLaunchKernelGGL(chunk_scan_kernel, grid, dim3(kThreads), 0, stream, hist, l.tiles, d.bits, rows, chunk_sum, total);
-        } else {
-            hipLaunchKernelGGL(bin_scan_kernel, dim3(((1u << d.bits) + kScanCols - 1) / kScanCols), dim3(kScanThreads), 0, stream, hist,
-                               l.tiles, d.bits, total);
-        }
-    }
+    launch_scan(l, d.bits, hist, total, chunk_sum, stream);
     TaserProfileSpan span(stream, "tcsr_radix_scatter");
     if (in.rec)
         hipLaunchKernelGGL((radix_scatter_kernel<false, kItems>), dim3(pass_grid(l.tiles)), dim3(kSortThreads), 0, stream, in, n, d, hist,
@@ -676,9 +921,10 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
     TaserRec* rec = reinterpret_cast<TaserRec*>(storage + l.rec);
     int64_t* level1 = reinterpret_cast<int64_t*>(storage + l.level[0]);
     uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
-    uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total);
+    uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total[0]);
     uint32_t* chunk_sum = reinterpret_cast<uint32_t*>(scratch + l.chunk_sum);
     const int32_t* sorted_key = src;
+    bool in_node_digits = false;   // launch_sorted did it all
 
     if (n > 0) {
         // ---- what the input looks like
@@ -689,6 +935,8 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
             const int passes = (bits + kMaxDigitBits - 1) / kMaxDigitBits;
             return passes > 0 ? (bits + passes - 1) / passes : 1;
         };
+        const bool two_digits = node_bits > kMaxDigitBits && node_bits <= 2 * kMaxDigitBits;   // of the node id
+        const int low_bits = two_digits ? node_bits / 2 : width_of(node_bits);                  // counted by the inspection
         unsigned long long info[4] = {0, 0, 0, ~0ull};
         unsigned long long* partial = reinterpret_cast<unsigned long long*>(scratch + l.partial);
         PinnedInfo pinned;
@@ -699,11 +947,11 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
             const unsigned grid = l.tiles < kInspectBlocks ? l.tiles : kInspectBlocks;
             if (small)
                 hipLaunchKernelGGL((inspect_kernel<kSmallItems>), dim3(grid), dim3(kSortThreads), 0, stream, src, ts, n, num_nodes, partial,
-                                   width_of(node_bits), hist, l.tiles);
+                                   low_bits, hist, l.tiles);
             else
                 hipLaunchKernelGGL((inspect_kernel<kLargeItems>), dim3(grid), dim3(kSortThreads), 0, stream, src, ts, n, num_nodes, partial,
-                                   width_of(node_bits), hist, l.tiles);
-            hipLaunchKernelGGL(fold_info_kernel, dim3(1), dim3(kSortThreads), 0, stream, partial, grid, d_info);
+                                   low_bits, hist, l.tiles);
+            hipLaunchKernelGGL(fold_info_kernel, dim3(1), dim3(kSortThreads), 0, stream, partial, grid, ts, n, d_info);
         }
         TASER_HIP_TRY(hipGetLastError());
         if (!pinned.words) TASER_HIP_TRY(hipMemcpyAsync(info, d_info, sizeof(info), hipMemcpyDeviceToHost, stream));
@@ -712,6 +960,12 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         if (pinned.words)
             for (int j = 0; j < 4; ++j) info[j] = __atomic_load_n(&pinned.words[j], __ATOMIC_RELAXED);
         if (info[0]) return taser_fail(TASER_E_RANGE, "tcsr_build: a src node id is outside [0, %d)", num_nodes);
+        in_node_digits = two_digits && !info[1] && info[3] - info[2] < (1ull << 32);
+        if (in_node_digits) {
+            const Items in = {nullptr, src, dst, ts, eid};
+            if (small) launch_sorted<kSmallItems>(l, in, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
+            else launch_sorted<kLargeItems>(l, in, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
+        }
         int ts_low = 0, ts_bits = 0;
         if (info[1]) {
             const unsigned long long differ = info[2] & ~info[3];   // not 0: the timestamps are not all equal
@@ -722,7 +976,7 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         // ---- one stable pass per digit; the last one writes the graph's own records
         const int key_bits = ts_bits + node_bits;
         const int width = width_of(key_bits);
-        const int passes = key_bits > 0 ? (key_bits + width - 1) / width : 1;
+        const int passes = in_node_digits ? 0 : key_bits > 0 ? (key_bits + width - 1) / width : 1;
         TaserRec* tmp_rec = reinterpret_cast<TaserRec*>(scratch + l.tmp_rec);
         Items in = {nullptr, src, dst, ts, eid};
         for (int pass = 0; pass < passes; ++pass) {
@@ -743,14 +997,14 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
             TaserRec* rec_out = ((passes - 1 - pass) & 1) ? tmp_rec : rec;
             int32_t* key_out = reinterpret_cast<int32_t*>(scratch + l.key[pass & 1]);
             // without timestamp digits the first digit is the one that inspect_kernel counted
-            const bool hist_known = pass == 0 && ts_bits == 0;
+            const bool hist_known = pass == 0 && ts_bits == 0 && low_bits == width;
             if (small) launch_pass<kSmallItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
             else launch_pass<kLargeItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
             in = Items{rec_out, key_out, nullptr, nullptr, nullptr};
             sorted_key = key_out;
         }
     }
-    {
+    if (!in_node_digits) {
         TaserProfileSpan span(stream, "tcsr_indptr");
         hipLaunchKernelGGL(indptr_kernel, dim3(blocks_for(n + 1, kThreads * 4)), dim3(kThreads), 0, stream, sorted_key, n, num_nodes, indptr);
     }
