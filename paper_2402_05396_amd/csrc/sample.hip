@@ -368,11 +368,11 @@ __device__ __forceinline__ void copy_wave_rows(const RowCopy& rc, const int32_t*
 // the most-recent finder on large hops that the kernel below does not take (lists of two entries, 32
 // slots, 160 000 roots: 26.2 us with one, 21.8 with two); the uniform and weighted finders, whose time
 // is mostly the arithmetic of their draws, gain nothing from them.
-// With ROWS (one root per group) a wavefront then also copies the table rows of the edges
-// it sampled into the hop's dense row output: the finder is bound by instruction issue and
+// With ROWS (one root per group; how many wave instructions of the copy are in flight) a wavefront then also copies
+// the table rows of the edges it sampled into the hop's dense row output: the finder is bound by instruction issue and
 // dependent reads, the copy by memory bandwidth, and in one kernel the wavefronts of a
 // compute unit that search overlap with those that copy.
-template <int POLICY, int G, int kRootsPerGroup, bool ROWS>
+template <int POLICY, int G, int kRootsPerGroup, int ROWS>
 __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
     const int64_t* __restrict__ indptr, const TaserRec* __restrict__ rec, const TaserTimeIndex index,
     const int32_t* __restrict__ roots, const int64_t* __restrict__ times, int64_t num_roots,
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
             if (sub == 0) o_count[q0 + r] = filled[r];
         }
     }
-    if (ROWS) {
+    if constexpr (ROWS > 0) {
         __shared__ int32_t eid_of_row[kThreads / kWave][kWave];   // per wave: k ids per group, slot order (kGroups * k <= 64)
         if (sub < k) eid_of_row[wave][group * k + sub] = slot[0].eid;
         // only this wave reads them back: its LDS operations complete in order
@@ -424,9 +424,7 @@ __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         int64_t roots_here = num_roots - wave_q0;
         if (roots_here > kGroups) roots_here = kGroups;
-        // wave instructions of the copy in flight: four where a wavefront has four roots' rows to move, two (and
-        // 28 registers fewer) where it has one or two roots
-        if (roots_here > 0) copy_wave_rows<(G == 16 ? 4 : 2)>(rows, eid_of_row[wave], (uint32_t)roots_here * (uint32_t)k, wave_q0 * k, lane);
+        if (roots_here > 0) copy_wave_rows<ROWS>(rows, eid_of_row[wave], (uint32_t)roots_here * (uint32_t)k, wave_q0 * k, lane);
     }
 }
 
@@ -1120,7 +1118,7 @@ __global__ __launch_bounds__(kThreads) void sample_hop_recent_quads_kernel(
     }
 }
 
-template <int POLICY, int G, int kRootsPerGroup, bool ROWS>
+template <int POLICY, int G, int kRootsPerGroup, int ROWS>
 void launch_hop_gr(const taser_tcsr* g, const int32_t* roots, const int64_t* times, int64_t n, int k,
                    uint64_t seed, uint32_t hop, int m, const uint32_t* edge_weight, const taser_hop_out& o,
                    const RowCopy& rows, hipStream_t stream) {
@@ -1135,9 +1133,11 @@ template <int POLICY, int G>
 void launch_hop_g(const taser_tcsr* g, const int32_t* roots, const int64_t* times, int64_t n, int k,
                   uint64_t seed, uint32_t hop, int m, const uint32_t* edge_weight, const taser_hop_out& o,
                   const RowCopy* rows, hipStream_t stream) {
-    if (rows) launch_hop_gr<POLICY, G, 1, true>(g, roots, times, n, k, seed, hop, m, edge_weight, o, *rows, stream);
-    else if (POLICY == TASER_RECENT && n >= 65536) launch_hop_gr<POLICY, G, 2, false>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
-    else launch_hop_gr<POLICY, G, 1, false>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
+    // wave instructions of the copy in flight: four where a wavefront has four roots' rows to move, two (and
+    // 28 registers fewer) where it has one or two roots
+    if (rows) launch_hop_gr<POLICY, G, 1, (G == 16 ? 4 : 2)>(g, roots, times, n, k, seed, hop, m, edge_weight, o, *rows, stream);
+    else if (POLICY == TASER_RECENT && n >= 65536) launch_hop_gr<POLICY, G, 2, 0>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
+    else launch_hop_gr<POLICY, G, 1, 0>(g, roots, times, n, k, seed, hop, m, edge_weight, o, RowCopy{}, stream);
 }
 
 // Lanes of a wavefront that serve one root.
@@ -1149,7 +1149,7 @@ int group_lanes(int policy, int k, int m) {
 template <int POLICY>
 void launch_hop(const taser_tcsr* g, const int32_t* roots, const int64_t* times, int64_t n, int k,
                 uint64_t seed, uint32_t hop, int m, const uint32_t* edge_weight,
-                const taser_hop_out& o, const RowCopy* rows, hipStream_t stream) {
+                const taser_hop_out& o, const RowCopy* rows, bool wave_per_root, hipStream_t stream) {
     static const char* const names[2][3] = {{"sample_hop_recent", "sample_hop_uniform", "sample_hop_weighted"},
                                             {"sample_rows_hop_recent", "sample_rows_hop_uniform", "sample_rows_hop_weighted"}};
     TaserProfileSpan span(stream, names[rows ? 1 : 0][POLICY]);
@@ -1166,7 +1166,8 @@ void launch_hop(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
                            times, n, g->num_nodes, k, magic_k, o.nbr, o.eid, o.ts, o.count);
         return;
     }
-    if (lanes == 16) launch_hop_g<POLICY, 16>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);
+    if (rows && wave_per_root) launch_hop_gr<POLICY, 64, 1, 8>(g, roots, times, n, k, seed, hop, m, edge_weight, o, *rows, stream);
+    else if (lanes == 16) launch_hop_g<POLICY, 16>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);
     else if (lanes == 32) launch_hop_g<POLICY, 32>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);
     else launch_hop_g<POLICY, 64>(g, roots, times, n, k, seed, hop, m, edge_weight, o, rows, stream);
 }
@@ -1212,6 +1213,14 @@ int check_sampling_arguments(const char* what, const taser_tcsr* g, const int32_
 // roots, 25 against 29 us with 16 lanes per root), beyond it up to 15 % slower.
 constexpr int64_t kFinderCopyMaxWaveBytes = 8192;
 
+// In a small hop a wavefront per root copies longer rows as well: one launch fewer, and with up to 8 KiB in flight a
+// wavefront a root's rows are a round or two of loads. Small is one round of wavefronts (127 registers: sixteen per
+// compute unit), of a last hop whose rows would otherwise be a launch of their own. One hop, k slots of `bytes`, us a
+// call with two launches and with one: 300 / 1 800 / 3 000 / 4 500 roots, most recent, 10 x 688: 11.8 8.6, 12.1 8.7, 11.9
+// 8.7, 14.7 14.5; uniform, 10 x 344: 12.4 8.7, 12.3 8.9, 12.0 9.2, 13.2 14.2; most recent, 20 x 1064: 12.3 10.1, 17.0 15.0,
+// 24.6 22.4, 33.5 35.9.
+constexpr int64_t kSmallHopRoots = 4096, kSmallHopWaveBytes = 24576;
+
 // All hops of one call. With `want`, hop h also leaves the table rows of its sampled edges in
 // want->out[h]: written by the hop kernel where the shapes allow it and the rows are short, else
 // by the plain gather launched after the last hop (same bytes either way), one launch for
@@ -1229,16 +1238,25 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
     int64_t n = num_roots;
     TaserGatherPart pending[TASER_MAX_HOPS];
     int n_pending = 0;
+    int64_t roots_of_last_hop = num_roots;
+    for (int h = 1; h < hops; ++h) roots_of_last_hop *= k;
     for (int h = 0; h < hops && n > 0; ++h) {
         // Can this hop's kernel write the rows itself? It copies per wavefront, in aligned 16-byte
         // pieces read at 4-byte alignment: rows, pitch and table must allow that, and the rows of
         // one wavefront's roots must be whole 16-byte pieces.
         RowCopy copy{};
         const RowCopy* rows = nullptr;
+        bool wave_per_root = false;
         if (want && policy != TASER_INVERSE_TIMESPAN) {
-            const int64_t wave_bytes = (int64_t)(kWave / group_lanes(policy, k, m)) * k * want->row_bytes;
+            int64_t wave_bytes = (int64_t)(kWave / group_lanes(policy, k, m)) * k * want->row_bytes;
+            int64_t most = kFinderCopyMaxWaveBytes;
+            if (wave_bytes > most && roots_of_last_hop <= kSmallHopRoots && (int64_t)k * want->row_bytes <= kSmallHopWaveBytes) {
+                wave_per_root = true;
+                wave_bytes = (int64_t)k * want->row_bytes;
+                most = kSmallHopWaveBytes;
+            }
             const uint64_t bits = (uint64_t)want->row_bytes | (uint64_t)want->pitch_bytes | (uint64_t)(uintptr_t)want->table;
-            if (want->row_bytes >= 16 && wave_bytes <= kFinderCopyMaxWaveBytes && (bits & 3) == 0 && (wave_bytes & 15) == 0 &&
+            if (want->row_bytes >= 16 && wave_bytes <= most && (bits & 3) == 0 && (wave_bytes & 15) == 0 &&
                 ((uintptr_t)want->out[h] & 15) == 0) {
                 const uint8_t* zeros = taser_gather::zero_chunk();
                 if (!zeros) return taser_fail(TASER_E_HIP, "sample_temporal_rows: the zero constant is not available on this device");
@@ -1250,8 +1268,8 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
             }
         }
         switch (policy) {
-            case TASER_RECENT: launch_hop<TASER_RECENT>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, stream); break;
-            case TASER_UNIFORM: launch_hop<TASER_UNIFORM>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, stream); break;
+            case TASER_RECENT: launch_hop<TASER_RECENT>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, wave_per_root, stream); break;
+            case TASER_UNIFORM: launch_hop<TASER_UNIFORM>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, wave_per_root, stream); break;
             case TASER_INVERSE_TIMESPAN: {
                 TaserProfileSpan span(stream, "sample_hop_inverse_timespan");
                 const int per_block = list_roots_per_block(g->num_entries, g->num_nodes, n);
@@ -1261,7 +1279,7 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
                                    (uint32_t)(seed >> 32), (uint32_t)h, out[h].nbr, out[h].eid, out[h].ts, out[h].count);
                 break;
             }
-            default: launch_hop<TASER_WEIGHTED>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, stream); break;
+            default: launch_hop<TASER_WEIGHTED>(g, cur_roots, cur_times, n, k, seed, (uint32_t)h, m, edge_weight, out[h], rows, wave_per_root, stream); break;
         }
         if (want && !rows) {
             uint8_t* to = static_cast<uint8_t*>(want->out[h]);

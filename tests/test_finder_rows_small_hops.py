@@ -1,0 +1,44 @@
+"""sample_temporal_rows on small hops: a wavefront per root copies the rows of its root's slots (and not one root more, nor
+where the rows of a root are too many bytes or no whole 16-byte pieces)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2402_05396_amd as T
+
+NODES, EVENTS = 700, 20_000
+
+
+def _graph():
+    rng = np.random.default_rng(4)
+    src = (np.minimum(rng.zipf(1.3, EVENTS), NODES) - 1).astype(np.int32)
+    ts = np.sort(rng.integers(0, 5_000, EVENTS)).astype(np.int64)
+    return src, rng.integers(0, NODES, EVENTS).astype(np.int32), ts, rng.permutation(EVENTS).astype(np.int32)
+
+
+ROOTS = [(1, 1), (5, 1), (4095, 1), (4096, 1), (4097, 1), (400, 2), (410, 2), (40, 3)]
+FINDERS = [(T.RECENT, 10, 0), (T.UNIFORM, 10, 0), (T.WEIGHTED, 10, 25), (T.RECENT, 64, 0), (T.UNIFORM, 33, 0), (T.RECENT, 1, 0)]
+ROWS = [(172, "float32", 0), (172, "float16", 4), (614, "float32", 2), (616, "float32", 0), (24, "float32", 1), (9000, "float16", 0)]
+CASES = [(*r, *f, *t) for r in ROOTS for f in FINDERS for t in ROWS if r[0] * f[1] ** r[1] * t[0] <= 60_000_000]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("roots,hops,policy,k,m,dim,dtype,pad", CASES)
+def test_rows_are_the_rows_of_the_sampled_edges(roots, hops, policy, k, m, dim, dtype, pad):
+    cols = _graph()
+    dev = lambda a: torch.from_numpy(a).cuda()
+    g, g_ref = T.tcsr_build(*map(dev, cols), NODES), oracle.tcsr_build(*cols, NODES)
+    rng = np.random.default_rng(roots)
+    q, t = rng.integers(-1, NODES, roots).astype(np.int32), rng.integers(-5, 5_010, roots).astype(np.int64)
+    table = torch.randn((EVENTS - 50, dim + pad), device="cuda").to(getattr(torch, dtype))[:, :dim]   # the last ids are outside: zero rows
+    w = rng.integers(1, 1000, EVENTS).astype(np.int32) if m else None
+    got, rows = T.sample_temporal_rows(g, dev(q), dev(t), k, hops, policy, 9, table, m=m, edge_weight=None if w is None else dev(w))
+    want = oracle.sample_temporal(g_ref, q, t, k, hops, policy, 9, m=m, edge_weight=None if w is None else w.astype(np.uint32))
+    for h in range(hops):
+        for f in ("nbr", "eid", "ts", "count"):
+            assert np.array_equal(got[h][f].cpu().numpy(), want[h][f]), (h, f)
+        eid = got[h]["eid"].reshape(-1).long()
+        ok = (eid >= 0) & (eid < table.shape[0])
+        expect = torch.where(ok[:, None], table[eid.clamp(0, table.shape[0] - 1)], torch.zeros((), dtype=table.dtype, device="cuda"))
+        assert torch.equal(rows[h].reshape(-1, dim), expect), h
