@@ -260,12 +260,12 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const int32_t* __restri
     move_sums(e, diff, lane, sum1, sum2);
 }
 
-// The whole update of a batch of at most 1 024 by one block: which position names an edge last is settled in
+// The whole update of a batch of at most 768 by one block: which position names an edge last is settled in
 // a hash table in LDS instead of the array of owners, so the chain of dependent reads is index -> score, in
-// one launch instead of two (us a call, million edges: 100 positions 3.4 -> 2.5, 600 4.3 -> 2.8, 1 024 4.4 -> 3.2).
-// With several positions per thread the random reads and adds of one compute unit outlast the second launch
-// (2 000 positions 4.4 -> 6.6).
-constexpr int kOneBlockThreads = 1024;
+// one launch instead of two (us a call, million edges: 100 positions 3.4 -> 2.5, 600 4.3 -> 2.8). The random reads and adds
+// of one compute unit take longer the more there are: by 8 blocks (next kernel) 600 / 800 / 1 000 positions are 2.5 /
+// 2.5 / 2.6, by one 2.4 / 2.7 / 3.1.
+constexpr int kOneBlockThreads = 1024, kOneBlockBatch = 768;
 
 __global__ __launch_bounds__(kOneBlockThreads) void update_one_block_kernel(const int32_t* __restrict__ idx, const uint32_t* __restrict__ value,
                                                                             int32_t b, uint32_t slots, int64_t n, uint32_t* __restrict__ score,
@@ -299,6 +299,79 @@ __global__ __launch_bounds__(kOneBlockThreads) void update_one_block_kernel(cons
         diff = (uint64_t)now - (uint64_t)old;
     }
     move_sums(e, diff, (int)(threadIdx.x & (kWave - 1)), sum1, sum2);
+}
+
+// The update of a batch of up to kClassBatch positions in one launch of several blocks: every block reads the whole
+// batch and takes the edges whose hash begins with its number, so that who names an edge last is settled inside a
+// block, as above, and no score is another block's. A block's table holds the batch even if all of it were its own. The level-2
+// sums' changes are added up per block first (a million edges share one). us a call, million edges, against the two
+// launches above: 1 500 positions 4.3 -> 2.8, 3 000 4.5 -> 3.8, 4 096 4.7 -> 4.1; with twice the table for 6 000 4.7 -> 6.3,
+// so larger batches stay with two.
+constexpr int kClassBatch = 4 * kOneBlockThreads;
+constexpr int kClassTops = 64;   // level-2 sums that fit the block's own (64 M edges)
+
+template <int kPer>   // positions per thread
+__global__ __launch_bounds__(kOneBlockThreads) void update_classes_kernel(const int32_t* __restrict__ idx, const uint32_t* __restrict__ value,
+                                                                          int32_t b, int class_bits, int64_t n, uint32_t* __restrict__ score,
+                                                                          uint64_t* __restrict__ sum1, uint64_t* __restrict__ sum2, int n2) {
+    constexpr uint32_t kSlots = 2 * kPer * kOneBlockThreads;
+    __shared__ int32_t edge[kSlots];                 // -1: free
+    __shared__ int32_t last[kSlots];                 // latest position that names it
+    __shared__ unsigned long long top_sum[kClassTops];
+    const int lane = threadIdx.x & (kWave - 1);
+    int32_t e[kPer];
+    uint32_t slot[kPer], old[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int32_t j = r * kOneBlockThreads + (int32_t)threadIdx.x;
+        e[r] = j < b ? idx[j] : -1;
+    }
+    for (uint32_t s = threadIdx.x; s < kSlots; s += kOneBlockThreads) {
+        edge[s] = -1;
+        last[s] = -1;
+    }
+    if (threadIdx.x < kClassTops) top_sum[threadIdx.x] = 0;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        slot[r] = edge_hash((uint32_t)e[r]);
+        if (e[r] >= n || slot[r] >> (32 - class_bits) != blockIdx.x) e[r] = -1;
+        old[r] = e[r] >= 0 ? score[e[r]] : 0;        // the block's own edges: every read lies before the barriers, every write after them
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        if (e[r] >= 0) {
+            slot[r] &= kSlots - 1;
+            for (;;) {   // at most half the slots are taken: ends at the edge or at a free one
+                const int32_t was = atomicCAS(&edge[slot[r]], -1, e[r]);
+                if (was == -1 || was == e[r]) break;
+                slot[r] = (slot[r] + 1) & (kSlots - 1);
+            }
+            atomicMax(&last[slot[r]], r * kOneBlockThreads + (int32_t)threadIdx.x);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int32_t j = r * kOneBlockThreads + (int32_t)threadIdx.x;
+        uint64_t diff = 0;
+        if (e[r] >= 0 && last[slot[r]] == j) {
+            const uint32_t now = value[j];
+            score[e[r]] = now;
+            diff = (uint64_t)now - (uint64_t)old[r];
+        }
+        if (diff) atomicAdd((unsigned long long*)&sum1[e[r] / kFan], (unsigned long long)diff);
+        const uint64_t changing = __ballot(diff != 0);
+        if (changing == 0) continue;                 // wave-uniform
+        const int leader = __ffsll((long long)changing) - 1;
+        const int32_t top = diff ? e[r] / (kFan * kFan) : -1;
+        const int32_t leader_top = __shfl(top, leader, kWave);
+        const uint64_t together = wave_sum64(top == leader_top ? diff : 0);
+        if (lane == leader) atomicAdd(&top_sum[leader_top], (unsigned long long)together);
+        else if (diff && top != leader_top) atomicAdd(&top_sum[top], (unsigned long long)diff);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < n2 && top_sum[threadIdx.x]) atomicAdd((unsigned long long*)&sum2[threadIdx.x], top_sum[threadIdx.x]);
 }
 
 void free_all(taser_selector* s) {
@@ -376,11 +449,16 @@ extern "C" int taser_selector_update(taser_selector* s, const int32_t* batch, co
     taser_clear_stale_hip_error();
     hipStream_t stream = (hipStream_t)hip_stream;
     TaserProfileSpan span(stream, "selector_update");
-    if (b <= kOneBlockThreads) {
+    if (b <= kOneBlockBatch) {
         uint32_t slots = 2;
         while (slots < 2 * (uint32_t)b) slots *= 2;
         hipLaunchKernelGGL(update_one_block_kernel, dim3(1), dim3(kOneBlockThreads), 0, stream, batch, new_scores, (int32_t)b, slots, s->n, s->score,
                            s->sum1, s->sum2);
+    } else if (b <= kClassBatch && s->n2 <= kClassTops) {
+        const int bits = b <= 2048 ? 3 : 4;   // about 250 positions a block
+        const auto kernel = b <= 2048 ? update_classes_kernel<2> : update_classes_kernel<4>;
+        hipLaunchKernelGGL(kernel, dim3(1u << bits), dim3(kOneBlockThreads), 0, stream, batch, new_scores, (int32_t)b, bits, s->n, s->score,
+                           s->sum1, s->sum2, (int)s->n2);
     } else {
         const unsigned blocks = (unsigned)((b + kThreads - 1) / kThreads);
         hipLaunchKernelGGL(claim_kernel, dim3(blocks), dim3(kThreads), 0, stream, batch, b, s->n, s->owner);
