@@ -502,13 +502,6 @@ template <bool NEAR> __device__ __forceinline__ uint32_t delta_of(const ListQuer
     return !NEAR && p < q.ones ? 0xFFFFFFFFu : q.t_low - low;
 }
 
-// What a wave wrote to LDS for itself alone can be read by its other lanes: its LDS operations complete in order.
-__device__ __forceinline__ void own_lds_ready() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // The sums over the wave of eight 32-bit values per lane, value l % 8 in lane l: three exchanges in which a lane
 // keeps half of its values and adds the other lane's half of the same ones, then the eighths of the wave.
 __device__ __forceinline__ uint32_t wave_sums_of_8(const uint32_t (&a)[8], int lane) {

@@ -182,4 +182,11 @@ template <int G> __device__ __forceinline__ int group_weighted_picks(uint32_t w,
     return mine;
 }
 
+// What a wave left in LDS for its own lanes can be read by them: its LDS operations complete in order.
+__device__ __forceinline__ void own_lds_ready() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 }  // namespace

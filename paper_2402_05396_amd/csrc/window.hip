@@ -8,8 +8,10 @@
 // IE[j][l] = 1 if u_j = u_l. The second draw of Alg. 1 then selects by one
 // weight per (root, candidate).
 //
-// Both kernels use a group of G = 16, 32 or 64 lanes per root (G >= m), one
-// lane per candidate.
+// The kernels use a group of G = 16, 32 or 64 lanes per root (G >= m), one lane per candidate; the
+// selection for many roots eight lanes per root.
+#include <type_traits>
+
 #include "sampling_device.h"
 #include "taser_internal.h"
 
@@ -159,6 +161,165 @@ __global__ __launch_bounds__(kThreads) void select_weighted_kernel(
     if (live && sub == 0) out_count[q] = filled;
 }
 
+// ---- octets: eight lanes per root, eight roots per wave -----------------------------------------------------
+// With a lane per candidate a wave of 32-lane groups spends the instructions of every draw on two roots. Here lane
+// `sub` of a root's octet holds its candidates sub * C to sub * C + C - 1, and a wave's instructions serve eight. All
+// exchanges are DPP moves inside rows of sixteen lanes: neighbors, pairs of neighbors (quad_perm), and the other quad of
+// the octet (row_half_mirror, where the quad's lanes agree).
+template <typename T, int CTRL> __device__ __forceinline__ T lanes_take(T v) {
+    if constexpr (sizeof(T) == 8) return (T)dpp_take64<CTRL, 0xf>((uint64_t)v);
+    else return (T)dpp_take32<CTRL, 0xf>((uint32_t)v);
+}
+template <typename T> __device__ __forceinline__ T octet_sum(T v) {
+    v += lanes_take<T, 0xB1>(v);
+    v += lanes_take<T, 0x4E>(v);
+    return v + lanes_take<T, 0x141>(v);
+}
+template <typename T> __device__ __forceinline__ T octet_max(T v) {
+    T o = lanes_take<T, 0xB1>(v);
+    v = v > o ? v : o;
+    o = lanes_take<T, 0x4E>(v);
+    v = v > o ? v : o;
+    o = lanes_take<T, 0x141>(v);
+    return v > o ? v : o;
+}
+// The value of the octet's lane AT.
+template <int AT, typename T> __device__ __forceinline__ T octet_get(T v, int sub) {
+    const T quad = lanes_take<T, (AT & 3) * 0x55>(v), other = lanes_take<T, 0x141>(quad);
+    return (sub >> 2) == (AT >> 2) ? quad : other;
+}
+__device__ __forceinline__ uint32_t scaled_draw(uint64_t u, uint32_t total) { return mulhi_64x32(u, total); }
+__device__ __forceinline__ uint64_t scaled_draw(uint64_t u, uint64_t total) { return __umul64hi(u, total); }
+
+// One draw: `run` the running sums of the weights still in play, x below their total. Returns the candidate whose
+// running sum first exceeds x (8 C where there is none), and takes it out.
+template <int C, typename T> __device__ __forceinline__ uint32_t octet_draw(T (&run)[C], T& total, T x) {
+    // entries that do not exceed x come first: their number is the candidate, and its weight what lies between the
+    // largest of their sums and the smallest of the others'
+    uint32_t below = 0;
+    T low = 0, high = ~(T)0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        below += run[i] <= x ? 1u : 0u;
+        low = run[i] <= x ? run[i] : low;
+    }
+#pragma unroll
+    for (int i = C - 1; i >= 0; --i) high = run[i] > x ? run[i] : high;
+    below = octet_sum(below);
+    low = octet_max(low);
+    high = (T)~octet_max((T)~high);
+    const T taken = below < 8u * C ? high - low : (T)0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) run[i] -= run[i] > x ? taken : (T)0;
+    total -= taken;
+    return below;
+}
+
+// k successive draws without replacement for every octet: draw j's candidate (-1 once nothing is left) goes to
+// picks[j], which is the octet's own. All lanes of the wave must call it.
+template <int C, typename T>
+__device__ __forceinline__ void octet_picks(const uint32_t (&w)[C], int k, uint32_t seed_lo, uint32_t seed_hi, uint32_t hop, uint64_t root, int sub,
+                                            int8_t* picks) {
+    T run[C], sum = 0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) run[i] = sum += w[i];
+    T upto = sum;    // over the octet's lanes up to this one
+    T o = lanes_take<T, 0x111>(upto);
+    upto += sub >= 1 ? o : (T)0;
+    o = lanes_take<T, 0x112>(upto);
+    upto += sub >= 2 ? o : (T)0;
+    o = lanes_take<T, 0x114>(upto);
+    upto += sub >= 4 ? o : (T)0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) run[i] += upto - sum;
+    T total = octet_max(upto);
+#pragma unroll 1
+    for (int j0 = 0; j0 < k; j0 += 8) {
+        const uint64_t u = draw64_wide(seed_lo, seed_hi, hop, root, (uint32_t)(j0 + sub));   // lane sub's is draw j0 + sub
+        auto one = [&](auto at) {
+            constexpr int AT = decltype(at)::value;
+            if (j0 + AT < k) {   // uniform
+                const T x = octet_get<AT>(scaled_draw(u, total), sub);
+                const uint32_t pick = octet_draw<C, T>(run, total, x);
+                if (sub == AT) picks[j0 + AT] = pick < 8u * C ? (int8_t)pick : (int8_t)-1;
+            }
+        };
+        one(std::integral_constant<int, 0>{});
+        one(std::integral_constant<int, 1>{});
+        one(std::integral_constant<int, 2>{});
+        one(std::integral_constant<int, 3>{});
+        one(std::integral_constant<int, 4>{});
+        one(std::integral_constant<int, 5>{});
+        one(std::integral_constant<int, 6>{});
+        one(std::integral_constant<int, 7>{});
+    }
+}
+
+// The same for whatever weights: in 32 bits where all sums of the wave's roots fit them.
+template <int C>
+__device__ __forceinline__ void octet_weighted_picks(const uint32_t (&w)[C], int k, bool active, uint32_t seed_lo, uint32_t seed_hi, uint32_t hop,
+                                                     uint64_t root, int sub, int8_t* picks) {
+    uint32_t any = 0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) any |= w[i];
+    if (!__ballot(active && any >= (1u << 26))) octet_picks<C, uint32_t>(w, k, seed_lo, seed_hi, hop, root, sub, picks);   // at most 64 of them
+    else octet_picks<C, uint64_t>(w, k, seed_lo, seed_hi, hop, root, sub, picks);
+}
+
+// The same for many roots: an octet of lanes per root draws (octet_weighted_picks); the slots of a wave's eight roots
+// are then written flat, so that all lanes load and store whatever k is. Bound by vector instructions like the other one, but
+// with fewer of them where that one has one or two roots per wave; its chain of dependent steps is longer, so it is for
+// numbers of roots that fill the chip, and not for windows that are all kept. us of the other one / of this one, 2 000,
+// 8 000, 40 000 roots: 10 of 16 candidates 3.9 4.3, 4.1 4.7, 9.0 8.9; 10 of 25 3.9 4.6, 5.0 4.9, 13.7 10.4; 24 of 25
+// 5.8 6.8, 7.9 7.3, 23.8 18.1; 20 of 49 5.5 7.7, 9.8 8.1, 33.4 21.0; 64 of 64 2.7 5.6, 4.2 6.5, 16.6 17.8.
+constexpr int64_t kOctetRoots = 8000;
+constexpr int kSelectRoots = kWave / 8;   // of a wave
+template <int C>
+__global__ __launch_bounds__(kThreads) void select_weighted_octets_kernel(
+    const uint32_t* __restrict__ weight, const int32_t* __restrict__ count, int64_t num_roots, int m, int k, uint32_t magic_k,
+    uint32_t seed_lo, uint32_t seed_hi, uint32_t hop, int32_t* __restrict__ sel, int32_t* __restrict__ out_count,
+    const int32_t* __restrict__ c_nbr, const int32_t* __restrict__ c_eid, const int64_t* __restrict__ c_ts,
+    int32_t* __restrict__ k_nbr, int32_t* __restrict__ k_eid, int64_t* __restrict__ k_ts) {
+    __shared__ int8_t picks[kThreads / kWave][kSelectRoots * TASER_MAX_K];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, octet = lane >> 3, sub = lane & 7;
+    const int64_t q0 = ((int64_t)blockIdx.x * (kThreads / kWave) + wave) * kSelectRoots, q = q0 + octet;   // the wave's first root, the octet's
+    if (q0 >= num_roots) return;
+    const int here = num_roots - q0 < kSelectRoots ? (int)(num_roots - q0) : kSelectRoots;
+    int c = 0;
+    if (octet < here) {
+        c = count[q];
+        c = c < 0 ? 0 : (c > m ? m : c);
+    }
+    uint32_t w[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        w[i] = 0;
+        if (sub * C + i < c) w[i] = weight[q * m + sub * C + i];
+    }
+    if (__ballot(c > k)) octet_weighted_picks<C>(w, k, c > k, seed_lo, seed_hi, hop, (uint64_t)q, sub, picks[wave] + octet * k);
+    if (octet < here && sub == 0) out_count[q] = c > k ? k : c;
+    own_lds_ready();
+    const uint32_t slots = (uint32_t)(here * k);
+    for (uint32_t s0 = 0; s0 < slots; s0 += kWave) {
+        const uint32_t s = s0 + (uint32_t)lane;
+        uint32_t r = k == 1 ? s : __umulhi(s, magic_k);        // exact: s < 2^10, k <= 64
+        const uint32_t j = s - r * (uint32_t)k;
+        if (r > kSelectRoots - 1) r = kSelectRoots - 1;        // past the wave's slots
+        const int of_root = __shfl(c, (int)r * 8, kWave);      // (all lanes take part)
+        if (s >= slots) continue;
+        const int pick = of_root > k ? picks[wave][s] : (int)j < of_root ? (int)j : -1;
+        const int64_t at = q0 * k + s;
+        sel[at] = pick;
+        if (k_nbr) {
+            const bool ok = pick >= 0;
+            const int64_t from = (q0 + r) * m + (ok ? pick : 0);
+            k_nbr[at] = ok ? c_nbr[from] : -1;
+            k_eid[at] = ok ? c_eid[from] : -1;
+            k_ts[at] = ok ? c_ts[from] : 0;
+        }
+    }
+}
+
 template <int G> unsigned grid_for(int64_t n) {
     constexpr int roots_per_block = (kThreads / kWave) * (kWave / G);
     return (unsigned)((n + roots_per_block - 1) / roots_per_block);
@@ -214,7 +375,13 @@ extern "C" int taser_select_weighted(const uint32_t* weight, const int32_t* coun
     const uint32_t s_lo = (uint32_t)seed, s_hi = (uint32_t)(seed >> 32);
     const int lanes = m > k ? m : k;
     TaserProfileSpan span(stream, "select_weighted");
-    if (lanes <= 16)
+    if (m > 16 && m > k && num_roots >= kOctetRoots) {
+        const auto kernel = m <= 32 ? select_weighted_octets_kernel<4> : select_weighted_octets_kernel<8>;
+        constexpr int roots_per_block = kThreads / kWave * kSelectRoots;
+        const uint32_t magic_k = k > 1 ? (uint32_t)((((uint64_t)1 << 32) + (uint32_t)k - 1) / (uint32_t)k) : 0u;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((num_roots + roots_per_block - 1) / roots_per_block)), dim3(kThreads), 0, stream, weight, count,
+                           num_roots, m, k, magic_k, s_lo, s_hi, hop, sel, out_count, c_nbr, c_eid, c_ts, k_nbr, k_eid, k_ts);
+    } else if (lanes <= 16)
         hipLaunchKernelGGL((select_weighted_kernel<16>), dim3(grid_for<16>(num_roots)), dim3(kThreads), 0, stream, weight, count, num_roots, m, k, s_lo, s_hi, hop, sel, out_count, c_nbr, c_eid, c_ts, k_nbr, k_eid, k_ts);
     else if (lanes <= 32)
         hipLaunchKernelGGL((select_weighted_kernel<32>), dim3(grid_for<32>(num_roots)), dim3(kThreads), 0, stream, weight, count, num_roots, m, k, s_lo, s_hi, hop, sel, out_count, c_nbr, c_eid, c_ts, k_nbr, k_eid, k_ts);
