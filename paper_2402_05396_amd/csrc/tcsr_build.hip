@@ -23,6 +23,7 @@
 #include <new>
 
 #include "pinned_info.h"
+#include "sampling_device.h"
 #include "taser_internal.h"
 
 namespace {
@@ -301,14 +302,14 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan_kernel(uint32_t* __rest
     if (r1 > num_tiles) r1 = num_tiles;
     if (!live || r0 > r1) r0 = r1;
     uint32_t* const a = hist + bin;
-    uint32_t sum = 0;
+    uint32_t sum = 0, v[kAhead];
     for (uint32_t r = r0; r < r1; r += kAhead) {
-        uint32_t v[kAhead];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) v[u] = r + u < r1 ? a[(size_t)(r + u) << bits] : 0u;
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) sum += v[u];
     }
+    const bool held = per_group <= (uint32_t)kAhead;   // uniform: v is still all of the group's rows
     // exclusive over the groups: a wave holds 64 / kScanCols of them, kScanCols lanes apart
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     uint32_t inc = sum;
@@ -328,9 +329,10 @@ __global__ __launch_bounds__(kScanThreads) void bin_scan_kernel(uint32_t* __rest
     }
     if (live && group == 0) total[bin] = all;
     for (uint32_t r = r0; r < r1; r += kAhead) {
-        uint32_t v[kAhead];
+        if (!held) {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) v[u] = r + u < r1 ? a[(size_t)(r + u) << bits] : 0u;
+            for (int u = 0; u < kAhead; ++u) v[u] = r + u < r1 ? a[(size_t)(r + u) << bits] : 0u;
+        }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) {
             if (r + u < r1) a[(size_t)(r + u) << bits] = run;
@@ -410,11 +412,7 @@ __global__ __launch_bounds__(kThreads) void chunk_scan_kernel(uint32_t* __restri
 // written before and read after the one barrier inside.
 __device__ __forceinline__ uint32_t scan_digits(uint32_t own, uint32_t* wave_sum) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    uint32_t inc = own;
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t y = __shfl_up(inc, d, kWave);
-        if (lane >= d) inc += y;
-    }
+    const uint32_t inc = wave_inclusive_scan32(own);
     if (lane == kWave - 1) wave_sum[wave] = inc;
     __syncthreads();
     uint32_t before = 0;
