@@ -792,7 +792,7 @@ inline int items_for(int64_t n) { return n <= kSmallEntries ? kSmallItems : kLar
 
 struct Layout {
     size_t indptr, rec, level[kTimeIndexLevels], storage;                                   // what the graph keeps
-    size_t src, dst, ts, eid, tmp_rec, key[2], hist, total[2], chunk_sum, partial, info, scratch;         // what the build needs
+    size_t src, dst, ts, eid, tmp_rec, key[2], hist, total, chunk_sum, partial, info, scratch;         // what the build needs
     int64_t level_len[kTimeIndexLevels];
     uint32_t tiles;
 };
@@ -826,7 +826,7 @@ Layout layout_of(int64_t n, int32_t num_nodes, bool copy_input) {
     l.key[0] = take((size_t)n * sizeof(int32_t));
     l.key[1] = take((size_t)n * sizeof(int32_t));
     l.hist = take((size_t)kBins * l.tiles * sizeof(uint32_t));
-    for (int i = 0; i < 2; ++i) l.total[i] = take(kBins * sizeof(uint32_t));
+    l.total = take(kBins * sizeof(uint32_t));
     l.chunk_sum = take((size_t)kMaxChunks * kBins * sizeof(uint32_t));
     l.partial = take((size_t)kInspectBlocks * 4 * sizeof(unsigned long long));
     l.info = take(4 * sizeof(unsigned long long));
@@ -857,11 +857,13 @@ void launch_scan(const Layout& l, int bits, uint32_t* hist, uint32_t* total, uin
 
 // Time-sorted input whose node digit of `low_bits` bits is counted in hist and whose others are `rest_bits`: both passes
 // and indptr.
+static_assert(kInspectBlocks * 4 * sizeof(unsigned long long) >= kBins * sizeof(uint32_t), "total[1] of launch_sorted");
 template <int kItems>
 void launch_sorted(const Layout& l, const Items& in, int64_t ts_first, int64_t n, int32_t num_nodes, int low_bits, int rest_bits, uint8_t* scratch,
                    TaserRec* rec, int64_t* level1, int64_t* indptr, hipStream_t stream) {
     uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
-    uint32_t* total[2] = {reinterpret_cast<uint32_t*>(scratch + l.total[0]), reinterpret_cast<uint32_t*>(scratch + l.total[1])};
+    // the second digit's totals go where the inspection's words were, which have been read
+    uint32_t* total[2] = {reinterpret_cast<uint32_t*>(scratch + l.total), reinterpret_cast<uint32_t*>(scratch + l.partial)};
     uint32_t* chunk_sum = reinterpret_cast<uint32_t*>(scratch + l.chunk_sum);
     NarrowRec* narrow = reinterpret_cast<NarrowRec*>(scratch + l.tmp_rec);   // 12 of its 16 bytes per entry
     uint16_t* rest = reinterpret_cast<uint16_t*>(scratch + l.key[0]);
@@ -922,7 +924,7 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
     TaserRec* rec = reinterpret_cast<TaserRec*>(storage + l.rec);
     int64_t* level1 = reinterpret_cast<int64_t*>(storage + l.level[0]);
     uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
-    uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total[0]);
+    uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total);
     uint32_t* chunk_sum = reinterpret_cast<uint32_t*>(scratch + l.chunk_sum);
     const int32_t* sorted_key = src;
     bool in_node_digits = false;   // launch_sorted did it all
