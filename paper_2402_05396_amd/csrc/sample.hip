@@ -466,23 +466,26 @@ constexpr int kListWaves = kListThreads / kWave;
 
 constexpr int kMostNearTiles = kMaxTiles / 2, kMostFarTiles = kMaxTiles - kMostNearTiles;
 
-// What is known about a root. Its valid entries are cut into a far part, [0, first), whose weights are below
-// w_end, and a near part, [first, cnt). The far part is described by its weights: the entries of weight w are
-// one run of the list, found by a search, so that a lane's work is a weight and not an entry. The near part is
-// read entry by entry, in rows of 64.
+// What is known about a root. Its valid entries are cut into up to three parts: the entries 2^32 and more before the
+// query, [0, far_begin), where they are many, which all weigh 1; a far part, [far_begin, first), whose weights are
+// below w_end; and a near part, [first, cnt). The first part is one tile that is never read: its sum is its number of
+// entries. The far part is described by its weights: the entries of weight w are one run of the list, found by a search,
+// so that a lane's work is a weight and not an entry. The near part is read entry by entry, in rows of 64.
 struct ListQuery {
     uint32_t lo, cnt;            // its list begins at record lo; cnt valid entries
     uint32_t ones;               // entries [0, ones) are 2^32 or more before the query
     uint32_t t_low;              // low word of the query time
+    uint32_t far_begin;          // first entry of the far part: `ones` where they are a tile of their own, else 0
     uint32_t first;              // first entry of the near part
     uint32_t tile_shift;         // near part: log2 of the rows of a tile
     uint32_t stride;             // far part: entries between two samples
     uint32_t alone;              // one wavefront's work
-    uint32_t w_first, w_end;     // far part: weight of the list's first entry, and the first weight of the near part
+    uint32_t w_first, w_end;     // far part: weight of its first entry, and the first weight of the near part
     uint32_t batches;            // batches of kBatch weights per far tile
-    uint32_t far_tiles, tiles;   // far tiles come first
+    uint32_t far_tiles, tiles;   // tiles before the near part's, the one of the `ones` included, and all of them
     uint32_t k;                  // the call's
     uint32_t near;               // every delta of the near part is below 2^24 (then none of it is among the `ones`)
+    __device__ uint32_t ones_tiles() const { return far_begin ? 1u : 0u; }   // tile 0 is the entries before far_begin
 };
 struct __attribute__((packed, aligned(4))) Low4 {
     uint32_t w[4];
@@ -492,7 +495,7 @@ constexpr uint32_t kBatch = kWave - 1;   // weights of a far batch: the last lan
 // A query as the whole wave read it from LDS, in scalar registers.
 __device__ __forceinline__ ListQuery uniform(const ListQuery& v) {
     auto get = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
-    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.first), get(v.tile_shift), get(v.stride), get(v.alone),
+    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.far_begin), get(v.first), get(v.tile_shift), get(v.stride), get(v.alone),
                      get(v.w_first), get(v.w_end),
                      get(v.batches), get(v.far_tiles), get(v.tiles), get(v.k), get(v.near)};
 }
@@ -654,7 +657,7 @@ __device__ __forceinline__ int pick_in_row(const ListQuery& q, uint32_t low, uin
 }
 
 // Far part: where the entries of weight w and more begin, that is how many entries have a delta above
-// floor(2^32 / w). w_first is the weight of entry 0. The samples (the deltas of every stride-th entry, in LDS) say between
+// floor(2^32 / w). w_first is the weight of the part's first entry. The samples (the deltas of every stride-th entry, in LDS) say between
 // which two, the list itself the rest: three probes a step, sixteen neighbors in the last. Probes behind the far
 // part read an entry of the near part or the list's last one, which is not above unless the whole list is.
 __device__ __forceinline__ uint32_t run_begin(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t w) {
@@ -695,7 +698,7 @@ __device__ __forceinline__ uint32_t run_begin(const ListQuery& q, const uint32_t
         for (int i = 0; i < half; ++i) d[i] = (upper & d[half + i]) | (~upper & d[i]);
     }
     at += c + (q.t_low - d[0] > most ? 1u : 0u);
-    return w <= q.w_first ? 0u : w >= q.w_end || at > q.first ? q.first : at;
+    return w <= q.w_first ? q.far_begin : w >= q.w_end || at > q.first ? q.first : at;
 }
 
 // The runs of one batch of a far tile: lane l < kBatch has the entries [begin, end) of weight w.
@@ -712,6 +715,8 @@ __device__ __forceinline__ Runs far_runs(const ListQuery& q, const uint32_t* __r
 }
 
 __device__ __forceinline__ uint64_t far_tile_weight(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t tile, int lane) {
+    if (tile < q.ones_tiles()) return q.far_begin;
+    tile -= q.ones_tiles();
     uint64_t s = 0;
     #pragma unroll 1
     for (uint32_t b = tile * q.batches; b < (tile + 1u) * q.batches; ++b) {
@@ -721,9 +726,24 @@ __device__ __forceinline__ uint64_t far_tile_weight(const ListQuery& q, const ui
     return wave_sum64(s);
 }
 
+// Entry number nth of a run that begins at `begin`, entries picked by the draws before number j left out.
+__device__ __forceinline__ uint32_t pick_in_run(uint32_t begin, uint32_t nth, int j, uint32_t my_pick, int lane) {
+    uint32_t pick = begin + nth;
+    for (;;) {   // ends: pick only grows, and is at most begin + nth + j
+        const uint32_t skipped = (uint32_t)__popcll(__ballot(lane < j && my_pick >= begin && my_pick <= pick));
+        if (begin + nth + skipped == pick) return pick;
+        pick = begin + nth + skipped;
+    }
+}
+
 // As pick_in_row, for a whole far tile: returns the entry.
 __device__ __forceinline__ uint32_t pick_in_far_tile(const ListQuery& q, const uint32_t* __restrict__ low, const uint32_t* sample, uint32_t tile,
                                                      uint64_t x, uint64_t before, int j, uint32_t my_pick, int lane, uint64_t& pick_w) {
+    if (tile < q.ones_tiles()) {   // (tile 0, before which there is nothing)
+        pick_w = 1;
+        return pick_in_run(0u, (uint32_t)x, j, my_pick, lane);
+    }
+    tile -= q.ones_tiles();
     #pragma unroll 1
     for (uint32_t b = tile * q.batches; b < (tile + 1u) * q.batches; ++b) {
         const Runs r = far_runs(q, low, sample, b, lane);
@@ -741,14 +761,8 @@ __device__ __forceinline__ uint32_t pick_in_far_tile(const ListQuery& q, const u
             const uint32_t begin = (uint32_t)__builtin_amdgcn_readlane((int)r.begin, at);
             const uint64_t rest = x - before - (at ? wave_get64(inc, at - 1) : 0);
             const uint32_t nth = (rest >> 32) ? (uint32_t)(rest / w) : (uint32_t)rest / w;   // of the run's entries that are left
-            uint32_t pick = begin + nth;
-            for (;;) {   // ends: pick only grows, and is at most begin + nth + j
-                const uint32_t skipped = (uint32_t)__popcll(__ballot(lane < j && my_pick >= begin && my_pick <= pick));
-                if (begin + nth + skipped == pick) break;
-                pick = begin + nth + skipped;
-            }
             pick_w = w;
-            return pick;
+            return pick_in_run(begin, nth, j, my_pick, lane);
         }
         before += wave_get64(inc, kWave - 1);
     }
@@ -829,6 +843,10 @@ __device__ __forceinline__ void sum_tiles(const ListQuery& q, const uint32_t* __
 // entries), and the shortest list that is looked at for it.
 constexpr float kRunEntries = 12.0f;
 constexpr uint32_t kFarEntries = 512;
+// Entries 2^32 and more before the query from which they are a tile of their own: a row of them. Read like any others, a list
+// of a million entries of which 50 are younger took 0.39 ms for 200 roots, so 0.010; 4 000 roots over lists of 1 000 entries,
+// 1 % of them younger, ten draws 28.9 us, so 20.0 (with a line at 256 entries the same, at 1 024 28.9).
+constexpr uint32_t kManyOnes = 64;
 constexpr uint32_t kWaveRows = 48, kFewRows = 8;   // a list of no more rows is one wavefront's work, in a block of its own and else
 
 // Roots per block of kListWaves wavefronts. With as many roots as wavefronts none of these is idle while lists are
@@ -855,24 +873,30 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
     uint64_t longest = (uint64_t)t - (uint64_t)rec[lo].ts;   // of all deltas
     // delta >= 2^32 is ts < t - (2^32 - 1); t is at least 2^32 above the smallest timestamp here
     if (longest >> 32) q.ones = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - 0xFFFFFFFFll, 0, lane);
+    if (q.ones >= kManyOnes) {
+        q.far_begin = q.first = q.ones;
+        q.far_tiles = 1;
+    }
+    const uint32_t rest = cnt - q.far_begin;
+    if (q.far_begin && rest >= kFarEntries) longest = (uint64_t)t - (uint64_t)rec[lo + q.ones].ts;
     if (cnt - q.ones >= kFarEntries && longest > kLastLargeDelta) {
-        const float every = (float)longest / (float)cnt;       // time between two entries
+        const float every = (float)longest / (float)rest;      // time between two entries
         float from = __builtin_sqrtf(kRunEntries * 4294967296.0f * every);   // around it a weight has kRunEntries entries
         if (from < (float)(kLastLargeDelta + 1u)) from = (float)(kLastLargeDelta + 1u);
         const uint32_t w_first = longest >> 32 ? 1u : quotient_of_delta<false>((uint32_t)longest);
         uint32_t w_end = (uint32_t)(4294967296.0f / from);
         if (w_end > kSmallWeight) w_end = kSmallWeight;
-        const float far = (float)cnt * (1.0f - from / (float)longest);   // entries, were they spread evenly
+        const float far = (float)rest * (1.0f - from / (float)longest);  // entries, were they spread evenly
         if (w_end > w_first && far > kRunEntries * (float)(w_end - w_first) + 1024.0f) {
             // weights below w_end are deltas above floor(2^32 / w_end), which is less than `longest`
             const uint32_t first = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - (int64_t)weight_of_delta(w_end), 0, lane);
-            if (first / (uint32_t)kRunEntries > w_end - w_first) {
+            if ((first - q.far_begin) / (uint32_t)kRunEntries > w_end - w_first) {
                 q.first = first;
                 q.w_first = w_first;
                 q.w_end = w_end;
                 const uint32_t batches = (w_end - w_first + kBatch - 1) / kBatch;
-                q.batches = (batches + kMostFarTiles - 1) / kMostFarTiles;
-                q.far_tiles = (batches + q.batches - 1) / q.batches;
+                q.batches = (batches + kMostFarTiles - 2) / (kMostFarTiles - 1);   // a tile is left for the `ones`
+                q.far_tiles = q.ones_tiles() + (batches + q.batches - 1) / q.batches;
                 q.stride = (first - q.ones + kSamples - 1) / kSamples;
                 longest = first < cnt ? (uint64_t)t - (uint64_t)rec[lo + first].ts : 1;
             }
@@ -931,7 +955,7 @@ __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8)
         } else {
             const ListQuery q = uniform(plan_list(rec, index, lo, hi, t, (uint32_t)cnt, k, per_block == 1 ? kFewRows : kWaveRows, lane));
             if (lane == 0) query[wave] = q;
-            if (q.far_tiles) {
+            if (q.far_tiles > q.ones_tiles()) {
                 uint32_t s[kSamples / kWave];
 #pragma unroll
                 for (uint32_t i = 0; i < kSamples / kWave; ++i) {
