@@ -459,12 +459,10 @@ __device__ __forceinline__ uint64_t weight_of_delta(uint32_t delta) {
     return w > 1u ? w : 1u;
 }
 
-constexpr int kMaxTiles = 4 * kWave;              // tile sums per root
+constexpr int kMaxTiles = 16 * kWave;             // tile sums of a block, divided among its roots
 constexpr int kSamples = 512;                     // of a far part, per root
 constexpr int kListThreads = 256;                 // block of the finder that reads whole lists
 constexpr int kListWaves = kListThreads / kWave;
-
-constexpr int kMostNearTiles = kMaxTiles / 2, kMostFarTiles = kMaxTiles - kMostNearTiles;
 
 // What is known about a root. Its valid entries are cut into up to three parts: the entries 2^32 and more before the
 // query, [0, far_begin), where they are many, which all weigh 1; a far part, [far_begin, first), whose weights are
@@ -782,7 +780,7 @@ __device__ __forceinline__ uint32_t draw_entries(const ListQuery& q, const uint3
     for (int g = 0; g < groups; ++g) {
         const uint32_t tile = (uint32_t)(g * kWave + lane);
         const uint64_t inc = wave_inclusive_scan64(tile < q.tiles ? tile_sum[tile] : 0);
-        tile_sum[tile] = inc;               // (kMaxTiles is a multiple of kWave)
+        tile_sum[tile] = inc;               // (every root has a multiple of kWave)
         total += wave_get64(inc, kWave - 1);
         if (lane >= g) group_run = total;   // lane g: the sum of the groups up to g; beyond the last one: all
     }
@@ -861,9 +859,9 @@ int list_roots_per_block(int64_t entries, int64_t nodes, int64_t roots) {
     return roots < 6000 ? 1 : roots < 12000 ? 2 : 4;
 }
 
-// How a list of cnt > k valid entries is cut up. By one wavefront.
+// How a list of cnt > k valid entries is cut up, into at most max_tiles tiles. By one wavefront.
 __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec, const TaserTimeIndex& index, int64_t lo, int64_t hi,
-                                               int64_t t, uint32_t cnt, int k, uint32_t alone_rows, int lane) {
+                                               int64_t t, uint32_t cnt, int k, uint32_t alone_rows, uint32_t max_tiles, int lane) {
     ListQuery q = {};
     q.lo = (uint32_t)lo;
     q.cnt = cnt;
@@ -895,7 +893,8 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
                 q.w_first = w_first;
                 q.w_end = w_end;
                 const uint32_t batches = (w_end - w_first + kBatch - 1) / kBatch;
-                q.batches = (batches + kMostFarTiles - 2) / (kMostFarTiles - 1);   // a tile is left for the `ones`
+                const uint32_t most = max_tiles / 2u - 1u;     // (a tile is left for the `ones`)
+                q.batches = (batches + most - 1u) / most;
                 q.far_tiles = q.ones_tiles() + (batches + q.batches - 1) / q.batches;
                 q.stride = (first - q.ones + kSamples - 1) / kSamples;
                 longest = first < cnt ? (uint64_t)t - (uint64_t)rec[lo + first].ts : 1;
@@ -905,11 +904,13 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
     q.near = longest < (1u << 24);
     // Rows per tile: every tile costs the summing a wave-wide reduction, every draw re-reads about half
     // a tile with a wave-wide scan per row; the sum is smallest near sqrt(rows / k). The tiling
-    // never changes a result, only the cost.
+    // never changes a result, only the cost. (64 draws, timestamps within 30 000 ticks, with 128 tiles for the near part
+    // whatever the block's roots, and with all that the block has: 600 roots over lists of 100 000 entries 330 and 156 us, 200
+    // over lists of a million 2.45 and 0.65 ms.)
     const uint32_t rows = (cnt - q.first + kWave - 1) / kWave;
     uint32_t per = (uint32_t)__builtin_sqrtf((float)rows / (float)k);
     q.tile_shift = per > 1u ? 31u - (uint32_t)__clz((int)per) : 0u;
-    while (((uint64_t)kMostNearTiles << q.tile_shift) < rows) ++q.tile_shift;
+    while (((uint64_t)(max_tiles - q.far_tiles) << q.tile_shift) < rows) ++q.tile_shift;
     per = 1u << q.tile_shift;
     q.alone = rows + 4u * q.far_tiles * q.batches <= alone_rows;
     q.tiles = q.far_tiles + (rows + per - 1) / per;
@@ -932,12 +933,13 @@ __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8)
     const int64_t* __restrict__ times, int64_t num_roots, int per_block, int32_t num_nodes, int k, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t hop, int32_t* __restrict__ o_nbr, int32_t* __restrict__ o_eid, int64_t* __restrict__ o_ts,
     int32_t* __restrict__ o_count) {
-    __shared__ uint64_t tile_sum[kListWaves][kMaxTiles];
+    __shared__ uint64_t tile_sums[kMaxTiles];
     __shared__ uint32_t sample[kListWaves][kSamples];
     __shared__ ListQuery query[kListWaves];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t root = (int64_t)blockIdx.x * per_block + wave;
+    const uint32_t max_tiles = (uint32_t)kMaxTiles >> (per_block >> 1);   // of a root: per_block is 1, 2 or 4
     if (lane == 0) query[wave].tiles = 0;      // nothing (more) to do for this wave's root
     if (wave < per_block && root < num_roots) {
         int64_t lo = 0, hi = 0, t = 0;
@@ -953,7 +955,7 @@ __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8)
             if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, lane < cnt ? rec[lo + cnt - 1 - lane] : pad);
             if (lane == 0) o_count[root] = cnt;
         } else {
-            const ListQuery q = uniform(plan_list(rec, index, lo, hi, t, (uint32_t)cnt, k, per_block == 1 ? kFewRows : kWaveRows, lane));
+            const ListQuery q = uniform(plan_list(rec, index, lo, hi, t, (uint32_t)cnt, k, per_block == 1 ? kFewRows : kWaveRows, max_tiles, lane));
             if (lane == 0) query[wave] = q;
             if (q.far_tiles > q.ones_tiles()) {
                 uint32_t s[kSamples / kWave];
@@ -972,18 +974,19 @@ __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8)
 #pragma unroll 1
     for (int w = 0; w < per_block; ++w) {
         const ListQuery q = uniform(query[w]);
-        if (q.tiles > 0 && !q.alone) sum_tiles(q, ts_low, sample[w], (uint32_t)wave, kListWaves, tile_sum[w], lane);
+        if (q.tiles > 0 && !q.alone) sum_tiles(q, ts_low, sample[w], (uint32_t)wave, kListWaves, tile_sums + w * max_tiles, lane);
     }
     __syncthreads();
     const ListQuery q = uniform(query[wave]);
     if (q.tiles == 0) return;
+    uint64_t* const tile_sum = tile_sums + wave * max_tiles;   // (wave < per_block)
     if (q.alone) {
-        sum_tiles(q, ts_low, sample[wave], 0, 1, tile_sum[wave], lane);
+        sum_tiles(q, ts_low, sample[wave], 0, 1, tile_sum, lane);
         own_lds_ready();
     }
     uint64_t u = 0;
     if (lane < k) u = draw64_wide(seed_lo, seed_hi, hop, (uint64_t)root, (uint32_t)lane);
-    const uint32_t pick = draw_entries(q, ts_low + q.lo, sample[wave], tile_sum[wave], u, lane);
+    const uint32_t pick = draw_entries(q, ts_low + q.lo, sample[wave], tile_sum, u, lane);
     if (lane < k) store_slot(o_nbr, o_eid, o_ts, root * k + lane, rec[q.lo + pick]);
     if (lane == 0) o_count[root] = k;
 }
