@@ -838,9 +838,12 @@ __device__ __forceinline__ void sum_tiles(const ListQuery& q, const uint32_t* __
 
 // Entries per weight from which a list is described by its weights: a batch of 63 weights costs about 180 vector
 // instructions, a row of 64 entries 16 (8, 12, 16 entries: 248, 245, 247 us for 40 000 roots over lists of 13 000
-// entries), and the shortest list that is looked at for it.
-constexpr float kRunEntries = 12.0f;
-constexpr uint32_t kFarEntries = 512;
+// entries). Entries per draw: a draw from the far part finds its tile's runs again, some 250 instructions more than one that
+// reads a row or two. 4 000 roots over lists of 10 000 entries, timestamps within 2^31 ticks, 10 / 25 / 64 draws: without this
+// term 44 80 212 us, with 150 entries per draw 44 80 143, 300 44 77 143, 1 200 45 76 143; lists of 25 000 entries, 25 draws
+// within 2^26 ticks 86 85 84 95. kFarEntries: with fewer there is no far part.
+constexpr float kRunEntries = 12.0f, kDrawEntries = 300.0f;
+constexpr uint32_t kFarEntries = 1024 + (uint32_t)(kRunEntries + kDrawEntries);
 // Entries 2^32 and more before the query from which they are a tile of their own: a row of them. Read like any others, a list
 // of a million entries of which 50 are younger took 0.39 ms for 200 roots, so 0.010; 4 000 roots over lists of 1 000 entries,
 // 1 % of them younger, ten draws 28.9 us, so 20.0 (with a line at 256 entries the same, at 1 024 28.9).
@@ -892,7 +895,7 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
         uint32_t w_end = (uint32_t)(4294967296.0f / from);
         if (w_end > kSmallWeight) w_end = kSmallWeight;
         const float far = (float)rest * (1.0f - from / (float)longest);  // entries, were they spread evenly
-        if (w_end > w_first && far > kRunEntries * (float)(w_end - w_first) + 1024.0f) {
+        if (w_end > w_first && far > kRunEntries * (float)(w_end - w_first) + 1024.0f + kDrawEntries * (float)k) {
             // weights below w_end are deltas above floor(2^32 / w_end), which is less than `longest`
             const uint32_t first = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - (int64_t)weight_of_delta(w_end), 0, lane);
             if ((first - q.far_begin) / (uint32_t)kRunEntries > w_end - w_first) {

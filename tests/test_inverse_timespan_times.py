@@ -38,3 +38,10 @@ def test_blocks_of_one_root_leave_room_for_others():
     """2 000 blocks are resident at once; of 3 000 the last thousand wait for room, but not for more than LDS takes: 1.33
     times as long (1.68 with the LDS of four roots in each)."""
     assert _ratio(_call(1_000_000, 3000, 1 << 28, 3000, 10), _call(1_000_000, 3000, 1 << 28, 2000, 10)) < 1.5
+
+
+@pytest.mark.gpu
+def test_many_draws_are_not_made_from_weights():
+    """64 draws from lists of 3 300 entries, few per weight: about as long where the timestamps spread over 2^31 ticks as where
+    they leave no weight with several entries (1.3 times with a list summed by weights, whatever the draws)."""
+    assert _ratio(_call(1_000_000, 300, 1 << 31, 4000, 64), _call(1_000_000, 300, 1 << 24, 4000, 64)) < 1.15
