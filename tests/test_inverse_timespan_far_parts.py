@@ -24,24 +24,52 @@ def _deltas(shape, n, rng):
         return rng.integers(1 << 30, 1 << 31, n)
     if shape == "beyond 2^32":             # weight 1 from entry 0 on, the low words wrap inside the far part
         return rng.integers(1 << 20, 1 << 34, n)
+    if shape == "gap":                     # 3 000 old entries, none between 2^31 and 2^32, many of weight 2
+        return np.concatenate([rng.integers(1 << 32, 1 << 40, 3000), rng.integers(1 << 30, 1 << 31, n - 3000)])
     if shape == "dense":                   # 40 000 weights: several batches per far tile, ties everywhere
         return rng.integers(1, 400_000, n)
     return np.repeat(rng.integers(1, 30_000_000, n // 16 + 1), 16)[:n]   # "ties": runs of one timestamp across samples
 
 
+def _far_entries(ts, t, k):
+    """How many of a list's entries the finder takes by their weights for a query at t (0: no far part): its rule, in double."""
+    valid = ts[ts < t]
+    if valid.shape[0] <= k:
+        return 0
+    delta = t - valid
+    ones = int(np.sum(delta >= 1 << 32))
+    begin = ones if ones >= 64 else 0
+    rest, longest = valid.shape[0] - begin, int(delta[begin]) if begin < valid.shape[0] else 1
+    if valid.shape[0] - ones < 1336 or longest <= 65536:
+        return 0
+    start = max((12 * 2 ** 32 * longest / rest) ** 0.5, 65537)
+    first_weight, end = max(2 ** 32 // longest, 1), min(int(2 ** 32 / start), 65535)
+    if end <= first_weight or rest * (1 - start / longest) <= 12 * (end - first_weight) + 1024 + 300 * k:
+        return 0
+    far = int(np.sum(delta > 2 ** 32 // end)) - begin
+    return far if far // 12 > end - first_weight else 0
+
+
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,n", [("even", 511), ("even", 513), ("even", 5000), ("even", 8209), ("even", 300_000), ("log", 40_000),
-                                     ("old burst", 600), ("old burst", 70_001), ("all far", 3000), ("all far", 100_000), ("beyond 2^32", 2000),
-                                     ("beyond 2^32", 150_000), ("dense", 3_000_000), ("ties", 513), ("ties", 100_000)])
-def test_far_parts_match_the_oracle(shape, n):
+@pytest.mark.parametrize("shape,n,ks,far", [
+    ("even", 5000, (1, 10), False), ("even", 8209, (1,), True), ("even", 8209, (5,), False), ("even", 300_000, (1, 10, 64), True),
+    ("log", 40_000, (1, 10), True), ("log", 100_000, (64,), True), ("old burst", 1700, (1,), False), ("old burst", 2200, (1,), True),
+    ("old burst", 70_001, (1, 10, 64), True), ("all far", 1600, (1,), False), ("all far", 1800, (1,), True), ("all far", 4200, (5,), True),
+    ("all far", 4200, (10,), False), ("all far", 100_000, (1, 10, 64), True), ("beyond 2^32", 2000, (1, 10, 64), False),
+    ("beyond 2^32", 12_000, (1, 5), True), ("beyond 2^32", 150_000, (1, 10, 64), True), ("dense", 3_000_000, (10,), True),
+    ("gap", 9000, (1, 10), True), ("ties", 513, (1, 10, 64), False), ("ties", 100_000, (1, 10, 64), True)])
+def test_far_parts_match_the_oracle(shape, n, ks, far):
+    """far: whether every query from NOW on has a far part."""
     rng = np.random.default_rng(n)
     ts = np.sort(NOW - _deltas(shape, n, rng)).astype(np.int64)
+    for k in ks:
+        assert all((_far_entries(ts, t, k) > 0) == far for t in (NOW, NOW + 1, NOW + 70_000)), [_far_entries(ts, t, k) for t in (NOW, NOW + 1, NOW + 70_000)]
     src, dst, eid = np.zeros(n, np.int32), rng.integers(0, 9, n).astype(np.int32), np.arange(n, dtype=np.int32)
     g = T.tcsr_build(*(torch.from_numpy(x).cuda() for x in (src, dst, ts, eid)), 9)
     g_ref = oracle.tcsr_build(src, dst, ts, eid, 9, THREADS)
     times = np.concatenate([[NOW, NOW + 1, NOW + 70_000, ts[-1], ts[n // 2], ts[n // 2] + 1], NOW + rng.integers(-1000, 1000, 4)]).astype(np.int64)
     roots = np.zeros(times.shape[0], np.int32)
-    for k in (1, 10, 64) if n < 1_000_000 else (10,):
+    for k in ks:
         want = oracle.sample_temporal(g_ref, roots, times, k, 1, T.INVERSE_TIMESPAN, 5, threads=THREADS)[0]
         got = T.sample_temporal(g, torch.from_numpy(roots).cuda(), torch.from_numpy(times).cuda(), k, 1, T.INVERSE_TIMESPAN, 5)[0]
         for f in ("nbr", "eid", "ts", "count"):
