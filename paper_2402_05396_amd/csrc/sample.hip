@@ -477,7 +477,7 @@ struct ListQuery {
     uint32_t first;              // first entry of the near part
     uint32_t tile_shift;         // near part: log2 of the rows of a tile
     uint32_t stride;             // far part: entries between two samples
-    uint32_t alone;              // one wavefront's work
+    uint32_t together;           // 1: its tiles are summed by all wavefronts of the block, 0: by its own
     uint32_t w_first, w_end;     // far part: weight of its first entry, and the first weight of the near part
     uint32_t batches;            // batches of kBatch weights per far tile
     uint32_t far_tiles, tiles;   // tiles before the near part's, the one of the `ones` included, and all of them
@@ -493,7 +493,7 @@ constexpr uint32_t kBatch = kWave - 1;   // weights of a far batch: the last lan
 // A query as the whole wave read it from LDS, in scalar registers.
 __device__ __forceinline__ ListQuery uniform(const ListQuery& v) {
     auto get = [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); };
-    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.far_begin), get(v.first), get(v.tile_shift), get(v.stride), get(v.alone),
+    return ListQuery{get(v.lo), get(v.cnt), get(v.ones), get(v.t_low), get(v.far_begin), get(v.first), get(v.tile_shift), get(v.stride), get(v.together),
                      get(v.w_first), get(v.w_end),
                      get(v.batches), get(v.far_tiles), get(v.tiles), get(v.k), get(v.near)};
 }
@@ -848,7 +848,7 @@ constexpr uint32_t kFarEntries = 1024 + (uint32_t)(kRunEntries + kDrawEntries);
 // of a million entries of which 50 are younger took 0.39 ms for 200 roots, so 0.010; 4 000 roots over lists of 1 000 entries,
 // 1 % of them younger, ten draws 28.9 us, so 20.0 (with a line at 256 entries the same, at 1 024 28.9).
 constexpr uint32_t kManyOnes = 64;
-constexpr uint32_t kWaveRows = 48, kFewRows = 8;   // a list of no more rows is one wavefront's work, in a block of its own and else
+constexpr uint32_t kWaveRows = 48, kFewRows = 8;   // a list of no more rows is one wavefront's work, beside other roots and in a block of its own
 
 // Roots per block of kListWaves wavefronts. With as many roots as wavefronts none of these is idle while lists are
 // short or while draws are made, with one the longest lists are spread widest. Lists of 4, 20, 141, 300 and 2 000
@@ -869,7 +869,8 @@ inline unsigned list_lds_bytes(int per_block) {
     return kListWaves * sizeof(ListQuery) + per_block * kSamples * sizeof(uint32_t) + kMaxTiles * sizeof(uint64_t);
 }
 
-// How a list of cnt > k valid entries is cut up, into at most max_tiles tiles. By one wavefront.
+// How a list of cnt > k valid entries is cut up, into at most max_tiles tiles. By one wavefront. Where the cuts lie changes the
+// time and never a result: approximate quotients and roots do.
 __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec, const TaserTimeIndex& index, int64_t lo, int64_t hi,
                                                int64_t t, uint32_t cnt, int k, uint32_t alone_rows, uint32_t max_tiles, int lane) {
     ListQuery q = {};
@@ -888,13 +889,13 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
     const uint32_t rest = cnt - q.far_begin;
     if (q.far_begin && rest >= kFarEntries) longest = (uint64_t)t - (uint64_t)rec[lo + q.ones].ts;
     if (cnt - q.ones >= kFarEntries && longest > kLastLargeDelta) {
-        const float every = (float)longest / (float)rest;      // time between two entries
-        float from = __builtin_sqrtf(kRunEntries * 4294967296.0f * every);   // around it a weight has kRunEntries entries
+        const float every = (float)longest * __builtin_amdgcn_rcpf((float)rest);   // time between two entries
+        float from = __builtin_amdgcn_sqrtf(kRunEntries * 4294967296.0f * every);   // around it a weight has kRunEntries entries
         if (from < (float)(kLastLargeDelta + 1u)) from = (float)(kLastLargeDelta + 1u);
         const uint32_t w_first = longest >> 32 ? 1u : quotient_of_delta<false>((uint32_t)longest);
-        uint32_t w_end = (uint32_t)(4294967296.0f / from);
+        uint32_t w_end = (uint32_t)(4294967296.0f * __builtin_amdgcn_rcpf(from));
         if (w_end > kSmallWeight) w_end = kSmallWeight;
-        const float far = (float)rest * (1.0f - from / (float)longest);  // entries, were they spread evenly
+        const float far = (float)rest * (1.0f - from * __builtin_amdgcn_rcpf((float)longest));  // entries, were they spread evenly
         if (w_end > w_first && far > kRunEntries * (float)(w_end - w_first) + 1024.0f + kDrawEntries * (float)k) {
             // weights below w_end are deltas above floor(2^32 / w_end), which is less than `longest`
             const uint32_t first = (uint32_t)group_cutoff<kWave>(rec, index, lo, hi, t - (int64_t)weight_of_delta(w_end), 0, lane);
@@ -918,11 +919,11 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
     // whatever the block's roots, and with all that the block has: 600 roots over lists of 100 000 entries 330 and 156 us, 200
     // over lists of a million 2.45 and 0.65 ms.)
     const uint32_t rows = (cnt - q.first + kWave - 1) / kWave;
-    uint32_t per = (uint32_t)__builtin_sqrtf((float)rows / (float)k);
+    uint32_t per = (uint32_t)(__builtin_amdgcn_sqrtf((float)rows * __builtin_amdgcn_rcpf((float)k)) * 1.00001f);
     q.tile_shift = per > 1u ? 31u - (uint32_t)__clz((int)per) : 0u;
     while (((uint64_t)(max_tiles - q.far_tiles) << q.tile_shift) < rows) ++q.tile_shift;
     per = 1u << q.tile_shift;
-    q.alone = rows + 4u * q.far_tiles * q.batches <= alone_rows;
+    q.together = rows + 4u * q.far_tiles * q.batches > alone_rows;
     q.tiles = q.far_tiles + (rows + per - 1) / per;
     return q;
 }
@@ -951,7 +952,7 @@ __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t root = (int64_t)blockIdx.x * per_block + wave;
     const uint32_t max_tiles = (uint32_t)kMaxTiles >> (per_block >> 1);   // of a root: per_block is 1, 2 or 4
-    if (lane == 0) query[wave].tiles = 0;      // nothing (more) to do for this wave's root
+    if (lane == 0) query[wave].tiles = query[wave].together = 0;   // nothing (more) to do for this wave's root
     if (wave < per_block && root < num_roots) {
         int64_t lo = 0, hi = 0, t = 0;
         const int32_t v = roots[root];
@@ -984,14 +985,16 @@ __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8)
     __syncthreads();
 #pragma unroll 1
     for (int w = 0; w < per_block; ++w) {
+        if (!__builtin_amdgcn_readfirstlane((int)query[w].together)) continue;
         const ListQuery q = uniform(query[w]);
-        if (q.tiles > 0 && !q.alone) sum_tiles(q, ts_low, sample[w], (uint32_t)wave, kListWaves, tile_sums + w * max_tiles, lane);
+        sum_tiles(q, ts_low, sample[w], (uint32_t)wave, kListWaves, tile_sums + w * max_tiles, lane);
     }
     __syncthreads();
+    if (wave >= per_block) return;
     const ListQuery q = uniform(query[wave]);
     if (q.tiles == 0) return;
-    uint64_t* const tile_sum = tile_sums + wave * max_tiles;   // (wave < per_block)
-    if (q.alone) {
+    uint64_t* const tile_sum = tile_sums + wave * max_tiles;
+    if (!q.together) {
         sum_tiles(q, ts_low, sample[wave], 0, 1, tile_sum, lane);
         own_lds_ready();
     }
