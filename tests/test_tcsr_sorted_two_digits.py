@@ -66,3 +66,18 @@ def test_one_entry_out_of_time_order(at):
     g = T.tcsr_build(*(torch.from_numpy(x).cuda() for x in (src, src, ts, np.arange(n, dtype=np.int32))), 1024)
     order = np.argsort(ts, kind="stable")
     assert np.array_equal(T.tcsr_view(g)[2].cpu().numpy(), ts[order]) and np.array_equal(T.tcsr_view(g)[3].cpu().numpy(), order)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nodes,passes", [(512, 1), (600, 2), (1025, 2), (17_000, 2), (131_072, 2), (131_073, 2), (262_144, 2), (262_145, 3)])
+def test_a_long_span_counts_its_first_digit_in_the_inspection(nodes, passes):
+    """In time order, but over 2^32 ticks and more: one histogram launch per digit after the first, whatever the digits' widths."""
+    n, rng = 9000, np.random.default_rng(nodes)
+    src = rng.integers(0, nodes, n).astype(np.int32)
+    ts = np.sort(rng.integers(0, 1 << 45, n)).astype(np.int64)
+    dev = [torch.from_numpy(x).cuda() for x in (src, src, ts)]
+    T.profile_begin()
+    T.tcsr_build(*dev, None, nodes)
+    kernels = T.profile_end()
+    assert kernels["tcsr_radix_scatter"][0] == passes and kernels.get("tcsr_radix_hist", (0, 0))[0] == passes - 1
+    _check(src, ts, nodes)
