@@ -272,33 +272,100 @@ __device__ __forceinline__ void octet_weighted_picks(const uint32_t (&w)[C], int
 // numbers of roots that fill the chip, and not for windows that are all kept. us of the other one / of this one, 2 000,
 // 8 000, 40 000 roots: 10 of 16 candidates 3.9 4.3, 4.1 4.7, 9.0 8.9; 10 of 25 3.9 4.6, 5.0 4.9, 13.7 10.4; 24 of 25
 // 5.8 6.8, 7.9 7.3, 23.8 18.1; 20 of 49 5.5 7.7, 9.8 8.1, 33.4 21.0; 64 of 64 2.7 5.6, 4.2 6.5, 16.6 17.8.
+//
+// An octet costs its wave as much as eight do, and most roots of a sparse graph have no more than k candidates and draw
+// nothing. So where few draw, each of them gets a lane per candidate as in the other kernel, G = 8 C lanes: with windows of
+// up to 32 the drawing roots of a wave if they are two at most, with longer ones, whose octets have the longer chain, those
+// of a block if they are four at most, one per wave; more than that are packed into octets. us of the other one, of octets
+// for every root, and so, 120 000 roots of which one in 8 / one in 30 has more than k candidates: 10 of 25 15.8 18.3 12.3,
+// 11.0 13.2 8.6; 32 of 64 40.1 63.0 32.1, 27.9 41.9 18.1; 60 of 64 60.1 112 55.2, 36.5 74.5 30.3; 16 000 roots: 10 of 25
+// 5.5 5.3 5.3, 5.3 5.3 5.4; 32 of 64 10.9 13.5 10.3, 8.8 13.3 9.0; 60 of 64 17.7 23.3 22.4, 13.5 22.9 15.1.
 constexpr int64_t kOctetRoots = 8000;
-constexpr int kSelectRoots = kWave / 8;   // of a wave
+constexpr int kSelectRoots = kWave / 8;                            // of a wave
+constexpr int kBlockRoots = kThreads / kWave * kSelectRoots;      // of a block
+
+// One draw after the other for the roots `root` (of the block) of those of the wave's groups that are active.
+template <int G>
+__device__ __forceinline__ void group_draws(const uint32_t* __restrict__ weight, int64_t root, int at, int candidates, bool active, int m, int k,
+                                            uint32_t seed_lo, uint32_t seed_hi, uint32_t hop, int group, int slot, int8_t* picks) {
+    uint32_t w = 0;
+    if (active && slot < candidates) w = weight[root * m + slot];
+    uint64_t u = 0;
+    if (active && slot < k) u = draw64_wide(seed_lo, seed_hi, hop, (uint64_t)root, (uint32_t)slot);
+    const int pick = group_weighted_picks<G>(w, u, k, active, group, slot);
+    if (active && slot < k) picks[at * k + slot] = (int8_t)pick;
+}
 template <int C>
-__global__ __launch_bounds__(kThreads) void select_weighted_octets_kernel(
+__device__ __forceinline__ void octet_draws(const uint32_t* __restrict__ weight, int64_t root, int at, int candidates, bool active, int m, int k,
+                                            uint32_t seed_lo, uint32_t seed_hi, uint32_t hop, int sub, int8_t* picks) {
+    uint32_t w[C];
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        w[i] = 0;
+        if (active && sub * C + i < candidates) w[i] = weight[root * m + sub * C + i];
+    }
+    octet_weighted_picks<C>(w, k, active, seed_lo, seed_hi, hop, (uint64_t)root, sub, picks + (active ? at : kBlockRoots) * k);
+}
+
+template <int C>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8))) void select_weighted_octets_kernel(
     const uint32_t* __restrict__ weight, const int32_t* __restrict__ count, int64_t num_roots, int m, int k, uint32_t magic_k,
     uint32_t seed_lo, uint32_t seed_hi, uint32_t hop, int32_t* __restrict__ sel, int32_t* __restrict__ out_count,
     const int32_t* __restrict__ c_nbr, const int32_t* __restrict__ c_eid, const int64_t* __restrict__ c_ts,
     int32_t* __restrict__ k_nbr, int32_t* __restrict__ k_eid, int64_t* __restrict__ k_ts) {
-    __shared__ int8_t picks[kThreads / kWave][kSelectRoots * TASER_MAX_K];
+    constexpr int G = 8 * C, kGroups = kWave / G, kWaves = kThreads / kWave;
+    __shared__ int8_t picks[(kBlockRoots + 1) * TASER_MAX_K];   // the last row is for octets that have no root
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, octet = lane >> 3, sub = lane & 7;
-    const int64_t q0 = ((int64_t)blockIdx.x * (kThreads / kWave) + wave) * kSelectRoots, q = q0 + octet;   // the wave's first root, the octet's
-    if (q0 >= num_roots) return;
-    const int here = num_roots - q0 < kSelectRoots ? (int)(num_roots - q0) : kSelectRoots;
+    const int64_t b0 = (int64_t)blockIdx.x * kBlockRoots, q0 = b0 + wave * kSelectRoots, q = q0 + octet;   // the block's first root, the wave's, the octet's
+    const int here = num_roots - q0 >= kSelectRoots ? kSelectRoots : num_roots > q0 ? (int)(num_roots - q0) : 0;
+    const int mine = wave * kSelectRoots + octet, group = lane / G, slot = lane % G;
     int c = 0;
     if (octet < here) {
         c = count[q];
         c = c < 0 ? 0 : (c > m ? m : c);
     }
-    uint32_t w[C];
+    const uint64_t draws = __ballot(sub == 0 && c > k);   // a bit per root that draws
+    if constexpr (C == 4) {
+        if (__popcll(draws) > kGroups) {
+            octet_draws<C>(weight, q, mine, c, c > k, m, k, seed_lo, seed_hi, hop, sub, picks);
+        } else if (draws) {
+            const int first = (__ffsll((long long)draws) - 1) >> 3, last = (63 - __clzll((long long)draws)) >> 3, r = group == 0 ? first : last;
+            group_draws<G>(weight, q0 + r, wave * kSelectRoots + r, __shfl(c, r * 8, kWave), group == 0 || last != first, m, k, seed_lo, seed_hi, hop,
+                           group, slot, picks);
+        }
+        own_lds_ready();
+    } else {
+        __shared__ uint8_t counts[kBlockRoots], drawing[kBlockRoots];   // candidates of the block's roots; those that draw, in order
+        __shared__ int draws_of_wave[kWaves];
+        if (sub == 0) counts[mine] = (uint8_t)c;
+        if (lane == 0) draws_of_wave[wave] = __popcll(draws);
+        __syncthreads();
+        int before = 0, all = 0;
 #pragma unroll
-    for (int i = 0; i < C; ++i) {
-        w[i] = 0;
-        if (sub * C + i < c) w[i] = weight[q * m + sub * C + i];
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) before += draws_of_wave[w];
+            all += draws_of_wave[w];
+        }
+        all = __builtin_amdgcn_readfirstlane(all);
+        if (all > 0) {   // uniform over the block, like the next
+            const bool own = all == kBlockRoots;   // every octet keeps its root: nothing passes from wave to wave
+            if (!own) {
+                if (sub == 0 && c > k) drawing[before + __popcll(draws & (((uint64_t)1 << lane) - 1))] = (uint8_t)mine;
+                __syncthreads();
+            }
+            const bool packed = all > kWaves * kGroups;
+            const int n = packed ? mine : wave + group * kWaves;   // of the roots that draw
+            const int at = own ? mine : drawing[n < all ? n : 0], candidates = own ? c : counts[at];
+            if (packed) {
+                if (wave * kSelectRoots < all) octet_draws<C>(weight, b0 + at, at, candidates, n < all, m, k, seed_lo, seed_hi, hop, sub, picks);
+            } else if (wave < all) {
+                group_draws<G>(weight, b0 + at, at, candidates, n < all, m, k, seed_lo, seed_hi, hop, group, slot, picks);
+            }
+            if (own) own_lds_ready();
+            else __syncthreads();
+        }
     }
-    if (__ballot(c > k)) octet_weighted_picks<C>(w, k, c > k, seed_lo, seed_hi, hop, (uint64_t)q, sub, picks[wave] + octet * k);
     if (octet < here && sub == 0) out_count[q] = c > k ? k : c;
-    own_lds_ready();
     const uint32_t slots = (uint32_t)(here * k);
     for (uint32_t s0 = 0; s0 < slots; s0 += kWave) {
         const uint32_t s = s0 + (uint32_t)lane;
@@ -307,7 +374,7 @@ __global__ __launch_bounds__(kThreads) void select_weighted_octets_kernel(
         if (r > kSelectRoots - 1) r = kSelectRoots - 1;        // past the wave's slots
         const int of_root = __shfl(c, (int)r * 8, kWave);      // (all lanes take part)
         if (s >= slots) continue;
-        const int pick = of_root > k ? picks[wave][s] : (int)j < of_root ? (int)j : -1;
+        const int pick = of_root > k ? picks[wave * kSelectRoots * k + s] : (int)j < of_root ? (int)j : -1;
         const int64_t at = q0 * k + s;
         sel[at] = pick;
         if (k_nbr) {
