@@ -1252,8 +1252,25 @@ constexpr int64_t kFinderCopyMaxWaveBytes = 8192;
 // compute unit), of a last hop whose rows would otherwise be a launch of their own. One hop, k slots of `bytes`, us a
 // call with two launches and with one: 300 / 1 800 / 3 000 / 4 500 roots, most recent, 10 x 688: 11.8 8.6, 12.1 8.7, 11.9
 // 8.7, 14.7 14.5; uniform, 10 x 344: 12.4 8.7, 12.3 8.9, 12.0 9.2, 13.2 14.2; most recent, 20 x 1064: 12.3 10.1, 17.0 15.0,
-// 24.6 22.4, 33.5 35.9.
+// 24.6 22.4, 33.5 35.9; 4 096 roots, uniform, 20 x 1064: 33.1 29.7, 10 of 25, 10 x 2400: 33.1 32.5.
+// With several hops the gather is one launch for all of them, and a copy in the kernels of the first hops, a few wavefronts
+// with all of a root's rows each, is a step that the next hop waits for. So then the rows have to be few, of a root and in
+// all: two hops from 240 / 400 roots, 10 x 1064: most recent 22.1 20.4, 24.4 26.1, uniform 22.1 21.5, 24.1 26.5; from 60 roots,
+// 20 x 1064: most recent 21.4 21.8, uniform 21.3 26.5. Other finders than the most recent one pay for 64 lanes per root in
+// every hop, the uniform one beyond 16 slots most of all (its draws are resolved one after the other there): three hops from 20
+// roots, 10 x 1064: most recent 28.0 25.8, uniform 27.7 28.4, 10 of 25 28.1 29.8; from 10 roots, 20 x 344: most recent 27.0
+// 23.9, uniform 27.4 28.8.
 constexpr int64_t kSmallHopRoots = 4096, kSmallHopWaveBytes = 24576;
+constexpr int64_t kSmallHopsBytes = (int64_t)28 << 20, kSmallHopsWaveBytes = 16384;   // of several hops: the last one's rows, and a root's
+bool small_hop_pays(int policy, int64_t roots, int k, int hops, int row_bytes) {
+    const int64_t of_root = (int64_t)k * row_bytes, all = roots * of_root;
+    if (roots > kSmallHopRoots || of_root > kSmallHopWaveBytes) return false;
+    if (hops == 1) return true;
+    if (all > kSmallHopsBytes || of_root > kSmallHopsWaveBytes) return false;
+    if (policy == TASER_RECENT) return true;
+    const bool few = of_root <= kSmallHopsWaveBytes / 2;
+    return policy == TASER_UNIFORM && k > 16 ? few && hops == 2 : few || hops == 2;
+}
 
 // All hops of one call. With `want`, hop h also leaves the table rows of its sampled edges in
 // want->out[h]: written by the hop kernel where the shapes allow it and the rows are short, else
@@ -1284,7 +1301,7 @@ int sample_hops(const taser_tcsr* g, const int32_t* roots, const int64_t* times,
         if (want && policy != TASER_INVERSE_TIMESPAN) {
             int64_t wave_bytes = (int64_t)(kWave / group_lanes(policy, k, m)) * k * want->row_bytes;
             int64_t most = kFinderCopyMaxWaveBytes;
-            if (wave_bytes > most && roots_of_last_hop <= kSmallHopRoots && (int64_t)k * want->row_bytes <= kSmallHopWaveBytes) {
+            if (wave_bytes > most && small_hop_pays(policy, roots_of_last_hop, k, hops, want->row_bytes)) {
                 wave_per_root = true;
                 wave_bytes = (int64_t)k * want->row_bytes;
                 most = kSmallHopWaveBytes;

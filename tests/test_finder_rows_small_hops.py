@@ -42,3 +42,27 @@ def test_rows_are_the_rows_of_the_sampled_edges(roots, hops, policy, k, m, dim, 
         ok = (eid >= 0) & (eid < table.shape[0])
         expect = torch.where(ok[:, None], table[eid.clamp(0, table.shape[0] - 1)], torch.zeros((), dtype=table.dtype, device="cuda"))
         assert torch.equal(rows[h].reshape(-1, dim), expect), h
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("roots,hops,policy,k,m,dim,one_launch", [
+    (4096, 1, T.RECENT, 20, 0, 266, True), (4096, 1, T.UNIFORM, 20, 0, 266, True), (4097, 1, T.RECENT, 20, 0, 266, False), (4096, 1, T.WEIGHTED, 10, 25, 600, True),
+    (240, 2, T.RECENT, 10, 0, 266, True), (240, 2, T.UNIFORM, 10, 0, 266, True), (280, 2, T.RECENT, 10, 0, 266, False), (60, 2, T.RECENT, 20, 0, 266, False),
+    (60, 2, T.UNIFORM, 20, 0, 172, False), (60, 2, T.RECENT, 20, 0, 172, True), (60, 2, T.UNIFORM, 20, 0, 100, True),
+    (20, 3, T.RECENT, 10, 0, 266, True), (20, 3, T.UNIFORM, 10, 0, 266, False), (20, 3, T.WEIGHTED, 10, 25, 266, False), (20, 3, T.UNIFORM, 10, 0, 172, True),
+    (5, 3, T.UNIFORM, 20, 0, 88, False), (5, 3, T.RECENT, 20, 0, 88, True)])
+def test_which_calls_take_no_gather(roots, hops, policy, k, m, dim, one_launch):
+    """Rows of several hops are copied by the hops' kernels only where they are few (measured beside the rule)."""
+    cols = _graph()
+    dev = lambda a: torch.from_numpy(a).cuda()
+    g = T.tcsr_build(*map(dev, cols), NODES)
+    rng = np.random.default_rng(roots)
+    q, t = dev(rng.integers(0, NODES, roots).astype(np.int32)), dev(rng.integers(2_000, 5_010, roots).astype(np.int64))
+    table = torch.randn((EVENTS, dim), device="cuda")
+    w = dev(rng.integers(1, 1000, EVENTS).astype(np.int32)) if m else None
+    T.profile_begin()
+    out, rows = T.sample_temporal_rows(g, q, t, k, hops, policy, 9, table, m=m, edge_weight=w)
+    assert ("gather_rows" not in T.profile_end()) == one_launch
+    for h in range(hops):
+        eid = out[h]["eid"].reshape(-1).long()
+        assert torch.equal(rows[h].reshape(-1, dim), torch.where((eid >= 0)[:, None], table[eid.clamp(min=0)], torch.zeros((), device="cuda"))), h
