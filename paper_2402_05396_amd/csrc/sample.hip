@@ -28,6 +28,7 @@
 #include "gather_kernel.h"
 #include "sampling_device.h"
 #include "taser_internal.h"
+#include "timespan_weight.h"
 
 namespace {
 
@@ -432,32 +433,10 @@ __global__ __launch_bounds__(kThreads) void sample_hop_kernel(
 // Weight of an entry at time ts for a query at t > ts: max(1, floor(2^32 / delta)), delta = t - ts.
 // Entries with delta >= 2^32 weigh 1 and are the first `ones` of a list; of the others the low words of
 // the timestamps say all: delta = (low word of t) - (low word of ts), in 32 bits.
-//
-// delta > kLastLargeDelta, so the quotient is at most kSmallWeight. A single-precision reciprocal is off by
-// less than 2^-22 of the quotient (conversion, v_rcp_f32's one unit in the last place, the product); scaled
-// down by 2^-21 it gives the quotient or one less, and the exact remainder says which. NEAR: delta < 2^24,
-// where the quotient is at least 256 and one full-rate 24-bit multiply-add does for the remainder.
-constexpr uint32_t kLastLargeDelta = 65536;      // its quotient is 2^16 itself: with it a tile of ties would sum to 2^32
-constexpr uint32_t kSmallWeight = (uint32_t)(((uint64_t)1 << 32) / (kLastLargeDelta + 1));
-static_assert(kSmallWeight == 65535, "the quotient of every larger delta is below 2^16");
 template <bool NEAR> __device__ __forceinline__ uint32_t quotient_of_delta(uint32_t delta) {
-    const uint32_t q = (uint32_t)(4294967296.0f * (1.0f - 4.76837158203125e-7f) * __builtin_amdgcn_rcpf((float)delta));
-    if (NEAR) return q + ((int32_t)(__umul24(q, delta) + delta) <= 0 ? 1u : 0u);   // (q + 1) delta is at most 2^32 (it is within delta of it)
-    const uint32_t rest = 0u - q * delta;                                 // 2^32 - q delta, below 2 delta; wraps only for delta > 2^31
-    const uint32_t w = q + (rest >= delta ? 1u : 0u);
-    return w > 1u ? w : 1u;                                               // (where the quotient is 1 in any case)
+    return quotient_by_reciprocal<NEAR>(delta, __builtin_amdgcn_rcpf((float)delta));
 }
-// Any delta >= 1; the quotient has up to 33 bits. The first estimate is at most 2^-20 of it too small (or one,
-// where that is less), so that the remainder is below 2^13 + 2 delta; the remainder's own quotient, found the same
-// way, is exact or one too small.
-__device__ __forceinline__ uint64_t weight_of_delta(uint32_t delta) {
-    const float r = (1.0f - 4.76837158203125e-7f) * __builtin_amdgcn_rcpf((float)delta);
-    const uint32_t q = (uint32_t)(4294967296.0f * r);
-    const uint32_t rest = 0u - q * delta;                 // 2^32 - q delta; wraps only for delta > 2^31 (q == 0)
-    const uint32_t more = (uint32_t)((float)rest * r), left = rest - more * delta;
-    const uint64_t w = (uint64_t)q + (more + (left >= delta ? 1u : 0u));
-    return w > 1u ? w : 1u;
-}
+__device__ __forceinline__ uint64_t weight_of_delta(uint32_t delta) { return weight_by_reciprocal(delta, __builtin_amdgcn_rcpf((float)delta)); }
 
 constexpr int kMaxTiles = 16 * kWave;             // tile sums of a block, divided among its roots
 constexpr int kSamples = 512;                     // of a far part, per root

@@ -92,19 +92,3 @@ def test_roots_per_block(roots, entries):
     got = T.sample_temporal(g, torch.from_numpy(q).cuda(), torch.from_numpy(t).cuda(), 4, 1, T.INVERSE_TIMESPAN, 11)[0]
     for f in ("nbr", "eid", "ts", "count"):
         assert np.array_equal(got[f].cpu().numpy(), want[f]), f
-
-
-def test_the_weight_of_every_delta_is_exact_whatever_the_reciprocals_last_bit():
-    rng = np.random.default_rng(2)
-    w = np.arange(1, 70_000, dtype=np.int64)
-    d = np.concatenate([np.arange(1, 1 << 20), 2 ** 32 // w, 2 ** 32 // w + 1, rng.integers(1 << 20, 1 << 32, 500_000), 2 ** 32 - np.arange(1, 999)])
-    d = d[(d >= 1) & (d < 1 << 32)].astype(np.uint64)
-    f, m = np.float32, np.uint64(0xffffffff)
-    for off in (None, f(np.inf), f(-np.inf)):
-        rcp = f(1) / d.astype(f)
-        r = f(1 - 2.0 ** -21) * (rcp if off is None else np.nextafter(rcp, off))
-        q = (f(4294967296.0) * r).astype(np.uint64)
-        rest = (np.uint64(0) - q * d) & m
-        more = (rest.astype(f) * r).astype(np.uint64)
-        left = (rest - more * d) & m
-        assert np.array_equal(np.maximum(q + more + (left >= d), 1), np.uint64(1 << 32) // d)

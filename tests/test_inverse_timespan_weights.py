@@ -1,5 +1,8 @@
 """The inverse-timespan finder where its weights change form: spans on both sides of 2^16, 2^24, 2^31 and 2^32,
 lists around a tile's and a row's ends, and the smallest and largest list it tiles."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 import torch
@@ -33,49 +36,75 @@ def test_picks_equal_the_oracle(n, near, far):
             assert np.array_equal(got[f].cpu().numpy(), want[f]), (k, f)
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("delta", [65_536, 65_537])
-def test_tiles_of_ties_at_the_largest_weights(delta):
-    """The shortest list whose tiles hold 1 024 rows of 64 entries, all of them one timestamp: a full tile weighs
-    65 536 * 65 536 = 2^32 where delta is 65 536, and 65 536 * 65 535 one later."""
-    n = 1023 * 512 * 64 + 1
+def _ties(n, delta, ks):
+    """One list of n entries, all of them delta before the queries."""
     ts = torch.zeros(n, dtype=torch.int64, device="cuda")
     src = torch.zeros(n, dtype=torch.int32, device="cuda")
     eid = torch.arange(n, dtype=torch.int32, device="cuda")
     g = T.tcsr_build(src, eid, ts, eid, 1)
     g_ref = oracle.tcsr_build(*(t.cpu().numpy() for t in (src, eid, ts, eid)), 1, THREADS)
     roots, times = np.zeros(5, np.int32), np.full(5, delta, np.int64)
-    for k in (1, 10):
+    for k in ks:
         want = oracle.sample_temporal(g_ref, roots, times, k, 1, T.INVERSE_TIMESPAN, 3, threads=THREADS)[0]
         got = T.sample_temporal(g, torch.from_numpy(roots).cuda(), torch.from_numpy(times).cuda(), k, 1, T.INVERSE_TIMESPAN, 3)[0]
         for f in ("nbr", "eid", "ts", "count"):
             assert np.array_equal(got[f].cpu().numpy(), want[f]), (k, f)
 
 
-def _quotient(delta, near):
-    """The device's arithmetic for delta > 65536 in numpy: float32 products, the reciprocal off by up to one unit in the
-    last place either way, then the remainder's correction."""
-    d = delta.astype(np.float32)
-    r = np.float32(1) / d
-    out = []
-    for off in (np.float32(0), np.float32(np.inf), np.float32(-np.inf)):
-        rr = r if off == 0 else np.nextafter(r, off)
-        q = (np.float32(4294967296.0 * (1 - 2.0 ** -21)) * rr).astype(np.float32).astype(np.uint64)
-        rest = (2 ** 32 - q * delta) % 2 ** 32
-        w = q + (rest >= delta)
-        out.append(w if near else np.maximum(w, 1))
-    return out
+@pytest.mark.gpu
+@pytest.mark.parametrize("delta", [65_536, 65_537])
+def test_tiles_of_ties_at_the_largest_weights(delta):
+    """The shortest list whose tiles hold 1 024 rows of 64 entries (a block of one root has 1 024 tiles), all of them one
+    timestamp: a full tile weighs 65 536 * 65 536 = 2^32 where delta is 65 536, and 65 536 * 65 535 one later."""
+    _ties(1024 * 512 * 64 + 1, delta, (1, 10))
 
 
-def test_the_quotient_is_exact_whatever_the_reciprocals_last_bit():
-    rng = np.random.default_rng(1)
-    q = rng.integers(1, 65536, 200_000).astype(np.uint64)
-    edges = np.concatenate([2 ** 32 // q, 2 ** 32 // q + 1, rng.integers(65536, 2 ** 32, 400_000).astype(np.uint64),
-                            np.arange(65536, 66000), np.arange(2 ** 24 - 300, 2 ** 24 + 300), np.arange(2 ** 31 - 300, 2 ** 31 + 300),
-                            np.arange(2 ** 32 - 300, 2 ** 32)]).astype(np.uint64)
-    edges = edges[(edges >= 65536) & (edges < 2 ** 32)]
-    for got in _quotient(edges, False):
-        assert np.array_equal(got, np.maximum(2 ** 32 // edges, 1))
-    edges = edges[edges < 2 ** 24]
-    for got in _quotient(edges, True):
-        assert np.array_equal(got, 2 ** 32 // edges)
+@pytest.mark.gpu
+@pytest.mark.parametrize("delta", [1, 2, 63, 64, 65, 127, 128, 129])
+@pytest.mark.parametrize("n", [8 * 64 - 1, 8 * 64, 8 * 64 + 1, 40 * 8 * 64 + 7])
+def test_rows_of_ties_at_the_ends_of_32_bits(delta, n):
+    """Groups of eight rows of 64 entries: a row weighs 64 * 2^26 = 2^32 at delta 64, 2^31 at the delta from which rows are
+    summed in 32 bits (128), and a lane's eight rows 2^29 there."""
+    _ties(n, delta, (1, 10, 64))
+
+
+PROGRAM = r"""
+#include "timespan_weight.h"
+#include <math.h>
+#include <random>
+#include <stdio.h>
+static int bad = 0;
+static void check(uint64_t d) {
+    if (d < 1 || d >> 32) return;
+    const uint32_t delta = (uint32_t)d;
+    const uint64_t want = ((uint64_t)1 << 32) / d;
+    const float r = 1.0f / (float)delta, of[3] = {r, nextafterf(r, 2.0f), nextafterf(r, 0.0f)};
+    for (int i = 0; i < 3; ++i) {
+        bool ok = weight_by_reciprocal(delta, of[i]) == want;
+        if (delta > kLastLargeDelta) ok = ok && quotient_by_reciprocal<false>(delta, of[i]) == want;
+        if (delta > kLastLargeDelta && delta < 1u << 24) ok = ok && quotient_by_reciprocal<true>(delta, of[i]) == want;
+        if (!ok && ++bad < 20) printf("delta %u, reciprocal %d\n", delta, i);
+    }
+}
+int main() {
+    for (uint64_t d = 1; d < (1u << 24) + 1000; ++d) check(d);
+    for (uint64_t w = 1; w < 70000; ++w)
+        for (int i = -2; i <= 2; ++i) check(((uint64_t)1 << 32) / w + i);
+    for (int bit = 24; bit <= 32; ++bit)
+        for (int i = -3000; i <= 3000; ++i) check(((uint64_t)1 << bit) + i);
+    std::mt19937_64 rng(1);
+    for (int i = 0; i < 3000000; ++i) check(rng() >> (32 + rng() % 9));
+    return bad != 0;
+}
+"""
+
+
+def test_the_weight_of_a_delta_is_exact_whatever_the_reciprocals_last_bit(tmp_path):
+    """The kernel's own functions (csrc/timespan_weight.h) in a CPU program: every delta below 2^24, and those above it at which
+    the quotient changes."""
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2402_05396_amd", "csrc")
+    (tmp_path / "w.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-w", "-D__HIP_PLATFORM_AMD__=1", "-I", csrc, "-isystem", "/opt/rocm/include", "-o", str(tmp_path / "w"),
+                    str(tmp_path / "w.cpp")], check=True)
+    r = subprocess.run([str(tmp_path / "w")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
