@@ -830,12 +830,12 @@ constexpr uint32_t kManyOnes = 64;
 constexpr uint32_t kWaveRows = 48, kFewRows = 8;   // a list of no more rows is one wavefront's work, beside other roots and in a block of its own
 
 // Roots per block of kListWaves wavefronts. With as many roots as wavefronts none of these is idle while lists are
-// short or while draws are made, with one the longest lists are spread widest. Lists of 4, 20, 141, 300 and 2 000
-// entries on average, one / two / four roots per block, us:
-//   4 000 roots:  20.9 19.1 18.8   28.3 25.9 26.6   34.6 29.6 29.3   53.3 56.6 69.5   74.1 74.1 86.9
-//   8 000 roots:  32.2 28.4 25.5   44.6 37.5 32.9   58.4 43.5 42.0   88.0 71.1 78.7    112  100  107
-//   16 000 roots: 52.0 43.6 37.6   76.1 58.9 50.1    107 76.0 64.4    142  112  105    195  152  159
-// (600 and 2 000 roots: one per block, or the same.)
+// short or while draws are made, with one the longest lists are spread widest. One / two / four roots per block, ten draws
+// each, over lists of one length and over lists by a power law (exponent 0.9), of 20, 400 and 4 000 entries on average, us:
+//   2 000 roots:  14.6 14.7 14.8   32.6 39.3 40.1    15.0 15.1 15.2   41.2 47.2 51.7    20.1 22.9 24.4   50.9 60.0 77.0
+//   4 000 roots:  21.9 18.6 18.6   39.6 48.9 48.8    26.3 19.0 18.9   51.7 57.3 61.9    31.4 28.7 29.5   66.5 72.7 85.8
+//   6 000 roots:  26.6 24.8 23.3   47.3 49.6 46.7    33.1 28.6 23.7   62.7 66.9 82.1    41.0 38.7 35.9   84.7 89.5  103
+//   12 000 roots: 40.3 37.0 34.6   70.7 71.0 75.9    56.4 47.5 39.6    101  101 95.5    70.0 62.7 57.0    137  137  139
 int list_roots_per_block(int64_t entries, int64_t nodes, int64_t roots) {
     if (entries < 256 * nodes) return roots < 4000 ? 1 : 4;
     return roots < 6000 ? 1 : roots < 12000 ? 2 : 4;
@@ -914,7 +914,7 @@ __device__ __forceinline__ ListQuery plan_list(const TaserRec* __restrict__ rec,
 // quarter of the bytes of the records). A block of four wavefronts: each finds the cutoff of a root and cuts up its
 // list; all of them sum the long lists' tiles; then each wavefront sums its own list if it is short, and makes its
 // root's draws. Bound by vector instructions (82 % of the issue slots): 16 per 64 entries, 180 per 63 weights, about 90 per
-// draw. Two hops of 10 from 4 000 roots (0.4 G weights, 0.23 G of them in far parts): 0.62 ms when every entry was weighed
+// draw. Two hops of 10 from 4 000 roots (0.41 G weights, 0.22 G of them in far parts): 0.62 ms when every entry was weighed
 // and one root had a block, 0.32 so. Eight wavefronts per SIMD take 96 scalar registers, which is what the attribute asks
 // for (0.36 ms with seven).
 __global__ __launch_bounds__(kListThreads) __attribute__((amdgpu_waves_per_eu(8))) void sample_hop_inverse_timespan_kernel(

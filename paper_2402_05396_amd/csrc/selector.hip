@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(const int32_t* __restri
 
 // The whole update of a batch of at most 768 by one block: which position names an edge last is settled in
 // a hash table in LDS instead of the array of owners, so the chain of dependent reads is index -> score, in
-// one launch instead of two (us a call, million edges: 100 positions 3.4 -> 2.5, 600 4.3 -> 2.8). The random reads and adds
+// one launch instead of two (us a call, million edges: 100 positions 3.4 -> 2.5, 600 4.3 -> 2.4). The random reads and adds
 // of one compute unit take longer the more there are: by 8 blocks (next kernel) 600 / 800 / 1 000 positions are 2.5 /
 // 2.5 / 2.6, by one 2.4 / 2.7 / 3.1.
 constexpr int kOneBlockThreads = 1024, kOneBlockBatch = 768;
