@@ -12,8 +12,8 @@
 //
 // A lookup is three launches:
 //   1. classify: every request probes the resident hash; a miss claims a slot
-//      of the miss table (compare-and-swap on the id) — the outcome per request
-//      is written to `loc`;
+//      of the miss table (compare-and-swap on the id, or a plain store where the
+//      table has a slot per row) — the outcome per request is written to `loc`;
 //   2. one launch with two kinds of blocks. A few stage: the claimed slots get
 //      consecutive rows of the staging area (so that what a call staged is one
 //      dense block of memory), a wave per slot copies that row host -> staging
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kThreads) void fill_kernel(int32_t* a, uint32_t n, 
     if (i < n) a[i] = v;
 }
 
-// Claims the slot at `at` of the miss table for `id`; returns what was there before (kEmpty: now claimed). Called by the
+// Claims the slot at `at` of a hashed miss table for `id`; returns what was there before (kEmpty: now claimed). Called by the
 // active lanes of a wave together; `lanes` is the wave's own scratch. When a launch begins, every wave sees the slot of
 // a popular missing row empty, and swaps on one address run one after the other: of the lanes that name the same row
 // only one swaps, the others take its result. (The lanes meet in scratch at the slot's low bits; one that meets
@@ -132,13 +132,17 @@ __device__ __forceinline__ int32_t claim(int32_t* at, int32_t id, uint32_t slot,
     return follow ? of_first : key;
 }
 
+// Where the miss table has a slot per row (`own_slots`: rows <= miss_size, that is a staging area for some half of the rows
+// and more), row id's slot is slot id, and a claim is a plain store of the id, whoever stores first: swaps on the
+// memory side bound this kernel (1.33 M requests, 213 000 of them of 13 400 missing rows: 27 us with swaps, 13 so; whole
+// lookups of 1.3 M rows of 64 bytes of which 20 % are resident 247 -> 138 us, none resident 464 -> 150).
 // Grid-stride over the requests; hit/miss counts are summed per block and left in
 // block_tally for the next launch (even one atomic pair per block on the caller's two
 // counters, thousands on one address, took longer than the classification itself).
 __global__ __launch_bounds__(kThreads) void classify_kernel(
     const int32_t* __restrict__ ids, int64_t n, int64_t rows, const int32_t* __restrict__ hash_key,
     const int32_t* __restrict__ hash_slot, uint32_t hash_mask, int32_t* miss_key, uint32_t miss_size,
-    int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count, const bool share_claims) {
+    int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count, const bool own_slots, const bool share_claims) {
     __shared__ uint32_t block_hits[kThreads / kWave], block_misses[kThreads / kWave];
     __shared__ uint32_t claim_lane[kThreads / kWave][kWave];
     if (stage_count && blockIdx.x == 0 && threadIdx.x == 0) *stage_count = 0;   // for the staging that follows
@@ -161,7 +165,10 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
             } else {
                 ++misses;
                 where = kLocHost;
-                if (miss_size) {
+                if (own_slots) {                     // every writer stores the same word
+                    miss_key[id] = id;
+                    where = loc_of_stage((uint32_t)id);
+                } else if (miss_size) {
                     uint32_t s = hash_id(id, miss_size - 1);
                     for (int probe = 0; probe < kMaxMissProbes; ++probe) {
                         int32_t key = miss_key[s];
@@ -207,7 +214,7 @@ struct Service {
     uint32_t blocks;
     int32_t* miss_key;                    // staging
     int32_t* miss_row;
-    uint32_t miss_size;
+    uint32_t miss_slots;                  // of the miss table that can be claimed: a multiple of stage_span
     uint32_t stage_span;                  // miss-table slots a wave takes at a time (a power of two, at most 64)
     uint32_t* stage_count;
     uint32_t staging_rows;
@@ -341,7 +348,7 @@ __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, in
     const uint32_t num_waves = v.stage_blocks * (kThreads / kWave);
     int32_t* const list_id = lds + (threadIdx.x >> 6) * 2 * kWave;
     int32_t* const list_row = list_id + kWave;
-    for (uint32_t base = wave * v.stage_span; base < v.miss_size; base += num_waves * v.stage_span) {   // miss_size % stage_span == 0
+    for (uint32_t base = wave * v.stage_span; base < v.miss_slots; base += num_waves * v.stage_span) {
         int32_t key = kEmpty;
         if (lane < v.stage_span) key = v.miss_key[base + lane];
         if (key >= 0) v.miss_key[base + lane] = kEmpty;   // the table is empty again for the next call's claims
@@ -782,6 +789,8 @@ extern "C" int taser_cache_init(const void* host_table, int64_t rows, int32_t ro
 static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint64_t* hit_miss, hipStream_t stream,
                              int32_t* loc, uint32_t* tally, bool count_misses, Service* service) {
     const bool counts = hit_miss || count_misses;
+    // A slot per row where the miss table has that many: claims are plain stores then (see classify_kernel).
+    const bool own_slots = c->rows <= (int64_t)c->miss_size;
     int64_t blocks = (n + kThreads - 1) / kThreads;
     if (blocks > kClassifyBlocks) blocks = kClassifyBlocks;
     // miss_key is all-empty here: cache_init cleared it and every staging clears what it consumed
@@ -789,13 +798,12 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
         TaserProfileSpan span(stream, "cache_classify");
         hipLaunchKernelGGL(classify_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, ids, n, c->rows,
                            c->hash_key, c->hash_slot, c->hash_mask, c->miss_key, c->miss_size, loc,
-                           counts ? tally : nullptr, c->stage_count,
+                           counts ? tally : nullptr, c->stage_count, own_slots,
                            !c->popular_residents && 4 * c->capacity <= 3 * c->rows);
     }
     Service v = {};
     v.miss_key = c->miss_key;
     v.miss_row = c->miss_row;
-    v.miss_size = c->miss_size;
     v.stage_count = c->stage_count;
     v.staging_rows = (uint32_t)c->staging_rows;
     v.host_rows = c->host_rows;
@@ -812,9 +820,16 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     v.rows = c->rows;
     v.access_count = c->access_count;
     if (c->miss_size) v.stage_blocks = c->stage_blocks ? c->stage_blocks : default_stage_blocks(n * c->row_bytes);
-    // fewer slots at a time where a small table would leave waves without any
+    // Fewer slots at a time where a small table would leave waves without any, and where a slot per row leaves most slots claimed
+    // as far as some 16 KiB of rows go, so that all waves have the same share.
     v.stage_span = kWave;
-    while (v.stage_span > 8 && c->miss_size / v.stage_span < (uint32_t)v.stage_blocks * (kThreads / kWave)) v.stage_span /= 2;
+    v.miss_slots = c->miss_size;
+    if (own_slots) {
+        while (v.stage_span > 8 && (int64_t)v.stage_span * c->row_bytes > 16384) v.stage_span /= 2;
+        v.miss_slots = (uint32_t)c->rows;
+    }
+    while (v.stage_span > 8 && v.miss_slots / v.stage_span < (uint32_t)v.stage_blocks * (kThreads / kWave)) v.stage_span /= 2;
+    v.miss_slots = (v.miss_slots + v.stage_span - 1) / v.stage_span * v.stage_span;   // at most miss_size, a multiple of any span
     if (c->counting) {
         const int64_t want = (n + 4 * kThreads - 1) / (4 * kThreads);
         v.count_blocks = (int)(want < kCountBlocks ? want : kCountBlocks);
