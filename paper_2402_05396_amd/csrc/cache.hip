@@ -14,7 +14,7 @@
 //   1. classify: every request probes the resident hash; a miss claims a slot
 //      of the miss table (compare-and-swap on the id, or a plain store where the
 //      table has a slot per row) — the outcome per request is written to `loc`;
-//   2. one launch with two kinds of blocks. A few stage: the claimed slots get
+//   2. one launch with two kinds of blocks (or two of them: see stage_twice). A few stage: the claimed slots get
 //      consecutive rows of the staging area (so that what a call staged is one
 //      dense block of memory), a wave per slot copies that row host -> staging
 //      and empties the slot, so the miss table is clear again for the next call.
@@ -58,9 +58,11 @@ __host__ __device__ inline uint32_t hash_id(int32_t id, uint32_t mask) {
     return h & mask;
 }
 // loc encoding: >= 0 cache slot (| kHotBit); kLocZero; kLocHost; otherwise -2 - s, where s is a slot of the
-// miss table. A gather whose rows have been staged turns the latter into -2 - (row of the staging area), or
-// kLocHost where the staging area was full (see CacheSource::resolve).
+// miss table. A gather whose rows have been staged turns the latter into -2 - (row of the staging area, | kSecondBit
+// unless it was staged by a whole lookup's first launch), or kLocHost where the staging area was full (see
+// CacheSource::resolve).
 __host__ __device__ inline int32_t loc_of_stage(uint32_t s) { return -2 - (int32_t)s; }
+constexpr uint32_t kSecondBit = 1u << 30;          // staging rows are below 2^29
 
 }  // namespace
 
@@ -79,7 +81,7 @@ struct taser_cache {
     int64_t staging_rows;
     int32_t* miss_key;          // device [miss_size], all kEmpty between lookups
     int32_t* miss_row;          // device [miss_size]: staging row of a claimed slot (-1: the staging area was full)
-    uint32_t* stage_count;      // device [3]: staging rows handed out by the running call; Service::missed
+    uint32_t* stage_count;      // device [4]: staging rows handed out by the running call; Service::missed
     uint32_t miss_size;         // 0 or a power of two >= 2 * staging_rows
     int32_t* loc;               // device [loc_capacity], per-request outcome
     int64_t loc_capacity;
@@ -204,6 +206,29 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
     }
 }
 
+// How many of the miss table's spans the first of a lookup's two staging launches takes. With a share f of them it lasts
+// f of the bus's time or as long as the gather of the rows that are there, whichever is more; the second launch the rest of
+// the bus's time, or f of what the staged rows take to write; and a last launch writes the others. The sum is least where
+// the second launch's two parts take the same time, f = bus / (bus + staged rows), as long as the first launch's bus
+// time is not the shorter one. Whole numbers: several workgroups work it out and have to agree. (1.33 M requests by a power
+// law, 17 000 rows, 20 % resident, 16 % of the requests missed: f = 0.81; with 0.70, 0.75, 0.80, 0.85 instead 529, 511,
+// 495, 500 us; without skew, 30 % resident: f = 0.46, 666 us, with 0.70 693.)
+struct Split {
+    uint32_t spans;          // of the table (0: there is one launch, which takes all)
+    int64_t requests, missing_rows;   // the call's, and how many rows can be missed
+    // In the time that a row takes to be written by a launch for missed rows: a row by the bus, a row by the gather of the others.
+    static constexpr uint64_t kBus = 67 * 64, kLate = 64, kThere = 39;
+    __device__ __forceinline__ uint32_t first(uint32_t missed) const {
+        const uint64_t distinct = missed < missing_rows ? missed : (uint64_t)missing_rows;
+        const uint64_t bus = kBus * distinct, late = kLate * missed, there = kThere * ((uint64_t)requests - missed);
+        if (bus <= there) return spans;
+        uint64_t share = (bus << 12) / (bus + late);
+        const uint64_t least = (there << 12) / bus;
+        if (share < least) share = least;
+        return (uint32_t)((spans * share + 4095u) >> 12);
+    }
+};
+
 // What a lookup does beside its gather, on blocks of their own in the launch after classify:
 // the first `stage_blocks` stage the missed rows, the next one adds up the hit/miss counts (if
 // tally_blocks), the next `count_blocks` count accesses. `blocks` in all, a multiple of the number
@@ -214,9 +239,11 @@ struct Service {
     uint32_t blocks;
     int32_t* miss_key;                    // staging
     int32_t* miss_row;
-    uint32_t miss_slots;                  // of the miss table that can be claimed: a multiple of stage_span
+    uint32_t spans;                       // of the miss table that can hold claims
     uint32_t stage_span;                  // miss-table slots a wave takes at a time (a power of two, at most 64)
     uint32_t* stage_count;
+    Split split;                          // of the spans, over two launches
+    bool second;                          // this is the second of them
     uint32_t staging_rows;
     const uint8_t* host_rows;
     int64_t pitch_bytes;
@@ -226,7 +253,7 @@ struct Service {
     const uint32_t* block_tally;          // hit/miss counts of tally_blocks classify blocks (0: not wanted)
     int tally_blocks;
     unsigned long long* hit_miss;         // the caller's counters, or null
-    uint32_t* missed;                     // [2]: the misses of this call alone, whether one row has many of them; or null
+    uint32_t* missed;                     // [3]: the misses of this call alone, whether one row has many of them, Split::first; or null
     const int32_t* loc;                   // the call's locations where missed[1] is wanted, else null
     const int32_t* ids;                   // access counting
     int64_t n, rows;
@@ -286,6 +313,7 @@ __device__ __forceinline__ void tally_block(const Service& v, int32_t* __restric
         if (v.hit_miss && h) atomicAdd(&v.hit_miss[0], h);
         if (v.hit_miss && m) atomicAdd(&v.hit_miss[1], m);
         if (v.missed) v.missed[0] = m < 0xffffffffull ? (uint32_t)m : 0xffffffffu;
+        if (v.split.spans) v.missed[2] = v.split.first((uint32_t)m);
     }
 }
 
@@ -340,6 +368,11 @@ inline int default_stage_blocks(int64_t out_bytes) {
     return out_bytes >= (int64_t)1 << 28 ? 32 : out_bytes >= (int64_t)1 << 26 ? 64 : 128;
 }
 
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {   // in every lane
+    for (int d = 1; d < kWave; d <<= 1) v += __shfl_xor(v, d, kWave);
+    return v;
+}
+
 // `lds`: 2 * kWave words per wave
 __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, int32_t* __restrict__ lds) {
     using taser_gather::Chunk16;
@@ -348,7 +381,24 @@ __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, in
     const uint32_t num_waves = v.stage_blocks * (kThreads / kWave);
     int32_t* const list_id = lds + (threadIdx.x >> 6) * 2 * kWave;
     int32_t* const list_row = list_id + kWave;
-    for (uint32_t base = wave * v.stage_span; base < v.miss_slots; base += num_waves * v.stage_span) {
+    uint32_t from = 0, end = v.spans;
+    if (v.split.spans) {
+        if (v.second) {
+            from = v.missed[2];
+        } else {                             // before anybody has added up the misses
+            __shared__ uint32_t part[kThreads / kWave];
+            uint32_t m = 0;
+            for (int b = threadIdx.x; b < v.tally_blocks; b += kThreads) m += v.block_tally[2 * b + 1];
+            m = wave_sum(m);
+            if (lane == 0) part[threadIdx.x >> 6] = m;
+            __syncthreads();
+            m = 0;
+            for (int w = 0; w < kThreads / kWave; ++w) m += part[w];
+            end = v.split.first(m);
+        }
+    }
+    for (uint32_t span = from + wave; span < end; span += num_waves) {
+        const uint32_t base = span * v.stage_span;
         int32_t key = kEmpty;
         if (lane < v.stage_span) key = v.miss_key[base + lane];
         if (key >= 0) v.miss_key[base + lane] = kEmpty;   // the table is empty again for the next call's claims
@@ -463,8 +513,15 @@ struct CacheSource {
     int64_t pitch_bytes;
     int owner_mode;   // 1: by source row; 2: by position only
     const int32_t* miss_row;
+    uint32_t spans, span;    // two staging launches: the miss table's spans, their slots
+    uint32_t second_from;    // the slots before it were staged by the first of the two
+    __device__ __forceinline__ bool split() const { return spans != 0; }
+    __device__ __forceinline__ void begin() {
+        if (split()) second_from = missed[2] * span;
+    }
+    __device__ __forceinline__ bool arrived() const { return second_from == spans * span; }
     __device__ __forceinline__ int32_t key(int64_t i) const { return loc[i]; }
-    const uint32_t* missed;   // [2]: requests that missed, whether one row has many of them (whole lookups only)
+    const uint32_t* missed;   // Service::missed (whole lookups only)
     __device__ __forceinline__ uint32_t late() const { return missed[0]; }
     __device__ __forceinline__ bool late_skewed() const { return missed[1] != 0; }
     // a missed row, on its way while the staging runs
@@ -472,15 +529,30 @@ struct CacheSource {
     // from miss-table slot to staging row, once that is known
     __device__ __forceinline__ int32_t resolve(int32_t where) const {
         if (where < kLocZero && where != kLocHost) {
-            const int32_t row = miss_row[-2 - where];
+            const uint32_t slot = (uint32_t)(-2 - where);
+            const int32_t row = miss_row[slot];
+            where = row >= 0 ? loc_of_stage((uint32_t)row | (slot < second_from ? 0u : kSecondBit)) : kLocHost;
+        }
+        return where;
+    }
+    // the same while the slots from second_from on are being staged (kLocHost: not there yet, or not to be)
+    __device__ __forceinline__ int32_t resolve_first(int32_t where) const {
+        if (where < kLocZero && where != kLocHost) {
+            const uint32_t slot = (uint32_t)(-2 - where);
+            const int32_t row = slot < second_from ? miss_row[slot] : -1;
             where = row >= 0 ? loc_of_stage((uint32_t)row) : kLocHost;
         }
         return where;
     }
+    template <int PHASE> __device__ __forceinline__ bool in_phase(int32_t where) const {
+        if (PHASE == 3) return where < kLocZero && !after(where);
+        return where < kLocZero && (where == kLocHost || ((uint32_t)(-2 - where) & kSecondBit));
+    }
+    __device__ __forceinline__ bool after(int32_t where) const { return where == kLocHost && !arrived(); }
     __device__ __forceinline__ const uint8_t* address(int32_t where, int64_t i) const {
         // cache row or staged row: one multiply-add either way, no branch
         const bool cached = where >= 0;
-        const uint8_t* at = (cached ? cache_rows : stage_rows) + (int64_t)(cached ? (where & kSlotMask) : -2 - where) * dev_pitch;
+        const uint8_t* at = (cached ? cache_rows : stage_rows) + (int64_t)(cached ? (where & kSlotMask) : (int32_t)((uint32_t)(-2 - where) & ~kSecondBit)) * dev_pitch;
         if (where == kLocZero) at = nullptr;
         if (__builtin_expect(where == kLocHost, 0)) at = host_rows + (int64_t)ids[i] * pitch_bytes;
         return at;
@@ -773,7 +845,7 @@ extern "C" int taser_cache_init(const void* host_table, int64_t rows, int32_t ro
         CACHE_TRY(hipMalloc((void**)&c->stage_rows, (size_t)staging_rows * c->dev_pitch));
         CACHE_TRY(hipMalloc((void**)&c->miss_key, (size_t)c->miss_size * sizeof(int32_t)));
         CACHE_TRY(hipMalloc((void**)&c->miss_row, (size_t)c->miss_size * sizeof(int32_t)));
-        CACHE_TRY(hipMalloc((void**)&c->stage_count, 3 * sizeof(uint32_t)));
+        CACHE_TRY(hipMalloc((void**)&c->stage_count, 4 * sizeof(uint32_t)));
         hipLaunchKernelGGL(fill_kernel, dim3((c->miss_size + kThreads - 1) / kThreads), dim3(kThreads), 0, stream,
                            c->miss_key, c->miss_size, kEmpty);
         hipLaunchKernelGGL(fill_kernel, dim3(1), dim3(kThreads), 0, stream, reinterpret_cast<int32_t*>(c->stage_count), 1u, 0);
@@ -823,13 +895,13 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     // Fewer slots at a time where a small table would leave waves without any, and where a slot per row leaves most slots claimed
     // as far as some 16 KiB of rows go, so that all waves have the same share.
     v.stage_span = kWave;
-    v.miss_slots = c->miss_size;
+    uint32_t slots = c->miss_size;
     if (own_slots) {
         while (v.stage_span > 8 && (int64_t)v.stage_span * c->row_bytes > 16384) v.stage_span /= 2;
-        v.miss_slots = (uint32_t)c->rows;
+        slots = (uint32_t)c->rows;
     }
-    while (v.stage_span > 8 && v.miss_slots / v.stage_span < (uint32_t)v.stage_blocks * (kThreads / kWave)) v.stage_span /= 2;
-    v.miss_slots = (v.miss_slots + v.stage_span - 1) / v.stage_span * v.stage_span;   // at most miss_size, a multiple of any span
+    while (v.stage_span > 8 && slots / v.stage_span < (uint32_t)v.stage_blocks * (kThreads / kWave)) v.stage_span /= 2;
+    v.spans = (slots + v.stage_span - 1) / v.stage_span;   // miss_size, a multiple of any span, has room for them
     if (c->counting) {
         const int64_t want = (n + 4 * kThreads - 1) / (4 * kThreads);
         v.count_blocks = (int)(want < kCountBlocks ? want : kCountBlocks);
@@ -839,7 +911,7 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
 }
 
 static CacheSource source_of(const taser_cache* c, const int32_t* ids, const int32_t* loc) {
-    return CacheSource{loc, ids, c->cache_rows, c->stage_rows, c->dev_pitch, c->host_rows, c->pitch_bytes, c->partitioned_gather, c->miss_row, c->stage_count ? c->stage_count + 1 : nullptr};
+    return CacheSource{loc, ids, c->cache_rows, c->stage_rows, c->dev_pitch, c->host_rows, c->pitch_bytes, c->partitioned_gather, c->miss_row, 0u, 0u, 0u, c->stage_count ? c->stage_count + 1 : nullptr};
 }
 
 static int source_alignment(const taser_cache* c) {
@@ -889,9 +961,22 @@ static int enqueue_gather(taser_cache* c, const int32_t* ids, int64_t n, void* o
     return TASER_OK;
 }
 
+// Whether the last of the missed rows are staged by a launch of their own, beside which those of the first are written: for
+// launches with 1 GiB and more to write, where a third of the rows and more can be missed and reading these may take half
+// as long as writing the output (the bus moves a hundredth of what memory does). How much is left to the second launch
+// follows the misses (see Split). us a lookup with one staging launch and with two, rows of 1652 bytes: 1.33 M requests by a
+// power law, 17 000 rows, 10 / 20 / 30 / 50 % of them resident 627 535, 540 497, 480 478, 435 440; without skew, 30 / 50 % 820
+// 666, 600 563; 700 000 requests of 60 000 rows, 20 % 1 270 1 242, 74 % 435 446. A launch more costs 4 us: 800 000 requests of
+// 1 064 bytes, 4 000 rows, 203 and 209; 727 MB by the 17 000 rows, 20 % resident, 457 and 443, without skew 574 and 585; 182
+// MB 326 and 332.
+static bool stage_twice(const taser_cache* c, int64_t n) {
+    const int64_t out_bytes = n * c->row_bytes, missing = c->rows - c->capacity;
+    return out_bytes >= (int64_t)1 << 30 && 3 * missing >= c->rows && missing * c->row_bytes >= out_bytes / 200;
+}
+
 // A whole lookup. Where there is a staging area to wait for, the output that does not need it is
-// written meanwhile (1.33 M rows of 1652 bytes, 0.46 ms of staging, 0.37 ms of gather: 0.91 ms one after the
-// other, 0.58 ms so; the launch for the staged rows takes 0.10 of that).
+// written meanwhile (1.33 M rows of 1652 bytes, 0.42 ms of staging, 0.34 ms of gather and 0.11 of staged rows: 0.91 ms one
+// after the other, 0.50 so).
 // Not with the working set re-written before the gather (that is for callers who run other kernels
 // between the halves) nor into an output that only the element kernel can write.
 static int enqueue_lookup(taser_cache* c, const int32_t* ids, int64_t n, void* out, uint64_t* hit_miss, hipStream_t stream,
@@ -905,10 +990,21 @@ static int enqueue_lookup(taser_cache* c, const int32_t* ids, int64_t n, void* o
     const uint8_t* zeros = tg::zero_chunk();
     if (!zeros) return taser_fail(TASER_E_HIP, "cache_lookup: the zero constant is not available on this device");
     const bool owned = c->partitioned_gather && tg::owned_applies(align, c->row_bytes, n, out);
-    const CacheSource source = source_of(c, ids, loc);
+    CacheSource source = source_of(c, ids, loc);
     Service v;
     enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, true, &v);
     if (owned) v.loc = loc;
+    const bool twice = owned && stage_twice(c, n);
+    Service second;
+    if (twice) {
+        v.split = Split{v.spans, n, c->rows - c->capacity};
+        source.spans = v.spans;
+        source.span = v.stage_span;
+        second = v;
+        second.second = true;
+        second.count_blocks = second.tally_blocks = 0;
+        second.blocks = (uint32_t)((v.stage_blocks + tg::kOwnerClasses - 1) / tg::kOwnerClasses * tg::kOwnerClasses);
+    }
     bool launched;
     {
         // the gather's blocks are behind the service blocks, so the staging starts first and its few blocks
@@ -916,6 +1012,10 @@ static int enqueue_lookup(taser_cache* c, const int32_t* ids, int64_t n, void* o
         TaserProfileSpan span(stream, "cache_stage_and_gather_rows");
         launched = owned ? tg::launch_owned<1>(source, c->row_bytes, n, out, zeros, stream, v)
                          : tg::launch_chunks<4, 1>(source, c->row_bytes, n, out, zeros, stream, v);
+    }
+    if (launched && twice) {
+        TaserProfileSpan span(stream, "cache_stage_and_gather_staged_rows");
+        launched = tg::launch_owned<3>(source, c->row_bytes, n, out, zeros, stream, second);
     }
     if (launched) {
         TaserProfileSpan span(stream, "cache_gather_staged_rows");

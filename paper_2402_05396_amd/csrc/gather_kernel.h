@@ -65,10 +65,19 @@ template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) 
 //   resolve(key)    the token for PHASES 0 and 2 (PHASE 1 takes it as it is read);
 //   late()          how many output rows PHASE 2 has to write (at most 2^32 - 1 of them counted);
 //   late_skewed()   many of them are copies of the same source row.
+// The owned-lines kernel can have a PHASE 3 between the two, when a part of the pending rows has arrived and the others
+// are still on their way: it writes the first of them, and PHASE 2 is left with the others. For that a Source has
+//   begin()              called when PHASE 2 or 3 begins: how far the rows are;
+//   split()              there was a PHASE 3 or will be;
+//   arrived()            all rows had arrived before PHASE 3, which then does all of PHASE 2's work;
+//   resolve_first(key)   the token for PHASE 3;
+//   in_phase<P>(key)     a row that PHASE P (2 or 3) writes, if it does not write everything;
+//   after(key)           PHASE 3: the row is still on its way.
 
 template <int PHASE, typename Source> __device__ __forceinline__ int32_t source_token(const Source& source, int64_t i) {
     const int32_t key = source.key(i);
-    return PHASE == 1 ? key : source.resolve(key);
+    if constexpr (PHASE == 3) return source.resolve_first(key);
+    else return PHASE == 1 ? key : source.resolve(key);
 }
 
 // UNIT: the size that divides rows, pitches and source addresses, 4 or 2 bytes; offsets are counted
@@ -264,14 +273,14 @@ struct ChunkGrid {   // slots: 16-byte chunks of the most lines a row can own; t
 };
 struct OwnedLines {
     uint32_t row_bytes;
-    ChunkGrid chunks, late_chunks;   // PHASE 2 takes the second while it only writes the rows that were on their way
+    ChunkGrid chunks, late_chunks;   // PHASES 2 and 3 take the second while they only write rows that were on their way
     int64_t total_bytes, n_rows;
-    uint32_t tiles, late_classes, whole_from;   // PHASE 2: super-tiles; classes; how many late rows make it write everything
+    uint32_t tiles, late_classes, whole_from;   // PHASES 2 and 3: super-tiles; classes; how many late rows make it write everything
 };
 
 // In PHASE 1 only the lines of rows that are there are written, up to where a pending row begins. In
-// PHASE 2 a pending row's share is the whole range from its own first byte (inside a line of the row
-// before it) to the end of its last line.
+// PHASES 2 and 3 a pending row's share is the whole range from its own first byte (inside a line of the row
+// before it) to the end of its last line, in PHASE 3 up to where a row begins that is still on its way.
 template <typename Source, int PHASE, typename Beside>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))) void gather_owned_lines_kernel(
     Source source, const OwnedLines g, const uint8_t* __restrict__ zeros, uint8_t* __restrict__ out, const Beside beside) {
@@ -290,13 +299,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
 
     const uint32_t row_bytes = g.row_bytes;
     const int64_t total_bytes = g.total_bytes, n_rows = g.n_rows;
-    // a unit of work is a super-tile's rows of one class (or all); outside PHASE 2 a workgroup has exactly one
+    // a unit of work is a super-tile's rows of one class (or all); before PHASE 2 a workgroup has exactly one
     uint32_t classes = kOwnerClasses, units = 0;
     bool only_late = false;   // write the rows that were on their way in PHASE 1, not the others
-    if constexpr (PHASE == 2) {
+    if constexpr (PHASE >= 2) {
         const uint32_t late = source.late();
         if (late == 0) return;
         only_late = late < g.whole_from || source.late_skewed();
+        source.begin();
+        // PHASE 3 writes what is there, PHASE 2 the rest; everything if all is there or if nothing has been written yet
+        if (PHASE == 3 && !source.arrived() && !only_late) return;
+        if (PHASE == 2 && source.split() && source.arrived()) return;
         if (only_late) classes = g.late_classes;
         units = classes * g.tiles;
         if (block >= units) return;
@@ -324,13 +337,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             const int64_t r = r0 + i;
             const int32_t key = tile_key[i];
             if (PHASE == 1 && source.pending(key)) continue;
-            if (only_late && !source.pending(key)) continue;
-            if ((PHASE != 2 || classes > 1) && source.owner(key, r) != cls) continue;
+            if constexpr (PHASE >= 2)
+                if (only_late && !source.template in_phase<PHASE>(key)) continue;
+            if ((PHASE < 2 || classes > 1) && source.owner(key, r) != cls) continue;
             const int64_t begin = r * row_bytes;
             // lines whose first byte is in row r, and for late rows the one that row r begins in
             const int64_t first = (begin + (only_late ? 0 : 127)) >> 7, next = (begin + row_bytes + 127) >> 7;
             const uint8_t* base = source.address(key, r);
-            const bool later = PHASE == 1 && i + 1 < keys_here && source.pending(tile_key[i + 1]);   // the next row is PHASE 2's
+            bool later = false;                                                     // the next row is another phase's
+            if (PHASE == 1) later = i + 1 < keys_here && source.pending(tile_key[i + 1]);
+            if constexpr (PHASE == 3) later = i + 1 < keys_here && source.after(tile_key[i + 1]);
             const uint8_t* after = i + 1 < keys_here && !later ? source.address(tile_key[i + 1], r + 1) : nullptr;
             const uint32_t at = atomicAdd(&n_owned, 1u);
             own_base[at] = base ? base : zeros;
@@ -345,7 +361,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
             const uint8_t* from[kUnroll];
             uint32_t out_off[kUnroll], which[kUnroll], in_off[kUnroll];
             bool whole[kUnroll], cross[kUnroll];
-            // (in_off: bytes from the row's start; with PHASE 2 negative before it)
+            // (in_off: bytes from the row's start; from PHASE 2 on negative before it)
             // one division per thread: its further chunks lie kThreads = step_rows * slots + step_rest chunks on
             const uint32_t w0 = round + threadIdx.x;
             uint32_t j = __umulhi(w0, chunks.slot_magic), within = w0 - j * slots;   // exact: w0 * slots < 2^32
@@ -361,9 +377,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 const bool beyond = off >= (int32_t)row_bytes;                         // the chunk lies in the next output row
                 const uint8_t* base = beyond ? own_next[jj] : own_base[jj];
                 const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
-                if (PHASE == 1) mine = mine && base != nullptr;
-                if (PHASE == 2) mine = mine && off > -16;                              // wholly the row before's otherwise
-                whole[u] = mine && out_off[u] + 16u <= tile_limit && (beyond || off + 16 <= (int32_t)row_bytes) && (PHASE != 2 || off >= 0);
+                if (PHASE & 1) mine = mine && base != nullptr;
+                if (PHASE >= 2) mine = mine && off > -16;                              // wholly the row before's otherwise
+                whole[u] = mine && out_off[u] + 16u <= tile_limit && (beyond || off + 16 <= (int32_t)row_bytes) && (PHASE < 2 || off >= 0);
                 cross[u] = mine && !whole[u] && out_off[u] < tile_limit;
                 from[u] = (whole[u] && !zero) ? base + off : zeros;
                 in_off[u] = (uint32_t)off;
@@ -394,7 +410,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                     const int32_t off = (int32_t)in_off[u] + 4 * e;
                     const bool beyond = off >= (int32_t)row_bytes;
                     const bool zero = (meta >> (beyond ? 31 : 30)) & 1u;
-                    ours[e] = out_off[u] + 4u * e < tile_limit && (PHASE != 1 || !beyond || b) && (PHASE != 2 || off >= 0);
+                    ours[e] = out_off[u] + 4u * e < tile_limit && (!(PHASE & 1) || !beyond || b) && (PHASE < 2 || off >= 0);
                     all = all && ours[e];
                     if (ours[e] && !zero) wds[e] = *(GlobalU32Ptr)((beyond ? b : a) + off);
                 }
@@ -411,7 +427,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
                 if (whole[u]) __builtin_nontemporal_store(vals[u], reinterpret_cast<u32x4*>(tile_out + out_off[u]));
             }
         }
-        if (PHASE != 2 || (unit += gridDim.x) >= units) return;
+        if (PHASE < 2 || (unit += gridDim.x - beside.blocks) >= units) return;
         __syncthreads();   // the lists are made again
     }
 }
@@ -558,7 +574,7 @@ inline bool launch_owned(const Source& source, int32_t row_bytes, int64_t n, voi
     const int64_t tiles = ((g.total_bytes + 127) / 128 + kOwnedTileLines - 1) / kOwnedTileLines;
     int64_t blocks = tiles * kOwnerClasses;
     if (blocks > 0x7fffffffLL) return false;
-    if (PHASE == 2) {
+    if (PHASE >= 2) {
         g.late_chunks = chunk_grid(lines + 1);
         g.tiles = (uint32_t)tiles;
         g.late_classes = blocks <= kOwnedLateBlocks ? kOwnerClasses : 1;

@@ -1,0 +1,69 @@
+"""Lookups with a gigabyte and more to write, whose last missed rows are staged by a launch of their own: shares of
+misses from which the first launch takes some spans, all of them or next to none, popular rows among the missed ones,
+staging areas that are too small, and replays from a graph."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_05396_amd as T
+
+pytestmark = pytest.mark.gpu
+
+ROWS, DIM, N = 6000, 850, 330_001          # 1.12 GB of output, 20 MB of rows
+
+
+def _requests(gen, kind):
+    if kind == "uniform":
+        ids = torch.randint(0, ROWS, (N,), generator=gen, device="cuda")
+    else:                                  # popular rows have the lowest ids, or the highest
+        ids = (torch.rand(N, generator=gen, device="cuda") ** 5 * ROWS).long().clamp_(max=ROWS - 1)
+        if kind == "popular_last":
+            ids = ROWS - 1 - ids
+    ids = ids.int()
+    ids[5::97], ids[7::89] = -1, ROWS
+    return ids
+
+
+@pytest.mark.parametrize("resident", [0, 2, 1500, 3000])
+@pytest.mark.parametrize("kind", ["uniform", "popular_first", "popular_last"])
+def test_every_split_writes_the_same(kind, resident):
+    gen = torch.Generator(device="cuda").manual_seed(resident + len(kind))
+    host = torch.randn((ROWS, DIM), generator=torch.Generator().manual_seed(1)).pin_memory()
+    table = torch.cat([host.cuda(), torch.zeros((1, DIM), device="cuda")])
+    residents = torch.arange(resident, dtype=torch.int32)
+    for staging in (ROWS - resident, 700):
+        c = T.cache_init(host, resident, residents, staging_rows=staging)
+        T.cache_count_accesses(c)
+        for _ in range(2):
+            ids = _requests(gen, kind)
+            ok = (ids >= 0) & (ids < ROWS)
+            buf = torch.full((N * DIM + 40,), 7.0, device="cuda")
+            hm = torch.zeros(2, dtype=torch.int64, device="cuda")
+            out = T.cache_lookup(c, ids, out=buf[:N * DIM].view(N, DIM), hit_miss=hm)
+            assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]) and bool((buf[N * DIM:] == 7.0).all()), staging
+            assert hm.tolist() == [int((ok & (ids < resident)).sum()), int((ok & (ids >= resident)).sum())]
+            out.fill_(3.0)
+            T.cache_gather(c, ids, out=out)    # accepted: the lookup of these ids was their prefetch as well
+            assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]), (staging, "gather after the lookup")
+        T.cache_free(c)
+
+
+def test_replays_with_other_requests():
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    host = torch.randn((ROWS, DIM), generator=torch.Generator().manual_seed(2)).pin_memory()
+    table = torch.cat([host.cuda(), torch.zeros((1, DIM), device="cuda")])
+    c = T.cache_init(host, 1500, torch.arange(1500, dtype=torch.int32), staging_rows=4500)
+    ids, out = torch.zeros(N, dtype=torch.int32, device="cuda"), torch.empty((N, DIM), device="cuda")
+    T.cache_lookup(c, ids, out=out)
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        T.cache_lookup(c, ids, out=out, stream=stream)
+    for kind in ("uniform", "popular_first", "popular_last", "uniform"):
+        ids.copy_(_requests(gen, kind))
+        out.fill_(1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        ok = (ids >= 0) & (ids < ROWS)
+        assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]), kind
+    T.cache_free(c)
