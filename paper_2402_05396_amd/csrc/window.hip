@@ -30,15 +30,20 @@ __device__ __forceinline__ uint32_t first_bits(int n, int from) {
 // freq is the mask's population count. The m x m identity bytes are those masks, one bit per byte: the
 // masks of the block's roots go into LDS as one string of bits, and the block's range of the output is
 // written from it 16 bytes at a time (4 bits times 0x204081 are 4 bytes), whatever m and the alignment.
-// Bound by its output: 40 000 windows of 25 (33 MB in all) take 12 us; with one lane shuffle per comparison
-// and per output byte it was 24 us of vector and LDS instructions.
+// Bound by its output: 40 000 windows of 25 (33 MB in all) take 9.2 us, 6.4 at the rate of a large copy; with one lane shuffle
+// per comparison and per output byte it was 24 us of vector and LDS instructions, with ordinary stores 9.8. (The next windows' loads ahead of
+// the present ones' work, in blocks that stay, or a load of the ids that does not wait for the count: 1.04 to 1.2 of the time.)
+// Roots of a block. The identity matrices of 16 are whole 16-byte pieces whatever m is: with 8 roots of 25 candidates every block
+// had a piece that it shared with its neighbor, written byte by byte, and 40 000 windows took 11.4 us where those of 32, with
+// more bytes, took 10.9. With 64 lanes per root 16 would be blocks of 1 024 threads (2 000 windows of 64 5.9 us, of 4 roots 4.8).
+constexpr int encoding_roots(int lanes) { return lanes == 64 ? 4 : 16; }
 template <int G>
-__global__ __launch_bounds__(kThreads) void candidate_encodings_kernel(
+__global__ __launch_bounds__(encoding_roots(G) * G) void candidate_encodings_kernel(
     const int32_t* __restrict__ nbr, const int32_t* __restrict__ count, int64_t num_roots, int m, int32_t* __restrict__ freq,
     uint8_t* __restrict__ identity) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    constexpr int kRoots = kThreads / G;                // roots of a block
+    constexpr int kRoots = encoding_roots(G), kThreads = kRoots * G;
     constexpr int kWords = kRoots * G * G / 32 + 1;     // bits of their identity matrices, and a word to read past the end
     constexpr int kParts = G > 32 ? 2 : 1;              // 32-bit parts of a mask
     __shared__ __align__(16) int32_t cand[kThreads];
@@ -106,10 +111,18 @@ __global__ __launch_bounds__(kThreads) void candidate_encodings_kernel(
             v.y = __umul24((x >> 4) & 15u, 0x204081u) & 0x01010101u;
             v.z = __umul24((x >> 8) & 15u, 0x204081u) & 0x01010101u;
             v.w = __umul24((x >> 12) & 15u, 0x204081u) & 0x01010101u;
-            *reinterpret_cast<u32x4*>(aligned + off) = v;
+            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(aligned + off));
         } else {   // the range's first or last bytes
-            for (uint32_t o = off; o < off + 16u; ++o)
-                if (o >= head && o < head + length) aligned[o] = (uint8_t)((bits[(o - head) / 32u] >> ((o - head) & 31u)) & 1u);
+            for (uint32_t o = off; o < off + 16u; o += 4u) {
+                if (o >= head && o + 4u <= head + length) {
+                    const uint32_t b = o - head;
+                    const uint32_t x = __builtin_amdgcn_alignbit(bits[b / 32u + 1u], bits[b / 32u], b & 31u) & 15u;
+                    *reinterpret_cast<uint32_t*>(aligned + o) = __umul24(x, 0x204081u) & 0x01010101u;
+                } else {
+                    for (uint32_t e = o; e < o + 4u; ++e)
+                        if (e >= head && e < head + length) aligned[e] = (uint8_t)((bits[(e - head) / 32u] >> ((e - head) & 31u)) & 1u);
+                }
+            }
         }
     }
 }
@@ -405,12 +418,9 @@ extern "C" int taser_candidate_encodings(const int32_t* nbr, const int32_t* coun
     taser_clear_stale_hip_error();
     hipStream_t stream = (hipStream_t)hip_stream;
     TaserProfileSpan span(stream, "candidate_encodings");
-    if (m <= 16)
-        hipLaunchKernelGGL((candidate_encodings_kernel<16>), dim3(grid_for<16>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, freq, identity);
-    else if (m <= 32)
-        hipLaunchKernelGGL((candidate_encodings_kernel<32>), dim3(grid_for<32>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, freq, identity);
-    else
-        hipLaunchKernelGGL((candidate_encodings_kernel<64>), dim3(grid_for<64>(num_roots)), dim3(kThreads), 0, stream, nbr, count, num_roots, m, freq, identity);
+    const int lanes = m <= 16 ? 16 : m <= 32 ? 32 : 64, roots = encoding_roots(lanes);
+    const auto kernel = lanes == 16 ? candidate_encodings_kernel<16> : lanes == 32 ? candidate_encodings_kernel<32> : candidate_encodings_kernel<64>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((num_roots + roots - 1) / roots)), dim3(roots * lanes), 0, stream, nbr, count, num_roots, m, freq, identity);
     TASER_HIP_TRY(hipGetLastError());
     return TASER_OK;
 }
