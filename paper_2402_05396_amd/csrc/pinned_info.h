@@ -1,4 +1,4 @@
-// Four words of page-locked host memory for one build's inspection result (host code only).
+// Eight words of page-locked host memory for what one build has to know from its kernels (host code only).
 #pragma once
 
 #include <hip/hip_runtime_api.h>
@@ -7,7 +7,7 @@
 #include <mutex>
 
 // The fold kernel writes the words itself, so that planning the sort waits for a kernel and not for a copy behind
-// it. 64 builds of the process can hold four words at a time (a page that stays until it ends); a further one finds
+// it. 64 builds of the process can hold eight words at a time (a page that stays until it ends); a further one finds
 // `words` null and reads its result back from the scratch block instead.
 //
 // A slot goes to another build only once nothing can write it any more: launched() says that kernels which may

@@ -16,6 +16,8 @@
 //     so the last pass leaves the final layout in place. The first pass reads the
 //     caller's columns directly: nothing is packed beforehand;
 //   * indptr is read off the sorted node column (no atomics, no histogram);
+//   * input in no order of at most 1.5 M entries is cut into buckets by sampled keys instead, which a workgroup each sorts
+//     in LDS (sort_bucket_kernel): two passes over memory however many bits the keys have;
 //   * time-sorted input with node ids of two digits and timestamps that span less than 2^32 (136 years of seconds, 49
 //     days of milliseconds) has two passes of its own that move fewer bytes (node_scatter_kernel), and its indptr comes
 //     from the scanned histogram.
@@ -86,6 +88,23 @@ template <uint32_t kOf = kCopies> __device__ __forceinline__ uint32_t count_of_d
 // histogram kernel. It reads 12 of an entry's 20 bytes and writes nothing per entry: 0.17 ms for
 // 64 M entries (4.5 TB/s, with 4- and 8-byte loads 0.177 ms), where packing the columns into records here, and
 // reading them back in the first pass, took 0.50.
+// On the way it also takes `samples` (if not null) out of every tile, one of each kStratum places, for rank_samples_kernel.
+struct Sample {
+    int64_t ts;
+    int32_t node;
+    uint32_t pos;
+};
+struct Samples {
+    Sample* at;        // null: none wanted
+    uint32_t* rank;    // set to 0
+};
+constexpr uint32_t kStratum = 256;   // of a small tile: one wave's run of four entries per lane
+__device__ __forceinline__ uint32_t sample_place(uint32_t sample) {   // in its stratum
+    uint32_t h = sample * 0x9E3779B1u;
+    h ^= h >> 15;
+    h *= 0x85EBCA77u;
+    return (h >> 13) % kStratum;
+}
 constexpr unsigned kInspectBlocks = 1024;   // 4 per compute unit; the fold below is one block over their words
 struct __attribute__((packed, aligned(4))) FourNodes {
     int32_t v[4];
@@ -97,8 +116,9 @@ template <int kItems>
 __global__ __launch_bounds__(kSortThreads) void inspect_kernel(const int32_t* __restrict__ src, const int64_t* __restrict__ ts,
                                                            int64_t n, int32_t num_nodes,
                                                            unsigned long long* __restrict__ partial, int low_bits,
-                                                           uint32_t* __restrict__ hist, uint32_t num_tiles) {
+                                                           uint32_t* __restrict__ hist, uint32_t num_tiles, const Samples samples) {
     constexpr int kTile = kSortThreads * kItems;
+    constexpr uint32_t kStrata = kTile / kStratum;
     __shared__ uint32_t bins[kBins * kCopies];
     const uint32_t low_mask = (1u << low_bits) - 1u, copy = threadIdx.x % kCopies;
     unsigned long long any_or = 0, all_and = ~0ull;
@@ -138,8 +158,22 @@ __global__ __launch_bounds__(kSortThreads) void inspect_kernel(const int32_t* __
                     all_and &= biased(x[j]);
                     atomicAdd(&bins[((uint32_t)s[u].v[j] & low_mask) * kCopies + copy], 1u);
                 }
+                if (kItems == kSmallItems && samples.at) {
+                    const uint32_t sample = tile * kStrata + threadIdx.x * 4u / kStratum, place = sample_place(sample);
+                    if (threadIdx.x * 4u % kStratum == place / 4u * 4u) {
+                        const uint32_t j = place % 4u;
+                        samples.rank[sample] = 0;
+                        samples.at[sample] = Sample{j == 0 ? x[0] : j == 1 ? x[1] : j == 2 ? x[2] : x[3], j == 0 ? s[u].v[0] : j == 1 ? s[u].v[1] : j == 2 ? s[u].v[2] : s[u].v[3],
+                                                 (uint32_t)tile0 + threadIdx.x * 4u + j};
+                    }
+                }
             }
         } else {
+            if (kItems == kSmallItems && samples.at && threadIdx.x < kStrata) {
+                const uint32_t sample = tile * kStrata + threadIdx.x, at = threadIdx.x * kStratum + sample_place(sample), i = at < last ? at : last;
+                samples.rank[sample] = 0;
+                samples.at[sample] = Sample{tile_ts[i], tile_src[i], (uint32_t)tile0 + i};
+            }
             for (uint32_t i = threadIdx.x; i <= last; i += kSortThreads) {
                 const int32_t node = tile_src[i];
                 const int64_t x = tile_ts[i];
@@ -564,7 +598,8 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
 // the lists of the nodes in (key[p - 1], key[p]]. A thread looks at four consecutive positions (one
 // 16-byte load; `key` is the start of an allocation) plus the key before them.
 __global__ __launch_bounds__(kThreads) void indptr_kernel(const int32_t* __restrict__ key, int64_t n,
-                                                          int32_t num_nodes, int64_t* __restrict__ indptr) {
+                                                          int32_t num_nodes, int64_t* __restrict__ indptr, const uint32_t* __restrict__ failed) {
+    if (failed && *failed) return;   // the column is not in order
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
     const int64_t p0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
     if (p0 > n) return;
@@ -747,6 +782,297 @@ __global__ __launch_bounds__(kSortThreads) void list_starts_kernel(const uint32_
     if (low == 0 && own == 0) indptr[num_nodes] = n;
 }
 
+// ---- input in no order, few entries ------------------------------------------------------------
+// The passes above move every entry once per digit, four times for 36 bits of key, and a pass over few entries is three
+// launches that do not fill the chip. Here the entries are moved once into buckets of some 2 000 to 3 000 neighbors in the final
+// order, and once more by a workgroup per bucket that sorts it in LDS. The buckets' limits are quantiles of the samples that
+// the inspection took (eight per 2 048 entries), with the position as the key's last digit, so that equal keys divide as well.
+// The largest bucket passes 2.7 times the mean, which is what LDS has room for at most, in some of a thousand inputs of the
+// largest size; then the passes above do it all. 1.34 M entries, 36 bits of key, with the plain view: 183 us by 17 launches, so
+// 157 by 11 (kernels: samples' ranks 10, buckets 13, scan 5, scatter 16, sort 41, which is what the largest bucket takes).
+// Builds by digits / by buckets, us: 2 000 entries of 300 nodes over 2^24 ticks 92 / 60, 20 000 of 17 000 nodes 108 / 88, 200 000
+// 121 / 90, 700 000 146 / 108, 1 570 000 172 / 138; over 2^32 ticks 194 / 144. With so few bits that the passes are three at most
+// it is a draw from half a million entries on: 1.34 M entries of 300 nodes over 1 000 ticks 113 / 121, of 17 000 121 / 120,
+// 700 000 104 / 95 and 108 / 100, 200 000 87 / 81 and 91 / 84. The bits of a whole key and the place in a bucket have to fit one word.
+constexpr int64_t kBucketEntries = (int64_t)3 << 19;   // of the whole input
+constexpr int64_t kOneBucketEntries = 4096;            // with no more there is one, and nothing to cut
+constexpr int kLocalThreads = 1024, kLocalWaves = kLocalThreads / kWave, kLocalItems = 8, kLocalMost = kLocalThreads * kLocalItems;
+constexpr int kLocalIndexBits = 13, kLocalDigitBits = 8, kLocalBins = 1 << kLocalDigitBits;
+static_assert(kLocalMost == 1 << kLocalIndexBits, "an item's place in its bucket");
+inline bool buckets_pay(int64_t n, int key_bits) {
+    return n <= kBucketEntries && key_bits <= 64 - kLocalIndexBits && (key_bits > 3 * kMaxDigitBits || n <= (int64_t)1 << 19);
+}
+static_assert(kLocalThreads == 4 * kLocalBins && kLocalWaves == 16, "four waves' counts of a digit per thread");
+
+// The sort key: the timestamp bits that differ, the node id above them; below 2^63.
+struct KeySpec {
+    int ts_low, ts_bits;
+    __device__ __forceinline__ uint64_t of(int64_t ts, int32_t node) const {
+        return ((uint64_t)(uint32_t)node << ts_bits) | ((biased(ts) >> ts_low) & (((uint64_t)1 << ts_bits) - 1u));
+    }
+};
+
+// rank[i] += how many samples are below sample i (equal keys: in the order of their positions). A lane per sample, a sixteenth of the
+// others per wave; the samples of equally spaced ranks are the limits of the buckets. (A sort of them by one workgroup takes longer than the
+// rest of the build.)
+constexpr uint32_t kRankParts = 16;  // workgroups per 64 samples
+__global__ __launch_bounds__(kThreads) void rank_samples_kernel(const Sample* __restrict__ samples, uint32_t num_samples, const KeySpec spec,
+                                                               uint32_t* __restrict__ rank, uint32_t* __restrict__ failed) {
+    constexpr uint32_t kWaves = kThreads / kWave;
+    __shared__ uint32_t part[kWaves][kWave];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const uint32_t own0 = blockIdx.x * kWave;
+    auto key_of = [&](uint32_t i) {   // past the last one: above all
+        if (i >= num_samples) return ~(uint64_t)0;
+        const Sample s = samples[i];
+        return spec.of(s.ts, s.node);
+    };
+    const uint64_t mine = key_of(own0 + lane);
+    uint32_t below = 0;
+    for (uint32_t j0 = (blockIdx.y * kWaves + wave) * kWave; j0 < num_samples; j0 += kRankParts * kWaves * kWave) {
+        const uint64_t theirs = key_of(j0 + lane), limit = j0 < own0 ? mine + 1u : mine;
+#pragma unroll 8
+        for (int t = 0; t < kWave; ++t) below += wave_get64(theirs, t) < limit ? 1u : 0u;
+        if (j0 == own0)
+            for (int t = 0; t < kWave; ++t) below += wave_get64(theirs, t) == mine && t < (int)lane ? 1u : 0u;
+    }
+    part[wave][lane] = below;
+    __syncthreads();
+    if (wave == 0 && own0 + lane < num_samples) {
+        for (uint32_t w = 1; w < kWaves; ++w) below += part[w][lane];
+        atomicAdd(&rank[own0 + lane], below);
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *failed = 0;
+}
+
+// Every entry's bucket, and how many of a tile's entries each bucket gets (as radix_hist_kernel).
+// Bucket b > 0 begins at the first entry whose (key, position) is not below those of the sample of rank b S / buckets.
+constexpr uint32_t kMostSamples = (uint32_t)(kBucketEntries / kStratum);
+__global__ __launch_bounds__(kSortThreads) void bucket_hist_kernel(const Items in, int64_t n, const KeySpec spec, const Sample* __restrict__ samples,
+                                                               const uint32_t* __restrict__ rank, uint32_t num_samples, uint32_t buckets, int bits,
+                                                               uint16_t* __restrict__ bucket, uint32_t* __restrict__ hist, uint64_t* __restrict__ first_key) {
+    constexpr int kItems = kSmallItems, kTile = kSortThreads * kItems;
+    __shared__ uint64_t split_key[kBins];
+    __shared__ uint32_t split_pos[kBins];
+    __shared__ uint32_t bins[kBins * kCopies];
+    __shared__ uint16_t of_rank[kMostSamples];
+    const uint32_t copy = threadIdx.x % kCopies;
+    clear_digit(bins);
+    for (uint32_t i = threadIdx.x; i < num_samples; i += kSortThreads) of_rank[rank[i]] = (uint16_t)i;
+    __syncthreads();
+    uint64_t limit = ~(uint64_t)0;   // the splitters that there are not are above every entry
+    uint32_t limit_pos = 0xffffffffu;
+    if (threadIdx.x + 1u < buckets) {
+        const Sample x = samples[of_rank[(threadIdx.x + 1u) * num_samples / buckets]];   // below 2^23
+        limit = spec.of(x.ts, x.node);
+        limit_pos = x.pos;
+    }
+    split_key[threadIdx.x] = limit;
+    if (blockIdx.x == 0) {   // the least key that bucket b may hold; behind the last one, one that none has
+        if (threadIdx.x < buckets) first_key[threadIdx.x + 1u] = limit;
+        if (threadIdx.x == 0) first_key[0] = 0;
+    }
+    split_pos[threadIdx.x] = limit_pos;
+    const int64_t tile0 = (int64_t)blockIdx.x * kTile;
+    uint64_t key[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const int64_t i = tile0 + r * kSortThreads + threadIdx.x, at = i < n ? i : n - 1;
+        key[r] = spec.of(in.ts[at], in.key[at]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const int64_t i = tile0 + r * kSortThreads + threadIdx.x;
+        uint32_t b = 0;
+#pragma unroll
+        for (uint32_t half = kBins / 2; half > 0; half /= 2) {
+            const uint64_t k = split_key[b + half - 1u];
+            if (k < key[r] || (k == key[r] && split_pos[b + half - 1u] <= (uint32_t)i)) b += half;
+        }
+        if (i < n) {
+            bucket[i] = (uint16_t)b;
+            atomicAdd(&bins[b * kCopies + copy], 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < (1u << bits)) hist[((size_t)blockIdx.x << bits) + threadIdx.x] = count_of_digit(bins);
+}
+
+// Stable scatter of one tile by the entries' buckets. As radix_scatter_kernel.
+__global__ __launch_bounds__(kSortThreads) void bucket_scatter_kernel(const Items in, const uint16_t* __restrict__ bucket, int64_t n, int bits,
+                                                                  const uint32_t* __restrict__ offs, const uint32_t* __restrict__ total,
+                                                                  uint32_t num_tiles, TaserRec* __restrict__ rec_out, int32_t* __restrict__ key_out) {
+    constexpr int kItems = kSmallItems, kTile = kSortThreads * kItems, kPart = 1024;
+    __shared__ uint16_t wave_count[kSortWaves][kBins];
+    __shared__ uint32_t block_base[kBins];
+    __shared__ uint32_t scan_tmp[2][kSortWaves];
+    __shared__ TaserRec tile_rec[kPart];
+    __shared__ int32_t tile_key[kPart];
+    __shared__ uint16_t tile_bucket[kPart];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const uint32_t tile = tile_of_block(blockIdx.x, num_tiles);
+    if (tile >= num_tiles) return;
+    const int64_t tile0 = (int64_t)tile * kTile;
+    const uint32_t count = n - tile0 < kTile ? (uint32_t)(n - tile0) : (uint32_t)kTile;
+    const uint32_t mine = (uint32_t)wave * (kWave * kItems) + (uint32_t)lane;
+    TaserRec item_rec[kItems];
+    int32_t item_key[kItems];
+    uint32_t dg[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const uint32_t i = mine + r * kWave;
+        dg[r] = 0;
+        if (i < count) {
+            dg[r] = (bucket + tile0)[i];
+            item_key[r] = (in.key + tile0)[i];
+            item_rec[r] = TaserRec{(in.ts + tile0)[i], (in.dst + tile0)[i], in.eid ? (in.eid + tile0)[i] : (int32_t)(tile0 + i)};
+        }
+    }
+    const uint32_t own = threadIdx.x;
+    {
+        const bool live = own < (1u << bits);
+        const uint32_t all = live ? total[own] : 0u;
+        const uint32_t before = live ? offs[((size_t)tile << bits) + own] : 0u;
+        for (int w = 0; w < kSortWaves; ++w) wave_count[w][own] = 0;
+        block_base[own] = scan_digits(all, scan_tmp[0]) + before;   // (its barrier also covers the counters)
+    }
+    uint32_t place[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) place[r] = rank_in_wave(dg[r], mine + r * kWave < count, bits, wave_count[wave]);
+    __syncthreads();
+    places_of_digit(wave_count, block_base, scan_tmp[1]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kItems; ++r)
+        if (mine + r * kWave < count) place[r] += wave_count[wave][dg[r]];
+    for (uint32_t part0 = 0; part0 < count; part0 += kPart) {
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            const uint32_t at = place[r] - part0;
+            if (mine + r * kWave < count && at < (uint32_t)kPart) {
+                tile_rec[at] = item_rec[r];
+                tile_key[at] = item_key[r];
+                tile_bucket[at] = (uint16_t)dg[r];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kPart / kSortThreads; ++r) {
+            const uint32_t j = (uint32_t)r * kSortThreads + threadIdx.x;
+            if (part0 + j < count) {
+                const uint32_t to = block_base[tile_bucket[j]] + (part0 + j);
+                rec_out[to] = tile_rec[j];
+                key_out[to] = tile_key[j];
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// One bucket into the final order: its entries' keys, less the bucket's least, with the place in the bucket below them, are
+// sorted by stable passes of at most eight bits in LDS (over the bits in which the bucket's limits differ: two to four passes for 36
+// bits of key and 500 buckets), then the records are fetched in that order. 74 KB of LDS and 64 registers: two workgroups to a
+// compute unit, as long as the loads of all eight rows are not issued together (with spills 69 us, so 41).
+// kColumns: the one bucket of a small input, from the caller's columns.
+template <bool kColumns>
+__global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(8))) void sort_bucket_kernel(
+    const Items in, int64_t n, const uint32_t* __restrict__ total, const KeySpec spec, TaserRec* __restrict__ rec_out,
+    int32_t* __restrict__ key_out, int64_t* __restrict__ level1, const uint64_t* __restrict__ first_key, uint64_t all_keys,
+    uint32_t* __restrict__ failed) {
+    __shared__ uint64_t item[kLocalMost];
+    __shared__ uint16_t wave_count[kLocalWaves][kLocalBins];
+    __shared__ uint32_t scan_tmp[kLocalWaves];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    uint32_t start = 0, count = (uint32_t)n;
+    uint64_t least = 0, most = all_keys;
+    if (kColumns) {
+        if (threadIdx.x == 0) *failed = 0;
+    } else {   // the buckets before this one
+        uint32_t before = threadIdx.x < blockIdx.x ? total[threadIdx.x] : 0u;   // (at most kBins of them)
+        count = total[blockIdx.x];
+        least = first_key[blockIdx.x];
+        most = first_key[blockIdx.x + 1u];
+        if (most > all_keys) most = all_keys;
+        if (count == 0) return;
+        before = wave_sum32(before);
+        if (lane == 0) scan_tmp[wave] = before;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kBins / kWave; ++w) start += scan_tmp[w];
+    }
+    if (count > (uint32_t)kLocalMost) {   // uniform
+        if (threadIdx.x == 0) *failed = 1;
+        return;
+    }
+    const int key_bits = most > least ? 64 - __clzll((long long)(most - least)) : 0;   // at most 64 - kLocalIndexBits
+    const uint32_t per = (count + kLocalThreads - 1) / kLocalThreads;   // rows of 64 of each wave
+    const uint32_t mine = wave * per * kWave + lane;
+    uint64_t v[kLocalItems];
+#pragma unroll
+    for (uint32_t r = 0; r < (uint32_t)kLocalItems; ++r) {
+        v[r] = 0;
+        const uint32_t i = mine + r * kWave;
+        if (r < per && i < count) {
+            v[r] = ((spec.of(kColumns ? in.ts[i] : in.rec[start + i].ts, in.key[start + i]) - least) << kLocalIndexBits) | i;
+            if (key_bits == 0) item[i] = v[r];
+        }
+        if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // the loads of four rows together: of all, the registers would spill
+    }
+    const int passes = (key_bits + kLocalDigitBits - 1) / kLocalDigitBits, digit_bits = passes ? (key_bits + passes - 1) / passes : 0;
+    const uint32_t digit_mask = (1u << digit_bits) - 1u;
+    for (int pass = 0, shift = kLocalIndexBits; pass < passes; ++pass, shift += digit_bits) {
+        for (uint32_t c = threadIdx.x; c < (uint32_t)(kLocalWaves * kLocalBins / 4); c += kLocalThreads) reinterpret_cast<uint64_t*>(&wave_count[0][0])[c] = 0;
+        __syncthreads();
+        uint32_t place[kLocalItems];
+#pragma unroll
+        for (uint32_t r = 0; r < (uint32_t)kLocalItems; ++r) {
+            if (r >= per) continue;   // uniform
+            const bool valid = mine + r * kWave < count;
+            const uint32_t dg = valid ? (uint32_t)(v[r] >> shift) & digit_mask : 0u;
+            place[r] = rank_in_wave(dg, valid, digit_bits, wave_count[wave]);
+        }
+        __syncthreads();
+        // how many of a digit a wave has becomes the place of its first one; a thread has four waves' of a digit
+        const uint32_t digit = threadIdx.x / 4u, w0 = threadIdx.x % 4u * 4u;
+        uint32_t here[4], all = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < 4; ++w) {
+            here[w] = wave_count[w0 + w][digit];
+            all += here[w];
+        }
+        const uint32_t inc = wave_inclusive_scan32(all);
+        if (lane == kWave - 1) scan_tmp[wave] = inc;
+        __syncthreads();
+        uint32_t run = inc - all;
+#pragma unroll
+        for (uint32_t w = 0; w < (uint32_t)kLocalWaves; ++w) run += w < wave ? scan_tmp[w] : 0u;
+#pragma unroll
+        for (uint32_t w = 0; w < 4; ++w) {
+            wave_count[w0 + w][digit] = (uint16_t)run;
+            run += here[w];
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t r = 0; r < (uint32_t)kLocalItems; ++r)
+            if (r < per && mine + r * kWave < count) item[place[r] + wave_count[wave][(uint32_t)(v[r] >> shift) & digit_mask]] = v[r];
+        __syncthreads();
+        if (pass + 1 < passes) {
+#pragma unroll
+            for (uint32_t r = 0; r < (uint32_t)kLocalItems; ++r)
+                if (r < per && mine + r * kWave < count) v[r] = item[mine + r * kWave];
+        }
+    }
+    if (key_bits == 0) __syncthreads();
+    for (uint32_t j = threadIdx.x; j < count; j += kLocalThreads) {
+        const uint32_t from = start + ((uint32_t)item[j] & (kLocalMost - 1u)), to = start + j;
+        const TaserRec r = kColumns ? TaserRec{in.ts[from], in.dst[from], in.eid ? in.eid[from] : (int32_t)from} : in.rec[from];
+        rec_out[to] = r;
+        key_out[to] = (int32_t)((least + (item[j] >> kLocalIndexBits)) >> spec.ts_bits);
+        if ((to & 15u) == 15u || (int64_t)to == n - 1) level1[to >> 4] = r.ts;
+    }
+}
+
 // The plain arrays of a graph, indptr among them: views of small graphs are bound by launches (2 000 to 670 000 entries with a
 // copy of indptr of its own 15.2 us, so 12.8).
 __global__ __launch_bounds__(kThreads) void unpack_kernel(const TaserRec* __restrict__ rec, int64_t n, const int64_t* __restrict__ indptr, int64_t starts,
@@ -770,8 +1096,10 @@ struct UpperLevels {
     int64_t end[kTimeIndexLevels - 1];     // running sum of their lengths
 };
 __global__ __launch_bounds__(kThreads) void time_index_upper_kernel(const int64_t* __restrict__ level1, int64_t len1,
-                                                                    UpperLevels up) {
+                                                                    UpperLevels up, const uint32_t* __restrict__ failed,
+                                                                    unsigned long long* __restrict__ report) {
     const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (g == 0 && failed) *report = *failed;
     int64_t begin = 0;
 #pragma unroll
     for (int l = 0; l < kTimeIndexLevels - 1; ++l) {
@@ -791,9 +1119,11 @@ __global__ __launch_bounds__(kThreads) void time_index_upper_kernel(const int64_
 constexpr int64_t kSmallEntries = (int64_t)1 << 21;
 inline int items_for(int64_t n) { return n <= kSmallEntries ? kSmallItems : kLargeItems; }
 
+constexpr int kInfoWords = 5;   // the inspection's four, and whether the buckets could not be sorted
 struct Layout {
     size_t indptr, rec, level[kTimeIndexLevels], storage;                                   // what the graph keeps
     size_t src, dst, ts, eid, tmp_rec, key[2], hist, total, chunk_sum, partial, info, scratch;         // what the build needs
+    // (inputs that may be cut into buckets have too few tiles for chunk_sum: samples and splitters are in its place)
     int64_t level_len[kTimeIndexLevels];
     uint32_t tiles;
 };
@@ -830,7 +1160,7 @@ Layout layout_of(int64_t n, int32_t num_nodes, bool copy_input) {
     l.total = take(kBins * sizeof(uint32_t));
     l.chunk_sum = take((size_t)kMaxChunks * kBins * sizeof(uint32_t));
     l.partial = take((size_t)kInspectBlocks * 4 * sizeof(unsigned long long));
-    l.info = take(4 * sizeof(unsigned long long));
+    l.info = take(kInfoWords * sizeof(unsigned long long));
     l.scratch = at;
     return l;
 }
@@ -889,6 +1219,56 @@ void launch_sorted(const Layout& l, const Items& in, int64_t ts_first, int64_t n
                        hist, total[1], l.tiles, num_nodes, indptr);
 }
 
+// Input in no order that is cut into buckets: everything up to the records and the sorted node column.
+struct BucketScratch {
+    Sample at[kMostSamples];
+    uint64_t first_key[kBins + 1];
+    uint32_t rank[kMostSamples];
+    uint32_t failed;   // a bucket could not be sorted
+};
+static_assert(sizeof(BucketScratch) <= (size_t)kMaxChunks * kBins * sizeof(uint32_t), "in place of chunk_sum");
+static_assert(kBucketEntries <= kSmallEntries && kBucketEntries / (kSortThreads * kSmallItems) < kChunkedTiles, "small tiles, one scan launch");
+inline BucketScratch* bucket_scratch(const Layout& l, uint8_t* scratch) { return reinterpret_cast<BucketScratch*>(scratch + l.chunk_sum); }
+void launch_buckets(const Layout& l, const Items& columns, int64_t n, int node_bits, const KeySpec& spec, uint8_t* scratch, TaserRec* rec, int64_t* level1, hipStream_t stream) {
+    uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
+    uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total);
+    int32_t* key_out = reinterpret_cast<int32_t*>(scratch + l.key[1]);
+    BucketScratch* own = bucket_scratch(l, scratch);
+    const uint64_t all_keys = ((uint64_t)1 << (spec.ts_bits + node_bits)) - 1u;
+    if (n <= kOneBucketEntries) {
+        TaserProfileSpan span(stream, "tcsr_sort_buckets");
+        hipLaunchKernelGGL((sort_bucket_kernel<true>), dim3(1), dim3(kLocalThreads), 0, stream, columns, n, nullptr, spec, rec, key_out, level1, nullptr,
+                           all_keys, &own->failed);
+        return;
+    }
+    const uint32_t buckets = l.tiles < (uint32_t)kBins ? l.tiles : (uint32_t)kBins, samples = l.tiles * (uint32_t)(kSortThreads * kSmallItems / kStratum);
+    {
+        TaserProfileSpan span(stream, "tcsr_rank_samples");
+        hipLaunchKernelGGL(rank_samples_kernel, dim3((samples + kWave - 1) / kWave, kRankParts), dim3(kThreads), 0, stream, own->at, samples, spec, own->rank,
+                           &own->failed);
+    }
+    int bits = 1;
+    while ((1u << bits) < buckets) ++bits;
+    uint16_t* bucket = reinterpret_cast<uint16_t*>(scratch + l.key[1]);   // read before the sorted column is written
+    TaserRec* tmp_rec = reinterpret_cast<TaserRec*>(scratch + l.tmp_rec);
+    int32_t* tmp_key = reinterpret_cast<int32_t*>(scratch + l.key[0]);
+    {
+        TaserProfileSpan span(stream, "tcsr_radix_hist");
+        hipLaunchKernelGGL(bucket_hist_kernel, dim3(l.tiles), dim3(kSortThreads), 0, stream, columns, n, spec, own->at, own->rank, samples, buckets,
+                           bits, bucket, hist, own->first_key);
+    }
+    launch_scan(l, bits, hist, total, nullptr, stream);
+    {
+        TaserProfileSpan span(stream, "tcsr_radix_scatter");
+        hipLaunchKernelGGL(bucket_scatter_kernel, dim3(pass_grid(l.tiles)), dim3(kSortThreads), 0, stream, columns, bucket, n, bits, hist, total, l.tiles,
+                           tmp_rec, tmp_key);
+    }
+    TaserProfileSpan span(stream, "tcsr_sort_buckets");
+    const Items in = {tmp_rec, tmp_key, nullptr, nullptr, nullptr};
+    hipLaunchKernelGGL((sort_bucket_kernel<false>), dim3(buckets), dim3(kLocalThreads), 0, stream, in, n, total, spec, rec, key_out, level1, own->first_key, all_keys,
+                       &own->failed);
+}
+
 template <int kItems>
 void launch_pass(const Layout& l, const Items& in, int64_t n, const DigitSpec& d, bool hist_known, uint32_t* hist, uint32_t* total, uint32_t* chunk_sum,
                  TaserRec* rec_out, int32_t* key_out, int64_t* level1, hipStream_t stream) {
@@ -927,10 +1307,38 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
     uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + l.hist);
     uint32_t* total = reinterpret_cast<uint32_t*>(scratch + l.total);
     uint32_t* chunk_sum = reinterpret_cast<uint32_t*>(scratch + l.chunk_sum);
-    const int32_t* sorted_key = src;
-    bool in_node_digits = false;   // launch_sorted did it all
+    TaserTimeIndex index = {};
+    index.num_entries = n;
+    for (int i = 0; i < kTimeIndexLevels; ++i) {
+        index.len[i] = l.level_len[i];
+        index.level[i] = reinterpret_cast<int64_t*>(storage + l.level[i]);
+    }
+    // indptr, if it is `wanted` from the sorted node column (not where *failed says that this is in no order), and the upper index
+    // levels; *report = *failed. Waits for the stream.
+    auto finish = [&](bool wanted, const int32_t* sorted_key, const uint32_t* failed, unsigned long long* report) -> int {
+        if (wanted) {
+            TaserProfileSpan span(stream, "tcsr_indptr");
+            hipLaunchKernelGGL(indptr_kernel, dim3(blocks_for(n + 1, kThreads * 4)), dim3(kThreads), 0, stream, sorted_key, n, num_nodes, indptr, failed);
+        }
+        if (n > 0) {
+            TaserProfileSpan span(stream, "tcsr_time_index");
+            UpperLevels up;
+            int64_t end = 0;
+            for (int i = 1; i < kTimeIndexLevels; ++i) {
+                up.out[i - 1] = reinterpret_cast<int64_t*>(storage + l.level[i]);
+                up.end[i - 1] = end += l.level_len[i];
+            }
+            hipLaunchKernelGGL(time_index_upper_kernel, dim3(blocks_for(end, kThreads)), dim3(kThreads), 0, stream, level1, l.level_len[0], up, failed, report);
+        }
+        TASER_HIP_TRY(hipGetLastError());
+        TASER_HIP_TRY(hipStreamSynchronize(stream));
+        return TASER_OK;
+    };
 
-    if (n > 0) {
+    if (n == 0) {
+        const int rc = finish(true, nullptr, nullptr, nullptr);
+        if (rc != TASER_OK) return rc;
+    } else {
         // ---- what the input looks like
         int node_bits = 0;
         while (((int64_t)1 << node_bits) < (int64_t)num_nodes) ++node_bits;
@@ -941,97 +1349,93 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         };
         const bool two_digits = node_bits > kMaxDigitBits && node_bits <= 2 * kMaxDigitBits;   // of the node id
         const int low_bits = two_digits ? node_bits / 2 : width_of(node_bits);                  // counted by the inspection
-        unsigned long long info[4] = {0, 0, 0, ~0ull};
+        unsigned long long info[kInfoWords] = {0, 0, 0, ~0ull, 0};
         unsigned long long* partial = reinterpret_cast<unsigned long long*>(scratch + l.partial);
         PinnedInfo pinned;
         unsigned long long* d_info = pinned.words ? pinned.words : reinterpret_cast<unsigned long long*>(scratch + l.info);
         pinned.launched(stream);
+        Samples wanted = {};
+        if (n <= kBucketEntries) wanted = Samples{bucket_scratch(l, scratch)->at, bucket_scratch(l, scratch)->rank};
         {
             TaserProfileSpan span(stream, "tcsr_inspect");
             const unsigned grid = l.tiles < kInspectBlocks ? l.tiles : kInspectBlocks;
             if (small)
                 hipLaunchKernelGGL((inspect_kernel<kSmallItems>), dim3(grid), dim3(kSortThreads), 0, stream, src, ts, n, num_nodes, partial,
-                                   low_bits, hist, l.tiles);
+                                   low_bits, hist, l.tiles, wanted);
             else
                 hipLaunchKernelGGL((inspect_kernel<kLargeItems>), dim3(grid), dim3(kSortThreads), 0, stream, src, ts, n, num_nodes, partial,
-                                   low_bits, hist, l.tiles);
+                                   low_bits, hist, l.tiles, wanted);
             hipLaunchKernelGGL(fold_info_kernel, dim3(1), dim3(kSortThreads), 0, stream, partial, grid, ts, n, d_info);
         }
         TASER_HIP_TRY(hipGetLastError());
-        if (!pinned.words) TASER_HIP_TRY(hipMemcpyAsync(info, d_info, sizeof(info), hipMemcpyDeviceToHost, stream));
+        if (!pinned.words) TASER_HIP_TRY(hipMemcpyAsync(info, d_info, 4 * sizeof(info[0]), hipMemcpyDeviceToHost, stream));
         TASER_HIP_TRY(hipStreamSynchronize(stream));
         pinned.settled();
         if (pinned.words)
             for (int j = 0; j < 4; ++j) info[j] = __atomic_load_n(&pinned.words[j], __ATOMIC_RELAXED);
         if (info[0]) return taser_fail(TASER_E_RANGE, "tcsr_build: a src node id is outside [0, %d)", num_nodes);
-        in_node_digits = two_digits && !info[1] && info[3] - info[2] < (1ull << 32);
-        if (in_node_digits) {
-            const Items in = {nullptr, src, dst, ts, eid};
-            if (small) launch_sorted<kSmallItems>(l, in, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
-            else launch_sorted<kLargeItems>(l, in, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
-        }
         int ts_low = 0, ts_bits = 0;
         if (info[1]) {
             const unsigned long long differ = info[2] & ~info[3];   // not 0: the timestamps are not all equal
             ts_low = __builtin_ctzll(differ);
             ts_bits = 64 - __builtin_clzll(differ) - ts_low;
         }
+        const Items columns = {nullptr, src, dst, ts, eid};
+        const bool in_node_digits = two_digits && !info[1] && info[3] - info[2] < (1ull << 32);
+        bool done = false;
+        if (in_node_digits) {
+            if (small) launch_sorted<kSmallItems>(l, columns, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
+            else launch_sorted<kLargeItems>(l, columns, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
+            const int rc = finish(false, nullptr, nullptr, nullptr);
+            if (rc != TASER_OK) return rc;
+            done = true;
+        } else if (info[1] && buckets_pay(n, ts_bits + node_bits)) {
+            pinned.launched(stream);
+            launch_buckets(l, columns, n, node_bits, KeySpec{ts_low, ts_bits}, scratch, rec, level1, stream);
+            const int rc = finish(true, reinterpret_cast<const int32_t*>(scratch + l.key[1]), &bucket_scratch(l, scratch)->failed, d_info + 4);
+            if (rc != TASER_OK) return rc;
+            pinned.settled();
+            if (pinned.words) info[4] = __atomic_load_n(&pinned.words[4], __ATOMIC_RELAXED);
+            else TASER_HIP_TRY(hipMemcpy(&info[4], d_info + 4, sizeof(info[4]), hipMemcpyDeviceToHost));
+            done = info[4] == 0;
+        }
 
         // ---- one stable pass per digit; the last one writes the graph's own records
-        const int key_bits = ts_bits + node_bits;
-        const int width = width_of(key_bits);
-        const int passes = in_node_digits ? 0 : key_bits > 0 ? (key_bits + width - 1) / width : 1;
-        // without timestamp digits the first digit is the one that inspect_kernel counted, also where the others are wider by a
-        // bit (64 M entries over 2^45 ticks, 131 000 nodes: 1.56 ms with equal digits and a count of their own, 1.44 so)
-        const int first_width = ts_bits ? width : low_bits;
-        TaserRec* tmp_rec = reinterpret_cast<TaserRec*>(scratch + l.tmp_rec);
-        Items in = {nullptr, src, dst, ts, eid};
-        for (int pass = 0; pass < passes; ++pass) {
-            const int s = pass ? first_width + (pass - 1) * width : 0, most = pass ? width : first_width;
-            DigitSpec d = {};
-            d.bits = key_bits - s < most ? key_bits - s : most;
-            if (d.bits < 1) d.bits = 1;               // a single node and sorted input: every digit is 0
-            if (s < ts_bits) {
-                const int have = ts_bits - s;         // timestamp bits from here on
-                d.from_ts = 1;
-                d.ts_shift = ts_low + s;
-                d.ts_mask = (1u << (have < d.bits ? have : d.bits)) - 1u;
-                d.node_left = have < 31 ? have : 31;
-            } else {
-                d.node_right = s - ts_bits;
+        if (!done) {
+            const int key_bits = ts_bits + node_bits;
+            const int width = width_of(key_bits);
+            const int passes = key_bits > 0 ? (key_bits + width - 1) / width : 1;
+            // without timestamp digits the first digit is the one that inspect_kernel counted, also where the others are wider by a
+            // bit (64 M entries over 2^45 ticks, 131 000 nodes: 1.56 ms with equal digits and a count of their own, 1.44 so)
+            const int first_width = ts_bits ? width : low_bits;
+            TaserRec* tmp_rec = reinterpret_cast<TaserRec*>(scratch + l.tmp_rec);
+            Items in = columns;
+            for (int pass = 0; pass < passes; ++pass) {
+                const int s = pass ? first_width + (pass - 1) * width : 0, most = pass ? width : first_width;
+                DigitSpec d = {};
+                d.bits = key_bits - s < most ? key_bits - s : most;
+                if (d.bits < 1) d.bits = 1;               // a single node and sorted input: every digit is 0
+                if (s < ts_bits) {
+                    const int have = ts_bits - s;         // timestamp bits from here on
+                    d.from_ts = 1;
+                    d.ts_shift = ts_low + s;
+                    d.ts_mask = (1u << (have < d.bits ? have : d.bits)) - 1u;
+                    d.node_left = have < 31 ? have : 31;
+                } else {
+                    d.node_right = s - ts_bits;
+                }
+                const bool last = pass + 1 == passes;
+                TaserRec* rec_out = ((passes - 1 - pass) & 1) ? tmp_rec : rec;
+                int32_t* key_out = reinterpret_cast<int32_t*>(scratch + l.key[pass & 1]);
+                const bool hist_known = pass == 0 && ts_bits == 0;
+                if (small) launch_pass<kSmallItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
+                else launch_pass<kLargeItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
+                in = Items{rec_out, key_out, nullptr, nullptr, nullptr};
             }
-            const bool last = pass + 1 == passes;
-            TaserRec* rec_out = ((passes - 1 - pass) & 1) ? tmp_rec : rec;
-            int32_t* key_out = reinterpret_cast<int32_t*>(scratch + l.key[pass & 1]);
-            const bool hist_known = pass == 0 && ts_bits == 0;
-            if (small) launch_pass<kSmallItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
-            else launch_pass<kLargeItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
-            in = Items{rec_out, key_out, nullptr, nullptr, nullptr};
-            sorted_key = key_out;
+            const int rc = finish(true, in.key, nullptr, nullptr);
+            if (rc != TASER_OK) return rc;
         }
     }
-    if (!in_node_digits) {
-        TaserProfileSpan span(stream, "tcsr_indptr");
-        hipLaunchKernelGGL(indptr_kernel, dim3(blocks_for(n + 1, kThreads * 4)), dim3(kThreads), 0, stream, sorted_key, n, num_nodes, indptr);
-    }
-    TaserTimeIndex index = {};
-    index.num_entries = n;
-    for (int i = 0; i < kTimeIndexLevels; ++i) {
-        index.len[i] = l.level_len[i];
-        index.level[i] = reinterpret_cast<int64_t*>(storage + l.level[i]);
-    }
-    if (n > 0) {
-        TaserProfileSpan span(stream, "tcsr_time_index");
-        UpperLevels up;
-        int64_t end = 0;
-        for (int i = 1; i < kTimeIndexLevels; ++i) {
-            up.out[i - 1] = reinterpret_cast<int64_t*>(storage + l.level[i]);
-            up.end[i - 1] = end += l.level_len[i];
-        }
-        hipLaunchKernelGGL(time_index_upper_kernel, dim3(blocks_for(end, kThreads)), dim3(kThreads), 0, stream, level1, l.level_len[0], up);
-    }
-    TASER_HIP_TRY(hipGetLastError());
-    TASER_HIP_TRY(hipStreamSynchronize(stream));
 
     taser_tcsr* g = new (std::nothrow) taser_tcsr();
     if (!g) return taser_fail(TASER_E_OOM, "tcsr_build: host allocation failed");
