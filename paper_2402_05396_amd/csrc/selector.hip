@@ -90,13 +90,16 @@ template <int R> __device__ __forceinline__ uint64_t total_of_row(const uint64_t
 // the lane by a prefix sum over that row alone, then the value. Draws from 1 M, 40 M, 500 M scores, us a launch with 16
 // neighboring values per lane / a prefix sum over every row / so: 600 draws 6.3 5.3 7.4 / 5.1 4.6 6.8 / 4.8 4.2 6.5,
 // 100 000 draws 193 119 175 / 136 130 200 / 88 83 141.
-template <typename T>
-__device__ __forceinline__ int64_t wave_descend_group(const T* __restrict__ a, int64_t begin, int64_t end, uint64_t& x,
-                                                      int lane) {
-    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-    constexpr int kVec = 16 / (int)sizeof(T);          // values per piece: 4 or 2
-    constexpr int kRows = kFan / (kWave * kVec);       // 4 or 8
+template <typename T> struct Group {
+    static constexpr int kVec = 16 / (int)sizeof(T);          // values per piece: 4 or 2
+    static constexpr int kRows = kFan / (kWave * kVec);       // 4 or 8
     T v[kRows][kVec];
+};
+template <typename T>
+__device__ __forceinline__ void load_group(const T* __restrict__ a, int64_t begin, int64_t end, int lane, Group<T>& group) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int kVec = Group<T>::kVec, kRows = Group<T>::kRows;
+    auto& v = group.v;
     const int64_t mine = begin + (int64_t)lane * kVec;
     if (begin + kFan <= end) {   // a whole group (wave-uniform); `begin` is a multiple of 1024 values, so the address is aligned
         u32x4 raw[kRows];
@@ -109,6 +112,10 @@ __device__ __forceinline__ int64_t wave_descend_group(const T* __restrict__ a, i
 #pragma unroll
             for (int i = 0; i < kVec; ++i) v[r][i] = mine + r * kWave * kVec + i < end ? a[mine + r * kWave * kVec + i] : (T)0;
     }
+}
+template <typename T> __device__ __forceinline__ int64_t pick_in_group(const Group<T>& group, int64_t begin, uint64_t& x) {
+    constexpr int kVec = Group<T>::kVec, kRows = Group<T>::kRows;
+    const auto& v = group.v;
     uint64_t own[kRows];
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
@@ -185,7 +192,10 @@ __global__ __launch_bounds__(kThreads) void fill_u32_kernel(uint32_t* __restrict
     for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) a[i] = v;
 }
 
-// One wavefront per draw.
+// One wavefront per draw. What does not depend on the draw is on its way before its random number is worked out: the top level
+// (of 64 sums at most, 64 M edges, it stays in the lanes) and, where that is one sum, the level below. (From 10^6 scores, us of the
+// launch: 2 000 draws 6.2 with the three levels read one after the other behind the random number, 5.6 so; a call of 8 000 10.4
+// and 9.5, of 100 000 89 and 76; from 60 M 82 and 76.)
 __global__ __launch_bounds__(kThreads) void batch_draw_kernel(const uint32_t* __restrict__ score, int64_t n,
                                                               const uint64_t* __restrict__ sum1, int64_t n1,
                                                               const uint64_t* __restrict__ sum2, int64_t n2, int64_t b,
@@ -194,19 +204,35 @@ __global__ __launch_bounds__(kThreads) void batch_draw_kernel(const uint32_t* __
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t j = (int64_t)blockIdx.x * (kThreads / kWave) + (threadIdx.x >> 6);
     if (j >= b) return;   // wave-uniform
-    uint64_t total = 0;
-    for (int64_t i = lane; i < n2; i += kWave) total += sum2[i];
-    total = wave_sum64(total);
+    const uint64_t top = lane < n2 ? sum2[lane] : 0;
+    Group<uint64_t> group;
+    if (n2 == 1) load_group(sum1, 0, n1, lane, group);   // (uniform)
+    const uint64_t u = draw64(seed_lo, seed_hi, kDrawTag, iteration, (uint32_t)j);
+    uint64_t inc = top, total;
+    if (n2 > kWave) {
+        for (int64_t i = kWave + lane; i < n2; i += kWave) inc += sum2[i];
+        total = wave_sum64(inc);
+    } else {
+        inc = wave_inclusive_scan64(top);
+        total = wave_get64(inc, kWave - 1);
+    }
     if (total == 0) {
         if (lane == 0) out[j] = -1;
         return;
     }
-    uint64_t x = __umul64hi(draw64(seed_lo, seed_hi, kDrawTag, iteration, (uint32_t)j), total);
-    const int64_t i2 = wave_descend(sum2, 0, n2, x, lane);
-    const int64_t end1 = (i2 + 1) * kFan < n1 ? (i2 + 1) * kFan : n1;
-    const int64_t i1 = wave_descend_group(sum1, i2 * kFan, end1, x, lane);
-    const int64_t end0 = (i1 + 1) * kFan < n ? (i1 + 1) * kFan : n;
-    const int64_t e = wave_descend_group(score, i1 * kFan, end0, x, lane);
+    uint64_t x = __umul64hi(u, total);
+    int64_t i2 = 0;
+    if (n2 > kWave) {
+        i2 = wave_descend(sum2, 0, n2, x, lane);
+    } else if (n2 > 1) {
+        i2 = __ffsll((long long)__ballot(inc > x)) - 1;   // x < total: there is one
+        x -= wave_get64(inc - top, (int)i2);
+    }
+    if (n2 > 1) load_group(sum1, i2 * kFan, (i2 + 1) * kFan < n1 ? (i2 + 1) * kFan : n1, lane, group);
+    const int64_t i1 = pick_in_group(group, i2 * kFan, x);
+    Group<uint32_t> scores;
+    load_group(score, i1 * kFan, (i1 + 1) * kFan < n ? (i1 + 1) * kFan : n, lane, scores);
+    const int64_t e = pick_in_group(scores, i1 * kFan, x);
     if (lane == 0) out[j] = (int32_t)e;
 }
 
@@ -320,11 +346,12 @@ __global__ __launch_bounds__(kOneBlockThreads) void update_classes_kernel(const 
     __shared__ unsigned long long top_sum[kClassTops];
     const int lane = threadIdx.x & (kWave - 1);
     int32_t e[kPer];
-    uint32_t slot[kPer], old[kPer];
+    uint32_t slot[kPer], old[kPer], now[kPer];
 #pragma unroll
     for (int r = 0; r < kPer; ++r) {
         const int32_t j = r * kOneBlockThreads + (int32_t)threadIdx.x;
         e[r] = j < b ? idx[j] : -1;
+        now[r] = j < b ? value[j] : 0;               // (read here, few of them are needed: behind the barriers it is one more wait)
     }
     for (uint32_t s = threadIdx.x; s < kSlots; s += kOneBlockThreads) {
         edge[s] = -1;
@@ -356,9 +383,8 @@ __global__ __launch_bounds__(kOneBlockThreads) void update_classes_kernel(const 
         const int32_t j = r * kOneBlockThreads + (int32_t)threadIdx.x;
         uint64_t diff = 0;
         if (e[r] >= 0 && last[slot[r]] == j) {
-            const uint32_t now = value[j];
-            score[e[r]] = now;
-            diff = (uint64_t)now - (uint64_t)old[r];
+            score[e[r]] = now[r];
+            diff = (uint64_t)now[r] - (uint64_t)old[r];
         }
         if (diff) atomicAdd((unsigned long long*)&sum1[e[r] / kFan], (unsigned long long)diff);
         const uint64_t changing = __ballot(diff != 0);
