@@ -16,7 +16,8 @@ def test_draws(n):
     score[: n // 2] = 0                      # the first sums of every level are 0
     score[-1] = 0xFFFFFFFF
     s = T.selector_init(torch.from_numpy(score.view(np.int32)).cuda())
-    assert np.array_equal(T.selector_draw(s, 2000, 3, 8).cpu().numpy(), oracle.batch_draw(score, 2000, seed=3, iteration=8))
+    b = 2000 if n < 1 << 22 else 40          # (the oracle adds up all scores for each)
+    assert np.array_equal(T.selector_draw(s, b, 3, 8).cpu().numpy(), oracle.batch_draw(score, b, seed=3, iteration=8))
     T.selector_free(s)
     s = T.selector_init(torch.zeros(n, dtype=torch.int32, device="cuda"))
     assert T.selector_draw(s, 5, 3, 8).tolist() == [-1] * 5
