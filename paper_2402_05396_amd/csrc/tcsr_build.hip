@@ -596,26 +596,43 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
 
 // indptr[v] = first position whose node id is >= v, from the sorted node column: position p starts
 // the lists of the nodes in (key[p - 1], key[p]]. A thread looks at four consecutive positions (one
-// 16-byte load; `key` is the start of an allocation) plus the key before them.
+// 16-byte load; `key` is the start of an allocation) plus the key before them. Ranges of more than kWideGap
+// nodes without entries, the one behind the last entry for instance, are written by the whole block: by their thread alone they
+// are a serial chain, 26 ns a store, and the whole launch waits for it (builds among 300 000 nodes of which the last tenth has no
+// entries: 2 000 entries in order of time 911 -> 160 us, 20 000 853 -> 95, 1.34 M 886 -> 110; among 20 000 nodes, 1.34 M in no
+// order 181 -> 132; no entries, 1 M nodes 25.7 ms -> 0.13).
+constexpr int32_t kWideGap = 256;
 __global__ __launch_bounds__(kThreads) void indptr_kernel(const int32_t* __restrict__ key, int64_t n,
                                                           int32_t num_nodes, int64_t* __restrict__ indptr, const uint32_t* __restrict__ failed) {
     if (failed && *failed) return;   // the column is not in order
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    const int64_t p0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
-    if (p0 > n) return;
-    int32_t k[5];   // k[0] = the key before p0, k[1 + j] = key at p0 + j (num_nodes from position n on)
-    k[0] = p0 > 0 ? key[p0 - 1] : -1;
-    if (p0 + 4 <= n) {
-        const i32x4 v = *reinterpret_cast<const i32x4*>(key + p0);
-        k[1] = v.x; k[2] = v.y; k[3] = v.z; k[4] = v.w;
-    } else {
+    __shared__ uint16_t wide[kThreads * 4];   // positions within the block that end a wide gap
+    __shared__ uint32_t n_wide;
+    if (threadIdx.x == 0) n_wide = 0;
+    __syncthreads();
+    const int64_t block0 = (int64_t)blockIdx.x * kThreads * 4, p0 = block0 + threadIdx.x * 4;
+    if (p0 <= n) {
+        int32_t k[5];   // k[0] = the key before p0, k[1 + j] = key at p0 + j (num_nodes from position n on)
+        k[0] = p0 > 0 ? key[p0 - 1] : -1;
+        if (p0 + 4 <= n) {
+            const i32x4 v = *reinterpret_cast<const i32x4*>(key + p0);
+            k[1] = v.x; k[2] = v.y; k[3] = v.z; k[4] = v.w;
+        } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) k[1 + j] = p0 + j < n ? key[p0 + j] : num_nodes;
+            for (int j = 0; j < 4; ++j) k[1 + j] = p0 + j < n ? key[p0 + j] : num_nodes;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (p0 + j > n) break;
+            if ((int64_t)k[1 + j] - k[j] > kWideGap) wide[atomicAdd(&n_wide, 1u)] = (uint16_t)(threadIdx.x * 4 + j);
+            else
+                for (int32_t v = k[j] + 1; v <= k[1 + j]; ++v) indptr[v] = p0 + j;
+        }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if (p0 + j > n) break;
-        for (int32_t v = k[j] + 1; v <= k[1 + j]; ++v) indptr[v] = p0 + j;
+    __syncthreads();
+    for (uint32_t i = 0; i < n_wide; ++i) {
+        const int64_t p = block0 + wide[i], before = p > 0 ? key[p - 1] : -1, to = p < n ? key[p] : num_nodes;
+        for (int64_t v = before + 1 + threadIdx.x; v <= to; v += kThreads) indptr[v] = p;
     }
 }
 

@@ -1,0 +1,28 @@
+"""List starts of graphs with long ranges of nodes that have no entries: before the first entry, between two, behind the last,
+around the length from which a whole block writes them, several in one block, and without any entry."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_05396_amd as T
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ordered", [True, False])
+@pytest.mark.parametrize("nodes", [[], [0], [255], [256], [257, 257, 513, 770], [5000] * 1023 + [5300], [7] * 1024 + [400_000],
+                                   list(range(0, 600_000, 257)), list(range(0, 600_000, 256)), [299, 300, 100_000, 599_999]])
+@pytest.mark.parametrize("num_nodes", [600_000, 600_256, 600_257, 1_000_001])
+def test_list_starts(nodes, num_nodes, ordered):
+    src = np.array(nodes, np.int32)
+    n = len(src)
+    ts = np.arange(n, dtype=np.int64)
+    if not ordered:
+        src, ts = src[::-1].copy(), ts[::-1].copy()
+    d = lambda a: torch.from_numpy(a).cuda()
+    g = T.tcsr_build(d(src), d(src), d(ts), None, num_nodes)
+    indptr, nbr, times, eids = T.tcsr_view(g)
+    order = np.lexsort((ts, src))
+    assert np.array_equal(indptr.cpu().numpy(), np.searchsorted(np.sort(src), np.arange(num_nodes + 1)))
+    assert np.array_equal(nbr.cpu().numpy(), src[order]) and np.array_equal(times.cpu().numpy(), ts[order])
+    assert np.array_equal(eids.cpu().numpy(), order)
