@@ -597,18 +597,20 @@ __global__ __launch_bounds__(kSortThreads) __attribute__((amdgpu_waves_per_eu(4)
 // indptr[v] = first position whose node id is >= v, from the sorted node column: position p starts
 // the lists of the nodes in (key[p - 1], key[p]]. A thread looks at four consecutive positions (one
 // 16-byte load; `key` is the start of an allocation) plus the key before them. Ranges of more than kWideGap
-// nodes without entries, the one behind the last entry for instance, are written by the whole block: by their thread alone they
-// are a serial chain, 26 ns a store, and the whole launch waits for it (builds among 300 000 nodes of which the last tenth has no
-// entries: 2 000 entries in order of time 911 -> 160 us, 20 000 853 -> 95, 1.34 M 886 -> 110; among 20 000 nodes, 1.34 M in no
-// order 181 -> 132; no entries, 1 M nodes 25.7 ms -> 0.13).
-constexpr int32_t kWideGap = 256;
+// nodes without entries, the one behind the last entry for instance, are written by a wave, of more than kLongGap by the whole
+// block: by their thread alone they are a serial chain, 26 ns a store, and the whole launch waits for it. Builds among 300 000
+// nodes of which the last tenth has no entries, in order of time: 2 000 entries 911 -> 127 us, 20 000 853 -> 91, 1.34 M 886 -> 116;
+// of no entries, 57 instead of 7 740. (By the block from 256 on: 2 000 entries 160; by a wave from 16 or 32 on: up to 5 % slower
+// where such ranges are many, 5 000 entries of 300 000 nodes 117 and 113 us, 110 so.)
+constexpr int32_t kWideGap = 64, kLongGap = kThreads * 8;
 __global__ __launch_bounds__(kThreads) void indptr_kernel(const int32_t* __restrict__ key, int64_t n,
                                                           int32_t num_nodes, int64_t* __restrict__ indptr, const uint32_t* __restrict__ failed) {
     if (failed && *failed) return;   // the column is not in order
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    __shared__ uint16_t wide[kThreads * 4];   // positions within the block that end a wide gap
-    __shared__ uint32_t n_wide;
-    if (threadIdx.x == 0) n_wide = 0;
+    __shared__ int32_t from[kThreads * 4], to[kThreads * 4];   // gaps: the wide ones from the front, the long ones from the back
+    __shared__ uint16_t at[kThreads * 4];                      // the position within the block that ends one
+    __shared__ uint32_t n_wide, n_long;
+    if (threadIdx.x == 0) n_wide = n_long = 0;
     __syncthreads();
     const int64_t block0 = (int64_t)blockIdx.x * kThreads * 4, p0 = block0 + threadIdx.x * 4;
     if (p0 <= n) {
@@ -624,15 +626,25 @@ __global__ __launch_bounds__(kThreads) void indptr_kernel(const int32_t* __restr
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (p0 + j > n) break;
-            if ((int64_t)k[1 + j] - k[j] > kWideGap) wide[atomicAdd(&n_wide, 1u)] = (uint16_t)(threadIdx.x * 4 + j);
-            else
+            const int64_t gap = (int64_t)k[1 + j] - k[j];
+            if (gap > kWideGap) {
+                const uint32_t i = gap > kLongGap ? kThreads * 4u - 1u - atomicAdd(&n_long, 1u) : atomicAdd(&n_wide, 1u);
+                from[i] = k[j] + 1;
+                to[i] = k[1 + j];
+                at[i] = (uint16_t)(threadIdx.x * 4 + j);
+            } else
                 for (int32_t v = k[j] + 1; v <= k[1 + j]; ++v) indptr[v] = p0 + j;
         }
     }
     __syncthreads();
-    for (uint32_t i = 0; i < n_wide; ++i) {
-        const int64_t p = block0 + wide[i], before = p > 0 ? key[p - 1] : -1, to = p < n ? key[p] : num_nodes;
-        for (int64_t v = before + 1 + threadIdx.x; v <= to; v += kThreads) indptr[v] = p;
+    const uint32_t lane = threadIdx.x & (kWave - 1), n_mine = n_wide;
+    for (uint32_t i = threadIdx.x >> 6; i < n_mine; i += kThreads / kWave) {
+        const int64_t p = block0 + at[i], end = to[i];
+        for (int64_t v = (int64_t)from[i] + lane; v <= end; v += kWave) indptr[v] = p;
+    }
+    for (uint32_t i = kThreads * 4u - n_long; i < kThreads * 4u; ++i) {
+        const int64_t p = block0 + at[i], end = to[i];
+        for (int64_t v = (int64_t)from[i] + threadIdx.x; v <= end; v += kThreads) indptr[v] = p;
     }
 }
 

@@ -1,5 +1,5 @@
 """List starts of graphs with long ranges of nodes that have no entries: before the first entry, between two, behind the last,
-around the length from which a whole block writes them, several in one block, and without any entry."""
+around the lengths from which a wave and a whole block write them, several in one block, and without any entry."""
 import numpy as np
 import pytest
 import torch
@@ -10,9 +10,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("ordered", [True, False])
-@pytest.mark.parametrize("nodes", [[], [0], [255], [256], [257, 257, 513, 770], [5000] * 1023 + [5300], [7] * 1024 + [400_000],
-                                   list(range(0, 600_000, 257)), list(range(0, 600_000, 256)), [299, 300, 100_000, 599_999]])
-@pytest.mark.parametrize("num_nodes", [600_000, 600_256, 600_257, 1_000_001])
+@pytest.mark.parametrize("nodes", [[], [0], [63], [64], [65, 65, 129, 194, 2242, 4291], [5000] * 1023 + [5300], [7] * 1024 + [400_000], [2047], [2048],
+                                   list(range(0, 600_000, 64)), list(range(0, 600_000, 65)), list(range(0, 600_000, 2049)), [299, 300, 100_000, 599_999]])
+@pytest.mark.parametrize("num_nodes", [600_000, 602_048, 602_049, 1_000_001])
 def test_list_starts(nodes, num_nodes, ordered):
     src = np.array(nodes, np.int32)
     n = len(src)
