@@ -58,9 +58,9 @@ __host__ __device__ inline uint32_t hash_id(int32_t id, uint32_t mask) {
     return h & mask;
 }
 // loc encoding: >= 0 cache slot (| kHotBit); kLocZero; kLocHost; otherwise -2 - s, where s is a slot of the
-// miss table. A gather whose rows have been staged turns the latter into -2 - (row of the staging area, | kSecondBit
-// unless it was staged by a whole lookup's first launch), or kLocHost where the staging area was full (see
-// CacheSource::resolve).
+// miss table. A gather whose rows have been staged turns the latter into -2 - (row of the staging area), or
+// kLocHost where the staging area was full (see CacheSource::resolve). Of a lookup with two staging launches, rows that
+// were not staged by the first have kSecondBit as well (see SplitCacheSource).
 __host__ __device__ inline int32_t loc_of_stage(uint32_t s) { return -2 - (int32_t)s; }
 constexpr uint32_t kSecondBit = 1u << 30;          // staging rows are below 2^29
 
@@ -134,17 +134,18 @@ __device__ __forceinline__ int32_t claim(int32_t* at, int32_t id, uint32_t slot,
     return follow ? of_first : key;
 }
 
-// Where the miss table has a slot per row (`own_slots`: rows <= miss_size, that is a staging area for some half of the rows
+// Where the miss table has a slot per row (OWN_SLOTS: rows <= miss_size, that is a staging area for some half of the rows
 // and more), row id's slot is slot id, and a claim is a plain store of the id, whoever stores first: swaps on the
 // memory side bound this kernel (1.33 M requests, 213 000 of them of 13 400 missing rows: 27 us with swaps, 13 so; whole
 // lookups of 1.3 M rows of 64 bytes of which 20 % are resident 247 -> 138 us, none resident 464 -> 150).
 // Grid-stride over the requests; hit/miss counts are summed per block and left in
 // block_tally for the next launch (even one atomic pair per block on the caller's two
 // counters, thousands on one address, took longer than the classification itself).
+template <bool OWN_SLOTS>
 __global__ __launch_bounds__(kThreads) void classify_kernel(
     const int32_t* __restrict__ ids, int64_t n, int64_t rows, const int32_t* __restrict__ hash_key,
     const int32_t* __restrict__ hash_slot, uint32_t hash_mask, int32_t* miss_key, uint32_t miss_size,
-    int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count, const bool own_slots, const bool share_claims) {
+    int32_t* __restrict__ loc, uint32_t* __restrict__ block_tally, uint32_t* stage_count, const bool share_claims) {
     __shared__ uint32_t block_hits[kThreads / kWave], block_misses[kThreads / kWave];
     __shared__ uint32_t claim_lane[kThreads / kWave][kWave];
     if (stage_count && blockIdx.x == 0 && threadIdx.x == 0) *stage_count = 0;   // for the staging that follows
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
             } else {
                 ++misses;
                 where = kLocHost;
-                if (own_slots) {                     // every writer stores the same word
+                if (OWN_SLOTS) {                     // every writer stores the same word
                     miss_key[id] = id;
                     where = loc_of_stage((uint32_t)id);
                 } else if (miss_size) {
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
 // law, 17 000 rows, 20 % resident, 16 % of the requests missed: f = 0.81; with 0.70, 0.75, 0.80, 0.85 instead 529, 511,
 // 495, 500 us; without skew, 30 % resident: f = 0.46, 666 us, with 0.70 693.)
 struct Split {
-    uint32_t spans;          // of the table (0: there is one launch, which takes all)
+    uint32_t spans;          // of the table
     int64_t requests, missing_rows;   // the call's, and how many rows can be missed
     // In the time that a row takes to be written by a launch for missed rows: a row by the bus, a row by the gather of the others.
     static constexpr uint64_t kBus = 67 * 64, kLate = 64, kThere = 39;
@@ -234,7 +235,7 @@ struct Split {
 // tally_blocks), the next `count_blocks` count accesses. `blocks` in all, a multiple of the number
 // of L2 partitions, so that the gather's blocks behind them keep their places.
 struct Service {
-    static constexpr bool kAny = true;
+    static constexpr bool kAny = true, kSplit = false;
     int stage_blocks, count_blocks;
     uint32_t blocks;
     int32_t* miss_key;                    // staging
@@ -242,8 +243,6 @@ struct Service {
     uint32_t spans;                       // of the miss table that can hold claims
     uint32_t stage_span;                  // neighboring miss-table slots that go to one wave (a power of two, 8 to 64)
     uint32_t* stage_count;
-    Split split;                          // of the spans, over two launches
-    bool second;                          // this is the second of them
     uint32_t staging_rows;
     const uint8_t* host_rows;
     int64_t pitch_bytes;
@@ -261,11 +260,19 @@ struct Service {
     __device__ __forceinline__ void run(uint32_t block, int32_t* lds) const;
 };
 
+// The same where two launches share the staging. (A type of its own, as SplitCacheSource.)
+struct SplitService : Service {
+    static constexpr bool kSplit = true;
+    Split split;                          // of the spans
+    bool second;                          // this is the second of them
+    __device__ __forceinline__ void run(uint32_t block, int32_t* lds) const;
+};
+
 // One block: adds up the per-block counts of the classify launch.
 // With `loc`, also whether one missing row is asked for often, from a sample of the requests: then the second
 // launch does not tie rows to partitions (see CacheSource::late_skewed).
 constexpr int kSample = 2048, kSampleSlots = 1024;
-__device__ __forceinline__ void tally_block(const Service& v, int32_t* __restrict__ lds) {
+template <typename V> __device__ __forceinline__ void tally_block(const V& v, int32_t* __restrict__ lds) {
     if (v.loc) {
         __shared__ uint32_t most[kThreads / kWave];
         uint32_t* const seen = reinterpret_cast<uint32_t*>(lds);
@@ -313,7 +320,7 @@ __device__ __forceinline__ void tally_block(const Service& v, int32_t* __restric
         if (v.hit_miss && h) atomicAdd(&v.hit_miss[0], h);
         if (v.hit_miss && m) atomicAdd(&v.hit_miss[1], m);
         if (v.missed) v.missed[0] = m < 0xffffffffull ? (uint32_t)m : 0xffffffffu;
-        if (v.split.spans) v.missed[2] = v.split.first((uint32_t)m);
+        if constexpr (V::kSplit) v.missed[2] = v.split.first((uint32_t)m);
     }
 }
 
@@ -374,7 +381,7 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {   // in every lane
 }
 
 // `lds`: 2 * kWave words per wave
-__device__ __forceinline__ void stage_block(const Service& v, uint32_t block, int32_t* __restrict__ lds) {
+template <typename V> __device__ __forceinline__ void stage_block(const V& v, uint32_t block, int32_t* __restrict__ lds) {
     using taser_gather::Chunk16;
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = block * (kThreads / kWave) + (threadIdx.x >> 6);
@@ -382,7 +389,7 @@ __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, in
     int32_t* const list_id = lds + (threadIdx.x >> 6) * 2 * kWave;
     int32_t* const list_row = list_id + kWave;
     uint32_t from = 0, end = v.spans;
-    if (v.split.spans) {
+    if constexpr (V::kSplit) {
         if (v.second) {
             from = v.missed[2];
         } else {                             // before anybody has added up the misses
@@ -456,15 +463,17 @@ __device__ __forceinline__ void stage_block(const Service& v, uint32_t block, in
 }
 
 static_assert(taser_gather::kBesideWords >= kSampleSlots && taser_gather::kBesideWords >= 2 * kTallySlots && taser_gather::tile_rows(4) >= 2 * kTallySlots, "the LDS of run()");
-__device__ __forceinline__ void Service::run(uint32_t block, int32_t* lds) const {
-    if ((int)block < stage_blocks) {
-        stage_block(*this, block, lds);
+template <typename V> __device__ __forceinline__ void run_service(const V& v, uint32_t block, int32_t* lds) {
+    if ((int)block < v.stage_blocks) {
+        stage_block(v, block, lds);
         return;
     }
-    int own = (int)block - stage_blocks;
-    if (tally_blocks && own-- == 0) tally_block(*this, lds);
-    else if (own < count_blocks) count_block(*this, own, lds);
+    int own = (int)block - v.stage_blocks;
+    if (v.tally_blocks && own-- == 0) tally_block(v, lds);
+    else if (own < v.count_blocks) count_block(v, own, lds);
 }
+__device__ __forceinline__ void Service::run(uint32_t block, int32_t* lds) const { run_service(*this, block, lds); }
+__device__ __forceinline__ void SplitService::run(uint32_t block, int32_t* lds) const { run_service(*this, block, lds); }
 
 __global__ __launch_bounds__(kThreads) void service_kernel(const Service v) {
     __shared__ int32_t lds[2 * kTallySlots];
@@ -520,20 +529,55 @@ struct CacheSource {
     int64_t pitch_bytes;
     int owner_mode;   // 1: by source row; 2: by position only
     const int32_t* miss_row;
-    uint32_t spans, span;    // two staging launches: the miss table's spans, their slots
-    uint32_t second_from;    // the slots before it were staged by the first of the two
-    __device__ __forceinline__ bool split() const { return spans != 0; }
-    __device__ __forceinline__ void begin() {
-        if (split()) second_from = missed[2] * span;
-    }
-    __device__ __forceinline__ bool arrived() const { return second_from == spans * span; }
-    __device__ __forceinline__ int32_t key(int64_t i) const { return loc[i]; }
     const uint32_t* missed;   // Service::missed (whole lookups only)
+    __device__ __forceinline__ int32_t key(int64_t i) const { return loc[i]; }
     __device__ __forceinline__ uint32_t late() const { return missed[0]; }
     __device__ __forceinline__ bool late_skewed() const { return missed[1] != 0; }
     // a missed row, on its way while the staging runs
     __device__ __forceinline__ bool pending(int32_t where) const { return where < kLocZero; }
     // from miss-table slot to staging row, once that is known
+    __device__ __forceinline__ int32_t resolve(int32_t where) const {
+        if (where < kLocZero && where != kLocHost) {
+            const int32_t row = miss_row[-2 - where];
+            where = row >= 0 ? loc_of_stage((uint32_t)row) : kLocHost;
+        }
+        return where;
+    }
+    __device__ __forceinline__ bool split() const { return false; }
+    __device__ __forceinline__ void begin() {}
+    __device__ __forceinline__ bool arrived() const { return true; }
+    template <int PHASE> __device__ __forceinline__ bool in_phase(int32_t where) const { return pending(where); }
+    __device__ __forceinline__ const uint8_t* address(int32_t where, int64_t i) const { return address(where, -2 - where, i); }
+    __device__ __forceinline__ const uint8_t* address(int32_t where, int32_t staged, int64_t i) const {
+        // cache row or staged row: one multiply-add either way, no branch
+        const bool cached = where >= 0;
+        const uint8_t* at = (cached ? cache_rows : stage_rows) + (int64_t)(cached ? (where & kSlotMask) : staged) * dev_pitch;
+        if (where == kLocZero) at = nullptr;
+        if (__builtin_expect(where == kLocHost, 0)) at = host_rows + (int64_t)ids[i] * pitch_bytes;
+        return at;
+    }
+    // Which L2 partition serves request i (see gather_owned_lines_kernel): chosen by the source row,
+    // so that a row is read through one partition only; by the request's position for zero rows,
+    // rows read from host memory and hot rows (a handful of rows that a large part of all requests
+    // name: they stay in every partition's L2 anyway, and tying each to one partition would give
+    // that partition several times the others' work).
+    __device__ __forceinline__ uint32_t owner(int32_t where, int64_t i) const {
+        uint32_t v = (uint32_t)i;
+        if (owner_mode == 2) return v % taser_gather::kOwnerClasses;
+        if (where >= 0 && !(where & kHotBit)) v = ((uint32_t)where * 0x9E3779B1u) >> 20;
+        else if (where < kLocZero && where != kLocHost) v = ((uint32_t)(-2 - where) * 0x9E3779B1u) >> 19;
+        return v % taser_gather::kOwnerClasses;
+    }
+};
+
+// The same for a lookup whose missed rows are staged by two launches. (A type of its own: these members, carried and looked at by
+// every lookup's kernels, cost those of a few thousand requests, three launches of 3 us each, 2 % of their time.)
+struct SplitCacheSource : CacheSource {
+    uint32_t spans, span;    // the miss table's spans, their slots
+    uint32_t second_from;    // the slots before it were staged by the first of the two
+    __device__ __forceinline__ bool split() const { return true; }
+    __device__ __forceinline__ void begin() { second_from = missed[2] * span; }
+    __device__ __forceinline__ bool arrived() const { return second_from == spans * span; }
     __device__ __forceinline__ int32_t resolve(int32_t where) const {
         if (where < kLocZero && where != kLocHost) {
             const uint32_t slot = (uint32_t)(-2 - where);
@@ -557,24 +601,7 @@ struct CacheSource {
     }
     __device__ __forceinline__ bool after(int32_t where) const { return where == kLocHost && !arrived(); }
     __device__ __forceinline__ const uint8_t* address(int32_t where, int64_t i) const {
-        // cache row or staged row: one multiply-add either way, no branch
-        const bool cached = where >= 0;
-        const uint8_t* at = (cached ? cache_rows : stage_rows) + (int64_t)(cached ? (where & kSlotMask) : (int32_t)((uint32_t)(-2 - where) & ~kSecondBit)) * dev_pitch;
-        if (where == kLocZero) at = nullptr;
-        if (__builtin_expect(where == kLocHost, 0)) at = host_rows + (int64_t)ids[i] * pitch_bytes;
-        return at;
-    }
-    // Which L2 partition serves request i (see gather_owned_lines_kernel): chosen by the source row,
-    // so that a row is read through one partition only; by the request's position for zero rows,
-    // rows read from host memory and hot rows (a handful of rows that a large part of all requests
-    // name: they stay in every partition's L2 anyway, and tying each to one partition would give
-    // that partition several times the others' work).
-    __device__ __forceinline__ uint32_t owner(int32_t where, int64_t i) const {
-        uint32_t v = (uint32_t)i;
-        if (owner_mode == 2) return v % taser_gather::kOwnerClasses;
-        if (where >= 0 && !(where & kHotBit)) v = ((uint32_t)where * 0x9E3779B1u) >> 20;
-        else if (where < kLocZero && where != kLocHost) v = ((uint32_t)(-2 - where) * 0x9E3779B1u) >> 19;
-        return v % taser_gather::kOwnerClasses;
+        return CacheSource::address(where, (int32_t)((uint32_t)(-2 - where) & ~kSecondBit), i);
     }
 };
 
@@ -875,9 +902,9 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
     // miss_key is all-empty here: cache_init cleared it and every staging clears what it consumed
     {
         TaserProfileSpan span(stream, "cache_classify");
-        hipLaunchKernelGGL(classify_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, stream, ids, n, c->rows,
+        hipLaunchKernelGGL(own_slots ? classify_kernel<true> : classify_kernel<false>, dim3((unsigned)blocks), dim3(kThreads), 0, stream, ids, n, c->rows,
                            c->hash_key, c->hash_slot, c->hash_mask, c->miss_key, c->miss_size, loc,
-                           counts ? tally : nullptr, c->stage_count, own_slots,
+                           counts ? tally : nullptr, c->stage_count,
                            !c->popular_residents && 4 * c->capacity <= 3 * c->rows);
     }
     Service v = {};
@@ -918,7 +945,7 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
 }
 
 static CacheSource source_of(const taser_cache* c, const int32_t* ids, const int32_t* loc) {
-    return CacheSource{loc, ids, c->cache_rows, c->stage_rows, c->dev_pitch, c->host_rows, c->pitch_bytes, c->partitioned_gather, c->miss_row, 0u, 0u, 0u, c->stage_count ? c->stage_count + 1 : nullptr};
+    return CacheSource{loc, ids, c->cache_rows, c->stage_rows, c->dev_pitch, c->host_rows, c->pitch_bytes, c->partitioned_gather, c->miss_row, c->stage_count ? c->stage_count + 1 : nullptr};
 }
 
 static int source_alignment(const taser_cache* c) {
@@ -997,37 +1024,43 @@ static int enqueue_lookup(taser_cache* c, const int32_t* ids, int64_t n, void* o
     const uint8_t* zeros = tg::zero_chunk();
     if (!zeros) return taser_fail(TASER_E_HIP, "cache_lookup: the zero constant is not available on this device");
     const bool owned = c->partitioned_gather && tg::owned_applies(align, c->row_bytes, n, out);
-    CacheSource source = source_of(c, ids, loc);
+    const CacheSource source = source_of(c, ids, loc);
     Service v;
     enqueue_classify(c, ids, n, hit_miss, stream, loc, tally, true, &v);
     if (owned) v.loc = loc;
-    const bool twice = owned && stage_twice(c, n);
-    Service second;
-    if (twice) {
-        v.split = Split{v.spans, n, c->rows - c->capacity};
-        source.spans = v.spans;
-        source.span = v.stage_span;
-        second = v;
+    // The gather's blocks are behind the service blocks, so the staging starts first and its few blocks
+    // stay for the whole launch, which takes the longer of the two instead of their sum.
+    bool launched;
+    if (owned && stage_twice(c, n)) {
+        const SplitService first = {v, Split{v.spans, n, c->rows - c->capacity}, false};
+        SplitService second = first;
         second.second = true;
         second.count_blocks = second.tally_blocks = 0;
         second.blocks = (uint32_t)((v.stage_blocks + tg::kOwnerClasses - 1) / tg::kOwnerClasses * tg::kOwnerClasses);
-    }
-    bool launched;
-    {
-        // the gather's blocks are behind the service blocks, so the staging starts first and its few blocks
-        // stay for the whole launch, which takes the longer of the two instead of their sum
-        TaserProfileSpan span(stream, "cache_stage_and_gather_rows");
-        launched = owned ? tg::launch_owned<1>(source, c->row_bytes, n, out, zeros, stream, v)
-                         : tg::launch_chunks<4, 1>(source, c->row_bytes, n, out, zeros, stream, v);
-    }
-    if (launched && twice) {
-        TaserProfileSpan span(stream, "cache_stage_and_gather_staged_rows");
-        launched = tg::launch_owned<3>(source, c->row_bytes, n, out, zeros, stream, second);
-    }
-    if (launched) {
-        TaserProfileSpan span(stream, "cache_gather_staged_rows");
-        launched = owned ? tg::launch_owned<2>(source, c->row_bytes, n, out, zeros, stream)
-                         : tg::launch_chunks<4, 2>(source, c->row_bytes, n, out, zeros, stream);
+        const SplitCacheSource parts = {source, v.spans, v.stage_span, 0u};
+        {
+            TaserProfileSpan span(stream, "cache_stage_and_gather_rows");
+            launched = tg::launch_owned<1>(parts, c->row_bytes, n, out, zeros, stream, first);
+        }
+        if (launched) {
+            TaserProfileSpan span(stream, "cache_stage_and_gather_staged_rows");
+            launched = tg::launch_owned<3>(parts, c->row_bytes, n, out, zeros, stream, second);
+        }
+        if (launched) {
+            TaserProfileSpan span(stream, "cache_gather_staged_rows");
+            launched = tg::launch_owned<2>(parts, c->row_bytes, n, out, zeros, stream);
+        }
+    } else {
+        {
+            TaserProfileSpan span(stream, "cache_stage_and_gather_rows");
+            launched = owned ? tg::launch_owned<1>(source, c->row_bytes, n, out, zeros, stream, v)
+                             : tg::launch_chunks<4, 1>(source, c->row_bytes, n, out, zeros, stream, v);
+        }
+        if (launched) {
+            TaserProfileSpan span(stream, "cache_gather_staged_rows");
+            launched = owned ? tg::launch_owned<2>(source, c->row_bytes, n, out, zeros, stream)
+                             : tg::launch_chunks<4, 2>(source, c->row_bytes, n, out, zeros, stream);
+        }
     }
     if (!launched) return gather_too_large(n, c->row_bytes);
     TASER_HIP_TRY(hipGetLastError());
