@@ -543,9 +543,7 @@ struct CacheSource {
         }
         return where;
     }
-    __device__ __forceinline__ bool split() const { return false; }
-    __device__ __forceinline__ void begin() {}
-    __device__ __forceinline__ bool arrived() const { return true; }
+    __device__ __forceinline__ bool begin(int) { return true; }
     template <int PHASE> __device__ __forceinline__ bool in_phase(int32_t where) const { return pending(where); }
     __device__ __forceinline__ const uint8_t* address(int32_t where, int64_t i) const { return address(where, -2 - where, i); }
     __device__ __forceinline__ const uint8_t* address(int32_t where, int32_t staged, int64_t i) const {
@@ -574,10 +572,12 @@ struct CacheSource {
 // every lookup's kernels, cost those of a few thousand requests, three launches of 3 us each, 2 % of their time.)
 struct SplitCacheSource : CacheSource {
     uint32_t spans, span;    // the miss table's spans, their slots
-    uint32_t second_from;    // the slots before it were staged by the first of the two
-    __device__ __forceinline__ bool split() const { return true; }
-    __device__ __forceinline__ void begin() { second_from = missed[2] * span; }
-    __device__ __forceinline__ bool arrived() const { return second_from == spans * span; }
+    uint32_t second_from;    // the slots before it were staged by the first of the two, and PHASE 3 writes their rows
+    __device__ __forceinline__ bool begin(int phase) {
+        const uint32_t first = missed[2];
+        second_from = first < spans ? first * span : 0u;   // all by the first: then they are all PHASE 2's
+        return phase == 2 || first < spans;
+    }
     __device__ __forceinline__ int32_t resolve(int32_t where) const {
         if (where < kLocZero && where != kLocHost) {
             const uint32_t slot = (uint32_t)(-2 - where);
@@ -599,7 +599,7 @@ struct SplitCacheSource : CacheSource {
         if (PHASE == 3) return where < kLocZero && !after(where);
         return where < kLocZero && (where == kLocHost || ((uint32_t)(-2 - where) & kSecondBit));
     }
-    __device__ __forceinline__ bool after(int32_t where) const { return where == kLocHost && !arrived(); }
+    __device__ __forceinline__ bool after(int32_t where) const { return where == kLocHost; }
     __device__ __forceinline__ const uint8_t* address(int32_t where, int64_t i) const {
         return CacheSource::address(where, (int32_t)((uint32_t)(-2 - where) & ~kSecondBit), i);
     }

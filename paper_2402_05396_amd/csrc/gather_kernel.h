@@ -67,9 +67,8 @@ template <int ALIGN> __device__ __forceinline__ u32x4 load16(const uint8_t* at) 
 //   late_skewed()   many of them are copies of the same source row.
 // The owned-lines kernel can have a PHASE 3 between the two, when a part of the pending rows has arrived and the others
 // are still on their way: it writes the first of them, and PHASE 2 is left with the others. For that a Source has
-//   begin()              called when PHASE 2 or 3 begins: how far the rows are;
-//   split()              there was a PHASE 3 or will be;
-//   arrived()            all rows had arrived before PHASE 3, which then does all of PHASE 2's work;
+//   begin(phase)         called when PHASE 2 or 3 begins: how far the rows are; false where PHASE 3 has nothing to do, because all rows
+//                        had arrived before it: they are PHASE 2's then;
 //   resolve_first(key)   the token for PHASE 3;
 //   in_phase<P>(key)     a row that PHASE P (2 or 3) writes, if it does not write everything;
 //   after(key)           PHASE 3: the row is still on its way.
@@ -306,10 +305,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(8, 8))
         const uint32_t late = source.late();
         if (late == 0) return;
         only_late = late < g.whole_from || source.late_skewed();
-        source.begin();
-        // PHASE 3 writes what is there, PHASE 2 the rest; everything if all is there or if nothing has been written yet
-        if (PHASE == 3 && !source.arrived() && !only_late) return;
-        if (PHASE == 2 && source.split() && source.arrived()) return;
+        // where the whole output is written once more it is PHASE 2 that does it
+        if (!source.begin(PHASE) || (PHASE == 3 && !only_late)) return;
         if (only_late) classes = g.late_classes;
         units = classes * g.tiles;
         if (block >= units) return;

@@ -1,6 +1,6 @@
 """Lookups with a gigabyte and more to write, whose last missed rows are staged by a launch of their own: shares of
-misses from which the first launch takes some spans, all of them or next to none, popular rows among the missed ones,
-staging areas that are too small, and replays from a graph."""
+misses of which the first launch takes a part or all, popular rows among the missed ones, no misses, staging areas that are
+too small, and replays from a graph."""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +13,8 @@ ROWS, DIM, N = 6000, 850, 330_001          # 1.12 GB of output, 20 MB of rows
 
 
 def _requests(gen, kind):
-    if kind == "uniform":
-        ids = torch.randint(0, ROWS, (N,), generator=gen, device="cuda")
+    if kind == "uniform" or kind == "residents":
+        ids = torch.randint(0, ROWS if kind == "uniform" else 1000, (N,), generator=gen, device="cuda")
     else:                                  # popular rows have the lowest ids, or the highest
         ids = (torch.rand(N, generator=gen, device="cuda") ** 5 * ROWS).long().clamp_(max=ROWS - 1)
         if kind == "popular_last":
@@ -24,7 +24,14 @@ def _requests(gen, kind):
     return ids
 
 
-@pytest.mark.parametrize("resident", [0, 2, 1500, 3000])
+def _first_takes_all(kind, resident, misses):
+    """Whether the first launch stages all rows: reading them takes no longer than the gather of the rows that are there.
+    (A row by the bus takes as long as 110 in the gather.)"""
+    takes_all = 67 * 64 * min(misses, ROWS - resident) <= 39 * (N - misses)
+    assert takes_all == ((kind, resident) == ("popular_first", 3500) or misses == 0), (kind, resident, misses)
+
+
+@pytest.mark.parametrize("resident", [0, 2, 1500, 3000, 3500])
 @pytest.mark.parametrize("kind", ["uniform", "popular_first", "popular_last"])
 def test_every_split_writes_the_same(kind, resident):
     gen = torch.Generator(device="cuda").manual_seed(resident + len(kind))
@@ -42,6 +49,7 @@ def test_every_split_writes_the_same(kind, resident):
             out = T.cache_lookup(c, ids, out=buf[:N * DIM].view(N, DIM), hit_miss=hm)
             assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]) and bool((buf[N * DIM:] == 7.0).all()), staging
             assert hm.tolist() == [int((ok & (ids < resident)).sum()), int((ok & (ids >= resident)).sum())]
+            _first_takes_all(kind, resident, hm.tolist()[1])
             out.fill_(3.0)
             T.cache_gather(c, ids, out=out)    # accepted: the lookup of these ids was their prefetch as well
             assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]), (staging, "gather after the lookup")
@@ -67,3 +75,28 @@ def test_replays_with_other_requests():
         ok = (ids >= 0) & (ids < ROWS)
         assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]), kind
     T.cache_free(c)
+
+
+def test_replays_with_all_some_and_none_of_the_rows_by_the_first_launch():
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    host = torch.randn((ROWS, DIM), generator=torch.Generator().manual_seed(3)).pin_memory()
+    table = torch.cat([host.cuda(), torch.zeros((1, DIM), device="cuda")])
+    for staging in (2500, 700):
+        c = T.cache_init(host, 3500, torch.arange(3500, dtype=torch.int32), staging_rows=staging)
+        ids, out = torch.zeros(N, dtype=torch.int32, device="cuda"), torch.empty((N, DIM), device="cuda")
+        hm = torch.zeros(2, dtype=torch.int64, device="cuda")
+        T.cache_lookup(c, ids, out=out, hit_miss=hm)
+        torch.cuda.synchronize()
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=stream):
+            T.cache_lookup(c, ids, out=out, hit_miss=hm, stream=stream)
+        for kind in ("uniform", "popular_first", "residents", "popular_last", "popular_first", "uniform"):
+            ids.copy_(_requests(gen, kind))
+            out.fill_(1.0)
+            hm.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            _first_takes_all(kind, 3500, hm.tolist()[1])
+            ok = (ids >= 0) & (ids < ROWS)
+            assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]), (staging, kind)
+        T.cache_free(c)
