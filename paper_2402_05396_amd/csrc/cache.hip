@@ -998,14 +998,21 @@ static int enqueue_gather(taser_cache* c, const int32_t* ids, int64_t n, void* o
 // Whether the last of the missed rows are staged by a launch of their own, beside which those of the first are written: for
 // launches with 1 GiB and more to write, where a third of the rows and more can be missed and reading these may take half
 // as long as writing the output (the bus moves a hundredth of what memory does). How much is left to the second launch
-// follows the misses (see Split). us a lookup with one staging launch and with two, rows of 1652 bytes: 1.33 M requests by a
-// power law, 17 000 rows, 10 / 20 / 30 / 50 % of them resident 627 535, 540 497, 480 478, 435 440; without skew, 30 / 50 % 820
-// 666, 600 563; 700 000 requests of 60 000 rows, 20 % 1 270 1 242, 74 % 435 446. A launch more costs 4 us: 800 000 requests of
-// 1 064 bytes, 4 000 rows, 203 and 209; 727 MB by the 17 000 rows, 20 % resident, 457 and 443, without skew 574 and 585; 182
-// MB 326 and 332.
+// follows the misses (see Split); where requests without skew would leave it next to nothing, the bus's time less than 5/4 of the
+// gather's, there is none, nor where the staging area has room for less than an eighth of the rows that can be missed. us a
+// lookup with one staging launch and with two, rows of 1652 bytes, without skew / by a power law with the popular rows resident:
+//   1.33 M requests of 17 000 rows, 20 / 30 / 50 / 55 % resident: 867 854, 827 668, 597 560, 615 620 / 535 492, 467 480, 437 443, 447 457
+//   700 000 of 60 000, 20 / 30 / 50 / 65 %: 1 784 1 796, 1 547 1 375, 1 141 1 020, 819 730 / 1 274 1 252, 1 099 1 089, 779 777, 546 550
+// (the power law's misses are fewer than the rule takes them to be: at most 3 % are lost there, a quarter won without skew);
+// rows of 3400 bytes, 330 000 of 6 000, 20 / 30 / 60 / 65 %: 504 525, 489 384, 290 248, 253 257 / 365 335, 322 314, 207 213, 208 214.
+// With a staging area for 10 and 200 rows, 1.33 M requests, half resident: 2 814 2 811, 2 728 2 737, without skew 16 597 16 612,
+// 16 240 16 165; for half of the missing rows 1 556 1 563, 8 494 6 580. A launch more costs 4 us: 800 000 requests of 1 064 bytes, 4 000
+// rows, 203 and 209; 727 MB by the 17 000 rows, 20 % resident, 457 and 443, without skew 574 and 585; 182 MB 326 and 332.
 static bool stage_twice(const taser_cache* c, int64_t n) {
     const int64_t out_bytes = n * c->row_bytes, missing = c->rows - c->capacity;
-    return out_bytes >= (int64_t)1 << 30 && 3 * missing >= c->rows && missing * c->row_bytes >= out_bytes / 200;
+    if (out_bytes < (int64_t)1 << 30 || 3 * missing < c->rows || missing * c->row_bytes < out_bytes / 200 || 8 * c->staging_rows < missing) return false;
+    const double hits = (double)n * (double)c->capacity / (double)c->rows;   // without skew
+    return 4.0 * (double)Split::kBus * (double)missing >= 5.0 * (double)Split::kThere * hits;
 }
 
 // A whole lookup. Where there is a staging area to wait for, the output that does not need it is

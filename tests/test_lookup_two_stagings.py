@@ -100,3 +100,18 @@ def test_replays_with_all_some_and_none_of_the_rows_by_the_first_launch():
             ok = (ids >= 0) & (ids < ROWS)
             assert torch.equal(out, table[torch.where(ok, ids, ROWS).long()]), (staging, kind)
         T.cache_free(c)
+
+
+@pytest.mark.parametrize("resident,staging,twice", [(1500, 4500, True), (1500, 563, True), (1500, 562, False), (1500, 10, False),
+                                                    (3600, 2400, True), (3750, 2250, False), (4000, 2000, False)])
+def test_one_launch_where_a_second_has_nothing_to_gain(resident, staging, twice):
+    gen = torch.Generator(device="cuda").manual_seed(resident + staging)
+    host = torch.randn((ROWS, DIM), generator=torch.Generator().manual_seed(4)).pin_memory()
+    table = torch.cat([host.cuda(), torch.zeros((1, DIM), device="cuda")])
+    c = T.cache_init(host, resident, torch.arange(resident, dtype=torch.int32), staging_rows=staging)
+    ids = _requests(gen, "popular_first")
+    T.profile_begin()
+    out = T.cache_lookup(c, ids)
+    assert ("cache_stage_and_gather_staged_rows" in T.profile_end()) == twice
+    assert torch.equal(out, table[torch.where((ids >= 0) & (ids < ROWS), ids, ROWS).long()])
+    T.cache_free(c)
