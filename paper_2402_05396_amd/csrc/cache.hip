@@ -280,7 +280,7 @@ template <typename V> __device__ __forceinline__ void tally_block(const V& v, in
         __syncthreads();
         for (int s = threadIdx.x; s < kSample; s += kThreads) {
             const int32_t where = v.loc[(uint64_t)s * (uint64_t)v.n / kSample];
-            if (where < kLocZero && where != kLocHost) atomicAdd(&seen[(uint32_t)(-2 - where) % kSampleSlots], 1u);
+            if (where < kLocZero && where != kLocHost) atomicAdd(&seen[hash_id(-2 - where, kSampleSlots - 1)], 1u);   // the slot may be the row's id
         }
         __syncthreads();
         uint32_t m = 0;

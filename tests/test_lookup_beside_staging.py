@@ -115,3 +115,23 @@ def test_lookup_replays_from_a_hip_graph_with_other_requests():
         assert tuple(hm.tolist()) == hits
         eager = T.cache_lookup(c, ids)            # the same handle, between replays
         assert eager.cpu().numpy().tobytes() == want
+
+
+def test_missing_rows_in_strides_are_not_taken_for_one_popular_row():
+    """3 750 rows whose ids are multiples of 16, all missing and equally popular: the launch for missed rows writes the whole
+    output, tied to partitions, as for neighboring ids (132 us of that launch, and 157 where they counted as one popular row)."""
+    rows, dim, n = 60_000, 413, 400_000
+    host = torch.randn((rows, dim), generator=torch.Generator().manual_seed(5)).pin_memory()
+    pick = torch.randint(0, rows // 16, (n,), generator=torch.Generator(device="cuda").manual_seed(8), device="cuda", dtype=torch.int32)
+    c, took = T.cache_init(host, 0, staging_rows=rows), {}
+    for stride in (16, 1):
+        ids, out = pick * stride, torch.empty((n, dim), device="cuda")
+        T.cache_lookup(c, ids, out=out)
+        assert torch.equal(out, host.cuda()[ids.long()])
+        took[stride] = 1e9
+        for _ in range(10):
+            T.profile_begin()
+            T.cache_lookup(c, ids, out=out)
+            took[stride] = min(took[stride], T.profile_end()["cache_gather_staged_rows"][1])
+    T.cache_free(c)
+    assert took[16] < 1.1 * took[1], took
