@@ -54,6 +54,26 @@ def test_waves_take_several_spans(rows, dim, stage_blocks):
         T.cache_free(c)
 
 
+def test_missing_rows_in_strides_are_every_waves():
+    """938 missing rows whose ids are multiples of 64 take no longer than as many neighboring ones, as long as the spans that hold them go
+    to different waves (163 us; 215 where they all went to every eighth)."""
+    rows, dim, n = 60_000, 413, 400_000
+    host = torch.randn((rows, dim), generator=torch.Generator().manual_seed(5)).pin_memory()
+    pick = torch.randint(0, rows // 64 + 1, (n,), generator=torch.Generator(device="cuda").manual_seed(8), device="cuda", dtype=torch.int32)
+    c, took = T.cache_init(host, 0, staging_rows=rows), {}
+    for stride in (64, 1):
+        ids, out = pick * stride, torch.empty((n, dim), device="cuda")
+        T.cache_lookup(c, ids, out=out)
+        assert torch.equal(out, host.cuda()[ids.long()])
+        took[stride] = 1e9
+        for _ in range(10):
+            T.profile_begin()
+            T.cache_lookup(c, ids, out=out)
+            took[stride] = min(took[stride], T.profile_end()["cache_stage_and_gather_rows"][1])
+    T.cache_free(c)
+    assert took[64] < 1.3 * took[1], took
+
+
 def test_few_misses_of_a_large_table_are_found_as_fast_with_a_slot_per_row():
     """500 requests of a million rows: looking through a slot per row may not take longer than through a hashed table of half
     as many slots by more than what the slots more are (24 and 22 us; 58 where waves looked at 8 slots at a time)."""
