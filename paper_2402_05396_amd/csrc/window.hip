@@ -30,20 +30,24 @@ __device__ __forceinline__ uint32_t first_bits(int n, int from) {
 // freq is the mask's population count. The m x m identity bytes are those masks, one bit per byte: the
 // masks of the block's roots go into LDS as one string of bits, and the block's range of the output is
 // written from it 16 bytes at a time (4 bits times 0x204081 are 4 bytes), whatever m and the alignment.
-// Bound by its output: 40 000 windows of 25 (33 MB in all) take 9.2 us, 6.4 at the rate of a large copy; with one lane shuffle
-// per comparison and per output byte it was 24 us of vector and LDS instructions, with ordinary stores 9.8. (The next windows' loads ahead of
-// the present ones' work, in blocks that stay, or a load of the ids that does not wait for the count: 1.04 to 1.2 of the time.)
-// Roots of a block. The identity matrices of 16 are whole 16-byte pieces whatever m is: with 8 roots of 25 candidates every block
-// had a piece that it shared with its neighbor, written byte by byte, and 40 000 windows took 11.4 us where those of 32, with
-// more bytes, took 10.9. With 64 lanes per root 16 would be blocks of 1 024 threads (2 000 windows of 64 5.9 us, of 4 roots 4.8).
-constexpr int encoding_roots(int lanes) { return lanes == 64 ? 4 : 16; }
-template <int G>
-__global__ __launch_bounds__(encoding_roots(G) * G) void candidate_encodings_kernel(
+// Bound by its output: 40 000 windows of 25 (33 MB in all) take 9.1 to 10.4 us, 6.4 at the rate of a large copy; with one lane shuffle per
+// comparison and per output byte it was 24 us of vector and LDS instructions.
+// ROOTS of a block: so many that their matrices are whole 16-byte pieces, of which none is shared by two blocks and written by
+// bytes: 8 where m is even, 16 where it is odd. us by 8 / by 16, windows of 25: 600 3.32 2.97, 8 000 4.61 4.20, 40 000 9.79 9.21; of
+// 32: 600 2.72 2.81, 8 000 4.06 4.30, 40 000 9.32 9.81. Up to 16 candidates have 16 lanes, and 16 roots in 256 threads; with 64 lanes
+// per root 16 would be 1 024 threads (2 000 windows of 64 5.9 us, of 4 roots 4.5).
+// PAST: the pieces go past the caches. With odd m most blocks end inside a 128-byte line, and the parts of a line that go past the caches
+// are late where there is little to write: us through the caches / past them, windows of 9: 2 000 2.26 2.54, 40 000 4.01 4.43; of 25:
+// 2 000 2.82 3.10, 8 000 3.80 4.19, 16 000 (10 MB) 5.49 5.55, 40 000 9.84 9.19. So there it is done from 12 MB on; with even m always: windows of
+// 32, 2 000 2.96 2.95, 16 000 6.40 5.61, 40 000 10.99 9.21.
+constexpr int64_t kPastFrom = 12 << 20;
+template <int G, int ROOTS, bool PAST>
+__global__ __launch_bounds__(ROOTS * G) void candidate_encodings_kernel(
     const int32_t* __restrict__ nbr, const int32_t* __restrict__ count, int64_t num_roots, int m, int32_t* __restrict__ freq,
     uint8_t* __restrict__ identity) {
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    constexpr int kRoots = encoding_roots(G), kThreads = kRoots * G;
+    constexpr int kRoots = ROOTS, kThreads = ROOTS * G;
     constexpr int kWords = kRoots * G * G / 32 + 1;     // bits of their identity matrices, and a word to read past the end
     constexpr int kParts = G > 32 ? 2 : 1;              // 32-bit parts of a mask
     __shared__ __align__(16) int32_t cand[kThreads];
@@ -111,7 +115,8 @@ __global__ __launch_bounds__(encoding_roots(G) * G) void candidate_encodings_ker
             v.y = __umul24((x >> 4) & 15u, 0x204081u) & 0x01010101u;
             v.z = __umul24((x >> 8) & 15u, 0x204081u) & 0x01010101u;
             v.w = __umul24((x >> 12) & 15u, 0x204081u) & 0x01010101u;
-            __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(aligned + off));
+            if (PAST) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(aligned + off));
+            else *reinterpret_cast<u32x4*>(aligned + off) = v;
         } else {   // the range's first or last bytes
             for (uint32_t o = off; o < off + 16u; o += 4u) {
                 if (o >= head && o + 4u <= head + length) {
@@ -418,8 +423,12 @@ extern "C" int taser_candidate_encodings(const int32_t* nbr, const int32_t* coun
     taser_clear_stale_hip_error();
     hipStream_t stream = (hipStream_t)hip_stream;
     TaserProfileSpan span(stream, "candidate_encodings");
-    const int lanes = m <= 16 ? 16 : m <= 32 ? 32 : 64, roots = encoding_roots(lanes);
-    const auto kernel = lanes == 16 ? candidate_encodings_kernel<16> : lanes == 32 ? candidate_encodings_kernel<32> : candidate_encodings_kernel<64>;
+    const bool past = m % 2 == 0 || num_roots * m * m >= kPastFrom;   // num_roots * m is below 2^31
+    const int lanes = m <= 16 ? 16 : m <= 32 ? 32 : 64, roots = lanes == 64 ? 4 : lanes == 32 && m % 2 == 0 ? 8 : 16;
+    const auto kernel = lanes == 64   ? (past ? candidate_encodings_kernel<64, 4, true> : candidate_encodings_kernel<64, 4, false>)
+                        : roots == 8  ? candidate_encodings_kernel<32, 8, true>
+                        : lanes == 32 ? (past ? candidate_encodings_kernel<32, 16, true> : candidate_encodings_kernel<32, 16, false>)
+                                      : (past ? candidate_encodings_kernel<16, 16, true> : candidate_encodings_kernel<16, 16, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((num_roots + roots - 1) / roots)), dim3(roots * lanes), 0, stream, nbr, count, num_roots, m, freq, identity);
     TASER_HIP_TRY(hipGetLastError());
     return TASER_OK;

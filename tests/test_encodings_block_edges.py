@@ -1,4 +1,5 @@
-"""Candidate encodings where a block's identity bytes begin and end inside a 16-byte piece, or a window is a block's only one."""
+"""Candidate encodings where a block's identity bytes begin and end inside a 16-byte piece, or a window is a block's only one, and
+around the size from which odd windows are written past the caches."""
 import numpy as np
 import pytest
 import torch
@@ -25,3 +26,14 @@ def test_encodings(m, roots, shift):
     assert np.array_equal(freq.cpu().numpy(), want_f)
     assert np.array_equal(view[:roots * m * m].cpu().numpy().reshape(roots, m, m), want_i)
     assert bool((buf[:shift] == 9).all()) and bool((view[roots * m * m:] == 9).all())
+
+
+@pytest.mark.parametrize("m", [7, 15, 17, 31, 33, 63])
+@pytest.mark.parametrize("above", [False, True])
+def test_odd_windows_around_twelve_megabytes(m, above):
+    rng = np.random.default_rng(m)
+    roots = -(-(12 << 20) // (m * m)) - (0 if above else 1)
+    nbr, count = rng.integers(0, max(2, m // 2), (roots, m)).astype(np.int32), rng.integers(0, m + 1, roots).astype(np.int32)
+    want_f, want_i = oracle.candidate_encodings(nbr, count)
+    freq, identity = T.candidate_encodings(torch.from_numpy(nbr).cuda(), torch.from_numpy(count).cuda())
+    assert np.array_equal(freq.cpu().numpy(), want_f) and np.array_equal(identity.cpu().numpy().reshape(want_i.shape), want_i)
