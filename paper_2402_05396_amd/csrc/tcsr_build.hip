@@ -1343,8 +1343,8 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         index.level[i] = reinterpret_cast<int64_t*>(storage + l.level[i]);
     }
     // indptr, if it is `wanted` from the sorted node column (not where *failed says that this is in no order), and the upper index
-    // levels; *report = *failed. Waits for the stream.
-    auto finish = [&](bool wanted, const int32_t* sorted_key, const uint32_t* failed, unsigned long long* report) -> int {
+    // levels; *report = *failed, copied to *read_back if that is not null. Waits for the stream.
+    auto finish = [&](bool wanted, const int32_t* sorted_key, const uint32_t* failed, unsigned long long* report, unsigned long long* read_back) -> int {
         if (wanted) {
             TaserProfileSpan span(stream, "tcsr_indptr");
             hipLaunchKernelGGL(indptr_kernel, dim3(blocks_for(n + 1, kThreads * 4)), dim3(kThreads), 0, stream, sorted_key, n, num_nodes, indptr, failed);
@@ -1360,12 +1360,13 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
             hipLaunchKernelGGL(time_index_upper_kernel, dim3(blocks_for(end, kThreads)), dim3(kThreads), 0, stream, level1, l.level_len[0], up, failed, report);
         }
         TASER_HIP_TRY(hipGetLastError());
+        if (read_back) TASER_HIP_TRY(hipMemcpyAsync(read_back, report, sizeof(*report), hipMemcpyDeviceToHost, stream));
         TASER_HIP_TRY(hipStreamSynchronize(stream));
         return TASER_OK;
     };
 
     if (n == 0) {
-        const int rc = finish(true, nullptr, nullptr, nullptr);
+        const int rc = finish(true, nullptr, nullptr, nullptr, nullptr);
         if (rc != TASER_OK) return rc;
     } else {
         // ---- what the input looks like
@@ -1415,17 +1416,17 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
         if (in_node_digits) {
             if (small) launch_sorted<kSmallItems>(l, columns, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
             else launch_sorted<kLargeItems>(l, columns, (int64_t)info[2], n, num_nodes, low_bits, node_bits - low_bits, scratch, rec, level1, indptr, stream);
-            const int rc = finish(false, nullptr, nullptr, nullptr);
+            const int rc = finish(false, nullptr, nullptr, nullptr, nullptr);
             if (rc != TASER_OK) return rc;
             done = true;
         } else if (info[1] && buckets_pay(n, ts_bits + node_bits)) {
             pinned.launched(stream);
             launch_buckets(l, columns, n, node_bits, KeySpec{ts_low, ts_bits}, scratch, rec, level1, stream);
-            const int rc = finish(true, reinterpret_cast<const int32_t*>(scratch + l.key[1]), &bucket_scratch(l, scratch)->failed, d_info + 4);
+            const int rc = finish(true, reinterpret_cast<const int32_t*>(scratch + l.key[1]), &bucket_scratch(l, scratch)->failed, d_info + 4,
+                                  pinned.words ? nullptr : &info[4]);
             if (rc != TASER_OK) return rc;
             pinned.settled();
             if (pinned.words) info[4] = __atomic_load_n(&pinned.words[4], __ATOMIC_RELAXED);
-            else TASER_HIP_TRY(hipMemcpy(&info[4], d_info + 4, sizeof(info[4]), hipMemcpyDeviceToHost));
             done = info[4] == 0;
         }
 
@@ -1461,7 +1462,7 @@ int build_in(const Layout& l, const int32_t* src, const int32_t* dst, const int6
                 else launch_pass<kLargeItems>(l, in, n, d, hist_known, hist, total, chunk_sum, rec_out, key_out, last ? level1 : nullptr, stream);
                 in = Items{rec_out, key_out, nullptr, nullptr, nullptr};
             }
-            const int rc = finish(true, in.key, nullptr, nullptr);
+            const int rc = finish(true, in.key, nullptr, nullptr, nullptr);
             if (rc != TASER_OK) return rc;
         }
     }
