@@ -1009,8 +1009,9 @@ __global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(8
     const Items in, int64_t n, const uint32_t* __restrict__ total, const KeySpec spec, TaserRec* __restrict__ rec_out,
     int32_t* __restrict__ key_out, int64_t* __restrict__ level1, const uint64_t* __restrict__ first_key, uint64_t all_keys,
     uint32_t* __restrict__ failed) {
+    typedef uint64_t __attribute__((may_alias)) FourCounts;
     __shared__ uint64_t item[kLocalMost];
-    __shared__ uint16_t wave_count[kLocalWaves][kLocalBins];
+    __shared__ __align__(8) uint16_t wave_count[kLocalWaves][kLocalBins];
     __shared__ uint32_t scan_tmp[kLocalWaves];
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     uint32_t start = 0, count = (uint32_t)n;
@@ -1051,7 +1052,7 @@ __global__ __launch_bounds__(kLocalThreads) __attribute__((amdgpu_waves_per_eu(8
     const int passes = (key_bits + kLocalDigitBits - 1) / kLocalDigitBits, digit_bits = passes ? (key_bits + passes - 1) / passes : 0;
     const uint32_t digit_mask = (1u << digit_bits) - 1u;
     for (int pass = 0, shift = kLocalIndexBits; pass < passes; ++pass, shift += digit_bits) {
-        for (uint32_t c = threadIdx.x; c < (uint32_t)(kLocalWaves * kLocalBins / 4); c += kLocalThreads) reinterpret_cast<uint64_t*>(&wave_count[0][0])[c] = 0;
+        for (uint32_t c = threadIdx.x; c < (uint32_t)(kLocalWaves * kLocalBins / 4); c += kLocalThreads) reinterpret_cast<FourCounts*>(&wave_count[0][0])[c] = 0;
         __syncthreads();
         uint32_t place[kLocalItems];
 #pragma unroll
