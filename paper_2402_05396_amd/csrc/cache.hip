@@ -213,7 +213,8 @@ __global__ __launch_bounds__(kThreads) void classify_kernel(
 // the second launch's two parts take the same time, f = bus / (bus + staged rows), as long as the first launch's bus
 // time is not the shorter one. Whole numbers: several workgroups work it out and have to agree. (1.33 M requests by a power
 // law, 17 000 rows, 20 % resident, 16 % of the requests missed: f = 0.81; with 0.70, 0.75, 0.80, 0.85 instead 529, 511,
-// 495, 500 us; without skew, 30 % resident: f = 0.46, 666 us, with 0.70 693.)
+// 495, 500 us; without skew, 30 % resident: f = 0.46, 666 us, with 0.70 693. It takes the misses to be spread evenly over the table; where the
+// ids follow popularity, most popular first / last, that lookup takes 500 / 543 us instead of 490, 577 with one launch.)
 struct Split {
     uint32_t spans;          // of the table
     int64_t requests, missing_rows;   // the call's, and how many rows can be missed

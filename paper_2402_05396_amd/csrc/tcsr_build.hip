@@ -817,8 +817,9 @@ __global__ __launch_bounds__(kSortThreads) void list_starts_kernel(const uint32_
 // order, and once more by a workgroup per bucket that sorts it in LDS. The buckets' limits are quantiles of the samples that
 // the inspection took (eight per 2 048 entries), with the position as the key's last digit, so that equal keys divide as well.
 // The largest bucket passes 2.7 times the mean, which is what LDS has room for at most, in some of a thousand inputs of the
-// largest size; then the passes above do it all. 1.34 M entries, 36 bits of key, with the plain view: 183 us by 17 launches, so
-// 157 by 11 (kernels: samples' ranks 10, buckets 13, scan 5, scatter 16, sort 41, which is what the largest bucket takes).
+// largest size; then the passes above do it all behind it (1.57 M entries 244 us, by the passes alone 169; 20 000 155 and 107). 1.34 M
+// entries, 36 bits of key, with the plain view: 183 us by 17 launches, so 157 by 10 (kernels: samples' ranks 10, buckets 13, scan 5,
+// scatter 16, sort 41, which is what the largest bucket takes).
 // Builds by digits / by buckets, us: 2 000 entries of 300 nodes over 2^24 ticks 92 / 60, 20 000 of 17 000 nodes 108 / 88, 200 000
 // 121 / 90, 700 000 146 / 108, 1 570 000 172 / 138; over 2^32 ticks 194 / 144. With so few bits that the passes are three at most
 // it is a draw from half a million entries on: 1.34 M entries of 300 nodes over 1 000 ticks 113 / 121, of 17 000 121 / 120,
