@@ -243,6 +243,7 @@ struct Service {
     int32_t* miss_row;
     uint32_t spans;                       // of the miss table that can hold claims
     uint32_t stage_span;                  // neighboring miss-table slots that go to one wave (a power of two, 8 to 64)
+    bool apart;                           // the waves begin at different places of the table
     uint32_t* stage_count;
     uint32_t staging_rows;
     const uint8_t* host_rows;
@@ -412,7 +413,13 @@ template <typename V> __device__ __forceinline__ void stage_block(const V& v, ui
     // ids in strides are every wave's: 400 000 requests of 938 rows, ids in steps of 64, 215 us with the same wave for all, 163 so.
     const uint32_t span_bits = 31u - (uint32_t)__clz((int)v.stage_span), per = (uint32_t)kWave >> span_bits, sub = lane >> span_bits;
     const uint32_t spans = end - from, round = num_waves * per, own = sub * num_waves + (wave + sub) % num_waves;
-    for (uint32_t done = 0; done < spans; done += round) {
+    // Each wave goes once through all its spans; `apart`: from a place of its own on. With a slot per row the waves would otherwise all read
+    // neighboring rows of host memory at any time, which is good where most are missed (without: 1 % slower) and bad where a wave waits for
+    // one row after the other: 60 000 requests of 10^6 rows of 1652 bytes, nine tenths resident, 86 us, apart 76, by hashed slots 74.
+    const uint32_t rounds = (spans + round - 1) / round;
+    uint32_t done = v.apart ? __umulhi(wave * 0x9E3779B1u, rounds) * round : 0u;
+    for (uint32_t left = rounds; left > 0; --left, done += round) {
+        if (done >= spans) done = 0;
         const uint32_t span = done + own;
         const uint32_t slot = ((from + span) << span_bits) + (lane & (v.stage_span - 1u));
         int32_t key = kEmpty;
@@ -937,6 +944,10 @@ static void enqueue_classify(taser_cache* c, const int32_t* ids, int64_t n, uint
         slots = (uint32_t)c->rows;
     }
     while (v.stage_span > 8 && slots / v.stage_span < (uint32_t)v.stage_blocks * (kThreads / kWave)) v.stage_span /= 2;
+    // Where at most a quarter of the rows can be claimed by 8 192 requests and more: 0.99 of the time over 66 shapes (0.88 to 1.05); by fewer
+    // requests 1.005 over 60 (up to 1.06), where half of the rows can be claimed 1.00.
+    const int64_t claims = n < c->rows - c->capacity ? n : c->rows - c->capacity;
+    v.apart = own_slots && n >= 8192 && 4 * claims <= c->rows;
     v.spans = (slots + v.stage_span - 1) / v.stage_span;   // miss_size, a multiple of any span, has room for them
     if (c->counting) {
         const int64_t want = (n + 4 * kThreads - 1) / (4 * kThreads);

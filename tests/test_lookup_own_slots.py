@@ -54,6 +54,27 @@ def test_waves_take_several_spans(rows, dim, stage_blocks):
         T.cache_free(c)
 
 
+@pytest.mark.parametrize("rows,dim,staging", [(4096, 512, 2048), (36_864, 1024, 18_500), (70_003, 300, 40_000), (131_071, 260, 70_000), (8000, 8, 4000),
+                                              (8200, 16, 8200)])
+@pytest.mark.parametrize("stage_blocks", [0, 1, 3, 50])
+def test_waves_begin_apart(rows, dim, staging, stage_blocks):
+    """At most a quarter of the rows can be missed, by 8 192 requests and more: the waves go through the table from places of their own."""
+    rng = np.random.default_rng(rows + 1)
+    host = torch.from_numpy(rng.standard_normal((rows, dim), dtype=np.float32)).pin_memory()
+    table = torch.cat([host.cuda(), torch.zeros((1, dim), device="cuda")])
+    missing = np.unique(np.concatenate([[0, 7, 8, rows - 1, rows - 8, rows - 9], rng.permutation(rows)[:rows // 4 - 6]]))
+    resident = torch.from_numpy(np.setdiff1d(np.arange(rows), missing).astype(np.int32))
+    some, every = rng.choice(missing, 100), np.concatenate([missing, rng.integers(-1, rows, 9000)])
+    c = T.cache_init(host, len(resident), resident, staging_rows=staging)
+    T.cache_tune(c, stage_blocks=stage_blocks)
+    for ids_np in (np.concatenate([some, np.full(8192 - 100, int(resident[0]))]), every, some, every[::-1].copy()):
+        ids, hm = torch.from_numpy(ids_np.astype(np.int32)).cuda(), torch.zeros(2, dtype=torch.int64, device="cuda")
+        out = T.cache_lookup(c, ids, hit_miss=hm)
+        assert torch.equal(out, table[ids.long()]), len(ids)
+        assert hm.tolist()[1] == int(np.isin(ids_np, missing).sum())
+    T.cache_free(c)
+
+
 def test_missing_rows_in_strides_are_every_waves():
     """938 missing rows whose ids are multiples of 64 take no longer than as many neighboring ones, as long as the spans that hold them go
     to different waves (163 us; 215 where they all went to every eighth)."""
